@@ -6,6 +6,7 @@
 // items is a device-side prefix array written by the permute kernel, so ragged, empty and skewed
 // groups need no host round trip.  Workgroups whose index is past the list exit at once.
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <type_traits>
 #include "cmoe_internal.h"
@@ -15,6 +16,7 @@ namespace cmoe {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
+typedef float floatx4_t __attribute__((ext_vector_type(4)));
 
 struct GemmArgs {
   const bf16_t* A;
@@ -490,19 +492,383 @@ __attribute__((amdgpu_waves_per_eu(min_waves_per_simd(BM, BN, BKT, STAGES, WGM* 
   }
 }
 
+// ---- deep ring: the kernel of the large tiles ------------------------------------------------------------
+// What bounds it: the matrix cores under the power limit at large batches (a loop of nothing but MFMAs on random
+// operands holds 2.06 PFLOP/s at 2.04 GHz with the 16x16x32 instruction and 1.77 PFLOP/s at 1.76 GHz with
+// 32x32x16: half the accumulator traffic per flop), bytes in flight from HBM at small ones.
+//
+// A 16x16x32 MFMA gives the bits of the two 32x32x16 ones of the kernel above, so the shapes stay interchangeable.
+//
+// Layout.  K runs in steps of 32, the depth of one MFMA.  A stage of the LDS ring is the A part and the B part
+// of one step in blocks of 16 rows x 32 K (1 KB): one block is one global_load_lds_dwordx4 of a wave and one
+// operand of the MFMA, and a weight block is 1 KB of consecutive memory (the tiled weight layout).  The 16-byte
+// chunks of a row are XOR-swizzled with (row >> 2) & 3, on the global side, so that the 16 rows a quarter of a
+// ds_read_b128 touches fall into 16 different 16-byte bank groups.
+//
+// Schedule.  While step kt is multiplied out of registers, the fragments of step kt + 1 are read from LDS into the
+// other register set and step kt + STAGES is fetched into the slot that step kt left: a step has STAGES - 1 steps
+// of time to arrive (128 KB in flight per CU for the 256 x 256 tile), its LDS reads have a quarter of a step
+// to return, and nothing is waited for between the barrier and the first MFMA.  (A step of 64 whose first
+// fragments were read behind its barrier, with one and a half steps in flight, took 2700-3000 cycles for 2048
+// cycles of MFMA issue.)  Memory instructions never follow one another: after an MFMA comes at most one LDS
+// read and one DMA instruction.
+//
+// Transfers are buffer loads: the lane's offset stays in one register for the whole K loop, the step's is a scalar, and
+// lanes without a source (rows past a segment's end, K past its end) carry an offset past the buffer's
+// size, for which the hardware delivers zeros.  A wave issues in order, so a transfer stalls its MFMAs until the
+// address unit has taken it: measured 65 cycles each with 64-bit global addresses, 22-27 with buffer offsets
+// (1650 against 1290 cycles per step of 1024 cycles of MFMA issue; 8192 x 22016 x 4096: 1203 -> 1364 TFLOP/s; the step
+// of 64 with global addresses that this replaces: 1174).  Giving the four waves different issue slots made it
+// slower in every form tried.
+
+constexpr uint32_t DMA_NONE = 0x80000000u;                    // an offset past the end of every buffer used here
+
+// A uniform pointer, in scalar registers.
+__device__ __forceinline__ const bf16_t* uniform_ptr(const bf16_t* ptr) {
+  const uint64_t v = reinterpret_cast<uint64_t>(ptr);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<const bf16_t*>(((uint64_t)hi << 32) | lo);
+}
+
+// 64 lanes x 16 bytes from base + lane_off + step_off (bytes; zeros where lane_off >= size) to 1 KB of LDS.
+__device__ __forceinline__ void dma16_buffer(const bf16_t* base, uint32_t size, uint32_t lane_off, uint32_t step_off, bf16_t* lds_dst) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, size, 0x00020000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(lds_dst), 16, lane_off, step_off, 0, 0);
+#endif
+}
+
+// acc += w * a (w: 16 weight rows x 32 K, a: 16 activation rows x 32 K).  Written as assembly to pin the
+// accumulators to the AGPRs: with the builtin the register allocator shuffles them between the two halves of the
+// register file inside the K loop (96 to 470 moves per step, and spills for the 256 x 256 tile of four waves).
+// The compiler does not see an MFMA here, so the wait states its result needs before anything but another MFMA
+// touches it are written out by mfma_drain().  Sources come from LDS reads only (waited for by the compiler as
+// for any use), and the accumulator is overwritten by nothing else inside the loop.
+__device__ __forceinline__ void mfma_acc(floatx4_t& acc, const bf16x8_t& w, const bf16x8_t& a) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(a));
+}
+__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory"); }
+
+constexpr int BK = 32;                                        // K step
+constexpr int BLK = 16 * BK;                                  // elements of a 16-row block
+constexpr int ring_stage_elems(int bm, int bn, int nw) {
+  return ((bm / 16 + nw - 1) / nw + (bn / 16 + nw - 1) / nw) * nw * BLK;
+}
+// The epilogue's strips take the ring's place: each wave stages its whole tile in rows padded by 16 bytes.
+constexpr int ring_strip_elems(int bm, int bn, int wgn, int mode) { return bm * wgn * ((mode == 1 ? bn / wgn / 2 : bn / wgn) + 8); }
+constexpr size_t ring_smem_bytes(int bm, int bn, int stages, int nw, int wgn, int mode) {
+  const int ring = stages * ring_stage_elems(bm, bn, nw), strips = ring_strip_elems(bm, bn, wgn, mode);
+  return (size_t)(ring > strips ? ring : strips) * sizeof(bf16_t);
+}
+// Workgroups a CU's 160 KB of LDS holds, hence waves per SIMD the register allocation has to leave room for.
+constexpr int ring_groups_per_cu(int bm, int bn, int stages, int nw) {
+  return (stages * ring_stage_elems(bm, bn, nw) * 2 <= 80 * 1024) ? 2 : 1;
+}
+
+// WIDE: the rows of a tile may lie 2 GB or more apart (a gather from a batch of that size): 64-bit addresses per lane.
+template <int BM, int BN, int STAGES, int KU, int WGM, int WGN, int MODE, bool WIDE = false>
+__global__ __launch_bounds__(WGM* WGN * 64)
+__attribute__((amdgpu_waves_per_eu(ring_groups_per_cu(BM, BN, STAGES * KU, WGM* WGN) * (WGM * WGN / 4)))) void grouped_gemm_bf16_ring(GemmArgs p) {
+  constexpr int NW = WGM * WGN;
+  constexpr int TM = BM / WGM, TN = BN / WGN, MB = TM / 16, NB = TN / 16;
+  constexpr int A_CH = (BM / 16 + NW - 1) / NW, B_CH = (BN / 16 + NW - 1) / NW;   // DMA instructions per wave and step
+  constexpr int LPT = A_CH + B_CH;
+  constexpr int A_ELEMS = A_CH * NW * BLK;                     // (a part that NW does not divide has spare blocks)
+  constexpr int STAGE_ELEMS = ring_stage_elems(BM, BN, NW);
+  static_assert(BM % (16 * WGM) == 0 && BN % (16 * WGN) == 0, "whole blocks per wave");
+  static_assert(MODE != 1 || TN % 64 == 0, "gate/up pairs must stay inside a wave tile");
+  static_assert(STAGES >= 3 && (STAGES - 1) * KU * LPT < 64, "ring depth");
+  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // wave-uniform: LDS destinations stay scalar
+  const int wm = wave / WGN, wn = wave % WGN;
+  const int r16 = lane & 15, kq = lane >> 4;
+
+  int g = 0, cnt, seg0 = 0, wp;
+  int64_t hoff = 0;
+  int n_work;
+  if (p.single) {
+    cnt = (int)p.T;
+    wp = p.groups[0].width_pad;
+    const int nc = (MODE == 1) ? 2 * wp : p.d;
+    n_work = ((cnt + BM - 1) / BM) * ((nc + BN - 1) / BN);
+  } else {
+    n_work = p.work[p.G];
+  }
+  // Workgroup b runs on XCD b % 8 (own L2).  Each XCD works through a contiguous range of the list so that
+  // tiles sharing an operand meet in one L2: equal parts of a single-group problem, and for work lists the
+  // shares of equal estimated cost that the permutation kernel left behind the prefix array.
+  int wid = blockIdx.x;
+  int k_part = 0;
+  if (p.k_split > 1) {
+    k_part = wid % p.k_split;
+    wid /= p.k_split;
+  }
+  if (p.xcd_remap) {
+    if (p.single) {
+      const int chunk = (n_work + 7) >> 3;
+      if ((wid >> 3) >= chunk) return;
+      wid = (wid & 7) * chunk + (wid >> 3);
+    } else {
+      const int first = p.work[p.G + 1 + (wid & 7)], end = p.work[p.G + 2 + (wid & 7)];
+      wid = first + (wid >> 3);
+      if (wid >= end) return;
+    }
+  }
+  if (wid >= n_work) return;
+  int local = wid;
+  if (!p.single) {
+    g = find_group(p.work, p.G, wid);
+    local = wid - p.work[g];
+    seg0 = p.seg_off[g];
+    cnt = p.seg_off[g + 1] - seg0;
+    wp = p.groups[g].width_pad;
+    hoff = p.h_off[g];
+    if (MODE == 2 && p.ws_skip && (wp == 352 || wp == 448 || wp == 704)) return;
+  }
+  // this workgroup's range of K steps (all of them without a K split); K counts from the start of the range
+  const int K_full = (MODE == 1) ? p.d : wp;
+  int K = K_full, k_first = 0;
+  if (p.k_split > 1) {
+    const int kt_all = (K_full + BK - 1) / BK;
+    const int per = (kt_all + p.k_split - 1) / p.k_split;
+    k_first = (k_part * per < kt_all ? k_part * per : kt_all) * BK;
+    const int k_end = ((k_part + 1) * per < kt_all) ? (k_part + 1) * per * BK : K_full;
+    K = k_end > k_first ? k_end - k_first : 0;
+  }
+  const int KT = (K + BK - 1) / BK;
+  const int n_cols = (MODE == 1) ? 2 * wp : p.d;
+  const int n_nt = (n_cols + BN - 1) / BN;
+  const int n_mt = (cnt + BM - 1) / BM;
+  constexpr int GM = 8;
+  const int sr = local / (GM * n_nt);
+  const int rem = local - sr * (GM * n_nt);
+  const int rows_in_sr = (n_mt - sr * GM) < GM ? (n_mt - sr * GM) : GM;
+  const int mt = sr * GM + rem % rows_in_sr;
+  const int nt = rem / rows_in_sr;
+
+  // Sources: transfer i of this wave fills block wave + i * NW; the lane writes physical chunk lane % 4 of row lane / 4
+  // and therefore fetches logical chunk (lane % 4) ^ (row >> 2) & 3.  Offsets count from the tile's first row
+  // (for a gather: the row of its first token; a segment's tokens ascend) and first column block.  Everything
+  // past the end of the segment, of the group's columns or of K (the loop fetches STAGES steps ahead to its end)
+  // is delivered as zeros.  (A product with zeros also draws less power than one with a repeated row, and the
+  // clock under MFMA load is set by power.)
+  const int coff = ((lane & 3) ^ ((lane >> 4) & 3)) << 3;
+  const int row_first = mt * BM;                               // of the segment
+  int64_t tok_first = 0;
+  const bf16_t* a_base;
+  int64_t a_bytes;                                             // from a_base to the end of the operand
+  if (MODE == 1) {
+    tok_first = __builtin_amdgcn_readfirstlane(p.slot2tok ? p.slot2tok[seg0 + row_first] : (seg0 + row_first));
+    a_base = p.A + tok_first * p.d + k_first;
+    a_bytes = ((p.T - tok_first) * p.d - k_first) * 2;
+  } else {
+    a_base = p.A + hoff + (int64_t)row_first * wp + k_first;
+    a_bytes = ((int64_t)(cnt - row_first) * wp - k_first) * 2;
+  }
+  a_base = uniform_ptr(a_base);
+  const uint32_t a_size = __builtin_amdgcn_readfirstlane((uint32_t)(a_bytes < (int64_t)DMA_NONE ? a_bytes : (int64_t)DMA_NONE));
+  uint32_t a_off[A_CH];
+  const bf16_t* a_src[WIDE ? A_CH : 1];
+#pragma unroll
+  for (int i = 0; i < A_CH; ++i) {
+    const int row = (wave + i * NW) * 16 + (lane >> 2);
+    const int r = row_first + row;
+    const bool ok = row < BM && r < cnt;
+    int64_t rel = row;                                         // row of A, relative to the first one
+    if (MODE == 1 && p.slot2tok) rel = ok ? p.slot2tok[seg0 + r] - tok_first : 0;
+    const int64_t off = rel * (MODE == 1 ? p.d : wp) + coff;
+    a_off[i] = ok ? (uint32_t)(off * 2) : DMA_NONE;
+    if constexpr (WIDE) a_src[i] = ok ? a_base + off : nullptr;
+  }
+  // K need not be a multiple of 32 (the weights are zero-padded, x is not): chunks of the last step past its end
+  const bool k_past = (KT - 1) * BK + coff >= K;
+  const int kt32 = (MODE == 1) ? p.ldb / TILE_K : wp / TILE_K;
+  const int col_blk0 = nt * (BN / 16);
+  const bf16_t* b_base = (MODE == 1) ? p.B + (int64_t)p.groups[g].w1_row0 * p.ldb : p.B + p.groups[g].w2_off;
+  b_base = uniform_ptr(b_base + ((int64_t)col_blk0 * kt32 + k_first / TILE_K) * TILE_ELEMS);
+  // column blocks the tile has: the rest of the buffer's size would be the next tile's
+  const int col_blks = min(BN / 16, (n_cols + 15) / 16 - col_blk0);
+  const uint32_t b_size = __builtin_amdgcn_readfirstlane((uint32_t)((col_blks * kt32 - k_first / TILE_K) * TILE_ELEMS * 2));
+  uint32_t b_off[B_CH];
+#pragma unroll
+  for (int i = 0; i < B_CH; ++i) {
+    const int blk = wave + i * NW;
+    b_off[i] = blk < col_blks ? (uint32_t)((blk * kt32 * TILE_ELEMS + (lane >> 2) * TILE_K + coff) * 2) : DMA_NONE;
+  }
+  auto issue_a = [&](int kt, int slot, int i) {
+    bf16_t* dst = smem + slot * STAGE_ELEMS + (wave + i * NW) * BLK;
+    if constexpr (WIDE) {
+      const bool none = a_src[i] == nullptr || kt >= KT || (kt == KT - 1 && k_past);
+      dma16(none ? (const void*)g_zero_chunk : (const void*)(a_src[i] + kt * BK), dst);
+    } else {
+      dma16_buffer(a_base, kt < KT ? a_size : 0u, (kt == KT - 1 && k_past) ? DMA_NONE : a_off[i], (uint32_t)kt * (BK * 2), dst);
+    }
+  };
+  auto issue_b = [&](int kt, int slot, int i) {
+    dma16_buffer(b_base, kt < KT ? b_size : 0u, b_off[i], (uint32_t)kt * (TILE_ELEMS * 2), smem + slot * STAGE_ELEMS + A_ELEMS + (wave + i * NW) * BLK);
+  };
+
+  // accumulator blocks of 16 x 16 (transposed, see mfma_acc): a lane holds columns kq * 4 .. + 3 of row r16
+  floatx4_t acc[MB][NB];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[mb][nb][i] = 0.0f;
+
+  // a lane's fragment of a block: row r16, logical chunk kq
+  const int frag = r16 * BK + ((kq ^ (r16 >> 2)) << 3);
+  constexpr int NM = MB * NB * KU, NF = (MB + NB) * KU, ND = LPT * KU;   // MFMAs, LDS reads and transfers per step
+  static_assert(ND <= NM, "at most one DMA instruction after an MFMA");
+  bf16x8_t af[2][KU][MB], wf[2][KU][NB];
+  auto load_frag = [&](int slot, int f, int set) {            // per K32: B fragments first, then A
+    const int u = f / (MB + NB), q = f % (MB + NB);
+    const bf16_t* st = smem + (slot * KU + u) * STAGE_ELEMS + frag;
+    if (q < NB) wf[set][u][q] = *reinterpret_cast<const bf16x8_t*>(st + A_ELEMS + (wn * NB + q) * BLK);
+    else af[set][u][q - NB] = *reinterpret_cast<const bf16x8_t*>(st + (wm * MB + q - NB) * BLK);
+  };
+  auto issue = [&](int step, int slot, int i) {               // transfer i of a step
+    const int u = i / LPT, q = i % LPT;
+    if (q < A_CH) issue_a(step * KU + u, slot * KU + u, q);
+    else issue_b(step * KU + u, slot * KU + u, q - A_CH);
+  };
+
+#pragma unroll
+  for (int st = 0; st < STAGES; ++st)
+#pragma unroll
+    for (int i = 0; i < ND; ++i) issue(st, st, i);
+  wait_vmcnt<(STAGES - 1) * ND>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int f = 0; f < NF; ++f) load_frag(0, f, 0);
+
+  const int n_steps = (KT + KU - 1) / KU;
+  int slot = 0;                                               // of the current step
+  auto step = [&](int ks, auto set_tag) {
+    constexpr int SET = decltype(set_tag)::value;
+    // Bare barrier: __syncthreads() would add a fence that drains every outstanding load.  What the barrier has to
+    // order is covered by hand: this wave's parts of step ks + 1 have landed (vmcnt), and its LDS reads of step
+    // ks have returned (lgkmcnt), so behind it step ks + 1 can be read and the slot of step ks refilled.
+    wait_vmcnt<(STAGES - 2) * ND>();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const int next = slot + 1 == STAGES ? 0 : slot + 1;
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      const int u = m / (MB * NB), mb = (m / NB) % MB, nb = m % NB;
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_acc(acc[mb][nb], wf[SET][u][nb], af[SET][u][mb]);
+      __builtin_amdgcn_sched_barrier(0);
+      // fragment f of the next step follows MFMA f * (3/4 NM) / NF: the last ones have a quarter of a step to return
+      const int f = (m * NF * 4 + NM * 3 - 1) / (NM * 3);
+      if (f < NF && f * NM * 3 / (NF * 4) == m) load_frag(next, f, SET ^ 1);
+      // (a small tile has more of them than MFMAs in three quarters of a step: then two follow one MFMA)
+      if (f + 1 < NF && (f + 1) * NM * 3 / (NF * 4) == m) load_frag(next, f + 1, SET ^ 1);
+      // DMA instruction i follows MFMA (i + 1) * NM / ND - 1
+      const int i = ((m + 1) * ND + NM - 1) / NM - 1;
+      if (i < ND && (i + 1) * NM / ND - 1 == m) issue(ks + STAGES, slot, i);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    slot = next;
+  };
+  int ks = 0;
+  for (; ks + 1 < n_steps; ks += 2) {
+    step(ks, std::integral_constant<int, 0>{});
+    step(ks + 1, std::integral_constant<int, 1>{});
+  }
+  if (ks < n_steps) step(ks, std::integral_constant<int, 0>{});
+  mfma_drain();
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- K split: the raw fp32 partial sums go to this part's slab, four consecutive columns per 16-byte store
+  // (the slab's row stride is d or 2 * max_width_pad, a multiple of 8) ----
+  if (p.k_split > 1) {
+    wait_vmcnt<0>();                                          // (no transfer into LDS may outlive the workgroup)
+    float* slab = p.P + (int64_t)k_part * p.p_rows * p.ldp;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      const int r = mt * BM + (wm * MB + mb) * 16 + r16;
+      if (r >= cnt) continue;
+      float* prow = slab + (int64_t)(seg0 + r) * p.ldp;
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const int col = nt * BN + wn * TN + nb * 16 + kq * 4;
+        if (col < n_cols) *reinterpret_cast<floatx4_t*>(prow + col) = acc[mb][nb];
+      }
+    }
+    return;
+  }
+  // ---- epilogue: through LDS, so that global stores are 16-byte vectors along the rows ----
+  // Each wave stages its tile in a private LDS strip (row stride padded by 16 bytes against bank conflicts), then
+  // every lane copies 16-byte pieces of rows out to global memory.
+  constexpr int TNO = (MODE == 1) ? TN / 2 : TN;          // output columns of a wave tile
+  constexpr int LDO = TNO + 8;                            // strip row stride in elements
+  constexpr int CPRO = TNO / 8;                           // 16-byte pieces per strip row
+  static_assert(NW * TM * LDO == ring_strip_elems(BM, BN, WGN, MODE), "strips");
+  wait_vmcnt<0>();
+  __syncthreads();                                        // every wave's reads of the ring and transfers into it are done
+  bf16_t* strip = smem + wave * TM * LDO;
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    bf16_t* srow = strip + (mb * 16 + r16) * LDO + kq * 4;
+    if constexpr (MODE == 1) {
+      // column blocks of a gate/up pair: two of 16 gate columns, then the two of the matching up columns
+#pragma unroll
+      for (int pb = 0; pb < NB / 2; ++pb) {
+        const floatx4_t gt = acc[mb][(pb / 2) * 4 + pb % 2], up = acc[mb][(pb / 2) * 4 + 2 + pb % 2];
+        // Swish(g) * u with the hardware exponential: the result is rounded to bf16 right after
+        ushort4 v;
+        v.x = f32_to_bf16(gt[0] * __frcp_rn(1.0f + __expf(-gt[0])) * up[0]);
+        v.y = f32_to_bf16(gt[1] * __frcp_rn(1.0f + __expf(-gt[1])) * up[1]);
+        v.z = f32_to_bf16(gt[2] * __frcp_rn(1.0f + __expf(-gt[2])) * up[2]);
+        v.w = f32_to_bf16(gt[3] * __frcp_rn(1.0f + __expf(-gt[3])) * up[3]);
+        *reinterpret_cast<ushort4*>(srow + pb * 16) = v;
+      }
+    } else {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        ushort4 v;
+        v.x = f32_to_bf16(acc[mb][nb][0]);
+        v.y = f32_to_bf16(acc[mb][nb][1]);
+        v.z = f32_to_bf16(acc[mb][nb][2]);
+        v.w = f32_to_bf16(acc[mb][nb][3]);
+        *reinterpret_cast<ushort4*>(srow + nb * 16) = v;
+      }
+    }
+  }
+  const int out_col0 = (MODE == 1) ? (nt * BN + wn * TN) / 2 : nt * BN + wn * TN;
+  const int out_cols = (MODE == 1) ? wp : p.d;
+  bf16_t* out_base = (MODE == 1) ? p.C + hoff : p.C + (int64_t)seg0 * p.d;
+  const int64_t out_ld = (MODE == 1) ? wp : p.d;
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the strip is private to this wave: no barrier
+  const int row0 = mt * BM + wm * TM;
+#pragma unroll 4
+  for (int q = lane; q < TM * CPRO; q += 64) {
+    const int rr = q / CPRO, cc = q % CPRO;
+    const int r = row0 + rr;
+    const int col = out_col0 + cc * 8;
+    const uint4 v = *reinterpret_cast<const uint4*>(strip + rr * LDO + cc * 8);
+    if (r < cnt && col < out_cols) *reinterpret_cast<uint4*>(out_base + (int64_t)r * out_ld + col) = v;
+  }
+}
+
 // ---- tile configurations ---------------------------------------------------------------------
 // Tile shapes (the tuning switches gemm1_cfg / gemm2_cfg select one by index).
 // stages >= 2: ring of whole K tiles; stages == 0: ring of five half tiles.
 struct TileCfg { int bm, bn, wgm, wgn, stages, bk; };
 static const TileCfg kCfgs[] = {
-    {256, 256, 2, 4, 0, 64},   // 0: half-tile ring, eight waves of 128x64
+    {256, 256, 2, 4, 5, 32},   // 0: deep ring (see grouped_gemm_bf16_ring), eight waves of 128x64
     {128, 128, 2, 2, 2, 64},   // 1: two stages, two workgroups per CU
     {256, 256, 2, 4, 2, 64},   // 2
     {128, 128, 2, 2, 0, 64},   // 3
     {256, 128, 4, 2, 3, 64},   // 4
     {256, 256, 2, 4, 4, 32},   // 5
-    {256, 256, 2, 2, 0, 64},   // 6: half-tile ring, four waves of 128x128, one per SIMD: a third less LDS read
-                               //    traffic than 0, 5-8 % faster under the power limit (the large-tile default)
+    {256, 256, 2, 2, 5, 32},   // 6: deep ring, four waves of 128x128
     {64, 128, 2, 2, 4, 64},    // 7: skinny tile for batches of tens of tokens per group, four whole K tiles deep: a
                                //    CU keeps 72 KB of loads in flight, two thirds of them weights (such a launch
                                //    is bound by HBM latency x bytes in flight, not by MFMA work).  Measured against
@@ -510,8 +876,7 @@ static const TileCfg kCfgs[] = {
     {128, 256, 2, 2, 3, 32},   // 8: four waves of 64x128, three K tiles of 32: 72 KB of LDS and at most 256 registers,
                                //    so two workgroups share a CU and one's epilogue overlaps the other's K loop
                                //    (the short-K down contraction; 256x128 in the same arrangement was slower)
-    {224, 256, 1, 4, 0, 64},   // 9: four waves of 224x64 (all rows, a quarter of the columns each): 7/8 of the
-                               //    MFMA work of 6 per tile, for segments that fill 256-row tiles poorly
+    {224, 256, 2, 2, 5, 32},   // 9: deep ring, four waves of 112x128
     {192, 256, 1, 4, 0, 64},   // 10: four waves of 192x64
     {256, 256, 1, 4, 0, 64},   // 11: four waves of 256x64 with a dynamic tile height (DYN): a ragged segment's last tile
                                //     costs its rows in steps of 32, so the tallest tile wastes the least
@@ -528,6 +893,9 @@ static const TileCfg kCfgs[] = {
     {256, 256, 2, 2, 0, 32},
     {512, 256, 2, 2, 0, 32},
     {1024, 256, 2, 2, 0, 32},  // 18: the same with 1024 rows per item
+    {160, 256, 2, 2, 5, 32},   // 19: deep ring, four waves of 80x128
+    {128, 128, 2, 2, 5, 32},   // 20: deep ring, four waves of 64x64
+    {64, 128, 2, 2, 6, 32},    // 21: deep ring in steps of 64, four waves of 32x64, two workgroups per CU
 };
 static bool cfg_is_ws(int ci) { return ci >= 15 && ci <= 18; }
 static bool cfg_is_dyn(int ci) { return ci >= 11 && ci <= 18; }
@@ -536,45 +904,59 @@ hipError_t launch_ws_down(const Engine& e, char* ws, const WsLayout& L, const vo
                           int xcd_remap, hipStream_t s);
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
 
+// Rows of x that one tile gathers can be 2 GB or more apart.
+static bool wide_gather(int d, int64_t T) { return T * d * 2 >= (int64_t)DMA_NONE; }
+
 // Which tile shape for contraction `which` (1: gate/up, 2: down) of a batch of T tokens: the tuning switches
 // gemm1_cfg / gemm2_cfg when set, else the models below.
 // Tile shape of the gate/up contraction: the one with the lowest estimated time = rounds x time per round,
 // rounds = ceil(tiles / workgroup slots on the chip).  Relative times per round measured on the
-// LLaMA-shaped layers (K = d for every shape, so the ratios carry over), in units of the eight-wave
-// 256x256 tile: 256x256 with four waves 0.95 (one workgroup per CU), 256x128 0.58 (one per CU), 128x128
-// 0.66 (two per CU), 64x128 0.30 (one per CU; it only wins while the launch is one or two rounds, i.e. up to
-// 128 tokens for the dense FFN and about 200 for the 16-expert layer).  224x256 and 192x256 tiles (four waves
-// side by side, each over all rows of the tile: a quarter more LDS reads per MFMA than 128x128 per wave) take
-// 0.875 and 0.81: when ragged segments fill 256-row tiles poorly, a lower tile with the same number of rounds
-// does less padded work (16 experts at 4096 tokens: 820 rows are four tiles either way, 204 -> 187 us).
-// The model picks the measured best shape at every batch size from 33 to 8192 tokens or one within a few
-// per cent of it.
+// LLaMA-shaped layers (K = d for every shape, so the ratios carry over): 256x256 0.95 (one workgroup per CU),
+// 224x256 0.875, 192x256 0.81, 160x256 0.75, 256x128 0.62, 128x128 0.66 with two per CU and, on the deep ring, 0.51
+// with one (333 tokens of the 16-expert layer: 112 -> 105 us; two of the ring's per CU are slower than two of
+// the other kernel's), 64x128 0.30 (one per CU; it only wins while the launch is one or two rounds, i.e. up to
+// 128 tokens for the dense FFN and about 200 for the 16-expert layer).  When ragged segments fill 256-row tiles
+// poorly, a lower tile with the same number of rounds does less padded work (16 experts at 4096 tokens: 820
+// rows are four tiles either way, 387 -> 367 us per forward).
+// Up to a model width of 2048 the 64x128 tile runs on the deep ring, two per CU: a K loop of 16 to 32 steps of 64 is
+// mostly prologue, which two workgroups share (d = 1024: 32.0 -> 31.2 us per forward at 20 tokens, d = 2048, 777
+// tokens: 64.4 -> 61.4; d = 4096 the other way round, 59.6 against 62.4 at 20 tokens).
+// The number of row tiles of the routed groups is an estimate, the full ones plus half a tile per touched group; a
+// group's last tile is filled uniformly between nothing and everything, so the sum strays by sqrt(groups / 12)
+// row tiles: the rounds are averaged over the estimate and two such deviations more (none where every touched group
+// has but one row tile).  (A flat margin of 8 %
+// counted a further round where there was none: 32 experts, 2048 tokens: 294 -> 270 us.)
 static int gate_up_cfg(const Engine& e, int64_t T) {
   struct Cand { int cfg, bm, bn, slots; double t; };
   const bool single = e.G == 1 && e.n_always == 1;
-  const Cand cands[] = {{3, 128, 128, 2, 0.66}, {4, 256, 128, 1, 0.58}, {6, 256, 256, 1, 0.95}, {7, 64, 128, 1, 0.30},
-                        {9, 224, 256, 1, 0.875}, {10, 192, 256, 1, 0.81}};
+  const bool narrow = e.d <= 2048;
+  const Cand cands[] = {{3, 128, 128, 512, 0.66}, {4, 256, 128, 256, 0.62}, {6, 256, 256, 256, 0.95},
+                        {narrow ? 21 : 7, 64, 128, narrow ? 512 : 256, narrow ? 0.45 : 0.30},
+                        {9, 224, 256, 256, 0.875}, {10, 192, 256, 256, 0.81}, {19, 160, 256, 256, 0.75}, {20, 128, 128, 256, 0.51}};
   int best = 0;
   double best_t = 1e30;
   for (const Cand& c : cands) {
-    // a tile of 192 rows or more for groups that average less than a quarter of it streams its weights at the
+    // a tile of 160 rows or more for groups that average less than a quarter of it streams its weights at the
     // pace of a full tile (measured with 256 rows at 224-256 tokens on 16 experts: 61 us against 52 us with
     // 128x128)
-    if (!single && c.bm >= 192 && T * e.S_dyn * 4 < (int64_t)std::min<int64_t>(e.G - e.n_always, T * e.S_dyn) * c.bm) continue;
-    int64_t tiles = 0;
+    if (!single && c.bm >= 160 && T * e.S_dyn * 4 < (int64_t)std::min<int64_t>(e.G - e.n_always, T * e.S_dyn) * c.bm) continue;
+    int64_t tiles = 0, hi = 0;
     for (int g = 0; g < e.n_always; ++g) tiles += ((T + c.bm - 1) / c.bm) * cdiv(2 * e.width_pad_host[g], c.bn);
+    hi = tiles;
     if (!single && e.G > e.n_always) {
       const int64_t entries = T * e.S_dyn;
       const int64_t touched = std::min<int64_t>(e.G - e.n_always, entries);
-      const int64_t rows = std::max<int64_t>((entries + c.bm - 1) / c.bm + touched / 2, touched);
-      tiles += rows * cdiv(2 * e.width_pad_host[e.n_always], c.bn);
+      const int64_t full = (entries + c.bm - 1) / c.bm + touched / 2, rows = std::max<int64_t>(full, touched);
+      const int64_t cols = cdiv(2 * e.width_pad_host[e.n_always], c.bn);
+      tiles += rows * cols;
+      hi = tiles;
+      if (full > touched) hi += (int64_t)(2.0 * std::sqrt((double)touched / 12.0) * (double)cols + 0.5);
     }
-    // the routed groups' partial tiles are an estimate: average over the estimate and 8 % more
-    const int64_t slots = 256 * c.slots, hi = single ? tiles : tiles + (tiles * 2 + 24) / 25;
-    double t = 0.5 * c.t * (double)((tiles + slots - 1) / slots + (hi + slots - 1) / slots);
-    // the skinny tile runs one workgroup per CU and its rounds are long: when the estimate is within 8 % of
+    double t = 0.5 * c.t * (double)((tiles + c.slots - 1) / c.slots + (hi + c.slots - 1) / c.slots);
+    if (c.cfg == 21 && hi <= 256) t = 0.30;                    // one workgroup on a CU
+    // the skinny tile runs one workgroup per CU and its rounds are long: when the estimate is close to
     // spilling into a second, nearly empty round, count that round in full
-    if (c.cfg == 7 && !single && tiles <= slots && hi > slots) t = 2.3 * c.t;      // (above one round of 128x128)
+    if (c.cfg == 7 && !single && tiles <= c.slots && hi > c.slots) t = 2.3 * c.t;      // (above one round of 128x128)
     if (t < best_t) {
       best_t = t;
       best = c.cfg;
@@ -599,11 +981,16 @@ static int cfg_index(int which, const Engine& e, int64_t T) {
       // a round of 256 tiles of 256x256 (eight waves, one workgroup per CU) and a round of 512 tiles of 128x256
       // (two per CU) take the same time, a round of 512 tiles of 128x128 two thirds of it.  The 128-row tiles
       // waste less of a ragged segment, and two workgroups on a CU overlap one's epilogue with the other's
-      // K loop; a single round of the two-per-CU shape costs 1.4 (both workgroups of a CU start together).
-      const int64_t n0 = est_tiles(e, T, 2, 256, 256), n9 = est_tiles(e, T, 2, 128, 256), n3 = est_tiles(e, T, 2, 128, 128);
-      const int64_t r0 = (n0 + 255) / 256, r9 = (n9 + 511) / 512, r3 = (n3 + 511) / 512;
-      const double t0 = (double)r0, t9 = (double)r9 + (r9 == 1 ? 0.4 : 0.0), t3 = 0.66 * (double)r3;
+      // K loop; a single round of the two-per-CU shape costs 1.4 (both workgroups of a CU start together), a round
+      // of 512 tiles of 64x128 on the deep ring 0.42 up to two of them, 0.5 beyond: the shape of batches of tens to a few hundred tokens, where
+      // an expert has fewer rows than a taller tile (8 experts of 704 at d = 2048, 512 tokens: 56 -> 48 us per
+      // forward; 28 of 448 at d = 4096, 64 tokens: 98.6 -> 93.5).
+      const int64_t n0 = est_tiles(e, T, 2, 256, 256), n9 = est_tiles(e, T, 2, 128, 256), n3 = est_tiles(e, T, 2, 128, 128),
+                    n21 = est_tiles(e, T, 2, 64, 128);
+      const int64_t r0 = (n0 + 255) / 256, r9 = (n9 + 511) / 512, r3 = (n3 + 511) / 512, r21 = (n21 + 511) / 512;
+      const double t0 = (double)r0, t9 = (double)r9 + (r9 == 1 ? 0.4 : 0.0), t3 = 0.66 * (double)r3, t21 = (r21 <= 2 ? 0.42 : 0.5) * (double)r21;
       dflt = (t3 < t9 && t3 < t0) ? 3 : (t9 <= t0 ? 8 : 0);
+      if (k_min <= 1024 && t21 < std::min(t3, std::min(t9, t0))) dflt = 21;      // (K = 1408: 134 -> 138 us at 64 tokens)
     } else {
       // Deep K (dense FFN, un-restructured experts): 256x256 tiles with four waves when every CU gets one;
       // below that 256x128, whose round takes 0.56 of the time, unless it would need a second round; 128x128
@@ -623,6 +1010,7 @@ static int cfg_index(int which, const Engine& e, int64_t T) {
       }
     }
   }
+  if (which == 1 && e.S_dyn > 0 && wide_gather(e.d, T)) return 6;      // (the only ring shape built with 64-bit row addresses)
   const int forced = which == 1 ? tuning().gemm1_cfg : tuning().gemm2_cfg;
   if (forced >= 0 && forced < kNumCfgs && !(which == 1 && cfg_is_ws(forced))) return forced;
   if (which == 2 && tuning().ws_down != 0 && !(e.G == 1 && e.n_always == 1) && e.w_tiled && e.d % 256 == 0) {
@@ -696,7 +1084,7 @@ int bf16_splitk(const Engine& e, int64_t T, int which) {
   // Split only while the launch stays well inside one round of workgroups (two tiles of 128 rows fit a CU, one of
   // the larger shapes): measured at 64..512 tokens, splitting a launch that already has a tile for most
   // CUs costs more (partial sums, a second launch) than the shorter K loop saves.
-  const int64_t slots = c.bm == 128 ? 2 : 1;
+  const int64_t slots = (c.bm == 128 && c.stages != 5) ? 2 : 1;      // (the deep ring's 128x128 counts as one per CU)
   while (ks < 8 && tiles * ks * 2 <= 192 * slots && kt / (ks * 2) >= 4 && per_part * ks * 2 <= SPLITK_MAX_BYTES) ks *= 2;
   return ks;
 }
@@ -779,23 +1167,37 @@ static hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
   return launch_kernel(grouped_gemm_bf16_dma<BM, BN, BKT, STAGES, WGM, WGN, MODE, DYN>, smem, WGM * WGN * 64, attr_done, a, s);
 }
 
+template <int BM, int BN, int STAGES, int KU, int WGM, int WGN, int MODE, bool WIDE = false>
+static hipError_t launch_ring(const GemmArgs& a, hipStream_t s) {
+  static bool attr_done = false;
+  constexpr size_t smem = ring_smem_bytes(BM, BN, STAGES * KU, WGM * WGN, WGN, MODE);
+  static_assert(smem <= 160 * 1024, "LDS of a CU");
+  return launch_kernel(grouped_gemm_bf16_ring<BM, BN, STAGES, KU, WGM, WGN, MODE, WIDE>, smem, WGM * WGN * 64, attr_done, a, s);
+}
+
 template <int MODE>
 static hipError_t launch_cfg(int ci, const GemmArgs& a, hipStream_t s) {
   switch (ci) {
-    case 0: return launch_dma<256, 256, 64, 0, 2, 4, MODE>(a, s);
+    case 0: return launch_ring<256, 256, 5, 1, 2, 4, MODE>(a, s);
     case 1: return launch_dma<128, 128, 64, 2, 2, 2, MODE>(a, s);
     case 2: return launch_dma<256, 256, 64, 2, 2, 4, MODE>(a, s);
     case 3: return launch_dma<128, 128, 64, 0, 2, 2, MODE>(a, s);
     case 4: return launch_dma<256, 128, 64, 3, 4, 2, MODE>(a, s);
-    case 6: return launch_dma<256, 256, 64, 0, 2, 2, MODE>(a, s);
+    case 6:
+      if constexpr (MODE == 1)
+        if (a.slot2tok && wide_gather(a.d, a.T)) return launch_ring<256, 256, 5, 1, 2, 2, MODE, true>(a, s);
+      return launch_ring<256, 256, 5, 1, 2, 2, MODE>(a, s);
     case 7: return launch_dma<64, 128, 64, 4, 2, 2, MODE>(a, s);
     case 8: return launch_dma<128, 256, 32, 3, 2, 2, MODE>(a, s);
-    case 9: return launch_dma<224, 256, 64, 0, 1, 4, MODE>(a, s);
+    case 9: return launch_ring<224, 256, 5, 1, 2, 2, MODE>(a, s);
     case 10: return launch_dma<192, 256, 64, 0, 1, 4, MODE>(a, s);
     case 11: return launch_dma<256, 256, 64, 0, 1, 4, MODE, true>(a, s);
     case 12: return launch_dma<128, 256, 32, 3, 1, 4, MODE, true>(a, s);
     case 13: return launch_dma<256, 256, 64, 0, 2, 2, MODE, true>(a, s);
     case 14: return launch_dma<128, 256, 32, 3, 2, 2, MODE, true>(a, s);
+    case 19: return launch_ring<160, 256, 5, 1, 2, 2, MODE>(a, s);
+    case 20: return launch_ring<128, 128, 5, 1, 2, 2, MODE>(a, s);
+    case 21: return launch_ring<64, 128, 3, 2, 2, 2, MODE>(a, s);
     default: return launch_dma<256, 256, 32, 4, 2, 4, MODE>(a, s);
   }
 }
@@ -823,7 +1225,7 @@ hipError_t launch_experts_bf16(const Engine& e, const void* x, int64_t T, char* 
   a.work = reinterpret_cast<const int32_t*>(ws + L.work1);
   a.slot2tok = a.single ? nullptr : reinterpret_cast<const int32_t*>(ws + L.slot2tok);
   {
-    // An XCD's share of a work list has equal estimated cost, not equal length (see place_tile): with tiles of
+    // An XCD's share of a work list has equal estimated cost, not equal length (see place_lists): with tiles of
     // dynamic height the cheapest tile counts 3 blocks of 32 rows and a full one bm / 32, so the longest share
     // can hold that many times an eighth of the list.
     const int ci = cfg_index(1, e, T);

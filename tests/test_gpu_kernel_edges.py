@@ -1,0 +1,78 @@
+"""GPU parity of the tile shapes, routing kernels and decode kernels at the sizes where their indexing can go wrong,
+against the CPU oracle (tolerances of parity_utils: 1e-2 for bf16, indices exact)."""
+import numpy as np
+import pytest
+
+from paper_2502_04416_amd import synth
+from parity_utils import check_dense, check_flat
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def binding():
+    from paper_2502_04416_amd import binding as b
+    b.load()
+    return b
+
+
+def _case(binding, d, N, m, n_s, k, T, seed=0, **kw):
+    cfg = synth.scaled(synth.CONFIGS[1], d_model=d, d_ff=N * m, n_experts=N, n_shared=n_s, top_k=k, n_centres=16)
+    weights = synth.make_weights(cfg, seed=3100 + seed)
+    part = synth.trivial_partition(cfg, seed=seed)
+    x = synth.make_token_source(cfg).eval_batch(seed, n=T)
+    layer = binding.Layer.from_partition(cfg, *weights, part["neuron_order"], part["rep_neuron"], **kw)
+    return cfg, weights, part, x, layer
+
+
+@pytest.mark.parametrize("which", ["CMOE_GEMM1_CFG", "CMOE_GEMM2_CFG"])
+@pytest.mark.parametrize("shape", [0, 6, 9, 19, 20, 21])
+@pytest.mark.parametrize("d,m,T", [(328, 100, 333), (40, 32, 300), (64, 48, 257), (96, 20, 161)])
+def test_deep_ring_shapes(binding, which, shape, d, m, T):
+    """The deep-ring tile shapes on K loops shorter than the ring (d = 40: two steps, the second ragged; width 32: one
+    step), of odd and even length, with row tiles, column tiles and 16-row blocks that end inside."""
+    cfg, weights, part, x, layer = _case(binding, d, 12, m, 2, 3, T)
+    try:
+        binding.cmoe_set_tuning("CMOE_SPLITK", 0)
+        ref = layer.forward(x)
+        binding.cmoe_set_tuning(which, shape)
+        out, dense = layer.forward(x), layer.dense_forward(x)
+    finally:
+        binding.cmoe_set_tuning("CMOE_SPLITK", 1)
+        binding.cmoe_set_tuning(which, -1)
+    check_flat(cfg, weights, part, x, out)
+    check_dense(cfg, weights, x, dense)
+    assert np.array_equal(out["y"], ref["y"])          # K in the same order: the shape changes no bit
+    layer.close()
+
+
+@pytest.mark.parametrize("shape", [6, 20, 21])
+def test_deep_ring_k_split(binding, shape):
+    """Partial sums of a K split whose last part is empty or short (d = 576: 18 steps over up to 4 parts)."""
+    cfg, weights, part, x, layer = _case(binding, 576, 8, 64, 1, 2, 90)
+    try:
+        binding.cmoe_set_tuning("CMOE_GEMM1_CFG", shape)
+        out, dense = layer.forward(x), layer.dense_forward(x)
+    finally:
+        binding.cmoe_set_tuning("CMOE_GEMM1_CFG", -1)
+    check_flat(cfg, weights, part, x, out)
+    check_dense(cfg, weights, x, dense)
+    layer.close()
+
+
+def test_gather_across_two_gigabytes(binding):
+    """A batch whose rows lie 2 GB and more apart: 64-bit row addresses in the gate/up contraction.  A forward of
+    the same tokens in two smaller batches gives the same bits token by token."""
+    import torch
+    T, d = 262144 + 77, 4096
+    cfg = synth.scaled(synth.CONFIGS[1], d_model=d, d_ff=8 * 32, n_experts=8, n_shared=1, top_k=1, n_centres=16)
+    part = synth.trivial_partition(cfg)
+    layer = binding.Layer.from_partition(cfg, *synth.make_weights(cfg), part["neuron_order"], part["rep_neuron"])
+    x = torch.randn((T, d), generator=torch.Generator(device="cuda").manual_seed(5), device="cuda", dtype=torch.bfloat16)
+    y, half, y2 = torch.empty_like(x), 131072, torch.empty_like(x)
+    layer.forward_device(x, y)
+    # (a multiple of 16384 tokens per piece keeps the router's K slices, hence its scores, those of the whole batch)
+    for lo, hi in ((0, half), (half, T)):
+        layer.forward_device(x[lo:hi], y2[lo:hi])
+    assert torch.equal(y, y2)
+    layer.close()
