@@ -42,7 +42,7 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Padded widths of the (at most two) groups a lane looks after in place_tile; a caller with other work to
+// Padded widths of the (at most two) groups a lane looks after in place_lists; a caller with other work to
 // do first requests them early so that their latency is hidden.
 struct LaneWidths { int w[MAX_GROUPS / 64]; };
 __device__ __forceinline__ LaneWidths load_lane_widths(const PlaceArgs& p, int lane) {
@@ -55,75 +55,81 @@ __device__ __forceinline__ LaneWidths load_lane_widths(const PlaceArgs& p, int l
   return lw;
 }
 
-// One wave places one 64-token tile.  `counts` is the per-tile histogram table [n_tiles][G] (global memory, or
-// LDS when the caller is the single-tile decode front end); sel_g / sel_w are the routed entries
-// [T][S_dyn] (the workspace arrays, or an LDS copy of the caller).  Must be called by exactly 64 threads
-// (lane = id).  Cost is O(S_dyn + G/64) per lane: the prefix over groups is a wave scan (two groups per
-// lane), and the rank of a token inside its group comes from a 64-bit presence mask per group that the
-// lanes build with LDS atomics, not from a pass over all groups.
-__device__ __forceinline__ void place_tile(const PlaceArgs& p, int tile, const int32_t* counts, int lane,
-                                           const int32_t* sel_g, const float* sel_w, const LaneWidths& lw) {
+// Tokens of the batch in each of a lane's groups, and how many of them lie in the tiles before this one.
+struct TileCounts { int tot[MAX_GROUPS / 64], prev[MAX_GROUPS / 64]; };
+
+// A batch of one tile: the counts are its own histogram (LDS).
+__device__ __forceinline__ TileCounts single_tile_counts(const PlaceArgs& p, const int32_t* hist, int lane) {
+  TileCounts tc;
+#pragma unroll
+  for (int k = 0; k < MAX_GROUPS / 64; ++k) {
+    const int g = lane + 64 * k;
+    tc.tot[k] = g >= p.G ? 0 : g < p.n_always ? (int)p.T : hist[g];
+    tc.prev[k] = 0;
+  }
+  return tc;
+}
+
+// One wave assigns the slots of one 64-token tile from its routed entries sel_g / sel_w [64][S_dyn] (LDS; those of
+// tokens past T are not read).  Must be called by exactly 64 threads (lane = id).  Cost is
+// O(S_dyn + G/64) per lane: the prefix over groups is a wave scan (two groups per lane), and the rank of a token
+// inside its group comes from a 64-bit presence mask per group that the lanes build with LDS atomics, not from a
+// pass over all groups.
+__device__ __forceinline__ void place_slots(const PlaceArgs& p, int tile, const TileCounts& tc, const int32_t* sel_g,
+                                            const float* sel_w, int lane) {
   constexpr int GPL = MAX_GROUPS / 64;      // groups per lane
   __shared__ int32_t base[MAX_GROUPS];      // first slot of each group for this tile
   __shared__ uint32_t present[MAX_GROUPS][2];   // which lanes (tokens of the tile) have an entry for the group
   const int S_all = p.n_always + p.S_dyn;
   const int64_t t = (int64_t)tile * TOK_TILE + lane;
   const bool valid = t < p.T;
-  // this token's routed entries, requested first: nothing below depends on them until the marking pass
-  // (S_dyn and G are the same for every lane: the unrolled loops below leave at the first unused entry
-  // through a scalar branch instead of running all MAX_DYN predicated bodies; one wave pays four cycles
-  // for every vector instruction, used or not)
-  int my_g[MAX_DYN];
-  float my_w[MAX_DYN];
-#pragma unroll
-  for (int i = 0; i < MAX_DYN; ++i) {
-    if (i >= p.S_dyn) break;
-    my_g[i] = valid ? sel_g[t * p.S_dyn + i] : -1;
-    my_w[i] = valid ? sel_w[t * p.S_dyn + i] : 0.0f;
-  }
 #pragma unroll
   for (int k = 0; k < GPL; ++k) {
     present[lane + 64 * k][0] = 0u;
     present[lane + 64 * k][1] = 0u;
   }
-  // totals and the count of all preceding tiles for this lane's groups
-  int tot[GPL], prev[GPL];
+  wave_lds_sync();                          // the cleared masks are visible to every lane
+  if (valid)
+    for (int i = 0; i < p.S_dyn; ++i) atomicOr(&present[sel_g[lane * p.S_dyn + i]][lane >> 5], 1u << (lane & 31));
+  int run0 = 0;
 #pragma unroll
   for (int k = 0; k < GPL; ++k) {
     const int g = lane + 64 * k;
-    tot[k] = 0;
-    prev[k] = 0;
-    if (64 * k >= p.G) continue;            // no lane has a group in this half
-    if (g < p.G) {
-      if (g < p.n_always) {
-        tot[k] = (int)p.T;
-      } else {
-        // independent loads, sixteen in flight at a time (the compiler does not batch them by itself)
-        int i = 0;
-        for (; i + 16 <= p.n_tiles; i += 16) {
-          int c[16];
-#pragma unroll
-          for (int q = 0; q < 16; ++q) c[q] = counts[(int64_t)(i + q) * p.G + g];
-#pragma unroll
-          for (int q = 0; q < 16; ++q) {
-            tot[k] += c[q];
-            prev[k] += (i + q < tile) ? c[q] : 0;
-          }
-        }
-        for (; i < p.n_tiles; ++i) {
-          const int c = counts[(int64_t)i * p.G + g];
-          tot[k] += c;
-          prev[k] += (i < tile) ? c : 0;
-        }
-      }
+    if (k > 0 && 64 * k >= p.G) continue;
+    const int inc = wave_incl_scan(tc.tot[k], lane);
+    if (g < p.G) base[g] = run0 + inc - tc.tot[k] + tc.prev[k];
+    run0 += __shfl(inc, 63, 64);
+  }
+  wave_lds_sync();                          // base[] and present[] are complete
+  // always-on groups: identity segments
+  if (valid)
+    for (int a = 0; a < p.n_always; ++a) {
+      const int slot = a * (int)p.T + (int)t;
+      p.slot2tok[slot] = (int)t;
+      p.tok2slot[t * S_all + a] = slot;
+      p.slot_w[t * S_all + a] = 1.0f;
+      p.w_by_slot[slot] = 1.0f;
     }
-  }
-  wave_lds_sync();                          // the cleared masks are visible to every lane
-#pragma unroll
-  for (int i = 0; i < MAX_DYN; ++i) {
-    if (i >= p.S_dyn) break;
-    if (my_g[i] >= 0) atomicOr(&present[my_g[i]][lane >> 5], 1u << (lane & 31));
-  }
+  // routed entries: stable (token-ascending) rank inside the group = lower lanes present in its mask
+  const uint32_t lt_lo = lane >= 32 ? 0xffffffffu : ((1u << lane) - 1u);
+  const uint32_t lt_hi = lane > 32 ? ((1u << (lane - 32)) - 1u) : 0u;
+  if (valid)
+    for (int i = 0; i < p.S_dyn; ++i) {
+      const int g = sel_g[lane * p.S_dyn + i];
+      const float w = sel_w[lane * p.S_dyn + i];
+      const int slot = base[g] + __popc(present[g][0] & lt_lo) + __popc(present[g][1] & lt_hi);
+      p.slot2tok[slot] = (int)t;
+      p.tok2slot[t * S_all + p.n_always + i] = slot;
+      p.slot_w[t * S_all + p.n_always + i] = w;
+      p.w_by_slot[slot] = w;
+    }
+}
+
+// One wave publishes what depends on the batch's counts alone: segment offsets, the work lists of the two
+// contractions and each group's offset in the hidden-activation buffer.  Run by another wave than the slots of
+// tile 0, next to it (both in one wave made that tile the last to finish).
+__device__ __forceinline__ void place_lists(const PlaceArgs& p, const TileCounts& tc, int lane, const LaneWidths& lw) {
+  constexpr int GPL = MAX_GROUPS / 64;
   // exclusive prefix over groups of: slots, work items of the two contractions, hidden-buffer elements
   int run0 = 0, w1_0 = 0, w2_0 = 0;
   long long h0 = 0;
@@ -135,7 +141,7 @@ __device__ __forceinline__ void place_tile(const PlaceArgs& p, int tile, const i
       n1[k] = 0; n2[k] = 0; w1x[k] = w1_0; w2x[k] = w2_0;
       continue;
     }
-    const int cnt = tot[k], wp = lw.w[k];
+    const int cnt = tc.tot[k], wp = lw.w[k];
     int a1, a2;
     if (p.decode) {
       a1 = cnt > 0 ? wp / p.dec_unit1 : 0;
@@ -153,126 +159,96 @@ __device__ __forceinline__ void place_tile(const PlaceArgs& p, int tile, const i
     const long long h = h0 + h_i - ah;
     n1[k] = a1; n2[k] = a2; w1x[k] = w1; w2x[k] = w2;
     if (g < p.G) {
-      base[g] = run + prev[k];
-      if (tile == 0) {
-        p.seg_off[g] = run;
-        p.counts[g] = cnt;
-        p.work1[g] = w1;
-        p.work2[g] = w2;
-        p.h_off[g] = h;
-        if (p.counts_out && g >= p.n_always) p.counts_out[g - p.n_always] = cnt;
-      }
+      p.seg_off[g] = run;
+      p.counts[g] = cnt;
+      p.work1[g] = w1;
+      p.work2[g] = w2;
+      p.h_off[g] = h;
+      if (p.counts_out && g >= p.n_always) p.counts_out[g - p.n_always] = cnt;
     }
     run0 += __shfl(run_i, 63, 64);
     w1_0 += __shfl(w1_i, 63, 64);
     w2_0 += __shfl(w2_i, 63, 64);
     h0 += __shfl(h_i, 63, 64);
   }
-  if (tile == 0) {
-    if (lane == 0) {
-      p.seg_off[p.G] = run0;
-      p.work1[p.G] = w1_0;
-      p.work2[p.G] = w2_0;
-      p.h_off[p.G] = h0;
-    }
+  if (lane == 0) {
+    p.seg_off[p.G] = run0;
+    p.work1[p.G] = w1_0;
+    p.work2[p.G] = w2_0;
+    p.h_off[p.G] = h0;
   }
-  if (tile == 0 && !p.decode) {            // (the decode kernels take their units in list order: no shares)
-    // Where each XCD's share of a work list starts (entries G+1 .. G+9 of the list): contiguous ranges of
-    // equal estimated cost, so that the tiles sharing operands stay in one L2 while the eight dies finish
-    // together.  A tile costs its depth (K steps of 64, plus a fixed part for prologue and epilogue: the shared
-    // group's down tiles are N_s times as deep as a routed expert's) times its height in 32-row blocks; with
-    // tiles of dynamic height the ragged last row tile of a group costs its own blocks (at least three: below
-    // that a tile is bound by fetching its weights), otherwise as much as a full one.  Inside a group the
-    // boundary falls in proportion to the cost.
-    __shared__ int32_t xs[2][N_XCD + 1];
-    if (lane <= N_XCD) {
-      xs[0][lane] = lane == N_XCD ? w1_0 : 0;
-      xs[1][lane] = lane == N_XCD ? w2_0 : 0;
-    }
-    wave_lds_sync();
+  if (p.decode) return;                    // (the decode kernels take their units in list order: no shares)
+  // Where each XCD's share of a work list starts (entries G+1 .. G+9 of the list): contiguous ranges of
+  // equal estimated cost, so that the tiles sharing operands stay in one L2 while the eight dies finish
+  // together.  A tile costs its depth (K steps of 64, plus a fixed part for prologue and epilogue: the shared
+  // group's down tiles are N_s times as deep as a routed expert's) times its height in 32-row blocks; with
+  // tiles of dynamic height the ragged last row tile of a group costs its own blocks (at least three: below
+  // that a tile is bound by fetching its weights), otherwise as much as a full one.  Inside a group the
+  // boundary falls in proportion to the cost.
+  __shared__ int32_t xs[2][N_XCD + 1];
+  if (lane <= N_XCD) {
+    xs[0][lane] = lane == N_XCD ? w1_0 : 0;
+    xs[1][lane] = lane == N_XCD ? w2_0 : 0;
+  }
+  wave_lds_sync();
 #pragma unroll
-    for (int list = 0; list < 2; ++list) {
-      const int bm = list == 0 ? p.bm1 : p.bm2, dyn = list == 0 ? p.dyn1 : p.dyn2;
-      const int blocks_full = bm / 32 > 0 ? bm / 32 : 1;
-      // (Which group a boundary falls into is decided in exact integers, so that every item lands in exactly
-      // one share; where inside the group, in single precision: the shares need to be about equal, not exact,
-      // and this wave is on the critical path of the whole forward: 64-bit divisions here doubled the
-      // kernel's duration.)
-      long long gc[GPL], gx[GPL];             // cost of this lane's groups and their exclusive prefix
-      long long c0 = 0;
+  for (int list = 0; list < 2; ++list) {
+    const int bm = list == 0 ? p.bm1 : p.bm2, dyn = list == 0 ? p.dyn1 : p.dyn2;
+    const int blocks_full = bm / 32 > 0 ? bm / 32 : 1;
+    // (Which group a boundary falls into is decided in exact integers, so that every item lands in exactly
+    // one share; where inside the group, in single precision: the shares need to be about equal, not exact,
+    // and this wave is on the critical path of the whole forward: 64-bit divisions here doubled the
+    // kernel's duration.)
+    long long gc[GPL], gx[GPL];             // cost of this lane's groups and their exclusive prefix
+    long long c0 = 0;
 #pragma unroll
-      for (int k = 0; k < GPL; ++k) {
-        gc[k] = 0;
-        gx[k] = c0;
-        if (k > 0 && 64 * k >= p.G) continue;
-        const int n_items = list == 0 ? n1[k] : n2[k];
-        const int cnt = tot[k], wp = lw.w[k];
-        if (n_items > 0) {
-          const int row_tiles = cdiv(cnt, bm), col_tiles = n_items / row_tiles;
-          const int depth = (list == 0 ? cdiv(p.d, 64) : cdiv(wp, 64)) + TILE_FIXED_COST;
-          const int full = cnt / bm, rem = cnt - full * bm;
-          int last = 0;
-          if (rem > 0) {
-            last = blocks_full;
-            if (dyn) {
-              last = cdiv(rem, dyn) * (dyn / 32);           // dyn = rows per height step
-              const int floor_blocks = blocks_full < 3 ? blocks_full : 3;
-              if (last < floor_blocks) last = floor_blocks;
-            }
+    for (int k = 0; k < GPL; ++k) {
+      gc[k] = 0;
+      gx[k] = c0;
+      if (k > 0 && 64 * k >= p.G) continue;
+      const int n_items = list == 0 ? n1[k] : n2[k];
+      const int cnt = tc.tot[k], wp = lw.w[k];
+      if (n_items > 0) {
+        const int row_tiles = cdiv(cnt, bm), col_tiles = n_items / row_tiles;
+        const int depth = (list == 0 ? cdiv(p.d, 64) : cdiv(wp, 64)) + TILE_FIXED_COST;
+        const int full = cnt / bm, rem = cnt - full * bm;
+        int last = 0;
+        if (rem > 0) {
+          last = blocks_full;
+          if (dyn) {
+            last = cdiv(rem, dyn) * (dyn / 32);           // dyn = rows per height step
+            const int floor_blocks = blocks_full < 3 ? blocks_full : 3;
+            if (last < floor_blocks) last = floor_blocks;
           }
-          gc[k] = (long long)col_tiles * depth * (full * blocks_full + last);
         }
-        const long long ci = wave_incl_scan(gc[k], lane);
-        gx[k] = c0 + ci - gc[k];
-        c0 += __shfl(ci, 63, 64);
+        gc[k] = (long long)col_tiles * depth * (full * blocks_full + last);
       }
+      const long long ci = wave_incl_scan(gc[k], lane);
+      gx[k] = c0 + ci - gc[k];
+      c0 += __shfl(ci, 63, 64);
+    }
 #pragma unroll
-      for (int k = 0; k < GPL; ++k) {
-        if (k > 0 && 64 * k >= p.G) continue;
-        const int n_items = list == 0 ? n1[k] : n2[k];
-        if (n_items <= 0) continue;
-        const float per_item = (float)n_items / (float)gc[k];
-        static_assert(N_XCD == 8, "the share boundaries divide by a shift");
+    for (int k = 0; k < GPL; ++k) {
+      if (k > 0 && 64 * k >= p.G) continue;
+      const int n_items = list == 0 ? n1[k] : n2[k];
+      if (n_items <= 0) continue;
+      const float per_item = (float)n_items / (float)gc[k];
+      static_assert(N_XCD == 8, "the share boundaries divide by a shift");
 #pragma unroll
-        for (int x = 1; x < N_XCD; ++x) {
-          const long long t = (x * c0) >> 3;
-          if (gx[k] <= t && t < gx[k] + gc[k]) {
-            int local = (int)((float)(t - gx[k]) * per_item);
-            if (local > n_items - 1) local = n_items - 1;
-            xs[list][x] = (list == 0 ? w1x[k] : w2x[k]) + local;
-          }
+      for (int x = 1; x < N_XCD; ++x) {
+        const long long t = (x * c0) >> 3;
+        if (gx[k] <= t && t < gx[k] + gc[k]) {
+          int local = (int)((float)(t - gx[k]) * per_item);
+          if (local > n_items - 1) local = n_items - 1;
+          xs[list][x] = (list == 0 ? w1x[k] : w2x[k]) + local;
         }
       }
     }
-    wave_lds_sync();
-    if (lane <= N_XCD) {
-      p.work1[p.G + 1 + lane] = xs[0][lane];
-      p.work2[p.G + 1 + lane] = xs[1][lane];
-    }
   }
-  wave_lds_sync();                          // base[] and present[] are complete
-  // always-on groups: identity segments
-  if (valid)
-    for (int a = 0; a < p.n_always; ++a) {
-      const int slot = a * (int)p.T + (int)t;
-      p.slot2tok[slot] = (int)t;
-      p.tok2slot[t * S_all + a] = slot;
-      p.slot_w[t * S_all + a] = 1.0f;
-      p.w_by_slot[slot] = 1.0f;
-    }
-  // routed entries: stable (token-ascending) rank inside the group = lower lanes present in its mask
-  const uint32_t lt_lo = lane >= 32 ? 0xffffffffu : ((1u << lane) - 1u);
-  const uint32_t lt_hi = lane > 32 ? ((1u << (lane - 32)) - 1u) : 0u;
-#pragma unroll
-  for (int i = 0; i < MAX_DYN; ++i) {
-    if (i >= p.S_dyn) break;
-    const int g = my_g[i];
-    if (g < 0) continue;
-    const int slot = base[g] + __popc(present[g][0] & lt_lo) + __popc(present[g][1] & lt_hi);
-    p.slot2tok[slot] = (int)t;
-    p.tok2slot[t * S_all + p.n_always + i] = slot;
-    p.slot_w[t * S_all + p.n_always + i] = my_w[i];
-    p.w_by_slot[slot] = my_w[i];
+  wave_lds_sync();
+  if (lane <= N_XCD) {
+    p.work1[p.G + 1 + lane] = xs[0][lane];
+    p.work2[p.G + 1 + lane] = xs[1][lane];
   }
 }
 

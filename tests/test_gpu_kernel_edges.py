@@ -76,3 +76,22 @@ def test_gather_across_two_gigabytes(binding):
         layer.forward_device(x[lo:hi], y2[lo:hi])
     assert torch.equal(y, y2)
     layer.close()
+
+
+@pytest.mark.parametrize("T", [1, 2, 20, 64])
+def test_non_finite_tokens_stay_in_their_rows(binding, T):
+    """A token of NaNs or infinities has no meaningful choice of experts, but it gets valid ones, and the other tokens of
+    the batch keep their outputs."""
+    cfg, weights, part, x, layer = _case(binding, 512, 16, 32, 1, 3, T, seed=2)
+    ref = layer.forward(x)
+    bad = x.copy()
+    bad[0] = np.nan
+    if T > 2:
+        bad[1] = np.inf
+    out = layer.forward(bad)
+    assert ((out["topk"] >= 0) & (out["topk"] < cfg.n_routed)).all()
+    assert all(len(set(row)) == cfg.top_k for row in out["topk"].tolist())
+    n_bad = 2 if T > 2 else 1
+    assert np.array_equal(out["topk"][n_bad:], ref["topk"][n_bad:])
+    assert np.array_equal(out["y"][n_bad:], ref["y"][n_bad:])
+    layer.close()
