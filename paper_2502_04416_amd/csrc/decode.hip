@@ -49,14 +49,13 @@ __device__ __forceinline__ bool find_unit(const DecArgs& p, int units_single, in
 }
 
 // ---- gate/up: H[slot][n] = Swish(x . wgate_n) * (x . wup_n) for 16 neurons of one group ---------------
-template <int NTT, int KSTEPS>
+template <int NTT, int KSTEPS, bool RUNS>
 __global__ __launch_bounds__(512) void decode_gate_up_kernel(DecArgs p) {
   __shared__ DecGateUpRed<NTT> red;
   int g, local, seg0, cnt, wp;
   int64_t hoff;
   if (!find_unit(p, p.single ? p.groups[0].width_pad / p.unit1 : 0, g, local, seg0, cnt, wp, hoff)) return;
-  if (p.unit1 == 8) decode_gate_up_unit8<NTT, KSTEPS>(p, g, local, seg0, cnt, wp, hoff, red);
-  else decode_gate_up_unit<NTT, KSTEPS>(p, g, local, seg0, cnt, wp, hoff, red);
+  decode_gate_up<NTT, KSTEPS, RUNS>(p, g, local, seg0, cnt, wp, hoff, red);
 }
 
 // ---- down: Y[slot][c] = sum_n H[slot][n] * Wdown[n][c] for 16 output columns of one group --------------
@@ -381,9 +380,7 @@ __global__ __launch_bounds__(DS_WAVES * 64) void decode_down_sparse_kernel(DecAr
 constexpr int DECODE_MAX_T = 16;
 bool decode_path_ok(const Engine& e, int64_t T) {
   if (e.dtype != 1 || T < 1 || T > DECODE_MAX_T) return false;
-  if (e.d % 256 != 0) return false;
-  const int ksteps = e.d / 256;
-  return ksteps == 16 || ksteps == 8 || ksteps == 4 || ksteps == 2;
+  return decode_k(e.d).ksteps != 0;
 }
 
 // The fused down + combine kernel serves every routed bf16 batch of at most 32 tokens with more than one slot
@@ -417,14 +414,11 @@ int64_t decode_unit_bound(const Engine& e, int64_t T, int which) {
 }
 
 template <int NTT>
-static hipError_t launch_gate_up(const DecArgs& a, int ksteps, int64_t n_blocks, hipStream_t s) {
+static hipError_t launch_gate_up(const DecArgs& a, int64_t n_blocks, hipStream_t s) {
   dim3 grid((unsigned)n_blocks), block(512);
-  switch (ksteps) {
-    case 16: hipLaunchKernelGGL((decode_gate_up_kernel<NTT, 16>), grid, block, 0, s, a); break;
-    case 8: hipLaunchKernelGGL((decode_gate_up_kernel<NTT, 8>), grid, block, 0, s, a); break;
-    case 4: hipLaunchKernelGGL((decode_gate_up_kernel<NTT, 4>), grid, block, 0, s, a); break;
-    default: hipLaunchKernelGGL((decode_gate_up_kernel<NTT, 2>), grid, block, 0, s, a); break;
-  }
+#define CMOE_GATE_UP(KS, RUNS) hipLaunchKernelGGL((decode_gate_up_kernel<NTT, KS, RUNS>), grid, block, 0, s, a)
+  CMOE_DECODE_KSTEPS(a.d, CMOE_GATE_UP)
+#undef CMOE_GATE_UP
   return hipGetLastError();
 }
 
@@ -447,6 +441,7 @@ DecArgs make_dec_args(const Engine& e, const void* x, int64_t T, char* ws, const
   a.single = (e.G == 1 && e.n_always == 1) ? 1 : 0;
   a.slot2tok = a.single ? nullptr : reinterpret_cast<const int32_t*>(ws + L.slot2tok);
   a.unit1 = decode_unit_neurons(e, T);
+  a.nch = decode_k(e.d).nch;
   return a;
 }
 
@@ -487,7 +482,7 @@ hipError_t launch_experts_decode(const Engine& e, const void* x, int64_t T, char
   if (stage != 2) {
     a.work = reinterpret_cast<const int32_t*>(ws + L.work1);
     const int64_t nb = a.single ? e.max_width_pad / a.unit1 : decode_unit_bound(e, T, 1);
-    hipError_t err = launch_gate_up<1>(a, e.d / 256, nb, s);
+    hipError_t err = launch_gate_up<1>(a, nb, s);
     if (err != hipSuccess || stage == 1) return err;
   }
   if (decode_fuses_combine(e, T)) return launch_decode_down_combine(e, T, ws, L, y, s);

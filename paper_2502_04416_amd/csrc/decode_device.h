@@ -27,6 +27,7 @@ struct DecArgs {
   int64_t T;
   int single;
   int unit1;                // neurons per gate/up unit: 16 or 8
+  int nch;                  // a wave's K slice in runs of KSTEPS steps of 32: d = 8 * KSTEPS * 32 * nch (1 but for the _runs forms)
 };
 
 __device__ __forceinline__ bf16x8_t ld_frag(const bf16_t* p) { return *reinterpret_cast<const bf16x8_t*>(p); }
@@ -44,7 +45,9 @@ struct DecGateUpRed { float v[8][2][NTT][16][17]; };
 // H[slot][n] = Swish(x . wgate_n) * (x . wup_n) for the 16 neurons [local*16, local*16+16) of group g, whose
 // cnt <= 16*NTT tokens are the slots seg0 .. seg0+cnt-1 and whose rows of H start at element hoff.
 // Called by all 512 threads of a workgroup: 8 waves, wave w multiplies the K slice [w*d/8, (w+1)*d/8).
-// NTT = token tiles of 16.  KSTEPS = d/8/32.
+// NTT = token tiles of 16.  KSTEPS = d/8/32.  The _runs forms below take a wave's slice in p.nch runs of KSTEPS steps
+// (d above 4096: the operands of the whole slice would leave room for one workgroup per CU); as one loop for both
+// cases the code of the single run came out 5-8 % slower (62 -> 67 us at 16 tokens, d = 4096).
 template <int NTT, int KSTEPS>
 __device__ __forceinline__ void decode_gate_up_unit(const DecArgs& p, int g, int local, int seg0, int cnt, int wp,
                                                     int64_t hoff, DecGateUpRed<NTT>& redbuf) {
@@ -93,6 +96,85 @@ __device__ __forceinline__ void decode_gate_up_unit(const DecArgs& p, int g, int
       accu[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(au, bx[tt][ks], accu[tt], 0, 0, 0);
     }
   }
+  // accumulator element i: neuron row (lane/16)*4 + i, token column lane%16
+#pragma unroll
+  for (int tt = 0; tt < NTT; ++tt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      red[wave][0][tt][kq * 4 + i][r16] = accg[tt][i];
+      red[wave][1][tt][kq * 4 + i][r16] = accu[tt][i];
+    }
+  __syncthreads();
+  for (int e = tid; e < NTT * 256; e += 512) {
+    const int tt = e >> 8, tok = (e >> 4) & 15, nn = e & 15;     // neuron fastest: contiguous stores
+    const int col = tt * 16 + tok;
+    if (col >= cnt) continue;
+    float sg = 0.0f, su = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) { sg += red[w][0][tt][nn][tok]; su += red[w][1][tt][nn][tok]; }
+    p.h[hoff + (int64_t)col * wp + neuron0 + nn] = f32_to_bf16(silu_f32(sg) * su);
+  }
+}
+
+template <int NTT, int KSTEPS>
+__device__ __forceinline__ void decode_gate_up_unit_runs(const DecArgs& p, int g, int local, int seg0, int cnt, int wp,
+                                                    int64_t hoff, DecGateUpRed<NTT>& redbuf) {
+  float (*red)[2][NTT][16][17] = redbuf.v;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r16 = lane & 15, kq = lane >> 4;
+  const int neuron0 = local * 16;
+  const int kbase = wave * (KSTEPS * 32 * p.nch) + kq * 8;
+  // weight rows of this lane: packed row = (n / IL) * 2 * IL + n % IL (+ IL for the up row)
+  const int n = neuron0 + r16;
+  const int64_t grow = (int64_t)p.groups[g].w1_row0 + (n / IL) * 2 * IL + (n % IL);
+  // (grow is a multiple of 16 plus lane%16, kbase a multiple of 32 plus (lane/16)*8: one tile per K step)
+  const bf16_t* wg = p.w1 + (p.tiled ? tiled_offset(grow, kbase, p.ldw / TILE_K) : grow * p.ldw + kbase);
+  const bf16_t* wu = wg + (p.tiled ? (int64_t)(IL / TILE_ROWS) * (p.ldw / TILE_K) * TILE_ELEMS : (int64_t)IL * p.ldw);
+  const int kadv = p.tiled ? TILE_ELEMS : 32;                 // elements from one K step's operand to the next
+  int64_t xoff[NTT];                                          // tokens (B operand), gathered
+  bool ok[NTT];
+  floatx4_t accg[NTT], accu[NTT];
+#pragma unroll
+  for (int tt = 0; tt < NTT; ++tt) {
+    const int col = tt * 16 + r16;
+    ok[tt] = col < cnt;
+    xoff[tt] = -1;                                            // (looked up behind the first weight loads)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { accg[tt][i] = 0.0f; accu[tt][i] = 0.0f; }
+  }
+  int ch = 0;
+  do {
+    // The gate rows of the unit are requested before anything else (the stream from HBM is what the kernel
+    // waits for; left to itself the compiler keeps half a dozen weight loads in flight per wave), the up rows
+    // as the loop goes.  Requesting those up front as well costs a third workgroup per CU and gains nothing.
+    bf16x8_t ag[KSTEPS];
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) ag[ks] = ld_frag(wg + ks * kadv);
+    __builtin_amdgcn_sched_barrier(0);
+    bf16x8_t bx[NTT][KSTEPS];
+#pragma unroll
+    for (int tt = 0; tt < NTT; ++tt) {
+      if (ch == 0) {
+        int64_t tok = 0;
+        if (ok[tt]) tok = p.slot2tok ? p.slot2tok[seg0 + tt * 16 + r16] : (seg0 + tt * 16 + r16);
+        xoff[tt] = tok * p.d + kbase;
+      }
+      const bf16_t* xr = p.x + xoff[tt] + ch * (KSTEPS * 32);
+#pragma unroll
+      for (int ks = 0; ks < KSTEPS; ++ks) bx[tt][ks] = ok[tt] ? ld_frag(xr + ks * 32) : zero_frag();
+    }
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) {
+      const bf16x8_t au = ld_frag(wu + ks * kadv);
+#pragma unroll
+      for (int tt = 0; tt < NTT; ++tt) {
+        accg[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ag[ks], bx[tt][ks], accg[tt], 0, 0, 0);
+        accu[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(au, bx[tt][ks], accu[tt], 0, 0, 0);
+      }
+    }
+    wg += KSTEPS * kadv;
+    wu += KSTEPS * kadv;
+  } while (++ch < p.nch);
   // accumulator element i: neuron row (lane/16)*4 + i, token column lane%16
 #pragma unroll
   for (int tt = 0; tt < NTT; ++tt)
@@ -166,6 +248,100 @@ __device__ __forceinline__ void decode_gate_up_unit8(const DecArgs& p, int g, in
     p.h[hoff + (int64_t)col * wp + neuron0 + nn] = f32_to_bf16(silu_f32(sg) * su);
   }
 }
+
+template <int NTT, int KSTEPS>
+__device__ __forceinline__ void decode_gate_up_unit8_runs(const DecArgs& p, int g, int local, int seg0, int cnt, int wp,
+                                                     int64_t hoff, DecGateUpRed<NTT>& redbuf) {
+  float (*red)[2][NTT][16][17] = redbuf.v;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r16 = lane & 15, kq = lane >> 4;
+  const int neuron0 = local * 8;
+  const int kbase = wave * (KSTEPS * 32 * p.nch) + kq * 8;
+  const int n = neuron0 + (r16 & 7);
+  const int64_t grow = (int64_t)p.groups[g].w1_row0 + (n / IL) * 2 * IL + (n % IL) + (r16 >= 8 ? IL : 0);
+  const bf16_t* wrow = p.w1 + (p.tiled ? tiled_offset(grow, kbase, p.ldw / TILE_K) : grow * p.ldw + kbase);
+  const int kadv = p.tiled ? TILE_ELEMS : 32;
+  floatx4_t acc[NTT];
+#pragma unroll
+  for (int tt = 0; tt < NTT; ++tt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[tt][i] = 0.0f;
+  int ch = 0;
+  do {
+    bf16x8_t a[KSTEPS];
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) a[ks] = ld_frag(wrow + ks * kadv);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int tt = 0; tt < NTT; ++tt) {
+      const int col = tt * 16 + r16;
+      const bool ok = col < cnt;
+      int64_t tok = 0;
+      if (ok) tok = p.slot2tok ? p.slot2tok[seg0 + col] : (seg0 + col);
+      const bf16_t* xr = p.x + tok * p.d + kbase + ch * (KSTEPS * 32);
+      bf16x8_t bx[KSTEPS];
+#pragma unroll
+      for (int ks = 0; ks < KSTEPS; ++ks) bx[ks] = ok ? ld_frag(xr + ks * 32) : zero_frag();
+#pragma unroll
+      for (int ks = 0; ks < KSTEPS; ++ks) acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks], bx[ks], acc[tt], 0, 0, 0);
+    }
+    wrow += KSTEPS * kadv;
+  } while (++ch < p.nch);
+  // accumulator element i: operand row (lane/16)*4 + i (0-7 gate, 8-15 up of neuron row % 8), token column lane%16
+#pragma unroll
+  for (int tt = 0; tt < NTT; ++tt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) red[wave][0][tt][kq * 4 + i][r16] = acc[tt][i];
+  __syncthreads();
+  for (int e = tid; e < NTT * 128; e += 512) {
+    const int tt = e >> 7, tok = (e >> 3) & 15, nn = e & 7;
+    const int col = tt * 16 + tok;
+    if (col >= cnt) continue;
+    float sg = 0.0f, su = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) { sg += red[w][0][tt][nn][tok]; su += red[w][0][tt][8 + nn][tok]; }
+    p.h[hoff + (int64_t)col * wp + neuron0 + nn] = f32_to_bf16(silu_f32(sg) * su);
+  }
+}
+
+// A unit of unit1 neurons, in whichever form.  RUNS: the slice of a wave is more than one run of KSTEPS steps.
+template <int NTT, int KSTEPS, bool RUNS>
+__device__ __forceinline__ void decode_gate_up(const DecArgs& p, int g, int local, int seg0, int cnt, int wp, int64_t hoff,
+                                               DecGateUpRed<NTT>& redbuf) {
+  if constexpr (RUNS) {
+    if (p.unit1 == 8) decode_gate_up_unit8_runs<NTT, KSTEPS>(p, g, local, seg0, cnt, wp, hoff, redbuf);
+    else decode_gate_up_unit_runs<NTT, KSTEPS>(p, g, local, seg0, cnt, wp, hoff, redbuf);
+  } else {
+    if (p.unit1 == 8) decode_gate_up_unit8<NTT, KSTEPS>(p, g, local, seg0, cnt, wp, hoff, redbuf);
+    else decode_gate_up_unit<NTT, KSTEPS>(p, g, local, seg0, cnt, wp, hoff, redbuf);
+  }
+}
+
+// Model widths of the decode kernels: d = 8 waves x nch runs x ksteps steps of 32.  One run of an even number of
+// steps up to d = 4096, above that runs of 8 or 10; zero steps for a width they do not serve.
+struct DecodeK { int ksteps, nch; };
+static inline DecodeK decode_k(int d) {
+  if (d % 512 != 0) return {0, 0};
+  const int ks = d / 256;
+  if (ks <= 16) return {ks, 1};
+  if (ks > 40) return {0, 0};
+  return ks % 8 == 0 ? DecodeK{8, ks / 8} : ks % 10 == 0 ? DecodeK{10, ks / 10} : DecodeK{0, 0};
+}
+// CALL(KSTEPS, RUNS) with the template arguments for model width d.
+#define CMOE_DECODE_KSTEPS(d, CALL)                \
+  if (decode_k(d).nch > 1) {                       \
+    if (decode_k(d).ksteps == 8) CALL(8, true);    \
+    else CALL(10, true);                           \
+  } else switch (decode_k(d).ksteps) {             \
+    case 16: CALL(16, false); break;               \
+    case 14: CALL(14, false); break;               \
+    case 12: CALL(12, false); break;               \
+    case 10: CALL(10, false); break;               \
+    case 8: CALL(8, false); break;                 \
+    case 6: CALL(6, false); break;                 \
+    case 4: CALL(4, false); break;                 \
+    default: CALL(2, false); break;                \
+  }
 
 // Host side (decode.hip): the argument block of a forward.
 DecArgs make_dec_args(const Engine& e, const void* x, int64_t T, char* ws, const WsLayout& L, void* y);

@@ -439,37 +439,40 @@ constexpr int DEC_SLICES = 8;
 
 template <int NTT, int KSTEPS>
 __global__ __launch_bounds__(64) void decode_score_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wr,
-                                                          int d, int T, int n_rows, float* __restrict__ pre_g) {
+                                                          int d, int nch, int T, int n_rows, float* __restrict__ pre_g) {
   const int lane = threadIdx.x;
   const int slice = blockIdx.y;
   const int r16 = lane & 15, kq = lane >> 4;
   const int row0 = blockIdx.x * 16;
-  const int kbase = slice * (KSTEPS * 32) + kq * 8;
+  const int kbase = slice * (KSTEPS * 32 * nch) + kq * 8;
   const bf16_t* wrow = wr + (int64_t)(row0 + r16) * d + kbase;
   floatx4_t acc[NTT];
 #pragma unroll
   for (int tt = 0; tt < NTT; ++tt)
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[tt][i] = 0.0f;
-  bf16x8_t a[KSTEPS];
+  int ch = 0;
+  do {
+    bf16x8_t a[KSTEPS];
 #pragma unroll
-  for (int ks = 0; ks < KSTEPS; ++ks) a[ks] = *reinterpret_cast<const bf16x8_t*>(wrow + ks * 32);
+    for (int ks = 0; ks < KSTEPS; ++ks) a[ks] = *reinterpret_cast<const bf16x8_t*>(wrow + ch * (KSTEPS * 32) + ks * 32);
 #pragma unroll
-  for (int tt = 0; tt < NTT; ++tt) {
-    const int col = tt * 16 + r16;
-    const bool ok = col < T;
-    const bf16_t* xr = x + (int64_t)(ok ? col : 0) * d + kbase;
+    for (int tt = 0; tt < NTT; ++tt) {
+      const int col = tt * 16 + r16;
+      const bool ok = col < T;
+      const bf16_t* xr = x + (int64_t)(ok ? col : 0) * d + kbase + ch * (KSTEPS * 32);
 #pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) {
-      bf16x8_t b;
-      if (ok) b = *reinterpret_cast<const bf16x8_t*>(xr + ks * 32);
-      else {
+      for (int ks = 0; ks < KSTEPS; ++ks) {
+        bf16x8_t b;
+        if (ok) b = *reinterpret_cast<const bf16x8_t*>(xr + ks * 32);
+        else {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) b[i] = (__bf16)0.0f;
+          for (int i = 0; i < 8; ++i) b[i] = (__bf16)0.0f;
+        }
+        acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks], b, acc[tt], 0, 0, 0);
       }
-      acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks], b, acc[tt], 0, 0, 0);
     }
-  }
+  } while (++ch < nch);
   // D layout: lane holds rows kq*4 .. kq*4+3 of column (token) r16
 #pragma unroll
   for (int tt = 0; tt < NTT; ++tt) {
@@ -599,7 +602,7 @@ __global__ __launch_bounds__(RT_THREADS) void route_place_kernel(RouterDev r, Ro
 // workgroup's chain of dependent steps, 8 us long at one token; the shared expert's share of the gate/up
 // stream (half of the bytes at one token) is read meanwhile instead of afterwards, with no hand-off between
 // workgroups and no second stream.  The gate/up work list then leaves that group out.
-template <int KSTEPS>
+template <int KSTEPS, bool RUNS>
 __global__ __launch_bounds__(512) void route_place_shared_kernel(RouterDev r, RouteIO io, PlaceArgs pl,
                                                                  const float* __restrict__ partial, int n_slices, int T,
                                                                  DecArgs da) {
@@ -609,8 +612,7 @@ __global__ __launch_bounds__(512) void route_place_shared_kernel(RouterDev r, Ro
     route_place_body(r, io, pl, partial, n_slices, T, pre);
     return;
   }
-  if (da.unit1 == 8) decode_gate_up_unit8<1, KSTEPS>(da, 0, (int)blockIdx.x - 1, 0, T, da.groups[0].width_pad, 0, red);
-  else decode_gate_up_unit<1, KSTEPS>(da, 0, (int)blockIdx.x - 1, 0, T, da.groups[0].width_pad, 0, red);
+  decode_gate_up<1, KSTEPS, RUNS>(da, 0, (int)blockIdx.x - 1, 0, T, da.groups[0].width_pad, 0, red);
 }
 
 // One token on a flat layer: the launch that selects and places also runs *every* gate/up unit, the routed
@@ -623,7 +625,7 @@ __global__ __launch_bounds__(512) void route_place_shared_kernel(RouterDev r, Ro
 // group id, so the expert's row of H starts after the shared group's and after the rows of the selected
 // experts with smaller ids.  One launch and its gap less than scoring + (selection, shared units) + routed
 // units; the separate gate/up launch is skipped.
-template <int KSTEPS>
+template <int KSTEPS, bool RUNS>
 __global__ __launch_bounds__(512) void route_place_all_kernel(RouterDev r, RouteIO io, PlaceArgs pl,
                                                               const float* __restrict__ partial, int n_slices,
                                                               DecArgs da, int units_shared, int units_routed,
@@ -635,8 +637,7 @@ __global__ __launch_bounds__(512) void route_place_all_kernel(RouterDev r, Route
   const int n_rows = r.n_sw_rows + r.n_lin_rows;
   const int b = (int)blockIdx.x - 1;
   if (b >= 0 && b < units_shared) {
-    if (da.unit1 == 8) decode_gate_up_unit8<1, KSTEPS>(da, 0, b, 0, 1, da.groups[0].width_pad, 0, red);
-    else decode_gate_up_unit<1, KSTEPS>(da, 0, b, 0, 1, da.groups[0].width_pad, 0, red);
+    decode_gate_up<1, KSTEPS, RUNS>(da, 0, b, 0, 1, da.groups[0].width_pad, 0, red);
     return;
   }
   if (wr) {
@@ -676,8 +677,7 @@ __global__ __launch_bounds__(512) void route_place_all_kernel(RouterDev r, Route
   for (int i = 0; i < r.top_k; ++i) rank += my_sel_g[i] < g ? 1 : 0;
   const int wp = da.groups[g].width_pad;
   const int64_t hoff = (r.n_always ? (int64_t)da.groups[0].width_pad : 0) + (int64_t)rank * wp;
-  if (da.unit1 == 8) decode_gate_up_unit8<1, KSTEPS>(da, g, local, 0, 1, wp, hoff, red);
-  else decode_gate_up_unit<1, KSTEPS>(da, g, local, 0, 1, wp, hoff, red);
+  decode_gate_up<1, KSTEPS, RUNS>(da, g, local, 0, 1, wp, hoff, red);
 }
 
 // Two to sixteen tokens on a flat layer, the same idea: workgroup 0 selects and places the batch, the next
@@ -689,7 +689,7 @@ __global__ __launch_bounds__(512) void route_place_all_kernel(RouterDev r, Route
 // workgroup, is gone.  Bit-identical to the two launches and slower than them at every batch size (the team
 // selection run by hundreds of workgroups at once takes 15 us instead of the 8 us it takes one workgroup on
 // an otherwise idle chip), so it is off unless the tuning switch front_tile asks for it.
-template <int KSTEPS>
+template <int KSTEPS, bool RUNS>
 __global__ __launch_bounds__(512) void route_place_tile_all_kernel(RouterDev r, RouteIO io, PlaceArgs pl,
                                                                    const float* __restrict__ partial, int n_slices, int T,
                                                                    DecArgs da, int units_shared, int units_routed) {
@@ -698,7 +698,7 @@ __global__ __launch_bounds__(512) void route_place_tile_all_kernel(RouterDev r, 
   __shared__ OwnSegment own;
   const int b = (int)blockIdx.x - 1;
   if (b >= 0 && b < units_shared) {
-    decode_gate_up_unit<1, KSTEPS>(da, 0, b, 0, T, da.groups[0].width_pad, 0, red);
+    decode_gate_up<1, KSTEPS, RUNS>(da, 0, b, 0, T, da.groups[0].width_pad, 0, red);
     return;
   }
   if (blockIdx.x == 0) {
@@ -710,7 +710,7 @@ __global__ __launch_bounds__(512) void route_place_tile_all_kernel(RouterDev r, 
   const int cnt = own.cnt;
   if (cnt == 0) return;
   da.slot2tok = own.tok;                          // slot j of this group = its j-th token in ascending order
-  decode_gate_up_unit<1, KSTEPS>(da, g, local, 0, cnt, da.groups[g].width_pad, own.h_off, red);
+  decode_gate_up<1, KSTEPS, RUNS>(da, g, local, 0, cnt, da.groups[g].width_pad, own.h_off, red);
 }
 
 // Per-tile histogram of the routed entries (used when the scoring kernel did not produce one).
@@ -792,22 +792,28 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
   int n_slices = DEC_SLICES;
   hipError_t err = hipSuccess;
   // one token, every gate/up unit in the selection launch: with front_all = 2 that launch also scores
-  const bool own_scores = L.gate_up_done && tuning().front_all >= 2 && e.wr_tiled != nullptr;
+  const bool own_scores = L.gate_up_done && tuning().front_all >= 2 && e.wr_tiled != nullptr && decode_k(e.d).nch == 1;
   if (own_scores) {
   } else if (T <= FRONT_SCORE_MAX_T) {
     dim3 grid(n_rows / 16, DEC_SLICES), block(64);
     const bf16_t* xx = static_cast<const bf16_t*>(x);
     const bf16_t* ww = static_cast<const bf16_t*>(e.wr);
-    const int ksteps = e.d / 256;                 // K steps of 32 per slice: d / (8 slices * 32)
-#define CMOE_SCORE(NTT, KS) hipLaunchKernelGGL((decode_score_kernel<NTT, KS>), grid, block, 0, s, xx, ww, e.d, Ti, n_rows, pre_g)
+    // (the scorer holds one operand, not two: runs of up to 16 steps)
+    const int ks_all = e.d / 256, nch = ks_all <= 16 ? 1 : ks_all <= 32 ? 2 : decode_k(e.d).nch;
+#define CMOE_SCORE(KS) hipLaunchKernelGGL((decode_score_kernel<1, KS>), grid, block, 0, s, xx, ww, e.d, nch, Ti, n_rows, pre_g)
     // (measurement aid: repeat_stage = 6 issues the scoring launch twice; it overwrites its partials)
-    for (int rep = tuning().repeat_stage == 6 ? 2 : 1; rep > 0; --rep)
-      switch (ksteps) {
-        case 16: CMOE_SCORE(1, 16); break;
-        case 8: CMOE_SCORE(1, 8); break;
-        case 4: CMOE_SCORE(1, 4); break;
-        default: CMOE_SCORE(1, 2); break;
+    for (int rep = tuning().repeat_stage == 6 ? 2 : 1; rep > 0; --rep) {
+      switch (ks_all / nch) {
+        case 16: CMOE_SCORE(16); break;
+        case 14: CMOE_SCORE(14); break;
+        case 12: CMOE_SCORE(12); break;
+        case 10: CMOE_SCORE(10); break;
+        case 8: CMOE_SCORE(8); break;
+        case 6: CMOE_SCORE(6); break;
+        case 4: CMOE_SCORE(4); break;
+        default: CMOE_SCORE(2); break;
       }
+    }
 #undef CMOE_SCORE
     err = hipGetLastError();
   } else {
@@ -826,12 +832,9 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
     const int ur = e.width_pad_host[e.n_always] / 16;
     const dim3 grid(1 + us + (e.G - e.n_always) * ur), block(512);
     for (int rep = tuning().repeat_stage == 3 ? 2 : 1; rep > 0; --rep)       // (measurement aid, as below)
-      switch (e.d / 256) {
-        case 16: hipLaunchKernelGGL(route_place_tile_all_kernel<16>, grid, block, smem, s, e.r, io, pl, pre_g, n_slices, Ti, da, us, ur); break;
-        case 8: hipLaunchKernelGGL(route_place_tile_all_kernel<8>, grid, block, smem, s, e.r, io, pl, pre_g, n_slices, Ti, da, us, ur); break;
-        case 4: hipLaunchKernelGGL(route_place_tile_all_kernel<4>, grid, block, smem, s, e.r, io, pl, pre_g, n_slices, Ti, da, us, ur); break;
-        default: hipLaunchKernelGGL(route_place_tile_all_kernel<2>, grid, block, smem, s, e.r, io, pl, pre_g, n_slices, Ti, da, us, ur); break;
-      }
+#define CMOE_LAUNCH(KS, RUNS) hipLaunchKernelGGL((route_place_tile_all_kernel<KS, RUNS>), grid, block, smem, s, e.r, io, pl, pre_g, n_slices, Ti, da, us, ur)
+      { CMOE_DECODE_KSTEPS(e.d, CMOE_LAUNCH) }
+#undef CMOE_LAUNCH
     return hipGetLastError();
   }
   if (L.gate_up_done) {
@@ -848,12 +851,9 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
     // only the scorer's partials, the token and the weights, and every write is a plain store of a value that
     // depends on those alone, so the second launch leaves the same bits)
     for (int rep = tuning().repeat_stage == 3 ? 2 : 1; rep > 0; --rep)
-      switch (e.d / 256) {
-        case 16: hipLaunchKernelGGL(route_place_all_kernel<16>, grid, block, smem, s, e.r, io, pl, pre_g, n_slices, da, us, ur, wr_in); break;
-        case 8: hipLaunchKernelGGL(route_place_all_kernel<8>, grid, block, smem, s, e.r, io, pl, pre_g, n_slices, da, us, ur, wr_in); break;
-        case 4: hipLaunchKernelGGL(route_place_all_kernel<4>, grid, block, smem, s, e.r, io, pl, pre_g, n_slices, da, us, ur, wr_in); break;
-        default: hipLaunchKernelGGL(route_place_all_kernel<2>, grid, block, smem, s, e.r, io, pl, pre_g, n_slices, da, us, ur, wr_in); break;
-      }
+#define CMOE_LAUNCH(KS, RUNS) hipLaunchKernelGGL((route_place_all_kernel<KS, RUNS>), grid, block, smem, s, e.r, io, pl, pre_g, n_slices, da, us, ur, wr_in)
+      { CMOE_DECODE_KSTEPS(e.d, CMOE_LAUNCH) }
+#undef CMOE_LAUNCH
     return hipGetLastError();
   }
   if (L.skip_always) {
@@ -862,12 +862,9 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
     da.slot2tok = nullptr;                        // group 0's slots are the tokens in order; the map is not written yet
     da.work = nullptr;
     const dim3 grid(1 + e.width_pad_host[0] / da.unit1), block(512);
-    switch (e.d / 256) {
-      case 16: hipLaunchKernelGGL(route_place_shared_kernel<16>, grid, block, smem, s, e.r, io, pl, pre_g, n_slices, Ti, da); break;
-      case 8: hipLaunchKernelGGL(route_place_shared_kernel<8>, grid, block, smem, s, e.r, io, pl, pre_g, n_slices, Ti, da); break;
-      case 4: hipLaunchKernelGGL(route_place_shared_kernel<4>, grid, block, smem, s, e.r, io, pl, pre_g, n_slices, Ti, da); break;
-      default: hipLaunchKernelGGL(route_place_shared_kernel<2>, grid, block, smem, s, e.r, io, pl, pre_g, n_slices, Ti, da); break;
-    }
+#define CMOE_LAUNCH(KS, RUNS) hipLaunchKernelGGL((route_place_shared_kernel<KS, RUNS>), grid, block, smem, s, e.r, io, pl, pre_g, n_slices, Ti, da)
+    { CMOE_DECODE_KSTEPS(e.d, CMOE_LAUNCH) }
+#undef CMOE_LAUNCH
     return hipGetLastError();
   }
   hipLaunchKernelGGL(route_place_kernel, dim3(1), dim3(RT_THREADS), smem, s, e.r, io, pl, pre_g, n_slices, Ti);

@@ -95,3 +95,15 @@ def test_non_finite_tokens_stay_in_their_rows(binding, T):
     assert np.array_equal(out["topk"][n_bad:], ref["topk"][n_bad:])
     assert np.array_equal(out["y"][n_bad:], ref["y"][n_bad:])
     layer.close()
+
+
+@pytest.mark.parametrize("d", [1536, 2560, 3584, 5120, 8192])
+@pytest.mark.parametrize("T,m", [(1, 40), (1, 96), (3, 40), (16, 40)])
+def test_decode_kernels_at_other_widths(binding, d, T, m):
+    """Model widths whose K slice per wave is not 2, 4, 8 or 16 steps, or two runs of them."""
+    cfg, weights, part, x, layer = _case(binding, d, 8, m, 1, 2, T, seed=3)
+    out = layer.forward(x)
+    check_flat(cfg, weights, part, x, out)
+    check_dense(cfg, weights, x, layer.dense_forward(x))
+    assert np.array_equal(out["y"], layer.forward(x)["y"])
+    layer.close()
