@@ -185,6 +185,9 @@ WsLayout ws_layout(const Engine& e, int64_t T, size_t splitk_cap = ~(size_t)0);
 // Kernel launchers (defined in the .hip files).  All enqueue on `s` and return the launch status.
 hipError_t launch_router(const Engine& e, const void* x, int64_t T, char* ws, const WsLayout& L,
                          int32_t* topk_out, int32_t* outer_out, float* scores_out, hipStream_t s);
+// The histogram table launch_router leaves behind: tokens per row (16, 32 or TOK_TILE) and where it is.
+struct CountTable { int tokens; size_t offset; };
+CountTable router_counts(const Engine& e, int64_t T, const WsLayout& L);
 hipError_t launch_permute(const Engine& e, int64_t T, char* ws, const WsLayout& L, int32_t* counts_out,
                           hipStream_t s);
 // stage: 0 = gate/up GEMM then down GEMM, 1 = gate/up only, 2 = down only

@@ -33,8 +33,9 @@ __global__ __launch_bounds__(PLACE_WAVES * 64) void place_kernel(PlaceArgs p) {
     sel_g[i] = p.sel_group[e0 + i];
     sel_w[i] = p.sel_weight[e0 + i];
   }
-  const int per = (p.n_tiles + PLACE_WAVES - 1) / PLACE_WAVES;
-  const int first = wave * per, end = first + per < p.n_tiles ? first + per : p.n_tiles;
+  const int per = (p.n_counts + PLACE_WAVES - 1) / PLACE_WAVES;
+  const int first = wave * per, end = first + per < p.n_counts ? first + per : p.n_counts;
+  const int row0 = tile * p.counts_per_tile;                   // the tile's first row of the table
 #pragma unroll
   for (int k = 0; k < GPL; ++k) {
     const int g = lane + 64 * k;
@@ -50,13 +51,13 @@ __global__ __launch_bounds__(PLACE_WAVES * 64) void place_kernel(PlaceArgs p) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
           tot += c[q];
-          prev += (i + q < tile) ? c[q] : 0;
+          prev += (i + q < row0) ? c[q] : 0;
         }
       }
       for (; i < end; ++i) {
         const int c = p.tile_counts[(int64_t)i * p.G + g];
         tot += c;
-        prev += (i < tile) ? c : 0;
+        prev += (i < row0) ? c : 0;
       }
     }
     part[wave][0][g] = tot;
@@ -86,7 +87,6 @@ PlaceArgs make_place_args(const Engine& e, int64_t T, char* ws, const WsLayout& 
   PlaceArgs p;
   p.sel_group = reinterpret_cast<const int32_t*>(ws + L.sel_group);
   p.sel_weight = reinterpret_cast<const float*>(ws + L.sel_weight);
-  p.tile_counts = reinterpret_cast<const int32_t*>(ws + L.tile_counts);
   p.groups = e.groups;
   p.seg_off = reinterpret_cast<int32_t*>(ws + L.seg_off);
   p.counts = reinterpret_cast<int32_t*>(ws + L.counts);
@@ -102,7 +102,10 @@ PlaceArgs make_place_args(const Engine& e, int64_t T, char* ws, const WsLayout& 
   p.G = e.G;
   p.n_always = e.n_always;
   p.S_dyn = e.S_dyn;
-  p.n_tiles = L.n_tok_tiles;
+  const CountTable ct = router_counts(e, T, L);
+  p.tile_counts = reinterpret_cast<const int32_t*>(ws + ct.offset);
+  p.n_counts = (int)((T + ct.tokens - 1) / ct.tokens);
+  p.counts_per_tile = TOK_TILE / ct.tokens;
   p.bm1 = gemm_tile(e, T, 1);
   p.bn1 = gemm_tile(e, T, 3);
   p.bm2 = gemm_tile(e, T, 2);

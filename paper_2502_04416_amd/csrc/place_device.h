@@ -11,7 +11,7 @@ constexpr int TILE_FIXED_COST = 4;    // prologue + epilogue of a tile, in units
 struct PlaceArgs {
   const int32_t* sel_group;    // [T][S_dyn]
   const float* sel_weight;     // [T][S_dyn]
-  const int32_t* tile_counts;  // [n_tiles][G]
+  const int32_t* tile_counts;  // [n_counts][G] histograms of consecutive runs of tokens, counts_per_tile rows per tile
   const GroupDev* groups;
   int32_t* seg_off;            // [G+1]
   int32_t* counts;             // [G]
@@ -24,7 +24,7 @@ struct PlaceArgs {
   float* w_by_slot;            // [n_slots] the same weights indexed by slot
   int32_t* counts_out;         // optional user output: counts of the routed groups [G - n_always]
   int64_t T;
-  int G, n_always, S_dyn, n_tiles;
+  int G, n_always, S_dyn, n_counts, counts_per_tile;
   int bm1, bn1, bm2, bn2, d;   // tile sizes of the grouped GEMMs (bn1 in packed gate/up rows)
   int dyn1, dyn2;              // > 0: that contraction runs tiles of dynamic height, in steps of this many rows (a
                                // ragged last tile costs its rows)

@@ -1,9 +1,11 @@
 // Router scoring (Eq. 8), wavefront-level top-N_k selection and the gate of Eq. 9, for flat layers
-// and for the two-level hierarchy of Sec. 4.4.  Two scoring kernels feed the same selection code:
+// and for the two-level hierarchy of Sec. 4.4.  Two scoring kernels feed the same selection code
 //   router_simt_kernel  one token per workgroup, fp32 FMA dot products (fp32 layers, decode batches)
 //   router_gemm_kernel  bf16 MFMA partial products over (32-token tile, K slice) workgroups, followed by
 //                       route_tile_kernel, which sums the slices in order, selects, and emits each
 //                       64-token tile's per-group histogram (prefill batches)
+// and score_route_kernel does both for prefill batches of a flat layer.
+#include <algorithm>
 #include <cstdlib>
 #include "cmoe_internal.h"
 #include "decode_device.h"
@@ -424,6 +426,129 @@ __global__ __launch_bounds__(RT_THREADS) void route_tile_kernel(RouterDev r, Rou
   for (int g = tid; g < G; g += RT_THREADS) tile_counts[(int64_t)blockIdx.x * G + g] = hist[g];
 }
 
+// ---- scoring and selection in one launch (prefill batches of flat layers) ------------------------------------
+// A workgroup of eight waves owns TB * 16 tokens and all of K: the partial sums that router_gemm_kernel leaves in memory
+// for route_tile_kernel stay in its LDS.  What bounds it is the router matrix (0.5 MB at d = 4096, 64 rows) that
+// every workgroup pulls through L2, so the matrix is read in operand order (1 KB of consecutive memory per MFMA
+// operand) and a wave has two chunks of K (2 x 64) in flight.  Where it pays: see score_route_units.
+//
+// The sums are those of the two launches, bit for bit: K falls into n_slices slices of k_slice, a slice into four
+// classes of 64-wide chunks (chunk number mod 4), each of which is one chain of MFMAs; ((c0 + c1) + c2) + c3 is
+// the slice, and the slices are added in order.  Wave w runs the (slice, class) units w * UPW .. + UPW - 1.
+template <int UPW, int TB, bool ONE>
+__global__ __launch_bounds__(512) void score_route_kernel(RouterDev r, RouteIO io, const bf16_t* __restrict__ x,
+                                                          const bf16_t* __restrict__ wrt, int d, int64_t T, int n_slices,
+                                                          int k_slice, int32_t* __restrict__ counts, int G) {
+  constexpr int NTOK = TB * 16, LDP = 64 + 4;
+  extern __shared__ __attribute__((aligned(16))) float sr_smem[];
+  __shared__ int32_t hist[MAX_GROUPS];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, kq = lane >> 4;
+  const int n_rows = r.n_sw_rows;
+  const int ld = n_rows + 1;
+  float* slice_sum = sr_smem;                                  // [n_slices][NTOK][LDP]
+  float* pre = sr_smem + n_slices * NTOK * LDP;                // [NTOK][ld]
+  float* sc = pre + NTOK * ld;                                 // [NTOK][LD_SC]
+  const int64_t t0 = (int64_t)blockIdx.x * NTOK;
+  for (int i = tid; i < MAX_GROUPS; i += 512) hist[i] = 0;
+  const bf16_t* xr[TB];
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) {
+    int64_t t = t0 + tb * 16 + r16;
+    if (t >= T) t = T - 1;                                     // (a copy of the last token; never used)
+    xr[tb] = x + t * d + kq * 8;
+  }
+  const int n_units = 4 * n_slices, n_i = k_slice / 256, kt = d / 32;
+  const int unit0 = wave * UPW;
+  struct Chunk { bf16x8_t w[2][4], a[2][TB]; };
+  Chunk c0, c1;
+  for (int rg = 0; rg < n_rows / 64; ++rg) {
+    auto load_chunk = [&](Chunk& c, int k, int i) {            // chunk i of this wave's k-th unit
+      const int q = unit0 + k;
+      if (q >= n_units) return;
+      const int kc = (q >> 2) * k_slice + (q & 3) * 64 + i * 256;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          c.w[h][b] = *reinterpret_cast<const bf16x8_t*>(wrt + (((int64_t)(rg * 4 + b) * kt + (kc >> 5) + h) * 64 + lane) * 8);
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) c.a[h][tb] = *reinterpret_cast<const bf16x8_t*>(xr[tb] + kc + h * 32);
+      }
+    };
+    floatx4_t acc[UPW][4][TB];
+#pragma unroll
+    for (int k = 0; k < UPW; ++k)
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[k][b][tb][i] = 0.0f;
+    auto mma_chunk = [&](const Chunk& c, floatx4_t (&ac)[4][TB]) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+          for (int tb = 0; tb < TB; ++tb) ac[b][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c.w[h][b], c.a[h][tb], ac[b][tb], 0, 0, 0);
+    };
+    load_chunk(c0, 0, 0);
+#pragma unroll
+    for (int k = 0; k < UPW; ++k) {
+      if (unit0 + k >= n_units) break;                         // (uniform)
+      if constexpr (ONE) {                                     // one chunk per unit: the buffers alternate with the units
+        if (k & 1) {
+          if (k + 1 < UPW) load_chunk(c0, k + 1, 0);
+          mma_chunk(c1, acc[k]);
+        } else {
+          if (k + 1 < UPW) load_chunk(c1, k + 1, 0);
+          mma_chunk(c0, acc[k]);
+        }
+      } else {
+        for (int i = 0; i < n_i; i += 2) {
+          load_chunk(c1, k, i + 1);
+          mma_chunk(c0, acc[k]);
+          if (i + 2 < n_i) load_chunk(c0, k, i + 2);
+          else if (k + 1 < UPW) load_chunk(c0, k + 1, 0);
+          mma_chunk(c1, acc[k]);
+        }
+      }
+    }
+    // D layout: a lane holds router rows b * 16 + kq * 4 .. + 3 of token tb * 16 + r16
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+#pragma unroll
+      for (int k = 0; k < UPW; ++k) {
+        const int q = unit0 + k;
+        if (q >= n_units || (q & 3) != c) continue;
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+          for (int tb = 0; tb < TB; ++tb) {
+            floatx4_t* dst = reinterpret_cast<floatx4_t*>(slice_sum + ((q >> 2) * NTOK + tb * 16 + r16) * LDP + b * 16 + kq * 4);
+            *dst = c == 0 ? acc[k][b][tb] : *dst + acc[k][b][tb];
+          }
+      }
+      __syncthreads();
+    }
+    for (int idx = tid; idx < NTOK * 64; idx += 512) {
+      const int tok = idx >> 6, row = idx & 63;
+      float v = 0.0f;
+      for (int sl = 0; sl < n_slices; ++sl) v += slice_sum[(sl * NTOK + tok) * LDP + row];
+      pre[tok * ld + rg * 64 + row] = v;
+    }
+    __syncthreads();
+  }
+  const int n_tok = (T - t0 < NTOK) ? (int)(T - t0) : NTOK;
+  score_tile(r, io, pre, ld, sc, LD_SC, n_tok, t0, tid, 512);
+  __syncthreads();
+  route_select_tile(r, io, sc, LD_SC, pre, ld, n_tok, t0, hist, tid, 512);
+  __syncthreads();
+  for (int g = tid; g < G; g += 512) counts[(int64_t)blockIdx.x * G + g] = hist[g];
+}
+
 // ---- decode front end ------------------------------------------------------------------------------
 // For batches of at most one 64-token tile scoring is one launch and selection + permutation a second one.
 // (Fusing all three behind a device-wide arrival counter was tried: on this multi-die part a device-scope
@@ -434,7 +559,6 @@ __global__ __launch_bounds__(RT_THREADS) void route_tile_kernel(RouterDev r, Rou
 // pre_g[slice][token][row] and are added in slice order by route_place_kernel.  Eight times as many
 // workgroups as a K loop inside the workgroup would give: the router matrix (0.5 MB at d = 4096) comes
 // cold from HBM, so the launch is one memory latency long instead of several.
-typedef float floatx4_t __attribute__((ext_vector_type(4)));
 constexpr int DEC_SLICES = 8;
 
 template <int NTT, int KSTEPS>
@@ -735,15 +859,62 @@ static bool mfma_scorer_ok(const Engine& e) {
   return e.dtype == 1 && e.d % 256 == 0 && n_rows % 32 == 0 && n_rows / 32 <= 5;
 }
 
+// K slices of the scorer: enough workgroups to fill 256 CUs, at least 256 of K per slice, at most the partial
+// buffer's 8.
+static int scorer_slices(const Engine& e, int64_t T) {
+  const int64_t n_tt = (T + RT_TOK - 1) / RT_TOK;
+  int n = (int)std::min<int64_t>((512 + n_tt - 1) / n_tt, 8);
+  while (n > 1 && (e.d % (n * 256) != 0)) --n;
+  return n;
+}
+
+// Units of (slice, class) per wave of score_route_kernel, 0: this batch takes the separate scorer.  A flat layer whose
+// router has a copy in operand order, whole pairs of chunks per unit (or one chunk), and either
+//  - at most two slices, i.e. a batch that fills the chip with 32 tokens per workgroup (8192 tokens of the 32-expert
+//    layer: 31 us against 34 + 10), or
+//  - five to eight slices, 16 tokens per workgroup, and a router matrix of at most 0.5 MB (333 and 2048 tokens of the
+//    16-expert layer: 109.9 -> 108.3 and 210.9 -> 207.8 us per forward; with 1 MB, d = 8192, 73 tokens: 113 -> 121).
+// Three and four slices (4096 tokens) take the two launches: 29 against 31 us.
+static int score_route_units(const Engine& e, int64_t T) {
+  if (!mfma_scorer_ok(e) || e.wr_tiled == nullptr || e.r.outer_top_k != 0 || e.r.n_lin_rows != 0 || e.r.n_sw_rows % 64 != 0) return 0;
+  const int S = scorer_slices(e, T), n_i = e.d / S / 256;
+  if (n_i != 1 && n_i % 2 != 0) return 0;
+  if (S > 2 && (S < 5 || (int64_t)e.r.n_sw_rows * e.d > 64 * 4096)) return 0;
+  return (4 * S + 7) / 8;
+}
+static int score_route_tokens(int upw) { return upw >= 3 ? 16 : 32; }
+
+CountTable router_counts(const Engine& e, int64_t T, const WsLayout& L) {
+  if (const int upw = score_route_units(e, T)) return {score_route_tokens(upw), L.scores};   // (no partial sums there)
+  return {TOK_TILE, L.tile_counts};
+}
+
+template <int UPW, bool ONE>
+static hipError_t launch_score_route(const Engine& e, const RouteIO& io, const void* x, int64_t T, int n_slices,
+                                     int32_t* counts, hipStream_t s) {
+  constexpr int TB = UPW >= 3 ? 1 : 2, NTOK = TB * 16;
+  const size_t smem = sizeof(float) * (size_t)NTOK * (n_slices * (64 + 4) + e.r.n_sw_rows + 1 + LD_SC);
+  static bool attr_done = false;
+  if (!attr_done) {
+    // at most 8 slices (UPW 3, 4) or 2 (UPW 1) and two groups of 64 rows
+    constexpr int most = (int)sizeof(float) * NTOK * ((UPW >= 3 ? 8 : 2) * (64 + 4) + 128 + 1 + LD_SC);
+    const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(score_route_kernel<UPW, TB, ONE>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    if (err != hipSuccess) return err;
+    attr_done = true;
+  }
+  hipLaunchKernelGGL((score_route_kernel<UPW, TB, ONE>), dim3((unsigned)((T + NTOK - 1) / NTOK)), dim3(512), smem, s, e.r, io,
+                     static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(e.wr_tiled), e.d, T, n_slices,
+                     e.d / n_slices, counts, e.G);
+  return hipGetLastError();
+}
+
 // Pre-activation partials [slice][T][n_rows] of all router rows by router_gemm_kernel.
 static hipError_t launch_scorer_gemm(const Engine& e, const void* x, int64_t T, float* partial, hipStream_t s,
                                      int& n_slices) {
   const int n_rows = e.r.n_sw_rows + e.r.n_lin_rows;
-  // K slices: enough workgroups to fill 256 CUs, at least 256 of K per slice, at most the partial buffer's 8
   const int n_tt = (int)((T + RT_TOK - 1) / RT_TOK);
-  n_slices = (512 + n_tt - 1) / n_tt;
-  if (n_slices > 8) n_slices = 8;
-  while (n_slices > 1 && (e.d % (n_slices * 256) != 0)) --n_slices;
+  n_slices = scorer_slices(e, T);
   const int k_slice = e.d / n_slices;
   dim3 grid(n_tt, n_slices), block(256);
   const bf16_t* xx = static_cast<const bf16_t*>(x);
@@ -904,6 +1075,16 @@ hipError_t launch_router(const Engine& e, const void* x, int64_t T, char* ws, co
   io.S_dyn = e.S_dyn;
   int32_t* tile_counts = reinterpret_cast<int32_t*>(ws + L.tile_counts);
   const int n_rows = e.r.n_sw_rows + e.r.n_lin_rows;
+  if (const int upw = score_route_units(e, T)) {
+    const int S = scorer_slices(e, T);
+    const bool one = e.d / S == 256;
+    tile_counts = reinterpret_cast<int32_t*>(ws + L.scores);
+    switch (upw) {
+      case 1: return one ? launch_score_route<1, true>(e, io, x, T, S, tile_counts, s) : launch_score_route<1, false>(e, io, x, T, S, tile_counts, s);
+      case 3: return one ? launch_score_route<3, true>(e, io, x, T, S, tile_counts, s) : launch_score_route<3, false>(e, io, x, T, S, tile_counts, s);
+      default: return one ? launch_score_route<4, true>(e, io, x, T, S, tile_counts, s) : launch_score_route<4, false>(e, io, x, T, S, tile_counts, s);
+    }
+  }
   if (mfma_scorer_ok(e)) {
     int n_slices = 1;
     float* partial = reinterpret_cast<float*>(ws + L.scores);

@@ -78,6 +78,32 @@ def test_gather_across_two_gigabytes(binding):
     layer.close()
 
 
+@pytest.mark.parametrize("gate", [False, True])
+@pytest.mark.parametrize("d,N,n_s,k,T", [
+    (512, 16, 1, 3, 65),        # two K slices of one chunk
+    (512, 40, 2, 5, 97),        # more than 32 routed experts: two groups of 64 router rows
+    (768, 12, 0, 1, 79),        # three slices
+    (1536, 12, 1, 4, 130),      # six slices: three units per wave, the last waves short
+    (2048, 65, 1, 16, 200),     # 64 routed experts, top-16
+    (2560, 16, 1, 3, 71),       # five slices of two chunks
+    (4096, 8, 1, 7, 2081),      # four slices, every routed expert chosen
+    (512, 8, 2, 2, 8300),       # two slices of two and of one chunk
+    (512, 8, 1, 2, 16500),      # one slice
+])
+def test_scoring_and_selection_in_one_launch(binding, d, N, n_s, k, T, gate):
+    """Prefill batches of a flat layer: K slices, units per wave, token blocks and histogram rows of every kind."""
+    cfg, weights, part, x, layer = _case(binding, d, N, 16, n_s, k, T, seed=1)
+    u = b = None
+    if gate:
+        u, b = synth.make_gate_params(cfg, seed=7300)
+        layer.set_gate_params(u, b)
+    out = layer.forward(x)
+    check_flat(cfg, weights, part, x, out, u=u, b=b)
+    counts = np.bincount(out["topk"].ravel(), minlength=cfg.n_routed)
+    assert np.array_equal(out["counts"], counts)
+    layer.close()
+
+
 @pytest.mark.parametrize("T", [1, 2, 20, 64])
 def test_non_finite_tokens_stay_in_their_rows(binding, T):
     """A token of NaNs or infinities has no meaningful choice of experts, but it gets valid ones, and the other tokens of
