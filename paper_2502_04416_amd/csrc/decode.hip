@@ -378,8 +378,11 @@ __global__ __launch_bounds__(DS_WAVES * 64) void decode_down_sparse_kernel(DecAr
 // contraction on skinny tiles is as fast for the routed layer and 10-20 us faster for the dense one
 // (measured at d = 4096).
 constexpr int DECODE_MAX_T = 16;
+// Above d = 4096 a wave's K slice takes several dependent runs of loads, and the tile kernels catch up earlier: d = 5120, 2
+// tokens 61.4 against 48.8 us per forward, d = 8192, 5 tokens 97.9 against 99.1.
+constexpr int DECODE_MAX_T_RUNS = 4;
 bool decode_path_ok(const Engine& e, int64_t T) {
-  if (e.dtype != 1 || T < 1 || T > DECODE_MAX_T) return false;
+  if (e.dtype != 1 || T < 1 || T > (decode_k(e.d).nch > 1 ? DECODE_MAX_T_RUNS : DECODE_MAX_T)) return false;
   return decode_k(e.d).ksteps != 0;
 }
 

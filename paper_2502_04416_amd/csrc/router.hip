@@ -931,14 +931,15 @@ static hipError_t launch_scorer_gemm(const Engine& e, const void* x, int64_t T, 
 
 // One tile of at most 64 tokens is scored in one launch and selected + placed by one workgroup in a second.
 // Up to 16 tokens (one MFMA token tile) the scorer is decode_score_kernel, which beats the general one by
-// 3-4 us there; from 17 tokens on it is the general scorer, whose work spreads over hundreds of workgroups
+// 3-4 us there; from 17 tokens on, and where the layer's width has no decode kernels, it is the general scorer, whose
+// work spreads over hundreds of workgroups
 // (measured at d = 4096, 13 routed experts).  The larger batches need the tile's pre-activations and scores
 // to fit the 64 KB of LDS a workgroup gets by default next to 14 KB of static arrays.
 constexpr int FRONT_SCORE_MAX_T = 16;
 bool decode_front_ok(const Engine& e, int64_t T) {
   const int n_rows = e.r.n_sw_rows + e.r.n_lin_rows;
   if (e.S_dyn <= 0 || T < 1 || T > TOK_TILE) return false;
-  if (T <= FRONT_SCORE_MAX_T) return decode_path_ok(e, T) && n_rows % 16 == 0;
+  if (T <= FRONT_SCORE_MAX_T && decode_path_ok(e, T)) return n_rows % 16 == 0;
   return mfma_scorer_ok(e) && sizeof(float) * (size_t)T * (n_rows + 1 + MAX_SCORED + 1) <= 48 * 1024;
 }
 
@@ -965,7 +966,7 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
   // one token, every gate/up unit in the selection launch: with front_all = 2 that launch also scores
   const bool own_scores = L.gate_up_done && tuning().front_all >= 2 && e.wr_tiled != nullptr && decode_k(e.d).nch == 1;
   if (own_scores) {
-  } else if (T <= FRONT_SCORE_MAX_T) {
+  } else if (T <= FRONT_SCORE_MAX_T && decode_path_ok(e, T)) {
     dim3 grid(n_rows / 16, DEC_SLICES), block(64);
     const bf16_t* xx = static_cast<const bf16_t*>(x);
     const bf16_t* ww = static_cast<const bf16_t*>(e.wr);
