@@ -206,7 +206,7 @@ def bench_hier(args, cfg, np, torch, binding, synth):
     act = cfg.outer_top_k * (cfg.n_shared + cfg.top_k)       # active sub-experts per token
     gu_ms = max(float(st[2]) - 0.0044, 1e-6)
     tf1, mhz1 = binding.cmoe_probe_mfma(True, 16384)
-    roofline = {"kernel": "grouped_gemm_bf16_dma<gate_up>", "bound": "mfma",
+    roofline = {"kernel": "grouped_gemm_bf16_{ring,dma}<gate_up>", "bound": "mfma",
                 "achieved": 4.0 * d * m * act * T / (gu_ms * 1e-3) / 1e12, "peak": MFMA_BF16_PEAK_TF, "unit": "TFLOP/s",
                 "traffic": None, "avg_launch_ms": gu_ms}
     roofline["frac"] = roofline["achieved"] / roofline["peak"]
@@ -353,7 +353,7 @@ def entry(cfg, T, ms, base_ms, costs, act_per_token, union=None, shared_front=Fa
         flops_gu = 4.0 * d * m * act_per_token * T
         n_router = cfg.n_routed * (cfg.n_outer or 1)
         flops_all = T * (6.0 * d * m * act_per_token + 4.0 * d * n_router + (2.0 * d * cfg.n_outer if cfg.n_outer else 0.0))
-        row.update({"dominant_kernel": "grouped_gemm_bf16_dma<gate_up>", "bound": "mfma", "kernel_ms": gu,
+        row.update({"dominant_kernel": "grouped_gemm_bf16_{ring,dma}<gate_up>", "bound": "mfma", "kernel_ms": gu,
                     "achieved": flops_gu / (gu * 1e-3) / 1e12, "peak": MFMA_BF16_PEAK_TF, "unit": "TFLOP/s",
                     "frac": flops_gu / (gu * 1e-3) / 1e12 / MFMA_BF16_PEAK_TF,
                     "down_frac_from_raw_events": 0.5 * flops_gu / (max(costs["events_raw"]["down"], 1e-6) * 1e-3) / 1e12 / MFMA_BF16_PEAK_TF,
@@ -365,7 +365,7 @@ def entry(cfg, T, ms, base_ms, costs, act_per_token, union=None, shared_front=Fa
         n_router = cfg.n_routed * (cfg.n_outer or 1)
         bytes_all = es * (3.0 * d * m * union + 2.0 * d * n_router)
         row.update({"dominant_kernel": ("route_place_all_kernel (selection + every gate/up unit)" if fused else
-                                        "decode_gate_up_kernel" if T <= 16 else "grouped_gemm_bf16_dma<gate_up> (64x128 tiles)"),
+                                        "decode_gate_up_kernel" if T <= 16 else "grouped_gemm_bf16_{ring,dma}<gate_up> (64x128 tiles)"),
                     "bound": "hbm", "kernel_ms": gu, "expert_groups_touched": union,
                     "shared_experts_in_front_launch": bool(shared_front), "all_gate_up_units_in_front_launch": fused,
                     "achieved": bytes_gu / (gu * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -743,7 +743,7 @@ def main():
     prefill = T >= 256
     if prefill:
         gu_ms = net(float(st_moe[2]))
-        roofline = {"kernel": "grouped_gemm_bf16_dma<gate_up>", "bound": "mfma",
+        roofline = {"kernel": "grouped_gemm_bf16_{ring,dma}<gate_up>", "bound": "mfma",
                     "achieved": flops_gate_up / (gu_ms * 1e-3) / 1e12, "peak": MFMA_BF16_PEAK_TF, "unit": "TFLOP/s",
                     "traffic": None}
     else:
