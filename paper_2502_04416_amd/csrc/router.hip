@@ -970,22 +970,11 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
     dim3 grid(n_rows / 16, DEC_SLICES), block(64);
     const bf16_t* xx = static_cast<const bf16_t*>(x);
     const bf16_t* ww = static_cast<const bf16_t*>(e.wr);
-    // (the scorer holds one operand, not two: runs of up to 16 steps)
-    const int ks_all = e.d / 256, nch = ks_all <= 16 ? 1 : ks_all <= 32 ? 2 : decode_k(e.d).nch;
-#define CMOE_SCORE(KS) hipLaunchKernelGGL((decode_score_kernel<1, KS>), grid, block, 0, s, xx, ww, e.d, nch, Ti, n_rows, pre_g)
+    const DecodeK sk = score_k(e.d);
+#define CMOE_SCORE(KS) hipLaunchKernelGGL((decode_score_kernel<1, KS>), grid, block, 0, s, xx, ww, e.d, sk.nch, Ti, n_rows, pre_g)
     // (measurement aid: repeat_stage = 6 issues the scoring launch twice; it overwrites its partials)
-    for (int rep = tuning().repeat_stage == 6 ? 2 : 1; rep > 0; --rep) {
-      switch (ks_all / nch) {
-        case 16: CMOE_SCORE(16); break;
-        case 14: CMOE_SCORE(14); break;
-        case 12: CMOE_SCORE(12); break;
-        case 10: CMOE_SCORE(10); break;
-        case 8: CMOE_SCORE(8); break;
-        case 6: CMOE_SCORE(6); break;
-        case 4: CMOE_SCORE(4); break;
-        default: CMOE_SCORE(2); break;
-      }
-    }
+    for (int rep = tuning().repeat_stage == 6 ? 2 : 1; rep > 0; --rep)
+      CMOE_EVEN_KSTEPS(sk.ksteps, CMOE_SCORE)
 #undef CMOE_SCORE
     err = hipGetLastError();
   } else {

@@ -5,6 +5,7 @@ import pytest
 
 from paper_2502_04416_amd import synth
 from parity_utils import check_dense, check_flat
+from test_gpu_hier import _check, _make
 
 pytestmark = pytest.mark.gpu
 
@@ -133,3 +134,27 @@ def test_decode_kernels_at_other_widths(binding, d, T, m):
     check_dense(cfg, weights, x, layer.dense_forward(x))
     assert np.array_equal(out["y"], layer.forward(x)["y"])
     layer.close()
+
+
+@pytest.mark.parametrize("d", list(range(512, 4097, 512)) + [5120, 6144, 7680, 8192, 10240])
+def test_every_decode_width(binding, d):
+    """Every model width that the weight-streaming kernels serve; the widths above 4096, whose K slice takes several runs,
+    up to four tokens (five take the tile kernels)."""
+    for T in (1, 4, 5):
+        cfg, weights, part, x, layer = _case(binding, d, 8, 40, 1, 2, T, seed=4)
+        out = layer.forward(x)
+        check_flat(cfg, weights, part, x, out)
+        check_dense(cfg, weights, x, layer.dense_forward(x))
+        layer.close()
+
+
+@pytest.mark.parametrize("d", [1536, 5120, 6144, 7680, 8192, 10240])
+def test_hierarchy_at_decode_widths(binding, d):
+    """The same for a hierarchy: its router has SwiGLU and linear rows, and the selection a launch of its own."""
+    cfg = synth.scaled(synth.CONFIGS[4], d_model=d, d_ff=8 * 40, n_experts=8, n_shared=2, top_k=2, n_outer=4,
+                       outer_top_k=2, n_centres=16)
+    hier, experts, w_router, offsets = _make(binding, cfg)
+    for T in (1, 4):
+        x = synth.make_token_source(cfg).eval_batch(6, n=T)
+        _check(cfg, experts, w_router, offsets, x, hier.forward(x), hier.dense_forward(x), np.arange(T))
+    hier.close()
