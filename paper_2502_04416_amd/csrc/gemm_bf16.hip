@@ -541,13 +541,17 @@ __device__ __forceinline__ void dma16_buffer(const bf16_t* base, uint32_t size, 
 // acc += w * a (w: 16 weight rows x 32 K, a: 16 activation rows x 32 K).  Written as assembly to pin the
 // accumulators to the AGPRs: with the builtin the register allocator shuffles them between the two halves of the
 // register file inside the K loop (96 to 470 moves per step, and spills for the 256 x 256 tile of four waves).
-// The compiler does not see an MFMA here, so the wait states its result needs before anything but another MFMA
-// touches it are written out by mfma_drain().  Sources come from LDS reads only (waited for by the compiler as
-// for any use), and the accumulator is overwritten by nothing else inside the loop.
+// The compiler does not see an MFMA here, so it puts no wait states in front of another use of the result (8 on this
+// part) and may place such a use anywhere behind the block, a spill or a copy of an accumulator among them.  WAIT, set for the
+// last MFMA of the last K step, therefore waits inside the block: whatever follows it finds every accumulator
+// complete.  (A wait in a statement of its own came too late: the allocator had spilled an accumulator in front of it.)
+// Sources come from LDS reads only (waited for by the compiler as for any use), and the accumulator is overwritten by
+// nothing else inside the loop.  tests/test_kernel_code_cpu.py checks these distances in the machine code.
+template <bool WAIT>
 __device__ __forceinline__ void mfma_acc(floatx4_t& acc, const bf16x8_t& w, const bf16x8_t& a) {
-  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(a));
+  if constexpr (WAIT) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\ts_nop 7" : "+a"(acc) : "v"(w), "v"(a) : "memory");
+  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(a));
 }
-__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory"); }
 
 constexpr int BK = 32;                                        // K step
 constexpr int BLK = 16 * BK;                                  // elements of a 16-row block
@@ -748,8 +752,9 @@ __attribute__((amdgpu_waves_per_eu(ring_groups_per_cu(BM, BN, STAGES * KU, WGM* 
 
   const int n_steps = (KT + KU - 1) / KU;
   int slot = 0;                                               // of the current step
-  auto step = [&](int ks, auto set_tag) {
+  auto step = [&](int ks, auto set_tag, auto wait_tag) {
     constexpr int SET = decltype(set_tag)::value;
+    constexpr bool WAIT = decltype(wait_tag)::value;
     // Bare barrier: __syncthreads() would add a fence that drains every outstanding load.  What the barrier has to
     // order is covered by hand: this wave's parts of step ks + 1 have landed (vmcnt), and its LDS reads of step
     // ks have returned (lgkmcnt), so behind it step ks + 1 can be read and the slot of step ks refilled.
@@ -762,7 +767,8 @@ __attribute__((amdgpu_waves_per_eu(ring_groups_per_cu(BM, BN, STAGES * KU, WGM* 
     for (int m = 0; m < NM; ++m) {
       const int u = m / (MB * NB), mb = (m / NB) % MB, nb = m % NB;
       __builtin_amdgcn_sched_barrier(0);
-      mfma_acc(acc[mb][nb], wf[SET][u][nb], af[SET][u][mb]);
+      if (WAIT && m == NM - 1) mfma_acc<true>(acc[mb][nb], wf[SET][u][nb], af[SET][u][mb]);
+      else mfma_acc<false>(acc[mb][nb], wf[SET][u][nb], af[SET][u][mb]);
       __builtin_amdgcn_sched_barrier(0);
       // fragment f of the next step follows MFMA f * (3/4 NM) / NF: the last ones have a quarter of a step to return
       const int f = (m * NF * 4 + NM * 3 - 1) / (NM * 3);
@@ -778,11 +784,10 @@ __attribute__((amdgpu_waves_per_eu(ring_groups_per_cu(BM, BN, STAGES * KU, WGM* 
   };
   int ks = 0;
   for (; ks + 1 < n_steps; ks += 2) {
-    step(ks, std::integral_constant<int, 0>{});
-    step(ks + 1, std::integral_constant<int, 1>{});
+    step(ks, std::integral_constant<int, 0>{}, std::false_type{});
+    step(ks + 1, std::integral_constant<int, 1>{}, std::true_type{});      // (the loop may end here)
   }
-  if (ks < n_steps) step(ks, std::integral_constant<int, 0>{});
-  mfma_drain();
+  if (ks < n_steps) step(ks, std::integral_constant<int, 0>{}, std::true_type{});
   __builtin_amdgcn_sched_barrier(0);
 
   // ---- K split: the raw fp32 partial sums go to this part's slab, four consecutive columns per 16-byte store
