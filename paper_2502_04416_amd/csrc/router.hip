@@ -29,25 +29,49 @@ struct RouteIO {
   int32_t S_dyn;
 };
 
-// ---- selection by rank ---------------------------------------------------------------------------------
-// The k-th largest of n keys is the one that exactly k - 1 keys beat.  Counting for every key how many beat it (a
-// larger key, or an equal one with a lower index) takes n independent compares per key and no exchange
-// between lanes, and every winner knows its place in the list at once, where rounds of arg-max are a chain of
-// dependent lane exchanges: 32 tokens, 28 experts, top-4 in one workgroup 17.6 -> 12.5 us for the whole launch, the
-// hierarchy's 4096 tokens 18.6 -> 10.2.
+// ---- selection -----------------------------------------------------------------------------------------
+// One wave with one token picks the best lane, its next best and so on (wave_argmax), a short chain per round whatever
+// the number of candidates: whole forward at d = 4096, 32 experts, top-1 19.8 us and top-2 17.0, by rank 21.1 and 18.3.
+// A workgroup with a tile of tokens selects by rank: the k-th largest of n keys is the one that exactly k - 1 keys
+// beat.  Counting for every key how many beat it (a larger key, or an equal one with a lower index) takes n
+// independent compares per key and no exchange between lanes, and every winner knows its place in the list at once:
+// 32 tokens, 28 experts, top-4 in one workgroup 17.6 -> 12.5 us for the whole launch, the hierarchy's 4096 tokens
+// 18.6 -> 10.2.
 // Keys are compared as ordered integers, a total order for every bit pattern (a NaN cannot make two experts share
 // a rank or leave one empty); -0 counts as +0.
 __device__ __forceinline__ uint32_t rank_key(float f) { return ordered_key(f + 0.0f); }
 
-// Number of lanes in [lo, lo + n) whose key beats this lane's.  All 64 lanes must call; lo and n are uniform.
-__device__ __forceinline__ int wave_rank(uint32_t key, int lo, int n) {
-  const int lane = threadIdx.x & 63;
+// How many of n keys in LDS (as float bits) beat key j.  The reads of eight candidates are in flight together (one at a
+// time, with a gate parameter from memory for each: 31.6 us per forward of 5 tokens, 31 experts; now 28.2).
+__device__ __forceinline__ int lds_rank(const float* keys, int n, int j) {
+  const uint32_t key = __float_as_uint(keys[j]);
   int rank = 0;
-  for (int i = lo; i < lo + n; ++i) {
-    const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)key, i);
-    rank += (o > key || (o == key && i < lane)) ? 1 : 0;
+  for (int q0 = 0; q0 < n; q0 += 8) {
+    uint32_t o[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) o[u] = __float_as_uint(keys[q0 + u < n ? q0 + u : q0]);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) rank += (q0 + u < n && (o[u] > key || (o[u] == key && q0 + u < j))) ? 1 : 0;
   }
   return rank;
+}
+
+// Gate parameters (Eq. 9) of all scored experts in LDS: requested when a kernel starts, stored when its first loads
+// are back, so that no selection waits for them.
+struct GateLds { float u[MAX_SCORED], b[MAX_SCORED]; };
+__device__ __forceinline__ float2 request_gate(const RouterDev& r, const RouteIO& io, int tid) {
+  float2 g = make_float2(0.0f, 0.0f);
+  if (r.use_gate && tid < r.n_scored) {
+    if (io.gate_u) g.x = io.gate_u[tid];
+    if (io.gate_b) g.y = io.gate_b[tid];
+  }
+  return g;
+}
+__device__ __forceinline__ void store_gate(GateLds& gl, float2 g, int tid) {
+  if (tid < MAX_SCORED) {
+    gl.u[tid] = g.x;
+    gl.b[tid] = g.y;
+  }
 }
 
 // Top-N_k among the routed experts held by lanes [lo, lo + n) (one lane per expert), Eq. 9:
@@ -58,23 +82,30 @@ __device__ __forceinline__ void select_routed(const RouterDev& r, const RouteIO&
                                               int32_t* topk_ptr, int32_t* hist) {
   const int lane = threadIdx.x & 63;
   const bool in_range = lane >= lo && lane < lo + n;
-  float key = skey, sp = 0.0f;
+  float key = skey, sp = 0.0f, gate_u = 0.0f, gate_b = 0.0f;
   if (r.use_gate) {
+    if (io.gate_u && in_range) gate_u = io.gate_u[lane];     // (needed last, requested first)
+    if (io.gate_b && in_range) gate_b = io.gate_b[lane];
     const float mx = wave_max(in_range ? skey : -INFINITY);
     const float ex = in_range ? expf(skey - mx) : 0.0f;
     const float sum = wave_sum(ex);
     sp = ex / sum;
-    key = sp + ((io.gate_b && in_range) ? io.gate_b[lane] : 0.0f);
+    key = sp + gate_b;
   }
-  const int rank = wave_rank(rank_key(key), lo, n);
-  if (in_range && rank < r.top_k) {
-    float gate = 1.0f;
-    if (r.use_gate && io.gate_u) gate = 1.0f + sp * io.gate_u[lane];
-    const int g = group_base + (lane - lo);
-    io.sel_group[t * io.S_dyn + n_entries + rank] = g;
-    io.sel_weight[t * io.S_dyn + n_entries + rank] = scale * gate;
-    if (topk_ptr) topk_ptr[rank] = lane - lo;
-    if (hist) atomicAdd(&hist[g], 1);
+  const uint32_t rkey = rank_key(key);
+  bool active = in_range;
+  for (int k = 0; k < r.top_k; ++k) {
+    const int w = wave_argmax(rkey, active);                  // uniform
+    if (lane == w) {
+      float gate = 1.0f;
+      if (r.use_gate && io.gate_u) gate = 1.0f + sp * gate_u;
+      const int g = group_base + (lane - lo);
+      io.sel_group[t * io.S_dyn + n_entries + k] = g;
+      io.sel_weight[t * io.S_dyn + n_entries + k] = scale * gate;
+      if (topk_ptr) topk_ptr[k] = lane - lo;
+      if (hist) atomicAdd(&hist[g], 1);
+      active = false;
+    }
   }
   n_entries += r.top_k;
 }
@@ -100,14 +131,16 @@ __device__ __forceinline__ void route_token(const RouterDev& r, const RouteIO& i
   }
   // two-level: outer linear logits -> top outer_top_k -> softmax over the selected logits
   float logit = -INFINITY;
-  if (lane < r.n_lin) logit = pre[r.n_sw_rows + lane] + (io.lin_off ? io.lin_off[lane] : 0.0f);
-  const int orank = wave_rank(rank_key(logit), 0, r.n_lin);
+  bool active = lane < r.n_lin;
+  if (active) logit = pre[r.n_sw_rows + lane] + (io.lin_off ? io.lin_off[lane] : 0.0f);
+  const uint32_t okey = rank_key(logit);
   int oe[MAX_OUTER_TOPK];
   float ol[MAX_OUTER_TOPK];
   for (int i = 0; i < r.outer_top_k; ++i) {
-    const int w = __ffsll((unsigned long long)__ballot(lane < r.n_lin && orank == i)) - 1;
+    const int w = wave_argmax(okey, active);
     oe[i] = w;
-    ol[i] = __shfl(logit, w, 64);
+    ol[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(logit), w));
+    if (lane == w) active = false;
   }
   float den = 0.0f;
   for (int i = 0; i < r.outer_top_k; ++i) den += expf(ol[i] - ol[0]);
@@ -131,13 +164,14 @@ __device__ __forceinline__ void route_token(const RouterDev& r, const RouteIO& i
 }
 
 // ---- a tile of tokens ----------------------------------------------------------------------------------
-// One thread per (token, candidate), all threads of the workgroup (which all must call: barriers).  `sc`: the
-// tile's scores [tok][ld_sc] (Eq. 8, signed); `pre`: its pre-activations [tok][ld], of which the linear logits
-// behind the n_sw_rows SwiGLU rows are read and the SwiGLU rows themselves, no longer needed, hold Softmax(s)
-// and the outer choice.  Sums run in the order ((j = 0 mod 4) + (1 mod 4)) + ((2 mod 4) + (3 mod 4)).
+// One thread per (token, candidate), all threads of the workgroup (which all must call: barriers).  `sc`: what
+// score_tile left, [tok][ld_sc]; `pre`: the tile's pre-activations [tok][ld], of which the linear logits
+// behind the n_sw_rows SwiGLU rows are read and the rows, no longer needed, then hold exp(s - max) [n_scored], the
+// outer choice [2 n_outer] and Softmax(s) [n_scored] (n_sw_rows is at least twice n_scored, and a hierarchy has 32 linear
+// rows).  Sums run in the order ((j = 0 mod 4) + (1 mod 4)) + ((2 mod 4) + (3 mod 4)).
 __device__ __forceinline__ void route_select_tile(const RouterDev& r, const RouteIO& io, float* sc, int ld_sc,
-                                                  float* pre, int ld, int n_tok, int64_t t0, int32_t* hist, int tid,
-                                                  int n_threads) {
+                                                  float* pre, int ld, int n_tok, int64_t t0, int32_t* hist,
+                                                  const GateLds& gl, int tid, int n_threads) {
   const int n_outer = r.outer_top_k > 0 ? r.outer_top_k : 1;
   // a token's outer choice: n_outer logits, then n_outer expert ids
   auto outer_of = [&](int tok) { return r.n_sw_rows > 0 ? pre + tok * ld + r.n_scored : sc + tok * ld_sc; };
@@ -167,22 +201,21 @@ __device__ __forceinline__ void route_select_tile(const RouterDev& r, const Rout
   auto first_of = [&](int tok, int i) {                               // first candidate of the token's i-th choice
     return r.outer_top_k > 0 ? __float_as_int(outer_of(tok)[n_outer + i]) * n : 0;
   };
-  auto rank_score = [&](float s) { return r.score_abs ? fabsf(s) : s; };
+  const int sp0 = r.n_scored + (r.outer_top_k > 0 ? 2 * n_outer : 0);
   if (r.use_gate && routed) {
     for (int idx = tid; idx < n_tok * per_tok; idx += n_threads) {
       const int tok = idx / per_tok, c = idx - tok * per_tok, i = c / n, j = c - i * n;
       const int lo = first_of(tok, i);
       const float* s = sc + tok * ld_sc + lo;
       float mx = -INFINITY;
-      for (int q = 0; q < n; ++q) mx = fmaxf(mx, rank_score(s[q]));
-      pre[tok * ld + lo + j] = expf(rank_score(s[j]) - mx);
+      for (int q0 = 0; q0 < n; q0 += 8)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) mx = fmaxf(mx, s[q0 + u < n ? q0 + u : q0]);
+      pre[tok * ld + lo + j] = expf(s[j] - mx);
     }
     __syncthreads();
-    // Softmax(s): read by every candidate of the choice before any overwrites it
-    for (int base = 0; base < n_tok * per_tok; base += n_threads) {
-      const int idx = base + tid;
-      const bool ok = idx < n_tok * per_tok;
-      const int tok = ok ? idx / per_tok : 0, c = ok ? idx - tok * per_tok : 0, i = c / n, j = c - i * n;
+    for (int idx = tid; idx < n_tok * per_tok; idx += n_threads) {
+      const int tok = idx / per_tok, c = idx - tok * per_tok, i = c / n, j = c - i * n;
       const int lo = first_of(tok, i);
       const float* ex = pre + tok * ld + lo;
       float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -191,7 +224,8 @@ __device__ __forceinline__ void route_select_tile(const RouterDev& r, const Rout
         for (int u = 0; u < 4; ++u)
           if (q + u < n) part[u] += ex[q + u];
       const float sp = ex[j] / ((part[0] + part[1]) + (part[2] + part[3]));
-      if (ok) sc[tok * ld_sc + lo + j] = sp;                           // (the scores were written out and are used up)
+      pre[tok * ld + sp0 + lo + j] = sp;
+      sc[tok * ld_sc + lo + j] = __uint_as_float(rank_key(sp + gl.b[lo + j]));      // (the scores are used up)
     }
     __syncthreads();
   }
@@ -199,10 +233,6 @@ __device__ __forceinline__ void route_select_tile(const RouterDev& r, const Rout
     const int tok = idx / per_tok, c = idx - tok * per_tok, i = c / n, j = c - i * n;
     const int64_t t = t0 + tok;
     const int lo = first_of(tok, i);
-    const float* s = sc + tok * ld_sc + lo;
-    auto key_of = [&](int q) {
-      return r.use_gate ? rank_key(s[q] + (io.gate_b ? io.gate_b[lo + q] : 0.0f)) : rank_key(rank_score(s[q]));
-    };
     float w_e = 1.0f;
     int entry = 0, gbase = r.n_always;
     if (r.outer_top_k > 0) {
@@ -223,15 +253,10 @@ __device__ __forceinline__ void route_select_tile(const RouterDev& r, const Rout
       }
     }
     if (!routed) continue;
-    const uint32_t key = key_of(j);
-    int rank = 0;
-    for (int q = 0; q < n; ++q) {
-      const uint32_t o = key_of(q);
-      rank += (o > key || (o == key && q < j)) ? 1 : 0;
-    }
+    const int rank = lds_rank(sc + tok * ld_sc + lo, n, j);
     if (rank < r.top_k) {
       float gate = 1.0f;
-      if (r.use_gate && io.gate_u) gate = 1.0f + s[j] * io.gate_u[lo + j];
+      if (r.use_gate && io.gate_u) gate = 1.0f + pre[tok * ld + sp0 + lo + j] * gl.u[lo + j];
       io.sel_group[t * io.S_dyn + entry + rank] = gbase + j;
       io.sel_weight[t * io.S_dyn + entry + rank] = w_e * gate;
       if (io.topk_out) io.topk_out[(t * n_outer + i) * r.top_k + rank] = j;
@@ -241,7 +266,8 @@ __device__ __forceinline__ void route_select_tile(const RouterDev& r, const Rout
 }
 
 // Scores of a tile of tokens, all threads of the workgroup in parallel (the exponentials are the
-// expensive part of routing): sc[tok][j] = Swish(gate_j) * up_j from pre[tok][...] (Eq. 8).
+// expensive part of routing): Swish(gate_j) * up_j from pre[tok][...] (Eq. 8).  sc[tok][j] gets what the selection
+// needs of it: the score to rank by, of which Eq. 9 takes the softmax, or without a gate its key.
 __device__ __forceinline__ void score_tile(const RouterDev& r, const RouteIO& io, const float* pre, int ld_pre,
                                            float* sc, int ld_sc, int n_tok, int64_t t0, int tid, int n_threads) {
   for (int idx = tid; idx < n_tok * r.n_scored; idx += n_threads) {
@@ -249,7 +275,8 @@ __device__ __forceinline__ void score_tile(const RouterDev& r, const RouteIO& io
     const int blk = j / IL, c = j % IL;
     const float g = pre[tok * ld_pre + blk * 2 * IL + c], u = pre[tok * ld_pre + blk * 2 * IL + IL + c];
     const float s = silu_f32(g) * u;
-    sc[tok * ld_sc + j] = s;
+    const float ranked = r.score_abs ? fabsf(s) : s;
+    sc[tok * ld_sc + j] = r.use_gate ? ranked : __uint_as_float(rank_key(ranked));
     if (io.scores_out) io.scores_out[(t0 + tok) * r.n_scored + j] = s;
   }
 }
@@ -410,18 +437,21 @@ __global__ __launch_bounds__(RT_THREADS) void route_tile_kernel(RouterDev r, Rou
                                                                 int G) {
   extern __shared__ float pre[];                 // [TOK_TILE][n_rows + 1], then scores [TOK_TILE][LD_SC]
   __shared__ int32_t hist[MAX_GROUPS];
+  __shared__ GateLds gl;
   const int tid = threadIdx.x;
   const int n_rows = r.n_sw_rows + r.n_lin_rows;
   const int ld = n_rows + 1;
   float* sc = pre + TOK_TILE * ld;
   const int64_t t0 = (int64_t)blockIdx.x * TOK_TILE;
+  const float2 gate = request_gate(r, io, tid);
   sum_partials(partial, n_slices, T, t0, TOK_TILE, n_rows, pre, ld, tid, RT_THREADS);
   for (int i = tid; i < MAX_GROUPS; i += RT_THREADS) hist[i] = 0;
+  store_gate(gl, gate, tid);
   __syncthreads();
   const int n_tok = (T - t0 < TOK_TILE) ? (int)(T - t0) : TOK_TILE;
   score_tile(r, io, pre, ld, sc, LD_SC, n_tok, t0, tid, RT_THREADS);
   __syncthreads();
-  route_select_tile(r, io, sc, LD_SC, pre, ld, n_tok, t0, hist, tid, RT_THREADS);
+  route_select_tile(r, io, sc, LD_SC, pre, ld, n_tok, t0, hist, gl, tid, RT_THREADS);
   __syncthreads();
   for (int g = tid; g < G; g += RT_THREADS) tile_counts[(int64_t)blockIdx.x * G + g] = hist[g];
 }
@@ -442,6 +472,7 @@ __global__ __launch_bounds__(512) void score_route_kernel(RouterDev r, RouteIO i
   constexpr int NTOK = TB * 16, LDP = 64 + 4;
   extern __shared__ __attribute__((aligned(16))) float sr_smem[];
   __shared__ int32_t hist[MAX_GROUPS];
+  __shared__ GateLds gl;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kq = lane >> 4;
@@ -452,6 +483,7 @@ __global__ __launch_bounds__(512) void score_route_kernel(RouterDev r, RouteIO i
   float* sc = pre + NTOK * ld;                                 // [NTOK][LD_SC]
   const int64_t t0 = (int64_t)blockIdx.x * NTOK;
   for (int i = tid; i < MAX_GROUPS; i += 512) hist[i] = 0;
+  const float2 gate = request_gate(r, io, tid);
   const bf16_t* xr[TB];
 #pragma unroll
   for (int tb = 0; tb < TB; ++tb) {
@@ -542,9 +574,10 @@ __global__ __launch_bounds__(512) void score_route_kernel(RouterDev r, RouteIO i
     __syncthreads();
   }
   const int n_tok = (T - t0 < NTOK) ? (int)(T - t0) : NTOK;
+  store_gate(gl, gate, tid);
   score_tile(r, io, pre, ld, sc, LD_SC, n_tok, t0, tid, 512);
   __syncthreads();
-  route_select_tile(r, io, sc, LD_SC, pre, ld, n_tok, t0, hist, tid, 512);
+  route_select_tile(r, io, sc, LD_SC, pre, ld, n_tok, t0, hist, gl, tid, 512);
   __syncthreads();
   for (int g = tid; g < G; g += 512) counts[(int64_t)blockIdx.x * G + g] = hist[g];
 }
@@ -663,6 +696,7 @@ __device__ __forceinline__ void route_place_body(const RouterDev& r, RouteIO io,
   __shared__ int32_t hist[MAX_GROUPS];
   __shared__ int32_t sel_g[TOK_TILE * MAX_DYN];
   __shared__ float sel_w[TOK_TILE * MAX_DYN];
+  __shared__ GateLds gl;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n_threads = blockDim.x;
   const int n_rows = r.n_sw_rows + r.n_lin_rows;
@@ -675,8 +709,10 @@ __device__ __forceinline__ void route_place_body(const RouterDev& r, RouteIO io,
     io.outer_out = nullptr;
     io.scores_out = nullptr;
   }
+  const float2 gate = request_gate(r, io, tid);
   sum_partials(partial, n_slices, T, 0, T, n_rows, pre, ld, tid, n_threads);
   for (int i = tid; i < MAX_GROUPS; i += n_threads) hist[i] = 0;
+  store_gate(gl, gate, tid);
   __syncthreads();
   io.sel_group = sel_g;
   io.sel_weight = sel_w;
@@ -690,7 +726,7 @@ __device__ __forceinline__ void route_place_body(const RouterDev& r, RouteIO io,
   }
   score_tile(r, io, pre, ld, sc, LD_SC, T, 0, tid, n_threads);
   __syncthreads();
-  route_select_tile(r, io, sc, LD_SC, pre, ld, T, 0, hist, tid, n_threads);
+  route_select_tile(r, io, sc, LD_SC, pre, ld, T, 0, hist, gl, tid, n_threads);
   __syncthreads();
   if (mine) {
     // T <= 16 tokens, G <= 64 groups (the caller checked): lane g holds group g's count and width, lane t token t
