@@ -106,16 +106,18 @@ PlaceArgs make_place_args(const Engine& e, int64_t T, char* ws, const WsLayout& 
   p.tile_counts = reinterpret_cast<const int32_t*>(ws + ct.offset);
   p.n_counts = (int)((T + ct.tokens - 1) / ct.tokens);
   p.counts_per_tile = TOK_TILE / ct.tokens;
-  p.bm1 = gemm_tile(e, T, 1);
-  p.bn1 = gemm_tile(e, T, 3);
-  p.bm2 = gemm_tile(e, T, 2);
-  p.bn2 = gemm_tile(e, T, 4);
   p.d = e.d;
-  p.dyn1 = gemm_tile(e, T, 5);
-  p.dyn2 = gemm_tile(e, T, 6);
   p.decode = (!use_simt_experts(e.dtype) && decode_path_ok(e, T)) ? 1 : 0;
   p.skip_always = L.skip_always;
   p.dec_unit1 = p.decode ? decode_unit_neurons(e, T) : 16;
+  // (a decode batch has no tiles; choosing their shapes all the same takes longer than one of its launches)
+  const bool tiles = p.decode == 0;
+  p.bm1 = tiles ? gemm_tile(e, T, 1) : 1;
+  p.bn1 = tiles ? gemm_tile(e, T, 3) : 1;
+  p.bm2 = tiles ? gemm_tile(e, T, 2) : 1;
+  p.bn2 = tiles ? gemm_tile(e, T, 4) : 1;
+  p.dyn1 = tiles ? gemm_tile(e, T, 5) : 0;
+  p.dyn2 = tiles ? gemm_tile(e, T, 6) : 0;
   return p;
 }
 
