@@ -158,3 +158,24 @@ def test_hierarchy_at_decode_widths(binding, d):
         x = synth.make_token_source(cfg).eval_batch(6, n=T)
         _check(cfg, experts, w_router, offsets, x, hier.forward(x), hier.dense_forward(x), np.arange(T))
     hier.close()
+
+
+@pytest.mark.parametrize("gate", [False, True])
+@pytest.mark.parametrize("N,n_s,k", [(40, 1, 9), (40, 1, 10), (13, 0, 1), (13, 1, 1), (65, 1, 16), (33, 1, 6), (33, 1, 7)])
+@pytest.mark.parametrize("T", [1, 3, 20, 64, 130])
+def test_selection_by_rounds_and_by_rank(binding, N, n_s, k, T, gate):
+    """Both sides of the line between the two selections of a tile (160 top_k against the square of the routed experts),
+    and one token; equal scores go to the lower expert either way."""
+    cfg, weights, part, x, layer = _case(binding, 512, N, 8, n_s, k, T, seed=5)
+    layer.close()
+    reps = part["rep_neuron"].copy()
+    reps[7] = reps[2]                                   # routed experts 2 and 7 share their representative
+    part = dict(part, rep_neuron=reps)
+    layer = binding.Layer.from_partition(cfg, *weights, part["neuron_order"], reps)
+    u = b = None
+    if gate:
+        u, b = synth.make_gate_params(cfg, seed=7300)
+        b[7] = b[2]
+        layer.set_gate_params(u, b)
+    check_flat(cfg, weights, part, x, layer.forward(x), u=u, b=b, exact_ties_strict=True)
+    layer.close()
