@@ -903,6 +903,7 @@ static const TileCfg kCfgs[] = {
     {64, 128, 2, 2, 6, 32},    // 21: deep ring in steps of 64, four waves of 32x64, two workgroups per CU
 };
 static bool cfg_is_ws(int ci) { return ci >= 15 && ci <= 18; }
+static bool cfg_is_ring(int ci) { return kCfgs[ci].stages >= 5; }
 static bool cfg_is_dyn(int ci) { return ci >= 11 && ci <= 18; }
 bool ws_down_handles(int width_pad);
 hipError_t launch_ws_down(const Engine& e, char* ws, const WsLayout& L, const void* y_slots, int rc, int n_blocks,
@@ -1075,21 +1076,25 @@ static int splitk_ldp(const Engine& e, int which) { return which == 1 ? 2 * e.ma
 
 int bf16_splitk(const Engine& e, int64_t T, int which) {
   if (T < 1 || T > 1024 || tuning().splitk == 0) return 1;
-  if (cfg_is_ws(cfg_index(which, e, T))) return 1;
-  const TileCfg& c = kCfgs[cfg_index(which, e, T)];
+  const int ci = cfg_index(which, e, T);
+  if (cfg_is_ws(ci)) return 1;
+  const TileCfg& c = kCfgs[ci];
   const int64_t tiles = est_tiles(e, T, which, c.bm, c.bn);
   int k_min = e.d;
   if (which == 2) {
     k_min = 1 << 30;
     for (int g = 0; g < e.G; ++g) k_min = std::min(k_min, e.width_pad_host[g]);
   }
-  const int kt = cdiv(k_min, c.bk);
+  // (On the deep ring a K tile counts 64 like the other shapes': counted in its steps of 32, parts of 128 were allowed, too
+  // short to be worth their partial sums: dense FFN, d = 512, 50 tokens 24.2 -> 21.2 us, 8 experts, d = 1536, 64 tokens
+  // 37.5 -> 34.3.)
+  const int kt = cdiv(k_min, cfg_is_ring(ci) ? 64 : c.bk);
   const size_t per_part = (size_t)splitk_rows(e, T) * splitk_ldp(e, which) * sizeof(float);
   int ks = 1;
   // Split only while the launch stays well inside one round of workgroups (two tiles of 128 rows fit a CU, one of
   // the larger shapes): measured at 64..512 tokens, splitting a launch that already has a tile for most
   // CUs costs more (partial sums, a second launch) than the shorter K loop saves.
-  const int64_t slots = (c.bm == 128 && c.stages != 5) ? 2 : 1;      // (the deep ring's 128x128 counts as one per CU)
+  const int64_t slots = (c.bm == 128 && !cfg_is_ring(ci)) ? 2 : 1;      // (the deep ring's 128x128 counts as one per CU)
   while (ks < 8 && tiles * ks * 2 <= 192 * slots && kt / (ks * 2) >= 4 && per_part * ks * 2 <= SPLITK_MAX_BYTES) ks *= 2;
   return ks;
 }

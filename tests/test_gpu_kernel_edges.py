@@ -47,17 +47,25 @@ def test_deep_ring_shapes(binding, which, shape, d, m, T):
     layer.close()
 
 
-@pytest.mark.parametrize("shape", [6, 20, 21])
-def test_deep_ring_k_split(binding, shape):
-    """Partial sums of a K split whose last part is empty or short (d = 576: 18 steps over up to 4 parts)."""
-    cfg, weights, part, x, layer = _case(binding, 576, 8, 64, 1, 2, 90)
+@pytest.mark.parametrize("which", ["CMOE_GEMM1_CFG", "CMOE_GEMM2_CFG"])
+@pytest.mark.parametrize("shape", [0, 6, 20, 21])
+def test_deep_ring_k_split(binding, which, shape):
+    """Partial sums of a K split whose last part is short: d = 1056 for gate/up (33 steps: parts of 9, the last of 6), the
+    dense layer's d_ff = 1088 for down (34: of 9, the last of 7)."""
+    cfg, weights, part, x, layer = _case(binding, 1056, 8, 136, 1, 2, 90)
+    flat, dense = {}, {}
     try:
-        binding.cmoe_set_tuning("CMOE_GEMM1_CFG", shape)
-        out, dense = layer.forward(x), layer.dense_forward(x)
+        for split in (0, 1):
+            binding.cmoe_set_tuning("CMOE_SPLITK", split)
+            binding.cmoe_set_tuning(which, shape)
+            flat[split], dense[split] = layer.forward(x), layer.dense_forward(x)
+            binding.cmoe_set_tuning(which, -1)
     finally:
-        binding.cmoe_set_tuning("CMOE_GEMM1_CFG", -1)
-    check_flat(cfg, weights, part, x, out)
-    check_dense(cfg, weights, x, dense)
+        binding.cmoe_set_tuning("CMOE_SPLITK", 1)
+        binding.cmoe_set_tuning(which, -1)
+    check_flat(cfg, weights, part, x, flat[1])
+    check_dense(cfg, weights, x, dense[1])
+    assert not np.array_equal(dense[0], dense[1])     # K was split: another order of the same sum
     layer.close()
 
 
