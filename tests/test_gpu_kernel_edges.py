@@ -65,7 +65,7 @@ def test_deep_ring_k_split(binding, which, shape):
         binding.cmoe_set_tuning(which, -1)
     check_flat(cfg, weights, part, x, flat[1])
     check_dense(cfg, weights, x, dense[1])
-    assert not np.array_equal(dense[0], dense[1])     # K was split: another order of the same sum
+    assert not np.array_equal(dense[0], dense[1])       # another order of the same sum
     layer.close()
 
 
