@@ -1029,8 +1029,11 @@ static int cfg_index(int which, const Engine& e, int64_t T) {
       }
     }
   }
-  if (which == 1 && e.S_dyn > 0 && wide_gather(e.d, T)) return 6;      // (the only ring shape built with 64-bit row addresses)
   const int forced = which == 1 ? tuning().gemm1_cfg : tuning().gemm2_cfg;
+  if (which == 1 && e.S_dyn > 0 && wide_gather(e.d, T)) {
+    // (of the ring shapes only 6 is built with 64-bit row addresses; the others have them)
+    return forced >= 0 && forced < kNumCfgs && !cfg_is_ws(forced) && !cfg_is_ring(forced) ? forced : 6;
+  }
   if (forced >= 0 && forced < kNumCfgs && !(which == 1 && cfg_is_ws(forced))) return forced;
   if (which == 2 && tuning().ws_down != 0 && !(e.G == 1 && e.n_always == 1) && e.w_tiled && e.d % 256 == 0) {
     // The weight-stationary kernel for the groups it handles, when the batch gives it enough work items to

@@ -70,34 +70,50 @@ def test_deep_ring_k_split(binding, which, shape):
 
 
 def test_gather_across_two_gigabytes(binding):
-    """A batch whose rows lie 2 GB and more apart: 64-bit row addresses in the gate/up contraction.  A forward of
-    the same tokens in two smaller batches gives the same bits token by token."""
+    """A batch whose rows lie 2 GB and more apart: 64-bit row addresses in the gate/up contraction.  Tokens from its
+    beginning, middle and end against the oracle; the same tokens in two smaller batches, and with a forced shape of
+    either kind (a ring shape without such addresses gives way to the one that has them), give the same bits."""
     import torch
     T, d = 262144 + 77, 4096
     cfg = synth.scaled(synth.CONFIGS[1], d_model=d, d_ff=8 * 32, n_experts=8, n_shared=1, top_k=1, n_centres=16)
-    part = synth.trivial_partition(cfg)
-    layer = binding.Layer.from_partition(cfg, *synth.make_weights(cfg), part["neuron_order"], part["rep_neuron"])
+    part, weights = synth.trivial_partition(cfg), synth.make_weights(cfg)
+    layer = binding.Layer.from_partition(cfg, *weights, part["neuron_order"], part["rep_neuron"])
     x = torch.randn((T, d), generator=torch.Generator(device="cuda").manual_seed(5), device="cuda", dtype=torch.bfloat16)
     y, half, y2 = torch.empty_like(x), 131072, torch.empty_like(x)
-    layer.forward_device(x, y)
+    topk = torch.empty((T, 1), dtype=torch.int32, device="cuda")
+    scores = torch.empty((T, 7), dtype=torch.float32, device="cuda")
+    layer.forward_device(x, y, topk=topk, scores=scores)
+    idx = torch.cat([torch.arange(t, t + 40) for t in (0, half - 20, 262144 - 20, T - 40)]).cuda()
+    out = {"y": y[idx].float().cpu().numpy(), "topk": topk[idx].cpu().numpy(), "scores": scores[idx].cpu().numpy()}
+    out["counts"] = np.bincount(out["topk"].ravel(), minlength=7)
+    check_flat(cfg, weights, part, x[idx].float().cpu().numpy(), out)
     # (a multiple of 16384 tokens per piece keeps the router's K slices, hence its scores, those of the whole batch)
     for lo, hi in ((0, half), (half, T)):
         layer.forward_device(x[lo:hi], y2[lo:hi])
     assert torch.equal(y, y2)
+    try:
+        for shape in (4, 9):
+            binding.cmoe_set_tuning("CMOE_GEMM1_CFG", shape)
+            y2.zero_()
+            layer.forward_device(x, y2)
+            assert torch.equal(y, y2)
+    finally:
+        binding.cmoe_set_tuning("CMOE_GEMM1_CFG", -1)
     layer.close()
 
 
 @pytest.mark.parametrize("gate", [False, True])
 @pytest.mark.parametrize("d,N,n_s,k,T", [
-    (512, 16, 1, 3, 65),        # two K slices of one chunk
+    (512, 16, 1, 3, 65),        # two K slices of one chunk, 32 tokens per workgroup
     (512, 40, 2, 5, 97),        # more than 32 routed experts: two groups of 64 router rows
-    (768, 12, 0, 1, 79),        # three slices
+    (768, 12, 0, 1, 79),        # three slices: the two launches
     (1536, 12, 1, 4, 130),      # six slices: three units per wave, the last waves short
-    (2048, 65, 1, 16, 200),     # 64 routed experts, top-16
+    (2048, 65, 1, 16, 200),     # 64 routed experts, top-16: eight slices of one chunk
     (2560, 16, 1, 3, 71),       # five slices of two chunks
-    (4096, 8, 1, 7, 2081),      # four slices, every routed expert chosen
-    (512, 8, 2, 2, 8300),       # two slices of two and of one chunk
-    (512, 8, 1, 2, 16500),      # one slice
+    (4096, 8, 1, 7, 2081),      # eight slices of two chunks, every routed expert chosen
+    (512, 8, 2, 2, 8300),       # two slices of one chunk, 32 tokens per workgroup
+    (1024, 8, 1, 2, 8300),      # two slices of two chunks
+    (512, 8, 1, 2, 16500),      # one slice of two chunks
 ])
 def test_scoring_and_selection_in_one_launch(binding, d, N, n_s, k, T, gate):
     """Prefill batches of a flat layer: K slices, units per wave, token blocks and histogram rows of every kind."""
@@ -113,11 +129,14 @@ def test_scoring_and_selection_in_one_launch(binding, d, N, n_s, k, T, gate):
     layer.close()
 
 
-@pytest.mark.parametrize("T", [1, 2, 20, 64])
-def test_non_finite_tokens_stay_in_their_rows(binding, T):
+@pytest.mark.parametrize("gate", [False, True])
+@pytest.mark.parametrize("d,T", [(512, 1), (512, 2), (512, 20), (512, 64), (512, 65), (512, 200), (768, 200)])
+def test_non_finite_tokens_stay_in_their_rows(binding, d, T, gate):
     """A token of NaNs or infinities has no meaningful choice of experts, but it gets valid ones, and the other tokens of
-    the batch keep their outputs."""
-    cfg, weights, part, x, layer = _case(binding, 512, 16, 32, 1, 3, T, seed=2)
+    the batch keep their outputs.  (One token, one tile, scoring and selection in one launch, and in two: d = 768.)"""
+    cfg, weights, part, x, layer = _case(binding, d, 16, 32, 1, 3, T, seed=2)
+    if gate:
+        layer.set_gate_params(*synth.make_gate_params(cfg, seed=7300))
     ref = layer.forward(x)
     bad = x.copy()
     bad[0] = np.nan
@@ -127,9 +146,29 @@ def test_non_finite_tokens_stay_in_their_rows(binding, T):
     assert ((out["topk"] >= 0) & (out["topk"] < cfg.n_routed)).all()
     assert all(len(set(row)) == cfg.top_k for row in out["topk"].tolist())
     n_bad = 2 if T > 2 else 1
-    assert np.array_equal(out["topk"][n_bad:], ref["topk"][n_bad:])
-    assert np.array_equal(out["y"][n_bad:], ref["y"][n_bad:])
+    if T > n_bad:
+        assert np.array_equal(out["topk"][n_bad:], ref["topk"][n_bad:])
+        assert np.array_equal(out["y"][n_bad:], ref["y"][n_bad:])
     layer.close()
+
+
+@pytest.mark.parametrize("T", [1, 2, 40, 130])
+def test_non_finite_tokens_in_a_hierarchy(binding, T):
+    cfg = synth.scaled(synth.CONFIGS[4], d_model=512, d_ff=8 * 40, n_experts=8, n_shared=2, top_k=2, n_outer=4,
+                       outer_top_k=2, n_centres=16)
+    hier, _, _, _ = _make(binding, cfg, gate=True)
+    x = synth.make_token_source(cfg).eval_batch(7, n=T)
+    ref = hier.forward(x)
+    bad = x.copy()
+    bad[0] = np.nan
+    out = hier.forward(bad)
+    assert all(len(set(row)) == 2 for row in out["outer"].tolist())
+    assert ((out["outer"] >= 0) & (out["outer"] < 4)).all() and ((out["sub"] >= 0) & (out["sub"] < 6)).all()
+    assert all(len(set(row)) == 2 for row in out["sub"].reshape(-1, 2).tolist())
+    if T > 1:
+        assert np.array_equal(out["outer"][1:], ref["outer"][1:]) and np.array_equal(out["sub"][1:], ref["sub"][1:])
+        assert np.array_equal(out["y"][1:], ref["y"][1:])
+    hier.close()
 
 
 @pytest.mark.parametrize("d", [1536, 2560, 3584, 5120, 8192])
