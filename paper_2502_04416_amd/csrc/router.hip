@@ -826,15 +826,17 @@ __global__ __launch_bounds__(512) void route_place_all_kernel(RouterDev r, Route
     decode_gate_up<1, KSTEPS, RUNS>(da, 0, b, 0, 1, da.groups[0].width_pad, 0, red);
     return;
   }
-  if (wr) {
-    // no scoring launch: every workgroup that needs the pre-activations computes the K-slice partials itself
-    // (the router matrix is a few hundred KB that all of them find in L2 after the first) and keeps them in
-    // LDS behind the selection's arrays
-    float* part = pre + ((n_rows + 1 + MAX_SCORED + 1 + 3) & ~3);      // 16-byte aligned
-    score_slices_in_workgroup<KSTEPS>(da.x, wr, da.d, 1, n_rows, part);
-    __syncthreads();
-    partial = part;
-    n_slices = DEC_SLICES;
+  if constexpr (!RUNS) {                                   // (own_scores asks for one run)
+    if (wr) {
+      // no scoring launch: every workgroup that needs the pre-activations computes the K-slice partials itself
+      // (the router matrix is a few hundred KB that all of them find in L2 after the first) and keeps them in
+      // LDS behind the selection's arrays
+      float* part = pre + ((n_rows + 1 + MAX_SCORED + 1 + 3) & ~3);      // 16-byte aligned
+      score_slices_in_workgroup<KSTEPS>(da.x, wr, da.d, 1, n_rows, part);
+      __syncthreads();
+      partial = part;
+      n_slices = DEC_SLICES;
+    }
   }
   if (blockIdx.x == 0) {
     route_place_body(r, io, pl, partial, n_slices, 1, pre);
