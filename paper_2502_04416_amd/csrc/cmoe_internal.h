@@ -137,7 +137,8 @@ struct Tuning {
   int gemm2_cfg = -1;      // same for the down contraction
   int xcd_remap = 1;       // 0: workgroups take work items in launch order instead of per-XCD shares
   int splitk = 1;          // 0: never split K
-  int zero_pad = 1;        // 0: tile rows past the end of a group repeat its last row instead of reading zeros
+  int zero_pad = 1;        // 0: tile rows past the end of a group repeat its last row instead of reading zeros (not on
+                           // the deep ring, whose buffer loads deliver zeros there)
   int decode_fuse = 1;     // 0: separate down and combine kernels for batches of at most 32 tokens
   int front_shared = 1;    // 0: the shared expert's gate/up units stay in the gate/up launch at decode
   int front_all = 1;       // one token on a flat layer.  0: the routed gate/up units keep a launch of their own;
@@ -147,9 +148,9 @@ struct Tuning {
                            // workgroups each pull the router matrix through L2 at the same time)
   int front_tile = 0;      // 0: batches of 2-16 tokens keep a gate/up launch for the routed experts; 1: every
                            // routed unit runs in the selection launch, each workgroup selecting the batch itself
-                           // (measured slower: the team selection of up to 16 tokens in 700 workgroups at once
-                           // costs more than the launch it saves: 51.4 against 37.8 us at 2 tokens, 71.8 against
-                           // 62.4 us at 16, 16 experts of 688)
+                           // (measured slower: the selection of up to 16 tokens in 700 workgroups at once costs
+                           // more than the launch it saves: 35.0 against 29.6 us at 2 tokens, 59.3 against 55.8 us
+                           // at 16, 16 experts of 688)
   int force_simt = 0;      // 1: bf16 layers run the plain FMA kernels
   int ldpad = 0;           // extra elements in the row stride of a row-major (fp32) packed gate/up matrix
   int host_threads = 0;    // worker threads of the host-side construction (0: hardware threads, at most 16)

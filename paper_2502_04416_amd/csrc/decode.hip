@@ -378,8 +378,11 @@ __global__ __launch_bounds__(DS_WAVES * 64) void decode_down_sparse_kernel(DecAr
 // contraction on skinny tiles is as fast for the routed layer and 10-20 us faster for the dense one
 // (measured at d = 4096).
 constexpr int DECODE_MAX_T = 16;
-// Above d = 4096 a wave's K slice takes several dependent runs of loads, and the tile kernels catch up earlier: d = 5120, 2
-// tokens 61.4 against 48.8 us per forward, d = 8192, 5 tokens 97.9 against 99.1.
+// Above d = 4096 a wave's K slice takes several dependent runs of loads, and the tile kernels catch up earlier.  us per
+// forward on tiles / streamed, d_ff = 11264, 16 experts, top-3: d = 5120 49.4 / 29.4 at one token, 64.3 / 50.7 at four, d = 8192
+// 55.9 / 38.6 and 86.2 / 77.5, d = 10240 63.8 / 46.4 and 117.6 / 109.8; at 16 tokens 79.2 / 81.0, 106.0 / 127.2 and 134.7 /
+// 154.0.  In between neither side wins throughout: five to eight tokens are 4 to 38 % faster streamed at d = 5120 and 6144,
+// 1 % slower to 10 % faster at d = 8192, and twelve tokens 3 % slower to 21 % faster.
 constexpr int DECODE_MAX_T_RUNS = 4;
 bool decode_path_ok(const Engine& e, int64_t T) {
   if (e.dtype != 1 || T < 1 || T > (decode_k(e.d).nch > 1 ? DECODE_MAX_T_RUNS : DECODE_MAX_T)) return false;

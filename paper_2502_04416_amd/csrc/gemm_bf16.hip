@@ -1,10 +1,11 @@
 // Grouped SwiGLU expert kernels for bf16 layers (Eq. 3 restricted to an expert's neurons):
 //   MODE 1  H_g = Swish(X_g Wgate_g) * (X_g Wup_g)     rows of X gathered through slot2tok, K = d
 //   MODE 2  Y_g = H_g Wdown_g                          K = width_pad(g), N = d
-// Both are C = A * B^T with K contiguous in A and in B, computed with v_mfma_f32_32x32x16_bf16 from
-// LDS-staged, XOR-swizzled tiles filled by direct global->LDS loads.  A work item is (group, row tile, column tile); the list of work
-// items is a device-side prefix array written by the permute kernel, so ragged, empty and skewed
-// groups need no host round trip.  Workgroups whose index is past the list exit at once.
+// Both are C = A * B^T with K contiguous in A and in B, computed from LDS-staged, XOR-swizzled tiles filled by direct
+// global->LDS loads, in two kernels: grouped_gemm_bf16_dma (v_mfma_f32_32x32x16_bf16, 64-bit addresses) and, for the
+// largest and some small tiles, grouped_gemm_bf16_ring (v_mfma_f32_16x16x32_bf16, buffer loads).  A work item is (group,
+// row tile, column tile); the list of work items is a device-side prefix array written by the permute kernel, so
+// ragged, empty and skewed groups need no host round trip.  Workgroups whose index is past the list exit at once.
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -500,7 +501,7 @@ __attribute__((amdgpu_waves_per_eu(min_waves_per_simd(BM, BN, BKT, STAGES, WGM* 
 // A 16x16x32 MFMA gives the bits of the two 32x32x16 ones of the kernel above, so the shapes stay interchangeable.
 //
 // Layout.  K runs in steps of 32, the depth of one MFMA.  A stage of the LDS ring is the A part and the B part
-// of one step in blocks of 16 rows x 32 K (1 KB): one block is one global_load_lds_dwordx4 of a wave and one
+// of one step in blocks of 16 rows x 32 K (1 KB): one block is one 1 KB buffer load of a wave and one
 // operand of the MFMA, and a weight block is 1 KB of consecutive memory (the tiled weight layout).  The 16-byte
 // chunks of a row are XOR-swizzled with (row >> 2) & 3, on the global side, so that the 16 rows a quarter of a
 // ds_read_b128 touches fall into 16 different 16-byte bank groups.

@@ -870,13 +870,13 @@ __global__ __launch_bounds__(512) void route_place_all_kernel(RouterDev r, Route
 
 // Two to sixteen tokens on a flat layer, the same idea: workgroup 0 selects and places the batch, the next
 // workgroups run the shared group's units, and every unit of *every* routed expert has a workgroup that
-// selects the whole batch by itself (the 256-thread team selection of route_place_kernel on the scorer's
-// partials, 16 KB that all workgroups share in L2), learns which tokens chose its expert and where the
-// expert's rows of H start, and runs its unit on them; the workgroups of experts nobody chose leave.  The
-// separate gate/up launch, which could not start before selection and placement had finished in one
-// workgroup, is gone.  Bit-identical to the two launches and slower than them at every batch size (the team
-// selection run by hundreds of workgroups at once takes 15 us instead of the 8 us it takes one workgroup on
-// an otherwise idle chip), so it is off unless the tuning switch front_tile asks for it.
+// selects the whole batch by itself (route_place_kernel's selection on the scorer's partials, 16 KB that all
+// workgroups share in L2), learns which tokens chose its expert and where the expert's rows of H start, and runs
+// its unit on them; the workgroups of experts nobody chose leave.  The separate gate/up launch, which could not
+// start before selection and placement had finished in one workgroup, is gone.  Bit-identical to the two launches
+// and slower than them almost everywhere (us per forward at 2, 4, 8, 16 tokens: 16 experts of 688 35.0, 38.0, 48.8, 59.3
+// against 29.6, 39.7, 43.1, 55.8; 32 of 448 40.1, 43.5, 51.2, 68.2 against 32.0, 41.7, 45.0, 61.7), so it is off unless
+// the tuning switch front_tile asks for it.
 template <int KSTEPS, bool RUNS>
 __global__ __launch_bounds__(512) void route_place_tile_all_kernel(RouterDev r, RouteIO io, PlaceArgs pl,
                                                                    const float* __restrict__ partial, int n_slices, int T,
@@ -936,9 +936,13 @@ static int scorer_slices(const Engine& e, int64_t T) {
 // router has a copy in operand order, whole pairs of chunks per unit (or one chunk), and either
 //  - at most two slices, i.e. a batch that fills the chip with 32 tokens per workgroup (8192 tokens of the 32-expert
 //    layer: 31 us against 34 + 10), or
-//  - five to eight slices, 16 tokens per workgroup, and a router matrix of at most 0.5 MB (333 and 2048 tokens of the
-//    16-expert layer: 109.9 -> 108.3 and 210.9 -> 207.8 us per forward; with 1 MB, d = 8192, 73 tokens: 113 -> 121).
-// Three and four slices (4096 tokens) take the two launches: 29 against 31 us.
+//  - five to eight slices, 16 tokens per workgroup, and a router matrix of at most 0.5 MB.
+// us per forward in two launches / in one, experts of 32: d = 512, 70 to 8192 tokens 31.6 / 27.5 to 55.0 / 49.6; d = 1536
+// 33.7 / 29.7 to 57.9 / 49.7; d = 2048 35.1 / 31.7 to 109 / 100; d = 4096, 64 router rows (0.5 MB) 40.3 / 39.3 at 70 tokens,
+// 78.9 / 75.0 at 2048.  Above 0.5 MB: 0.66 MB (d = 2560, 128 rows) 47.0 / 44.6 at 70 tokens, 74.1 / 63.2 at 2048 (one
+// launch would be the better one there); 1 MB (d = 4096, 128 rows) 50.0 / 53.0 and 93.9 / 85.0, (d = 8192, 64 rows)
+// 51.6 / 55.2 and 126 / 124; 2 MB (d = 8192, 128 rows) 63.8 / 76.1 and 151 / 145.
+// Three and four slices (4096 tokens) take the two launches: 29 against 31 us for them.
 static int score_route_units(const Engine& e, int64_t T) {
   if (!mfma_scorer_ok(e) || e.wr_tiled == nullptr || e.r.outer_top_k != 0 || e.r.n_lin_rows != 0 || e.r.n_sw_rows % 64 != 0) return 0;
   const int S = scorer_slices(e, T), n_i = e.d / S / 256;
