@@ -914,6 +914,22 @@ constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
 // Rows of x that one tile gathers can be 2 GB or more apart.
 static bool wide_gather(int d, int64_t T) { return T * d * 2 >= (int64_t)DMA_NONE; }
 
+// Routed groups of one width and load: the experts of a flat layer; the outer experts' shared groups and the
+// sub-experts of a hierarchy.
+struct LoadClass { int64_t groups, entries; int width_pad; };
+static int load_classes(const Engine& e, int64_t T, LoadClass (&c)[2]) {
+  const int routed = e.G - e.n_always;
+  if (routed <= 0 || e.S_dyn <= 0) return 0;
+  if (e.r.outer_top_k > 0 && e.r.sub_has_shared && e.r.top_k > 0) {
+    const int64_t outer = routed / e.r.groups_per_outer, entries = T * e.r.outer_top_k;
+    c[0] = {outer, entries, e.width_pad_host[e.n_always]};
+    c[1] = {routed - outer, entries * e.r.top_k, e.width_pad_host[e.n_always + 1]};
+    return 2;
+  }
+  c[0] = {routed, T * e.S_dyn, e.width_pad_host[e.n_always]};
+  return 1;
+}
+
 // Which tile shape for contraction `which` (1: gate/up, 2: down) of a batch of T tokens: the tuning switches
 // gemm1_cfg / gemm2_cfg when set, else the models below.
 // Tile shape of the gate/up contraction: the one with the lowest estimated time = rounds x time per round,
@@ -932,7 +948,9 @@ static bool wide_gather(int d, int64_t T) { return T * d * 2 >= (int64_t)DMA_NON
 // group's last tile is filled uniformly between nothing and everything, so the sum strays by sqrt(groups / 12)
 // row tiles: the rounds are averaged over the estimate and two such deviations more (none where every touched group
 // has but one row tile).  (A flat margin of 8 % counted a further round where there was none: 32 experts, 2048
-// tokens: 294 -> 270 us.)
+// tokens: 294 -> 270 us.)  A hierarchy's shared groups and its sub-experts differ in load and in width and are estimated
+// apart, with 2.5 deviations for its outer choice (8 outer experts, top-2 of 6 sub-experts, d = 512, 1998 tokens: 81 -> 70
+// us, before the ring 76; d = 1024, 1496 tokens: 92 -> 82; 4 outer experts, d = 2048, 753 tokens: 96 -> 86).
 // 256x128 and the ring's 128x128 are taken for single rounds that nearly fill the chip, and there the groups that hold
 // more than the average decide: routed loads spread about like an exponential (the library's partitions on clustered
 // tokens), a group of mean load m needs a further row tile with probability exp(-bm / m), and the margin is 1.5
@@ -946,6 +964,8 @@ static int gate_up_cfg(const Engine& e, int64_t T) {
   const Cand cands[] = {{3, 128, 128, 512, 0.66}, {4, 256, 128, 256, 0.62}, {6, 256, 256, 256, 0.95},
                         {narrow ? 21 : 7, 64, 128, narrow ? 512 : 256, narrow ? 0.45 : 0.30},
                         {9, 224, 256, 256, 0.875}, {10, 192, 256, 256, 0.81}, {19, 160, 256, 256, 0.75}, {20, 128, 128, 256, 0.51}};
+  LoadClass classes[2];
+  const int n_classes = load_classes(e, T, classes);
   int best = 0;
   double best_t = 1e30;
   for (const Cand& c : cands) {
@@ -953,26 +973,29 @@ static int gate_up_cfg(const Engine& e, int64_t T) {
     // pace of a full tile (measured with 256 rows at 224-256 tokens on 16 experts: 61 us against 52 us with
     // 128x128)
     if (!single && c.bm >= 160 && T * e.S_dyn * 4 < (int64_t)std::min<int64_t>(e.G - e.n_always, T * e.S_dyn) * c.bm) continue;
-    int64_t tiles = 0, hi = 0;
+    int64_t tiles = 0;
+    double var = 0.0;
     for (int g = 0; g < e.n_always; ++g) tiles += ((T + c.bm - 1) / c.bm) * cdiv(2 * e.width_pad_host[g], c.bn);
-    hi = tiles;
-    if (!single && e.G > e.n_always) {
-      const int64_t entries = T * e.S_dyn;
-      const int64_t touched = std::min<int64_t>(e.G - e.n_always, entries);
+    for (int i = 0; i < n_classes; ++i) {
+      const int64_t entries = classes[i].entries;
+      const int64_t touched = std::min<int64_t>(classes[i].groups, entries);
       const int64_t full = (entries + c.bm - 1) / c.bm + touched / 2, rows = std::max<int64_t>(full, touched);
-      const int64_t cols = cdiv(2 * e.width_pad_host[e.n_always], c.bn);
+      const double cols = cdiv(2 * classes[i].width_pad, c.bn);
+      double dev = 0.0;                                        // tiles
       if (c.cfg == 4 || c.cfg == 20) {
         const double more = std::exp(-(double)c.bm * (double)touched / (double)entries);
-        const double mean = (double)touched / (1.0 - more), dev = std::sqrt((double)touched * std::min(more, 1.0 / 12.0));
-        hi = tiles + (int64_t)((mean + 1.5 * dev) * (double)cols + 0.5);
-        tiles += (int64_t)(mean * (double)cols + 0.5);
+        tiles += (int64_t)((double)touched / (1.0 - more) * cols + 0.5);
+        dev = 1.5 * std::sqrt((double)touched * std::min(more, 1.0 / 12.0)) * cols;
       } else {
-        tiles += rows * cols;
-        hi = tiles;
-        if (full > touched) hi += (int64_t)(2.0 * std::sqrt((double)touched / 12.0) * (double)cols + 0.5);
+        tiles += (int64_t)((double)rows * cols);
+        if (full > touched) dev = (e.r.outer_top_k > 0 ? 2.5 : 2.0) * std::sqrt((double)touched / 12.0) * cols;
       }
+      var += dev * dev;
     }
+    const int64_t hi = tiles + (int64_t)(std::sqrt(var) + 0.5);
     double t = 0.5 * c.t * (double)((tiles + c.slots - 1) / c.slots + (hi + c.slots - 1) / c.slots);
+    // (a short K loop shows more of a tall tile's prologue and epilogue: 8 outer experts, d = 512, 2052 tokens 89 -> 78 us)
+    if (narrow && c.bm >= 160 && c.bn == 256) t *= 1.1;
     if (c.cfg == 21 && hi <= 256) t = 0.30;                    // one workgroup on a CU
     // the skinny tile runs one workgroup per CU and its rounds are long: when the estimate is close to
     // spilling into a second, nearly empty round, count that round in full
