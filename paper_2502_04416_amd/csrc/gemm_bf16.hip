@@ -12,41 +12,9 @@
 #include <type_traits>
 #include "cmoe_internal.h"
 #include "device_utils.h"
+#include "gemm_device.h"
 
 namespace cmoe {
-
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float floatx16_t __attribute__((ext_vector_type(16)));
-typedef float floatx4_t __attribute__((ext_vector_type(4)));
-
-struct GemmArgs {
-  const bf16_t* A;
-  const bf16_t* B;
-  bf16_t* C;
-  const GroupDev* groups;
-  const int32_t* seg_off;    // [G+1]
-  const int32_t* work;       // [G+1]
-  const int64_t* h_off;      // [G+1]
-  const int32_t* slot2tok;   // MODE 1 gather; null = identity
-  int G;
-  int d;
-  int ldb;                   // elements per row of B in MODE 1 (packed gate/up rows)
-  int b_tiled;               // 1: the weight matrices are tiled 16 x 32 (see cmoe_internal.h)
-  int64_t T;
-  int single;                // 1: one always-on group holding all T tokens; no device schedule is read
-  int n_blocks;              // grid size (multiple of 8) before the K split
-  int xcd_remap;             // 1: consecutive work items run on the same XCD
-  int zero_pad;              // 1: tile rows past the end of a group read zeros instead of repeating its last row
-  int ws_skip;               // 1 (down contraction): groups the weight-stationary kernel handles are left to it
-  // K split: k_split > 1 workgroups share one tile, each multiplies a contiguous range of K tiles and
-  // stores its fp32 partial sums to P [k_split][p_rows][ldp] (row = slot, column = column of the tile
-  // grid); a finishing kernel adds the parts in order and applies the epilogue.  Used when a launch has
-  // too few tiles to fill the chip (batches of a few hundred tokens).
-  int k_split;
-  float* P;
-  int64_t p_rows;
-  int ldp;
-};
 
 // ---- global->LDS loads and a ring of K tiles ------------------------------------------------------
 // Each global_load_lds_dwordx4 moves 64 lanes x 16 bytes into 1 KB of consecutive LDS (8 tile rows);
@@ -60,12 +28,6 @@ __device__ __attribute__((aligned(16))) uint32_t g_zero_chunk[4] = {0, 0, 0, 0};
 constexpr int ZERO_ROW_ELEMS = 32768;
 __device__ __attribute__((aligned(256))) bf16_t g_zero_row[ZERO_ROW_ELEMS];
 
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
 
 __device__ __forceinline__ void dma16(const void* gsrc, bf16_t* lds_dst) {
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gsrc),
@@ -522,40 +484,6 @@ __attribute__((amdgpu_waves_per_eu(min_waves_per_simd(BM, BN, BKT, STAGES, WGM* 
 // of 64 with global addresses that this replaces: 1174).  Giving the four waves different issue slots made it
 // slower in every form tried.
 
-constexpr uint32_t DMA_NONE = 0x80000000u;                    // an offset past the end of every buffer used here
-
-// A uniform pointer, in scalar registers.
-__device__ __forceinline__ const bf16_t* uniform_ptr(const bf16_t* ptr) {
-  const uint64_t v = reinterpret_cast<uint64_t>(ptr);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<const bf16_t*>(((uint64_t)hi << 32) | lo);
-}
-
-// 64 lanes x 16 bytes from base + lane_off + step_off (bytes; zeros where lane_off >= size) to 1 KB of LDS.
-__device__ __forceinline__ void dma16_buffer(const bf16_t* base, uint32_t size, uint32_t lane_off, uint32_t step_off, bf16_t* lds_dst) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, size, 0x00020000);
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(lds_dst), 16, lane_off, step_off, 0, 0);
-#endif
-}
-
-// acc += w * a (w: 16 weight rows x 32 K, a: 16 activation rows x 32 K).  Written as assembly to pin the
-// accumulators to the AGPRs: with the builtin the register allocator shuffles them between the two halves of the
-// register file inside the K loop (96 to 470 moves per step, and spills for the 256 x 256 tile of four waves).
-// The compiler does not see an MFMA here, so it puts no wait states in front of another use of the result (8 on this
-// part) and may place such a use anywhere behind the block, a spill or a copy of an accumulator among them.  WAIT, set for the
-// last MFMA of the last K step, therefore waits inside the block: whatever follows it finds every accumulator
-// complete.  (A wait in a statement of its own came too late: the allocator had spilled an accumulator in front of it.)
-// Sources come from LDS reads only (waited for by the compiler as for any use), and the accumulator is overwritten by
-// nothing else inside the loop.  tests/test_kernel_code_cpu.py checks these distances in the machine code.
-template <bool WAIT>
-__device__ __forceinline__ void mfma_acc(floatx4_t& acc, const bf16x8_t& w, const bf16x8_t& a) {
-  if constexpr (WAIT) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\ts_nop 7" : "+a"(acc) : "v"(w), "v"(a) : "memory");
-  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(a));
-}
-
-constexpr int BK = 32;                                        // K step
-constexpr int BLK = 16 * BK;                                  // elements of a 16-row block
 constexpr int ring_stage_elems(int bm, int bn, int nw) {
   return ((bm / 16 + nw - 1) / nw + (bn / 16 + nw - 1) / nw) * nw * BLK;
 }
@@ -902,11 +830,14 @@ static const TileCfg kCfgs[] = {
     {160, 256, 2, 2, 5, 32},   // 19: deep ring, four waves of 80x128
     {128, 128, 2, 2, 5, 32},   // 20: deep ring, four waves of 64x64
     {64, 128, 2, 2, 6, 32},    // 21: deep ring in steps of 64, four waves of 32x64, two workgroups per CU
+    {128, 256, 2, 2, 3, 32},   // 22: the persistent down contraction (gemm_stream.hip)
 };
 static bool cfg_is_ws(int ci) { return ci >= 15 && ci <= 18; }
-static bool cfg_is_ring(int ci) { return kCfgs[ci].stages >= 5; }
+static bool cfg_is_stream(int ci) { return ci == 22; }
+static bool cfg_is_ring(int ci) { return kCfgs[ci].stages >= 5 && !cfg_is_stream(ci); }
 static bool cfg_is_dyn(int ci) { return ci >= 11 && ci <= 18; }
 bool ws_down_handles(int width_pad);
+hipError_t launch_down_stream(const Engine& e, const GemmArgs& a, hipStream_t s);
 hipError_t launch_ws_down(const Engine& e, char* ws, const WsLayout& L, const void* y_slots, int rc, int n_blocks,
                           int xcd_remap, hipStream_t s);
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
@@ -1010,6 +941,14 @@ static int gate_up_cfg(const Engine& e, int64_t T) {
 
 static int64_t est_tiles(const Engine& e, int64_t T, int which, int bm, int bn);
 
+// The persistent down contraction: a work list, and at least as many K steps in every group as its ring is deep.
+static bool stream_ok(const Engine& e) {
+  if ((e.G == 1 && e.n_always == 1) || !e.w_tiled) return false;
+  for (int g = 0; g < e.G; ++g)
+    if (e.width_pad_host[g] < 3 * TILE_K) return false;
+  return true;
+}
+
 static int cfg_index(int which, const Engine& e, int64_t T) {
   int dflt = 0;
   if (which == 1) dflt = gate_up_cfg(e, T);
@@ -1034,6 +973,15 @@ static int cfg_index(int which, const Engine& e, int64_t T) {
       const double t0 = (double)r0, t9 = (double)r9 + (r9 == 1 ? 0.4 : 0.0), t3 = 0.66 * (double)r3, t21 = (r21 <= 2 ? 0.42 : 0.5) * (double)r21;
       dflt = (t3 < t9 && t3 < t0) ? 3 : (t9 <= t0 ? 8 : 0);
       if (k_min <= 1024 && t21 < std::min(t3, std::min(t9, t0))) dflt = 21;      // (K = 1408: 134 -> 138 us at 64 tokens)
+      // The persistent kernel (128x256, two per CU) from 0.8 of a round of tiles on, for narrow experts from 0.44, where the
+      // average touched group half fills a row tile.  Below, its lookup of all tiles in advance costs more than it saves
+      // (8 experts of 692, d = 2048, 441 tokens, 0.17 rounds: 54 against 65 us; 27 groups of 17 rows: 76 against 89).  From there
+      // on, against the shape the models above take: 12 experts of 439, d = 2048, 2295 tokens 94 -> 84 us per forward, 32 of 324 at
+      // 603 tokens 119 -> 111, 16 of 300, d = 1536, 3254 tokens 80 -> 75; at worst 258.6 for 254.7 (16 of 704, d = 8192, 678 tokens).
+      // With a K loop of more than 32 steps of 32 it takes the place of shape 8 only (8 experts of 1357, 5544 tokens: shape 0
+      // 415, this one 426, shape 8 430).
+      const int64_t entries = T * e.S_dyn, touched = std::min<int64_t>(e.G - e.n_always, entries);
+      if (stream_ok(e) && entries >= 64 * touched && n9 >= (k_min <= 640 ? 225 : 400) && (k_min <= 1024 || dflt == 8)) dflt = 22;
     } else {
       // Deep K (dense FFN, un-restructured experts): 256x256 tiles with four waves when every CU gets one;
       // below that 256x128, whose round takes 0.56 of the time, unless it would need a second round; 128x128
@@ -1058,7 +1006,8 @@ static int cfg_index(int which, const Engine& e, int64_t T) {
     // (of the ring shapes only 6 is built with 64-bit row addresses; the others have them)
     return forced >= 0 && forced < kNumCfgs && !cfg_is_ws(forced) && !cfg_is_ring(forced) ? forced : 6;
   }
-  if (forced >= 0 && forced < kNumCfgs && !(which == 1 && cfg_is_ws(forced))) return forced;
+  if (forced >= 0 && forced < kNumCfgs && !(which == 1 && (cfg_is_ws(forced) || cfg_is_stream(forced))) &&
+      (!cfg_is_stream(forced) || stream_ok(e))) return forced;
   if (which == 2 && tuning().ws_down != 0 && !(e.G == 1 && e.n_always == 1) && e.w_tiled && e.d % 256 == 0) {
     // The weight-stationary kernel for the groups it handles, when the batch gives it enough work items to
     // fill the chip several times over: the largest row chunk that still leaves four rounds of items (a chunk
@@ -1080,7 +1029,8 @@ static int cfg_index(int which, const Engine& e, int64_t T) {
 }
 
 // which = 1: BM of gate/up, 2: BM of down, 3: BN of gate/up (packed rows), 4: BN of down,
-// 5 / 6: rows per height step when the gate/up / down contraction runs tiles of dynamic height, else 0
+// 5 / 6: rows per height step when the gate/up / down contraction runs tiles of dynamic height, else 0,
+// 7: width of the narrowest group when the down contraction is the persistent one, else 0
 int bf16_gemm_tile(int which, const Engine& e, int64_t T) {
   switch (which) {
     case 1: return kCfgs[cfg_index(1, e, T)].bm;
@@ -1088,6 +1038,7 @@ int bf16_gemm_tile(int which, const Engine& e, int64_t T) {
     case 3: return kCfgs[cfg_index(1, e, T)].bn;
     case 4: return kCfgs[cfg_index(2, e, T)].bn;
     case 5: return cfg_is_dyn(cfg_index(1, e, T)) ? 32 * kCfgs[cfg_index(1, e, T)].wgm : 0;
+    case 7: return cfg_is_stream(cfg_index(2, e, T)) ? *std::min_element(e.width_pad_host, e.width_pad_host + e.G) : 0;
     default: return cfg_is_dyn(cfg_index(2, e, T)) ? 32 * kCfgs[cfg_index(2, e, T)].wgm : 0;
   }
 }
@@ -1117,7 +1068,7 @@ static int splitk_ldp(const Engine& e, int which) { return which == 1 ? 2 * e.ma
 int bf16_splitk(const Engine& e, int64_t T, int which) {
   if (T < 1 || T > 1024 || tuning().splitk == 0) return 1;
   const int ci = cfg_index(which, e, T);
-  if (cfg_is_ws(ci)) return 1;
+  if (cfg_is_ws(ci) || cfg_is_stream(ci)) return 1;
   const TileCfg& c = kCfgs[ci];
   const int64_t tiles = est_tiles(e, T, which, c.bm, c.bn);
   int k_min = e.d;
@@ -1326,6 +1277,7 @@ hipError_t launch_experts_bf16(const Engine& e, const void* x, int64_t T, char* 
   a.ldp = splitk_ldp(e, 2);
   {
     const int ci2 = cfg_index(2, e, T);
+    if (cfg_is_stream(ci2)) return launch_down_stream(e, a, s);
     if (cfg_is_ws(ci2)) {
       bool wide = false;
       for (int g = 0; g < e.G; ++g) wide = wide || !ws_down_handles(e.width_pad_host[g]);

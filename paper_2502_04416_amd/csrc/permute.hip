@@ -118,6 +118,7 @@ PlaceArgs make_place_args(const Engine& e, int64_t T, char* ws, const WsLayout& 
   p.bn2 = tiles ? gemm_tile(e, T, 4) : 1;
   p.dyn1 = tiles ? gemm_tile(e, T, 5) : 0;
   p.dyn2 = tiles ? gemm_tile(e, T, 6) : 0;
+  p.stream2 = tiles ? gemm_tile(e, T, 7) : 0;
   return p;
 }
 

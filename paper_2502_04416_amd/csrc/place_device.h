@@ -28,6 +28,8 @@ struct PlaceArgs {
   int bm1, bn1, bm2, bn2, d;   // tile sizes of the grouped GEMMs (bn1 in packed gate/up rows)
   int dyn1, dyn2;              // > 0: that contraction runs tiles of dynamic height, in steps of this many rows (a
                                // ragged last tile costs its rows)
+  int stream2;                 // > 0: the down contraction is the persistent one, and groups wider than this come first in its
+                               // list (see there)
   int decode;                  // 1: the work lists count decode units (dec_unit1 neurons / 16 output columns per unit)
   int dec_unit1;               // neurons per gate/up unit of the decode kernels (16 or 8)
   int skip_always;             // 1: no gate/up work items for the always-on groups (another launch ran them)
@@ -131,7 +133,7 @@ __device__ __forceinline__ void place_slots(const PlaceArgs& p, int tile, const 
 __device__ __forceinline__ void place_lists(const PlaceArgs& p, const TileCounts& tc, int lane, const LaneWidths& lw) {
   constexpr int GPL = MAX_GROUPS / 64;
   // exclusive prefix over groups of: slots, work items of the two contractions, hidden-buffer elements
-  int run0 = 0, w1_0 = 0, w2_0 = 0;
+  int run0 = 0, w1_0 = 0, w2_0 = 0, w2_deep = 0;
   long long h0 = 0;
   int n1[GPL], n2[GPL], w1x[GPL], w2x[GPL];     // work items of this lane's groups and their exclusive prefix
 #pragma unroll
@@ -153,9 +155,16 @@ __device__ __forceinline__ void place_lists(const PlaceArgs& p, const TileCounts
     if (g >= p.G) { a1 = 0; a2 = 0; }
     if (p.skip_always && g < p.n_always) a1 = 0;
     const long long ah = (long long)cnt * wp;
-    const int run_i = wave_incl_scan(cnt, lane), w1_i = wave_incl_scan(a1, lane), w2_i = wave_incl_scan(a2, lane);
+    const bool deep = p.stream2 > 0 && wp > p.stream2;
+    const int run_i = wave_incl_scan(cnt, lane), w1_i = wave_incl_scan(a1, lane), w2_i = wave_incl_scan(deep ? 0 : a2, lane);
     const long long h_i = wave_incl_scan(ah, lane);
-    const int run = run0 + run_i - cnt, w1 = w1_0 + w1_i - a1, w2 = w2_0 + w2_i - a2;
+    const int run = run0 + run_i - cnt, w1 = w1_0 + w1_i - a1;
+    int w2 = w2_0 + w2_i - a2;
+    if (p.stream2 > 0) {
+      const int deep_i = wave_incl_scan(deep ? a2 : 0, lane);
+      if (deep) w2 = w2_deep + deep_i - a2;
+      w2_deep += __shfl(deep_i, 63, 64);
+    }
     const long long h = h0 + h_i - ah;
     n1[k] = a1; n2[k] = a2; w1x[k] = w1; w2x[k] = w2;
     if (g < p.G) {
@@ -177,6 +186,18 @@ __device__ __forceinline__ void place_lists(const PlaceArgs& p, const TileCounts
     p.work2[p.G] = w2_0;
     p.h_off[p.G] = h0;
   }
+  if (p.stream2 > 0) {
+    // the other tiles follow the deep ones: work2[g] = first tile of group g, [G] = tiles, [G + 1] = deep ones
+#pragma unroll
+    for (int k = 0; k < GPL; ++k) {
+      const int g = lane + 64 * k;
+      if (g < p.G && lw.w[k] <= p.stream2) p.work2[g] = w2_deep + w2x[k];
+    }
+    if (lane == 0) {
+      p.work2[p.G] = w2_deep + w2_0;
+      p.work2[p.G + 1] = w2_deep;
+    }
+  }
   if (p.decode) return;                    // (the decode kernels take their units in list order: no shares)
   // Where each XCD's share of a work list starts (entries G+1 .. G+9 of the list): contiguous ranges of
   // equal estimated cost, so that the tiles sharing operands stay in one L2 while the eight dies finish
@@ -193,6 +214,7 @@ __device__ __forceinline__ void place_lists(const PlaceArgs& p, const TileCounts
   wave_lds_sync();
 #pragma unroll
   for (int list = 0; list < 2; ++list) {
+    if (list == 1 && p.stream2 > 0) break;
     const int bm = list == 0 ? p.bm1 : p.bm2, dyn = list == 0 ? p.dyn1 : p.dyn2;
     const int blocks_full = bm / 32 > 0 ? bm / 32 : 1;
     // (Which group a boundary falls into is decided in exact integers, so that every item lands in exactly
@@ -248,7 +270,7 @@ __device__ __forceinline__ void place_lists(const PlaceArgs& p, const TileCounts
   wave_lds_sync();
   if (lane <= N_XCD) {
     p.work1[p.G + 1 + lane] = xs[0][lane];
-    p.work2[p.G + 1 + lane] = xs[1][lane];
+    if (p.stream2 == 0) p.work2[p.G + 1 + lane] = xs[1][lane];
   }
 }
 

@@ -226,3 +226,49 @@ def test_selection_by_rounds_and_by_rank(binding, N, n_s, k, T, gate):
         layer.set_gate_params(u, b)
     check_flat(cfg, weights, part, x, layer.forward(x), u=u, b=b, exact_ties_strict=True)
     layer.close()
+
+
+@pytest.mark.parametrize("remap", [1, 0])
+@pytest.mark.parametrize("d,N,m,n_s,k,T", [
+    (328, 12, 100, 2, 3, 333),     # K of 7 and 4 steps, column tiles and 16-row blocks that end inside
+    (40, 12, 96, 0, 4, 1000),      # K as short as the ring is deep, no deep tiles, fewer columns than a wave has
+    (1024, 8, 160, 3, 2, 700),     # 15 and 5 steps, deep tiles that do not divide among the workgroups of a die
+    (512, 66, 97, 2, 5, 2100),     # more than 64 groups, rows that fill a tile to the last
+])
+def test_persistent_down_contraction(binding, d, N, m, n_s, k, T, remap):
+    """The persistent down kernel against the oracle, and bit for bit against a workgroup per tile."""
+    cfg, weights, part, x, layer = _case(binding, d, N, m, n_s, k, T)
+    try:
+        binding.cmoe_set_tuning("CMOE_SPLITK", 0)
+        binding.cmoe_set_tuning("CMOE_XCD_REMAP", remap)
+        binding.cmoe_set_tuning("CMOE_GEMM2_CFG", 8)
+        ref = layer.forward(x)
+        binding.cmoe_set_tuning("CMOE_GEMM2_CFG", 22)
+        out = layer.forward(x)
+    finally:
+        binding.cmoe_set_tuning("CMOE_GEMM2_CFG", -1)
+        binding.cmoe_set_tuning("CMOE_XCD_REMAP", 1)
+        binding.cmoe_set_tuning("CMOE_SPLITK", 1)
+    check_flat(cfg, weights, part, x, out)
+    assert np.array_equal(out["y"], ref["y"])
+    layer.close()
+
+
+def test_persistent_down_contraction_many_tiles(binding):
+    """More tiles per workgroup (65) than it looks up at a time."""
+    import torch
+    T = 38000
+    cfg = synth.scaled(synth.CONFIGS[1], d_model=4096, d_ff=8 * 96, n_experts=8, n_shared=1, top_k=6, n_centres=16)
+    part, weights = synth.trivial_partition(cfg), synth.make_weights(cfg)
+    layer = binding.Layer.from_partition(cfg, *weights, part["neuron_order"], part["rep_neuron"])
+    x = torch.randn((T, 4096), generator=torch.Generator(device="cuda").manual_seed(5), device="cuda", dtype=torch.bfloat16)
+    y = {}
+    try:
+        for shape in (8, 22):
+            binding.cmoe_set_tuning("CMOE_GEMM2_CFG", shape)
+            y[shape] = torch.empty_like(x)
+            layer.forward_device(x, y[shape])
+    finally:
+        binding.cmoe_set_tuning("CMOE_GEMM2_CFG", -1)
+    assert torch.equal(y[8], y[22])
+    layer.close()

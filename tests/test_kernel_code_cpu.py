@@ -132,6 +132,23 @@ def test_mfma_results_are_waited_for(ring_kernels):
     assert not bad, bad
 
 
+def test_mfma_results_of_the_persistent_kernel_are_waited_for(tmp_path):
+    """The same distances in the persistent down contraction, whose accumulators are read between the tiles of its loop; and no
+    memory access of the compiler's own inside that loop, where it would count among the transfers waited for."""
+    code = {}
+    for i, obj in enumerate(code_objects(LIB)):
+        if b"down_stream_kernel" in obj:
+            path = tmp_path / ("%d.o" % i)
+            path.write_bytes(obj)
+            listing = subprocess.run([OBJDUMP, "-d", str(path)], capture_output=True, text=True, check=True).stdout
+            code.update(parse(listing, "down_stream_kernel"))
+    (code,) = code.values()
+    mfmas = [i for i, ins in enumerate(code) if ins[1] == "v_mfma_f32_16x16x32_bf16"]
+    assert len(mfmas) == 4 * 32                     # two sets of fragment registers, each for a first and a later step
+    assert not violations(code)
+    assert not [ins for ins in code[mfmas[0]:mfmas[-1]] if ins[1].startswith(("scratch_", "global_", "flat_"))]
+
+
 def test_the_check_sees_an_early_use():
     """Straight code, a loop and a join, with the use at the distance and one wait state closer."""
     mfma = "v_mfma_f32_16x16x32_bf16", "a[0:3], v[0:3], v[4:7], a[0:3]"
