@@ -113,7 +113,7 @@ void parallel_for(int64_t n, const std::function<void(int64_t)>& fn, int max_thr
 bool use_simt_experts(int dtype) { return dtype != CMOE_BF16 || tuning().force_simt != 0; }
 
 int gemm_tile(const Engine& e, int64_t T, int which) {
-  return use_simt_experts(e.dtype) ? simt_gemm_tile(which) : bf16_gemm_tile(which, e, T);
+  return use_simt_experts(e.dtype) ? simt_gemm_tile(which, e, T) : bf16_gemm_tile(which, e, T);
 }
 
 int64_t gemm_work_bound(const Engine& e, int64_t T, int which) {

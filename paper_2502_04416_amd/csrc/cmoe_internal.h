@@ -189,6 +189,7 @@ hipError_t launch_router(const Engine& e, const void* x, int64_t T, char* ws, co
 // The histogram table launch_router leaves behind: tokens per row (16, 32 or TOK_TILE) and where it is.
 struct CountTable { int tokens; size_t offset; };
 CountTable router_counts(const Engine& e, int64_t T, const WsLayout& L);
+bool place_counts_itself(const Engine& e, int64_t T);      // ... or none: the placement counts the entries
 hipError_t launch_permute(const Engine& e, int64_t T, char* ws, const WsLayout& L, int32_t* counts_out,
                           hipStream_t s);
 // stage: 0 = gate/up GEMM then down GEMM, 1 = gate/up only, 2 = down only
@@ -206,7 +207,7 @@ int bf16_gemm_tile(int which, const Engine& e, int64_t T);
 // K split of the bf16 contractions at small batches (1 = none) and the bytes of fp32 partial sums it needs.
 int bf16_splitk(const Engine& e, int64_t T, int which);
 size_t bf16_splitk_bytes(const Engine& e, int64_t T);
-int simt_gemm_tile(int which);
+int simt_gemm_tile(int which, const Engine& e, int64_t T);
 hipError_t launch_experts_bf16(const Engine& e, const void* x, int64_t T, char* ws, const WsLayout& L, void* y,
                                hipStream_t s, int stage);
 hipError_t launch_experts_simt(const Engine& e, const void* x, int64_t T, char* ws, const WsLayout& L, void* y,

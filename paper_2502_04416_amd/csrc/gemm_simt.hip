@@ -1,8 +1,9 @@
-// Grouped SwiGLU expert kernels with plain fp32 FMA arithmetic (no matrix cores).  They serve the
+// Grouped SwiGLU expert kernels with fp32 arithmetic.  They serve the
 // fp32 layers (tolerance 1e-5, where bf16 MFMA inputs would be too coarse) and follow the same work
 // list, gather and ragged layouts as the bf16 MFMA kernels:
 //   MODE 1  H_g = Swish(X_g Wgate_g) * (X_g Wup_g)   (Eq. 3, first line, on the group's neurons)
 //   MODE 2  Y_g = H_g Wdown_g                        (Eq. 3, second line)
+#include <algorithm>
 #include "cmoe_internal.h"
 #include "device_utils.h"
 
@@ -169,6 +170,139 @@ __global__ __launch_bounds__(256) void grouped_gemm_simt(SimtArgs<T> p) {
   }
 }
 
+// ---- small fp32 problems, on the fp32 matrix instruction -----------------------------------------------------
+// What bounds it: the numerics layers are small (tens to hundreds of tokens, experts of tens of neurons), so a launch is a
+// chain of memory round trips, and tiles of 64 x 64 left most of the chip idle and multiplied groups of nine rows as 64.
+// Here a workgroup takes 16 rows x 32 columns (MODE 1: the gate and the up row of 16 neurons); its four waves take every
+// fourth chunk of 16 of K, all of a wave's operand loads (up to 128 of K) in flight at once, straight from memory in operand
+// order, and the four partial sums are added in wave order.  v_mfma_f32_16x16x4_f32 multiplies and adds in fp32 like the
+// FMAs of the kernel above; a lane's float4 holds k = 4 (lane / 16) .. + 3 of a chunk, and MFMA j takes element j of
+// both operands, so a chunk is summed in the order 0, 4, 8, 12, 1, 5, ...
+// d = 256, 8 experts of 128, 64 tokens: gate/up 25.2 and down 14.4 us before, 5.9 and 4.4 now.
+constexpr int FM = 16, FN = 32;       // rows and columns of a tile
+constexpr int FC = 8;                 // chunks of a wave in flight
+
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+template <int MODE, bool VEC>
+__global__ __launch_bounds__(256) void grouped_gemm_f32(SimtArgs<float> p) {
+  __shared__ float red[4][FM][FN + 1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r16 = lane & 15, kq = lane >> 4;
+  int g = 0, local = blockIdx.x, cnt, seg0 = 0, wp;
+  int64_t hoff = 0;
+  if (p.single) {
+    cnt = (int)p.T_tokens;
+    wp = p.groups[0].width_pad;
+  } else {
+    if (local >= p.work[p.G]) return;
+    g = find_group(p.work, p.G, local);
+    local -= p.work[g];
+    seg0 = p.seg_off[g];
+    cnt = p.seg_off[g + 1] - seg0;
+    wp = p.groups[g].width_pad;
+    hoff = p.h_off[g];
+  }
+  const int K = (MODE == 1) ? p.d : wp;
+  const int n_nt = (MODE == 1) ? wp / 16 : (p.d + FN - 1) / FN;
+  const int n_mt = (cnt + FM - 1) / FM;
+  if (p.single && local >= n_mt * n_nt) return;
+  const int mt = local % n_mt, nt = local / n_mt;              // neighbours share the weights
+  // this lane's row of A and rows of the two 16-row blocks of B (past the end: a row that exists, never stored)
+  const int ar = min(mt * FM + r16, cnt - 1);
+  const float *b0, *b1;
+  if (MODE == 1) {
+    b0 = p.B + ((int64_t)p.groups[g].w1_row0 + (nt >> 1) * 2 * IL + (nt & 1) * 16 + r16) * p.ldb;
+    b1 = b0 + (int64_t)IL * p.ldb;
+  } else {
+    b0 = p.B + p.groups[g].w2_off + (int64_t)min(nt * FN + r16, p.d - 1) * wp;
+    b1 = p.B + p.groups[g].w2_off + (int64_t)min(nt * FN + 16 + r16, p.d - 1) * wp;
+  }
+  auto fetch = [&](const float* row, int k) {
+    f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (VEC) {
+      if (k < K) v = *reinterpret_cast<const f32x4_t*>(row + k);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (k + j < K) v[j] = row[k + j];
+    }
+    return v;
+  };
+  f32x4_t acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = acc0;
+  const float* a = nullptr;
+  for (int k0 = wave * 16; k0 < K; k0 += FC * 64) {
+    f32x4_t av[FC], b0v[FC], b1v[FC];
+#pragma unroll
+    for (int c = 0; c < FC; ++c)
+      if (k0 + c * 64 < K) {
+        b0v[c] = fetch(b0, k0 + c * 64 + kq * 4);
+        b1v[c] = fetch(b1, k0 + c * 64 + kq * 4);
+      }
+    if (!a) {                                                  // (behind the first weights: the map is one more round trip)
+      if (MODE == 1) a = p.A + (int64_t)(p.slot2tok ? p.slot2tok[seg0 + ar] : seg0 + ar) * p.d;
+      else a = p.A + hoff + (int64_t)ar * wp;
+    }
+#pragma unroll
+    for (int c = 0; c < FC; ++c)
+      if (k0 + c * 64 < K) av[c] = fetch(a, k0 + c * 64 + kq * 4);
+#pragma unroll
+    for (int c = 0; c < FC; ++c)
+      if (k0 + c * 64 < K) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[c][j], b0v[c][j], acc0, 0, 0, 0);
+          acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[c][j], b1v[c][j], acc1, 0, 0, 0);
+        }
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {                                // a lane holds rows 4 kq .. + 3 of column r16
+    red[wave][kq * 4 + i][r16] = acc0[i];
+    red[wave][kq * 4 + i][16 + r16] = acc1[i];
+  }
+  __syncthreads();
+  const int row = tid >> 4, col = tid & 15, r = mt * FM + row;
+  if (r >= cnt) return;
+  float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    s0 += red[w][row][col];
+    s1 += red[w][row][16 + col];
+  }
+  if (MODE == 1) {
+    p.C[hoff + (int64_t)r * wp + nt * 16 + col] = silu_f32(s0) * s1;
+  } else {
+    float* out = p.C + (int64_t)(seg0 + r) * p.d + nt * FN + col;
+    if (nt * FN + col < p.d) out[0] = s0;
+    if (nt * FN + 16 + col < p.d) out[16] = s1;
+  }
+}
+
+// Which kernel an fp32 batch runs.  The small tiles read three times the operands of the large ones per product: up to 4096 of
+// them (down contraction, estimated) they win (12 experts of 128, d = 512, 512 tokens, 2128 tiles: 86 -> 54 us per forward; 8
+// experts of 512, d = 1024, 512 tokens, 3168: 152 -> 138), beyond the others do (the former at 4096 tokens: 186 against 231).
+static bool f32_small(const Engine& e, int64_t T) {
+  if (e.dtype == 1) return false;
+  const int64_t entries = T * e.S_dyn, touched = std::min<int64_t>(e.G - e.n_always, entries);
+  const int64_t rows = e.n_always * ((T + FM - 1) / FM) + entries / FM + touched / 2;
+  return rows * cdiv(e.d, FN) <= 4096;
+}
+
+template <int MODE>
+static hipError_t launch_simt(const Engine& e, int64_t T, const SimtArgs<float>& a, int64_t n, hipStream_t s) {
+  const dim3 grid((unsigned)n), block(256);
+  if (!f32_small(e, T)) hipLaunchKernelGGL((grouped_gemm_simt<float, MODE>), grid, block, 0, s, a);
+  else if (a.vec) hipLaunchKernelGGL((grouped_gemm_f32<MODE, true>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((grouped_gemm_f32<MODE, false>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
+template <int MODE>
+static hipError_t launch_simt(const Engine&, int64_t, const SimtArgs<bf16_t>& a, int64_t n, hipStream_t s) {
+  hipLaunchKernelGGL((grouped_gemm_simt<bf16_t, MODE>), dim3((unsigned)n), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
 template <typename T>
 static hipError_t run_simt(const Engine& e, const void* x, int64_t Tn, char* ws, const WsLayout& L, void* y,
                            hipStream_t s, int stage) {
@@ -190,8 +324,7 @@ static hipError_t run_simt(const Engine& e, const void* x, int64_t Tn, char* ws,
   // (the workspace and the weights are 256-byte aligned and H's rows a multiple of 32 wide; x is the caller's)
   a.vec = (sizeof(T) == 4 && !e.w_tiled && e.d % 4 == 0 && e.ldw1 % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0) ? 1 : 0;
   if (stage != 2) {
-    hipLaunchKernelGGL((grouped_gemm_simt<T, 1>), dim3((unsigned)gemm_work_bound(e, Tn, 1)), dim3(256), 0, s, a);
-    hipError_t err = hipGetLastError();
+    const hipError_t err = launch_simt<1>(e, Tn, a, gemm_work_bound(e, Tn, 1), s);
     if (err != hipSuccess || stage == 1) return err;
   }
   a.vec = (sizeof(T) == 4 && !e.w_tiled) ? 1 : 0;
@@ -200,8 +333,7 @@ static hipError_t run_simt(const Engine& e, const void* x, int64_t Tn, char* ws,
   a.C = e.direct_output() ? static_cast<T*>(y) : reinterpret_cast<T*>(ws + L.y_slots);
   a.work = reinterpret_cast<const int32_t*>(ws + L.work2);
   a.slot2tok = nullptr;
-  hipLaunchKernelGGL((grouped_gemm_simt<T, 2>), dim3((unsigned)gemm_work_bound(e, Tn, 2)), dim3(256), 0, s, a);
-  return hipGetLastError();
+  return launch_simt<2>(e, Tn, a, gemm_work_bound(e, Tn, 2), s);
 }
 
 hipError_t launch_experts_simt(const Engine& e, const void* x, int64_t T, char* ws, const WsLayout& L, void* y,
@@ -210,6 +342,10 @@ hipError_t launch_experts_simt(const Engine& e, const void* x, int64_t T, char* 
   return run_simt<float>(e, x, T, ws, L, y, s, stage);
 }
 
-int simt_gemm_tile(int which) { return which >= 5 ? 0 : SB; }   // (5, 6: no tiles of dynamic height here)
+// which as in bf16_gemm_tile (no tiles of dynamic height and no persistent kernel here)
+int simt_gemm_tile(int which, const Engine& e, int64_t T) {
+  if (which >= 5) return 0;
+  return !f32_small(e, T) ? SB : which <= 2 ? FM : FN;
+}
 
 }  // namespace cmoe

@@ -33,13 +33,24 @@ __global__ __launch_bounds__(PLACE_WAVES * 64) void place_kernel(PlaceArgs p) {
     sel_g[i] = p.sel_group[e0 + i];
     sel_w[i] = p.sel_weight[e0 + i];
   }
+  if (p.count_here) {
+    int32_t(*flat)[MAX_GROUPS] = part[0];                      // tot, prev; the other waves' parts stay zero
+    for (int i = threadIdx.x; i < PLACE_WAVES * 2 * MAX_GROUPS; i += PLACE_WAVES * 64) (&part[0][0][0])[i] = 0;
+    __syncthreads();
+    const int n = (int)(p.T * p.S_dyn);
+    for (int i = threadIdx.x; i < n; i += PLACE_WAVES * 64) {
+      const int g = p.sel_group[i];
+      atomicAdd(&flat[0][g], 1);
+      if (i < e0) atomicAdd(&flat[1][g], 1);
+    }
+  }
   const int per = (p.n_counts + PLACE_WAVES - 1) / PLACE_WAVES;
   const int first = wave * per, end = first + per < p.n_counts ? first + per : p.n_counts;
   const int row0 = tile * p.counts_per_tile;                   // the tile's first row of the table
 #pragma unroll
   for (int k = 0; k < GPL; ++k) {
     const int g = lane + 64 * k;
-    if (64 * k >= p.G) continue;
+    if (64 * k >= p.G || p.count_here) continue;
     int tot = 0, prev = 0;
     if (g < p.G && g >= p.n_always) {
       // independent loads, eight in flight at a time (the compiler does not batch them by itself)
@@ -118,6 +129,7 @@ PlaceArgs make_place_args(const Engine& e, int64_t T, char* ws, const WsLayout& 
   p.bn2 = tiles ? gemm_tile(e, T, 4) : 1;
   p.dyn1 = tiles ? gemm_tile(e, T, 5) : 0;
   p.dyn2 = tiles ? gemm_tile(e, T, 6) : 0;
+  p.count_here = place_counts_itself(e, T) ? 1 : 0;
   p.stream2 = tiles ? gemm_tile(e, T, 7) : 0;
   return p;
 }

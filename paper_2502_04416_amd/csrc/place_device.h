@@ -30,6 +30,7 @@ struct PlaceArgs {
                                // ragged last tile costs its rows)
   int stream2;                 // > 0: the down contraction is the persistent one, and groups wider than this come first in its
                                // list (see there)
+  int count_here;              // 1: there is no histogram, place_kernel counts the batch's entries (few)
   int decode;                  // 1: the work lists count decode units (dec_unit1 neurons / 16 output columns per unit)
   int dec_unit1;               // neurons per gate/up unit of the decode kernels (16 or 8)
   int skip_always;             // 1: no gate/up work items for the always-on groups (another launch ran them)

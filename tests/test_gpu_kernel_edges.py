@@ -272,3 +272,30 @@ def test_persistent_down_contraction_many_tiles(binding):
         binding.cmoe_set_tuning("CMOE_GEMM2_CFG", -1)
     assert torch.equal(y[8], y[22])
     layer.close()
+
+
+@pytest.mark.parametrize("d,N,m,n_s,k,T", [
+    (70, 4, 9, 0, 1, 1),           # rows that are not whole float4s, K ragged in every wave, widths padded to 32
+    (64, 8, 40, 1, 2, 17),         # fewer chunks of K than waves; one row past a tile
+    (328, 12, 50, 2, 3, 100),      # K = 20.5 chunks, columns that end inside a tile
+    (640, 8, 136, 1, 1, 48),       # K of more than one batch of loads
+    (512, 12, 64, 1, 2, 690),      # as many entries as the placement counts by itself, over several tiles of tokens
+    (512, 12, 64, 1, 3, 1500),     # batches of the large tiles
+])
+def test_fp32_tiles(binding, d, N, m, n_s, k, T):
+    """The fp32 contraction kernels and the scorer at their edges, with and without aligned rows of x."""
+    import torch
+    cfg = synth.scaled(synth.CONFIGS[0], d_model=d, d_ff=N * m, n_experts=N, n_shared=n_s, top_k=k, n_centres=16)
+    weights = synth.make_weights(cfg, seed=3300)
+    part = synth.trivial_partition(cfg, seed=1)
+    x = synth.make_token_source(cfg).eval_batch(1, n=T)
+    layer = binding.Layer.from_partition(cfg, *weights, part["neuron_order"], part["rep_neuron"])
+    out = layer.forward(x)
+    check_flat(cfg, weights, part, x, out)
+    check_dense(cfg, weights, x, layer.dense_forward(x))
+    buf = torch.empty(T * d + 1, device="cuda")
+    xu = buf[1:].view(T, d).copy_(torch.from_numpy(x))           # rows that start 4 bytes past a 16-byte boundary
+    y = torch.empty((T, d), device="cuda")
+    layer.forward_device(xu, y)
+    assert np.array_equal(y.cpu().numpy(), out["y"])             # the same sums in the same order
+    layer.close()
