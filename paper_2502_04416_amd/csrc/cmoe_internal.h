@@ -230,6 +230,16 @@ hipError_t launch_decode_down_sparse(const Engine& e, int64_t T, char* ws, const
 hipError_t launch_mask_hidden(const Engine& e, int64_t T, char* ws, const WsLayout& L, hipStream_t s);
 hipError_t launch_experts_decode(const Engine& e, const void* x, int64_t T, char* ws, const WsLayout& L, void* y,
                                  hipStream_t s, int stage);
+// Gate/up contraction of batches of 2 to STREAM_ROWS tokens by streamed units (gate_up_stream.hip): of a decode batch, and as
+// a tile shape of its own.
+constexpr int STREAM_ROWS = 64;
+bool stream_gate_up_ok(const Engine& e, int64_t T);
+int stream_neurons(const Engine& e, int64_t T);            // neurons per unit, 16 or 8
+bool decode_gate_up_streams(const Engine& e, int64_t T);   // a decode batch runs it
+bool tiles_gate_up_streams(const Engine& e, int64_t T);    // a batch on tiles does
+// The scorer of the front end leaves a copy of the tokens for it, [K step of 32][token][32], where the slot outputs go later.
+bool front_lays_tokens(const Engine& e, int64_t T);
+hipError_t launch_stream_gate_up(const Engine& e, const void* x, int64_t T, char* ws, const WsLayout& L, int neurons, int n_blocks, hipStream_t s);
 // Upper bound of work items of grouped GEMM `which` (1: gate/up, 2: down) for T tokens.
 int64_t gemm_work_bound(const Engine& e, int64_t T, int which);
 

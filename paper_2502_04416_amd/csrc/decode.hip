@@ -374,11 +374,11 @@ __global__ __launch_bounds__(DS_WAVES * 64) void decode_down_sparse_kernel(DecAr
 }
 
 // Up to 16 tokens (one MFMA token tile) the weight-streaming kernels are the fastest form of both
-// contractions; from 17 tokens on a second token tile would double their register footprint, and the tiled
-// contraction on skinny tiles is as fast for the routed layer and 10-20 us faster for the dense one
-// (measured at d = 4096).
+// contractions; from 17 tokens on the routed layer chooses between streamed units and tiles (streams_small_batch), and the
+// dense one is 10-20 us faster on skinny tiles (measured at d = 4096).
 constexpr int DECODE_MAX_T = 16;
-// Above d = 4096 a wave's K slice takes several dependent runs of loads, and the tile kernels catch up earlier.  us per
+// Above d = 4096 the batches from five tokens on choose as those from 17 on do below it.  (Measured before the streamed units, when
+// a wave's K slice took several dependent runs of loads and the tile kernels caught up early:)  us per
 // forward on tiles / streamed, d_ff = 11264, 16 experts, top-3: d = 5120 49.4 / 29.4 at one token, 64.3 / 50.7 at four, d = 8192
 // 55.9 / 38.6 and 86.2 / 77.5, d = 10240 63.8 / 46.4 and 117.6 / 109.8; at 16 tokens 79.2 / 81.0, 106.0 / 127.2 and 134.7 /
 // 154.0.  In between neither side wins throughout: five to eight tokens are 4 to 38 % faster streamed at d = 5120 and 6144,
@@ -405,6 +405,7 @@ bool decode_fuses_combine(const Engine& e, int64_t T) {
 int decode_unit_neurons(const Engine& e, int64_t T) {
   const int forced = tuning().decode_split;
   if (forced == 8 || forced == 16) return forced;
+  if (decode_gate_up_streams(e, T)) return stream_neurons(e, T);
   if (decode_front_runs_all(e, T)) return 16;     // (measured: 27.9 against 31.4 us and 30.4 against 31.6 us at one token)
   const int64_t dyn_groups = std::min<int64_t>(T * e.S_dyn, e.G - e.n_always);
   int64_t units8 = e.G > e.n_always ? dyn_groups * (e.width_pad_host[e.n_always] / 8) : 0;
@@ -448,6 +449,8 @@ DecArgs make_dec_args(const Engine& e, const void* x, int64_t T, char* ws, const
   a.slot2tok = a.single ? nullptr : reinterpret_cast<const int32_t*>(ws + L.slot2tok);
   a.unit1 = decode_unit_neurons(e, T);
   a.nch = decode_k(e.d).nch;
+  a.x_row = e.d;
+  a.x_step = 32;
   return a;
 }
 
@@ -488,7 +491,7 @@ hipError_t launch_experts_decode(const Engine& e, const void* x, int64_t T, char
   if (stage != 2) {
     a.work = reinterpret_cast<const int32_t*>(ws + L.work1);
     const int64_t nb = a.single ? e.max_width_pad / a.unit1 : decode_unit_bound(e, T, 1);
-    hipError_t err = launch_gate_up<1>(a, nb, s);
+    hipError_t err = decode_gate_up_streams(e, T) ? launch_stream_gate_up(e, x, T, ws, L, a.unit1, (int)nb, s) : launch_gate_up<1>(a, nb, s);
     if (err != hipSuccess || stage == 1) return err;
   }
   if (decode_fuses_combine(e, T)) return launch_decode_down_combine(e, T, ws, L, y, s);

@@ -2,6 +2,7 @@
 // gate/up contraction of one 16-neuron unit (the routing front end runs the shared expert's units in the
 // launch that selects and places the tokens).
 #pragma once
+#include <type_traits>
 #include "cmoe_internal.h"
 #include "device_utils.h"
 
@@ -27,6 +28,7 @@ struct DecArgs {
   int64_t T;
   int single;
   int unit1;                // neurons per gate/up unit: 16 or 8
+  int x_row, x_step;        // stream_gate_up_unit: elements from one token to the next and from one K step of 32 to the next
   int nch;                  // a wave's K slice in runs of KSTEPS steps of 32: d = 8 * KSTEPS * 32 * nch (1 but for the _runs forms)
 };
 
@@ -317,6 +319,125 @@ __device__ __forceinline__ void decode_gate_up(const DecArgs& p, int g, int loca
   }
 }
 
+// The same contraction for up to 16 * NTT rows of a group whose tokens do not stay in registers: K is walked in chunks of
+// CS steps, the operands of the next chunk requested before the current one is multiplied, so that between one and two
+// chunks of weights are always on their way.  What bounds a unit is the stream of its weights from HBM; its tokens, NTT KB
+// for every KB of gate and every KB of up rows, come from L2.  NEUR = 16, or 8 as in decode_gate_up_unit8 (gate and up rows in
+// one operand).  row0, cnt: the unit's first slot and how many there are; columns past them repeat the first row and are not
+// stored.  d must be a multiple of 256 * CS, the weights tiled.
+constexpr int STREAM_RED_FLOATS = 8 * 2 * 16 * 17;
+template <int NTT, int CS, int NEUR>
+__device__ __forceinline__ void stream_gate_up_unit(const DecArgs& p, int g, int local, int row0, int cnt, int wp, int64_t hoff,
+                                                    float* redbuf) {
+  constexpr int OPS = NEUR / 8;                               // operands per K step: gate and up, or both in one
+  float (*red)[OPS][16][17] = reinterpret_cast<float (*)[OPS][16][17]>(redbuf);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, kq = lane >> 4;
+  const int neuron0 = local * NEUR;
+  const int steps = p.d / 256, kbase = wave * steps * 32 + kq * 8, chunks = steps / CS;
+  const int n = neuron0 + (r16 & (NEUR - 1));
+  const int64_t grow = (int64_t)p.groups[g].w1_row0 + (n / IL) * 2 * IL + (n % IL) + (r16 >= NEUR ? IL : 0);
+  const bf16_t* w[OPS];
+  w[0] = p.w1 + tiled_offset(grow, kbase, p.ldw / TILE_K);
+  if (OPS == 2) w[OPS - 1] = w[0] + (int64_t)(IL / TILE_ROWS) * (p.ldw / TILE_K) * TILE_ELEMS;
+  bf16x8_t a[2][OPS][CS], bx[2][NTT][CS];
+  auto load_w = [&](auto buf, int c) {
+    constexpr int B = decltype(buf)::value;
+#pragma unroll
+    for (int s = 0; s < CS; ++s)
+#pragma unroll
+      for (int o = 0; o < OPS; ++o) a[B][o][s] = ld_frag(w[o] + (int64_t)(c * CS + s) * TILE_ELEMS);
+  };
+  using B0 = std::integral_constant<int, 0>;
+  using B1 = std::integral_constant<int, 1>;
+  load_w(B0{}, 0);                                            // before anything else: HBM is what the unit waits for
+  __builtin_amdgcn_sched_barrier(0);
+  uint32_t xo[NTT];
+#pragma unroll
+  for (int tt = 0; tt < NTT; ++tt) {
+    const int row = row0 + (tt * 16 + r16 < cnt ? tt * 16 + r16 : 0);
+    xo[tt] = (uint32_t)((p.slot2tok ? p.slot2tok[row] : row) * p.x_row + kq * 8);
+  }
+  auto load_x = [&](auto buf, int c) {
+    constexpr int B = decltype(buf)::value;
+#pragma unroll
+    for (int s = 0; s < CS; ++s) {
+      const bf16_t* xs = p.x + (int64_t)(wave * steps + c * CS + s) * p.x_step;
+#pragma unroll
+      for (int tt = 0; tt < NTT; ++tt) bx[B][tt][s] = ld_frag(xs + xo[tt]);
+    }
+  };
+  floatx4_t acc[OPS][NTT];
+#pragma unroll
+  for (int o = 0; o < OPS; ++o)
+#pragma unroll
+    for (int tt = 0; tt < NTT; ++tt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[o][tt][i] = 0.0f;
+  auto multiply = [&](auto buf) {
+    constexpr int B = decltype(buf)::value;
+#pragma unroll
+    for (int s = 0; s < CS; ++s)
+#pragma unroll
+      for (int tt = 0; tt < NTT; ++tt)
+#pragma unroll
+        for (int o = 0; o < OPS; ++o) acc[o][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[B][o][s], bx[B][tt][s], acc[o][tt], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto load = [&](auto buf, int c) {
+    load_w(buf, c);
+    load_x(buf, c);
+    __builtin_amdgcn_sched_barrier(0);                        // (requested here, not where the compiler finds a use)
+  };
+  load_x(B0{}, 0);
+  int c = 0;
+  for (; c + 2 < chunks; c += 2) {
+    load(B1{}, c + 1);
+    multiply(B0{});
+    load(B0{}, c + 2);
+    multiply(B1{});
+  }
+  if (c + 1 < chunks) {
+    load(B1{}, c + 1);
+    multiply(B0{});
+    multiply(B1{});
+  } else {
+    multiply(B0{});
+  }
+  // one token tile at a time: accumulator element i is operand row (lane/16)*4 + i, token column lane%16
+#pragma unroll
+  for (int tt = 0; tt < NTT; ++tt) {
+    if (tt > 0) __syncthreads();
+#pragma unroll
+    for (int o = 0; o < OPS; ++o)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) red[wave][o][kq * 4 + i][r16] = acc[o][tt][i];
+    __syncthreads();
+    const int tok = tid / NEUR, nn = tid % NEUR, col = tt * 16 + tok;       // neuron fastest: contiguous stores
+    if (tok < 16 && col < cnt) {
+      float sg = 0.0f, su = 0.0f;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) { sg += red[k][0][nn][tok]; su += red[k][OPS - 1][NEUR == 8 ? 8 + nn : nn][tok]; }
+      p.h[hoff + (int64_t)col * wp + neuron0 + nn] = f32_to_bf16(silu_f32(sg) * su);
+    }
+  }
+}
+
+// A unit in the instantiation for its rows; MAXT: token tiles of the fullest unit the caller can have.
+template <int MAXT, int CS, int NEUR>
+__device__ __forceinline__ void stream_gate_up(const DecArgs& p, int g, int local, int row0, int cnt, int wp, int64_t hoff, float* redbuf) {
+  if (MAXT == 1 || cnt <= 16) stream_gate_up_unit<1, CS, NEUR>(p, g, local, row0, cnt, wp, hoff, redbuf);
+  else if (MAXT == 2 || cnt <= 32) stream_gate_up_unit<MAXT < 2 ? MAXT : 2, CS, NEUR>(p, g, local, row0, cnt, wp, hoff, redbuf);
+  else stream_gate_up_unit<MAXT, NEUR == 8 ? CS : 2, NEUR>(p, g, local, row0, cnt, wp, hoff, redbuf);    // (16 neurons, four steps: spills)
+}
+
+// CALL(MAXT, CS) with the template arguments for a batch of T <= 64 tokens at model width d (a multiple of 512).
+#define CMOE_STREAM_FORM(T, d, CALL)                                                            \
+  if ((T) <= 16) { if ((d) % 1024 == 0) { CALL(1, 4); } else { CALL(1, 2); } }                  \
+  else if ((T) <= 32) { CALL(2, 2); }                                                           \
+  else { if ((d) % 1024 == 0) { CALL(4, 4); } else { CALL(4, 2); } }
+
 // Model widths of the decode kernels: d = 8 waves x nch runs x ksteps steps of 32.  One run of an even number of
 // steps up to d = 4096, above that runs of 8 or 10; zero steps for a width they do not serve.
 struct DecodeK { int ksteps, nch; };
@@ -379,6 +500,8 @@ static_assert(decode_widths_covered(), "a model width without its step count");
 
 // Host side (decode.hip): the argument block of a forward.
 DecArgs make_dec_args(const Engine& e, const void* x, int64_t T, char* ws, const WsLayout& L, void* y);
+// The same for the streamed units (gate_up_stream.hip): tokens as the scorer of the front end laid them out, if it did.
+DecArgs make_stream_args(const Engine& e, const void* x, int64_t T, char* ws, const WsLayout& L);
 // Neurons per gate/up unit of the decode kernels for this batch (16, or 8 when that fills the chip better).
 int decode_unit_neurons(const Engine& e, int64_t T);
 

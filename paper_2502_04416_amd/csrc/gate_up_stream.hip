@@ -1,0 +1,64 @@
+// Gate/up contraction of batches of 2 to 64 tokens, a few rows to a group.  The launch is bound by the stream of the touched
+// experts' weights from HBM; a workgroup takes 16 or 8 neurons over all of K (stream_gate_up_unit).  Against keeping a unit's
+// tokens in registers (decode_gate_up_unit): two to three workgroups fit a CU instead of one or two, weight loads never pause
+// for a new run of tokens, and the tokens come from a copy laid out [K step][token][32] by the scorer, where the 16 rows of an
+// operand are neighbours; in the caller's matrix they are a power of two apart at d = 4096 and 8192 and meet in one L2 channel.
+// Gate/up + selection launches, d = 8192, 8 experts, 5 tokens: 63.6 -> 56.2 us.
+#include "cmoe_internal.h"
+#include "decode_device.h"
+#include "device_utils.h"
+
+namespace cmoe {
+
+template <int MAXT, int CS, int NEUR>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MAXT <= 2 ? 4 : 2))) void stream_gate_up_kernel(DecArgs p) {
+  __shared__ float red[STREAM_RED_FLOATS];
+  const int u = blockIdx.x;
+  if (u >= p.work[p.G]) return;
+  const int g = find_group(p.work, p.G, u);
+  stream_gate_up<MAXT, CS, NEUR>(p, g, u - p.work[g], p.seg_off[g], p.seg_off[g + 1] - p.seg_off[g], p.groups[g].width_pad, p.h_off[g], red);
+}
+
+bool stream_gate_up_ok(const Engine& e, int64_t T) {
+  return e.dtype == 1 && !use_simt_experts(e.dtype) && e.w_tiled && e.d % 512 == 0 && T >= 2 && T <= STREAM_ROWS && e.S_dyn > 0;
+}
+
+// Units of 8 are shorter, and a last round of workgroups that does not fill the chip costs less; units of 16 read the tokens half
+// as often.  us per forward with 16 / 8 neurons, d = 4096, 16 experts, top-3: 4 tokens 45.5 / 41.8, 16 tokens 59.5 / 55.4, 24 tokens
+// 67.0 / 68.3; d = 5120, 16 experts, top-2: 17 tokens 75.6 / 77.7; d = 8192, 32 experts, top-5: 8 tokens 86.9 / 81.7, 24 tokens 122.9 / 120.5.
+int stream_neurons(const Engine& e, int64_t T) { return T <= 16 || e.d > 5120 ? 8 : 16; }
+
+// us per forward on decode_gate_up_kernel / streamed: d = 4096, 16 experts, top-3: 2 tokens 34.4 / 33.2, 16 tokens 62.2 / 55.4; d = 5120
+// 44.1 / 37.1 at two tokens; d = 8192 85.9 / 72.2; up to d = 2048 both are bound by the host (20.3 / 20.5).  Without an always-on
+// group next to the selection, two tokens are the other way round at d = 4096 (30.8 / 32.1), three even.
+bool decode_gate_up_streams(const Engine& e, int64_t T) {
+  if (!decode_path_ok(e, T) || !stream_gate_up_ok(e, T) || decode_front_runs_all(e, T)) return false;
+  return T > 3 || e.n_always == 1 || e.r.outer_top_k != 0 || decode_k(e.d).nch > 1;
+}
+
+bool front_lays_tokens(const Engine& e, int64_t T) {
+  return decode_front_ok(e, T) && (decode_path_ok(e, T) ? decode_gate_up_streams(e, T) : tiles_gate_up_streams(e, T));
+}
+
+DecArgs make_stream_args(const Engine& e, const void* x, int64_t T, char* ws, const WsLayout& L) {
+  DecArgs a = make_dec_args(e, x, T, ws, L, nullptr);
+  if (front_lays_tokens(e, T)) {
+    a.x = reinterpret_cast<const bf16_t*>(ws + L.y_slots);
+    a.x_row = 32;
+    a.x_step = 32 * (int)T;
+  }
+  return a;
+}
+
+hipError_t launch_stream_gate_up(const Engine& e, const void* x, int64_t T, char* ws, const WsLayout& L, int neurons, int n_blocks, hipStream_t s) {
+  DecArgs a = make_stream_args(e, x, T, ws, L);
+  a.work = reinterpret_cast<const int32_t*>(ws + L.work1);
+#define CMOE_LAUNCH_N(MAXT, CS, NEUR) hipLaunchKernelGGL((stream_gate_up_kernel<MAXT, CS, NEUR>), dim3((unsigned)n_blocks), dim3(512), 0, s, a)
+#define CMOE_LAUNCH(MAXT, CS) if (neurons == 8) CMOE_LAUNCH_N(MAXT, CS, 8); else CMOE_LAUNCH_N(MAXT, CS, 16)
+  CMOE_STREAM_FORM(T, e.d, CMOE_LAUNCH)
+#undef CMOE_LAUNCH
+#undef CMOE_LAUNCH_N
+  return hipGetLastError();
+}
+
+}  // namespace cmoe

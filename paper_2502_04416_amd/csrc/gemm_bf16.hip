@@ -831,10 +831,13 @@ static const TileCfg kCfgs[] = {
     {128, 128, 2, 2, 5, 32},   // 20: deep ring, four waves of 64x64
     {64, 128, 2, 2, 6, 32},    // 21: deep ring in steps of 64, four waves of 32x64, two workgroups per CU
     {128, 256, 2, 2, 3, 32},   // 22: the persistent down contraction (gemm_stream.hip)
+    {STREAM_ROWS, 32, 1, 8, 2, 32},   // 23: streamed gate/up units of 16 neurons (gate_up_stream.hip)
+    {STREAM_ROWS, 16, 1, 8, 2, 32},   // 24: ... of 8
 };
 static bool cfg_is_ws(int ci) { return ci >= 15 && ci <= 18; }
 static bool cfg_is_stream(int ci) { return ci == 22; }
 static bool cfg_is_ring(int ci) { return kCfgs[ci].stages >= 5 && !cfg_is_stream(ci); }
+static bool cfg_is_units(int ci) { return ci == 23 || ci == 24; }
 static bool cfg_is_dyn(int ci) { return ci >= 11 && ci <= 18; }
 bool ws_down_handles(int width_pad);
 hipError_t launch_down_stream(const Engine& e, const GemmArgs& a, hipStream_t s);
@@ -949,9 +952,21 @@ static bool stream_ok(const Engine& e) {
   return true;
 }
 
+// Streamed units instead of a tile: few rows per expert, counted as routed entries per expert times d (what an operand of
+// tokens costs grows with the rows, what it is hidden behind does not).  us per forward on tiles / streamed: d = 512, 8
+// experts, 64 tokens 29.7 / 25.2; d = 2048, 12 experts, top-2: 17 tokens 36.7 / 30.9, 64 (26214) 47.5 / 45.5; d = 4096, 32
+// experts, top-4: 32 tokens (18724) 75.5 / 73.8, 48 (28086) 88.3 / 89.2; 16 experts, top-3: 17 tokens (13926) 63.1 / 62.4, 24
+// (19660) 65.9 / 67.0; d = 5120, 16 experts, top-2: 8 tokens 69.7 / 61.5, 32 (20480) 84.7 / 84.4, 48 86.1 / 90.9; d = 8192, 8
+// experts, top-2: 5 tokens 102.6 / 93.5, 12 (28086) 115.1 / 113.7, 16 119.7 / 121.0; 32 experts, top-5: 17 (24011) 110.2 / 109.6,
+// 24 117.4 / 120.5.  A hierarchy's outer experts meet more rows than its groups do on average: 17 tokens 65.3 / 66.1, 64 90 / 97.
+static bool streams_small_batch(const Engine& e, int64_t T) {
+  if (!stream_gate_up_ok(e, T) || e.r.outer_top_k != 0) return false;
+  return T * e.S_dyn * e.d <= (e.d <= 2048 || e.d > 5120 ? 26500 : 19000) * (int64_t)(e.G - e.n_always);
+}
+
 static int cfg_index(int which, const Engine& e, int64_t T) {
   int dflt = 0;
-  if (which == 1) dflt = gate_up_cfg(e, T);
+  if (which == 1) dflt = streams_small_batch(e, T) ? (stream_neurons(e, T) == 8 ? 24 : 23) : gate_up_cfg(e, T);
   if (which == 2) {
     const bool single = e.G == 1 && e.n_always == 1;
     int k_min = 1 << 30;
@@ -1004,10 +1019,10 @@ static int cfg_index(int which, const Engine& e, int64_t T) {
   const int forced = which == 1 ? tuning().gemm1_cfg : tuning().gemm2_cfg;
   if (which == 1 && e.S_dyn > 0 && wide_gather(e.d, T)) {
     // (of the ring shapes only 6 is built with 64-bit row addresses; the others have them)
-    return forced >= 0 && forced < kNumCfgs && !cfg_is_ws(forced) && !cfg_is_ring(forced) ? forced : 6;
+    return forced >= 0 && forced < kNumCfgs && !cfg_is_ws(forced) && !cfg_is_ring(forced) && !cfg_is_units(forced) ? forced : 6;
   }
   if (forced >= 0 && forced < kNumCfgs && !(which == 1 && (cfg_is_ws(forced) || cfg_is_stream(forced))) &&
-      (!cfg_is_stream(forced) || stream_ok(e))) return forced;
+      (!cfg_is_stream(forced) || stream_ok(e)) && (!cfg_is_units(forced) || (which == 1 && stream_gate_up_ok(e, T)))) return forced;
   if (which == 2 && tuning().ws_down != 0 && !(e.G == 1 && e.n_always == 1) && e.w_tiled && e.d % 256 == 0) {
     // The weight-stationary kernel for the groups it handles, when the batch gives it enough work items to
     // fill the chip several times over: the largest row chunk that still leaves four rounds of items (a chunk
@@ -1026,6 +1041,10 @@ static int cfg_index(int which, const Engine& e, int64_t T) {
     }
   }
   return dflt;
+}
+
+bool tiles_gate_up_streams(const Engine& e, int64_t T) {
+  return stream_gate_up_ok(e, T) && !decode_path_ok(e, T) && cfg_is_units(cfg_index(1, e, T));
 }
 
 // which = 1: BM of gate/up, 2: BM of down, 3: BN of gate/up (packed rows), 4: BN of down,
@@ -1068,7 +1087,7 @@ static int splitk_ldp(const Engine& e, int which) { return which == 1 ? 2 * e.ma
 int bf16_splitk(const Engine& e, int64_t T, int which) {
   if (T < 1 || T > 1024 || tuning().splitk == 0) return 1;
   const int ci = cfg_index(which, e, T);
-  if (cfg_is_ws(ci) || cfg_is_stream(ci)) return 1;
+  if (cfg_is_ws(ci) || cfg_is_stream(ci) || cfg_is_units(ci)) return 1;
   const TileCfg& c = kCfgs[ci];
   const int64_t tiles = est_tiles(e, T, which, c.bm, c.bn);
   int k_min = e.d;
@@ -1244,7 +1263,8 @@ hipError_t launch_experts_bf16(const Engine& e, const void* x, int64_t T, char* 
   a.k_split = splitk_that_fits(e, T, 1, L);
   a.ldp = splitk_ldp(e, 1);
   if (stage != 2) {
-    hipError_t err = launch_cfg<1>(cfg_index(1, e, T), a, s);
+    const int ci = cfg_index(1, e, T);
+    hipError_t err = cfg_is_units(ci) ? launch_stream_gate_up(e, x, T, ws, L, ci == 24 ? 8 : 16, a.n_blocks, s) : launch_cfg<1>(ci, a, s);
     if (err == hipSuccess && a.k_split > 1) {
       hipLaunchKernelGGL(splitk_finish_gate_up, dim3((unsigned)a.p_rows), dim3(256), 0, s, a.P, a.k_split, a.p_rows, a.ldp,
                          a.groups, a.seg_off, a.h_off, a.G, a.single, a.C);

@@ -362,9 +362,11 @@ __global__ __launch_bounds__(256) void router_simt_kernel(RouterDev r, RouteIO i
 // memory, then the four partial sums are added in a fixed order through LDS.  NT = n_rows / 32 <= 5.
 constexpr int RT_TOK = 32;
 
-template <int NT>
+// COPY: the tokens also go to xt, [K step of 32][token][32].
+template <int NT, bool COPY>
 __global__ __launch_bounds__(256) void router_gemm_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wr,
-                                                          int d, int64_t T, int k_slice, float* __restrict__ partial) {
+                                                          int d, int64_t T, int k_slice, float* __restrict__ partial,
+                                                          bf16_t* __restrict__ xt) {
   __shared__ float red[RT_TOK][NT * 32 + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t t0 = (int64_t)blockIdx.x * RT_TOK;
@@ -398,15 +400,23 @@ __global__ __launch_bounds__(256) void router_gemm_kernel(const bf16_t* __restri
 #pragma unroll
       for (int ni = 0; ni < NT; ++ni) acc[ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s4], b[ni][s4], acc[ni], 0, 0, 0);
   };
+  auto copy_chunk = [&](int kc, bf16x8_t (&a)[4]) {
+    if (!COPY || t0 + l32 >= T) return;
+#pragma unroll
+    for (int s4 = 0; s4 < 4; ++s4)
+      *reinterpret_cast<bf16x8_t*>(xt + (((int64_t)(kc / 32 + s4 / 2) * T + t) * 32 + (s4 % 2) * 16 + lh * 8)) = a[s4];
+  };
   int kc = k_begin + wave * 64;
   if (kc < k_end) load_chunk(kc, a0, b0);
   while (kc < k_end) {
     if (kc + 256 < k_end) load_chunk(kc + 256, a1, b1);
     mma_chunk(a0, b0);
+    copy_chunk(kc, a0);
     kc += 256;
     if (kc >= k_end) break;
     if (kc + 256 < k_end) load_chunk(kc + 256, a0, b0);
     mma_chunk(a1, b1);
+    copy_chunk(kc, a1);
     kc += 256;
   }
   for (int wsel = 0; wsel < 4; ++wsel) {
@@ -639,7 +649,8 @@ constexpr int DEC_SLICES = 8;
 
 template <int NTT, int KSTEPS>
 __global__ __launch_bounds__(64) void decode_score_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wr,
-                                                          int d, int nch, int T, int n_rows, float* __restrict__ pre_g) {
+                                                          int d, int nch, int T, int n_rows, float* __restrict__ pre_g,
+                                                          bf16_t* __restrict__ xt) {
   const int lane = threadIdx.x;
   const int slice = blockIdx.y;
   const int r16 = lane & 15, kq = lane >> 4;
@@ -670,6 +681,9 @@ __global__ __launch_bounds__(64) void decode_score_kernel(const bf16_t* __restri
           for (int i = 0; i < 8; ++i) b[i] = (__bf16)0.0f;
         }
         acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks], b, acc[tt], 0, 0, 0);
+        // (the first row block's workgroups also leave the copy [K step][token][32], where one is wanted)
+        if (xt && ok && blockIdx.x == 0)
+          *reinterpret_cast<bf16x8_t*>(xt + ((int64_t)(slice * nch * KSTEPS + ch * KSTEPS + ks) * T + col) * 32 + kq * 8) = b;
       }
     }
   } while (++ch < nch);
@@ -816,6 +830,18 @@ __global__ __launch_bounds__(512) void route_place_shared_kernel(RouterDev r, Ro
     return;
   }
   decode_gate_up<1, KSTEPS, RUNS>(da, 0, (int)blockIdx.x - 1, 0, T, da.groups[0].width_pad, 0, red);
+}
+
+// The same for the batches of 2 to 64 tokens that run streamed units (the form above is left with one token).
+template <int MAXT, int CS, int NEUR>
+__global__ __launch_bounds__(512) void route_place_stream_kernel(RouterDev r, RouteIO io, PlaceArgs pl, const float* __restrict__ partial,
+                                                                 int n_slices, int T, DecArgs da) {
+  extern __shared__ float pre[];
+  if (blockIdx.x == 0) {
+    route_place_body(r, io, pl, partial, n_slices, T, pre);
+    return;
+  }
+  stream_gate_up<MAXT, CS, NEUR>(da, 0, (int)blockIdx.x - 1, 0, T, da.groups[0].width_pad, 0, pre);
 }
 
 // One token on a flat layer: the launch that selects and places also runs *every* gate/up unit, the routed
@@ -996,7 +1022,7 @@ static hipError_t launch_score_route(const Engine& e, const RouteIO& io, const v
 
 // Pre-activation partials [slice][T][n_rows] of all router rows by router_gemm_kernel.
 static hipError_t launch_scorer_gemm(const Engine& e, const void* x, int64_t T, float* partial, hipStream_t s,
-                                     int& n_slices) {
+                                     int& n_slices, bf16_t* xt = nullptr) {
   const int n_rows = e.r.n_sw_rows + e.r.n_lin_rows;
   const int n_tt = (int)((T + RT_TOK - 1) / RT_TOK);
   n_slices = scorer_slices(e, T);
@@ -1004,13 +1030,17 @@ static hipError_t launch_scorer_gemm(const Engine& e, const void* x, int64_t T, 
   dim3 grid(n_tt, n_slices), block(256);
   const bf16_t* xx = static_cast<const bf16_t*>(x);
   const bf16_t* ww = static_cast<const bf16_t*>(e.wr);
+#define CMOE_SCORER(NT)                                                                                              \
+  if (xt) hipLaunchKernelGGL((router_gemm_kernel<NT, true>), grid, block, 0, s, xx, ww, e.d, T, k_slice, partial, xt); \
+  else hipLaunchKernelGGL((router_gemm_kernel<NT, false>), grid, block, 0, s, xx, ww, e.d, T, k_slice, partial, xt)
   switch (n_rows / 32) {
-    case 1: hipLaunchKernelGGL(router_gemm_kernel<1>, grid, block, 0, s, xx, ww, e.d, T, k_slice, partial); break;
-    case 2: hipLaunchKernelGGL(router_gemm_kernel<2>, grid, block, 0, s, xx, ww, e.d, T, k_slice, partial); break;
-    case 3: hipLaunchKernelGGL(router_gemm_kernel<3>, grid, block, 0, s, xx, ww, e.d, T, k_slice, partial); break;
-    case 4: hipLaunchKernelGGL(router_gemm_kernel<4>, grid, block, 0, s, xx, ww, e.d, T, k_slice, partial); break;
-    default: hipLaunchKernelGGL(router_gemm_kernel<5>, grid, block, 0, s, xx, ww, e.d, T, k_slice, partial); break;
+    case 1: CMOE_SCORER(1); break;
+    case 2: CMOE_SCORER(2); break;
+    case 3: CMOE_SCORER(3); break;
+    case 4: CMOE_SCORER(4); break;
+    default: CMOE_SCORER(5); break;
   }
+#undef CMOE_SCORER
   return hipGetLastError();
 }
 
@@ -1047,6 +1077,7 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
   float* pre_g = reinterpret_cast<float*>(ws + L.scores);
   const int Ti = (int)T;
   int n_slices = DEC_SLICES;
+  bf16_t* xt = front_lays_tokens(e, T) ? reinterpret_cast<bf16_t*>(ws + L.y_slots) : nullptr;
   hipError_t err = hipSuccess;
   // one token, every gate/up unit in the selection launch: with front_all = 2 that launch also scores
   const bool own_scores = L.gate_up_done && tuning().front_all >= 2 && e.wr_tiled != nullptr && decode_k(e.d).nch == 1;
@@ -1056,14 +1087,14 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
     const bf16_t* xx = static_cast<const bf16_t*>(x);
     const bf16_t* ww = static_cast<const bf16_t*>(e.wr);
     const DecodeK sk = score_k(e.d);
-#define CMOE_SCORE(KS) hipLaunchKernelGGL((decode_score_kernel<1, KS>), grid, block, 0, s, xx, ww, e.d, sk.nch, Ti, n_rows, pre_g)
+#define CMOE_SCORE(KS) hipLaunchKernelGGL((decode_score_kernel<1, KS>), grid, block, 0, s, xx, ww, e.d, sk.nch, Ti, n_rows, pre_g, xt)
     // (measurement aid: repeat_stage = 6 issues the scoring launch twice; it overwrites its partials)
     for (int rep = tuning().repeat_stage == 6 ? 2 : 1; rep > 0; --rep)
       CMOE_EVEN_KSTEPS(sk.ksteps, CMOE_SCORE)
 #undef CMOE_SCORE
     err = hipGetLastError();
   } else {
-    err = launch_scorer_gemm(e, x, T, pre_g, s, n_slices);
+    err = launch_scorer_gemm(e, x, T, pre_g, s, n_slices, xt);
   }
   if (err != hipSuccess) return err;
   if (tuning().skip_stage == 6) return hipSuccess;        // measurement aid: the scoring launch only
@@ -1102,8 +1133,23 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
 #undef CMOE_LAUNCH
     return hipGetLastError();
   }
+  if (L.skip_always && front_lays_tokens(e, T)) {
+    // (the caller set this from decode_front_runs_shared: one always-on group, streamed gate/up units)
+    DecArgs da = make_stream_args(e, x, T, ws, L);
+    da.slot2tok = nullptr;                        // as below
+    smem = std::max(smem, sizeof(float) * (size_t)STREAM_RED_FLOATS);
+    // (units of 8 neurons while each finds a CU of its own: 17 tokens, 16 experts of 688, 63.2 -> 62.5 us per forward)
+    const bool half = tuning().decode_split == 8 || (tuning().decode_split != 16 && e.width_pad_host[0] / 8 < 256);
+    const dim3 grid(1 + e.width_pad_host[0] / (half ? 8 : 16)), block(512);
+#define CMOE_LAUNCH_N(MAXT, CS, NEUR) hipLaunchKernelGGL((route_place_stream_kernel<MAXT, CS, NEUR>), grid, block, smem, s, e.r, io, pl, pre_g, n_slices, Ti, da)
+#define CMOE_LAUNCH(MAXT, CS) if (half) CMOE_LAUNCH_N(MAXT, CS, 8); else CMOE_LAUNCH_N(MAXT, CS, 16)
+    CMOE_STREAM_FORM(T, e.d, CMOE_LAUNCH)
+#undef CMOE_LAUNCH
+#undef CMOE_LAUNCH_N
+    return hipGetLastError();
+  }
   if (L.skip_always) {
-    // (the caller set this from decode_front_runs_shared: one always-on group, decode kernels, T <= 16)
+    // (likewise, one token whose routed units have a launch of their own)
     DecArgs da = make_dec_args(e, x, T, ws, L, nullptr);
     da.slot2tok = nullptr;                        // group 0's slots are the tokens in order; the map is not written yet
     da.work = nullptr;
@@ -1118,7 +1164,8 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
 }
 
 bool decode_front_runs_shared(const Engine& e, int64_t T) {
-  return tuning().front_shared != 0 && T <= FRONT_SCORE_MAX_T && e.n_always == 1 && decode_front_ok(e, T) && decode_path_ok(e, T);
+  if (tuning().front_shared == 0 || e.n_always != 1 || !decode_front_ok(e, T)) return false;
+  return decode_path_ok(e, T) ? T <= FRONT_SCORE_MAX_T : tiles_gate_up_streams(e, T);
 }
 
 // One token (switch front_all), or two to sixteen (switch front_tile; at most 64 groups, 16-neuron units), on a

@@ -299,3 +299,34 @@ def test_fp32_tiles(binding, d, N, m, n_s, k, T):
     layer.forward_device(xu, y)
     assert np.array_equal(y.cpu().numpy(), out["y"])             # the same sums in the same order
     layer.close()
+
+
+@pytest.mark.parametrize("d,N,m,n_s,k,T", [
+    (512, 8, 100, 1, 2, 2),        # one chunk of K per wave, padded widths, two tokens
+    (2560, 8, 64, 1, 2, 16),       # an odd number of chunks; a full token tile
+    (1024, 8, 64, 0, 3, 17),       # one chunk of four steps, no always-on group, one row past a token tile
+    (1536, 6, 50, 2, 1, 33),       # three chunks of two; four token tiles, the third with one row
+    (2048, 4, 96, 1, 3, 64),       # the largest batch, routed groups of two to four token tiles
+    (5632, 8, 40, 1, 2, 5),        # a width without decode kernels
+    (8192, 8, 32, 1, 2, 12),       # a width of several runs, past the decode kernels' four tokens
+    (4096, 66, 32, 2, 4, 3),       # more than 64 groups
+])
+def test_streamed_gate_up(binding, d, N, m, n_s, k, T):
+    """The streamed gate/up units, with the always-on group inside the selection launch and in the list, in both sizes and
+    where the batch's rule takes them or not, against the oracle; all of them bit for bit."""
+    cfg, weights, part, x, layer = _case(binding, d, N, m, n_s, k, T)
+    outs = []
+    try:
+        for shared in (1, 0):
+            for split, shape in ((16, 23), (8, 24)):
+                binding.cmoe_set_tuning("CMOE_FRONT_SHARED", shared)
+                binding.cmoe_set_tuning("CMOE_DECODE_SPLIT", split)
+                binding.cmoe_set_tuning("CMOE_GEMM1_CFG", shape)
+                outs.append(layer.forward(x))
+    finally:
+        for name, value in (("CMOE_FRONT_SHARED", 1), ("CMOE_DECODE_SPLIT", -1), ("CMOE_GEMM1_CFG", -1)):
+            binding.cmoe_set_tuning(name, value)
+    check_flat(cfg, weights, part, x, outs[0])
+    check_flat(cfg, weights, part, x, layer.forward(x))
+    assert all(np.array_equal(o["y"], outs[0]["y"]) for o in outs)
+    layer.close()
