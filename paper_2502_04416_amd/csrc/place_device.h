@@ -131,7 +131,9 @@ __device__ __forceinline__ void place_slots(const PlaceArgs& p, int tile, const 
 // One wave publishes what depends on the batch's counts alone: segment offsets, the work lists of the two
 // contractions and each group's offset in the hidden-activation buffer.  Run by another wave than the slots of
 // tile 0, next to it (both in one wave made that tile the last to finish).
-__device__ __forceinline__ void place_lists(const PlaceArgs& p, const TileCounts& tc, int lane, const LaneWidths& lw) {
+// DECODE: the lists count decode units (p.decode).
+template <bool DECODE>
+__device__ __forceinline__ void place_lists_of(const PlaceArgs& p, const TileCounts& tc, int lane, const LaneWidths& lw) {
   constexpr int GPL = MAX_GROUPS / 64;
   // exclusive prefix over groups of: slots, work items of the two contractions, hidden-buffer elements
   int run0 = 0, w1_0 = 0, w2_0 = 0, w2_deep = 0;
@@ -146,7 +148,7 @@ __device__ __forceinline__ void place_lists(const PlaceArgs& p, const TileCounts
     }
     const int cnt = tc.tot[k], wp = lw.w[k];
     int a1, a2;
-    if (p.decode) {
+    if (DECODE) {
       a1 = cnt > 0 ? wp / p.dec_unit1 : 0;
       a2 = cnt > 0 ? p.d / 16 : 0;
     } else {
@@ -156,12 +158,12 @@ __device__ __forceinline__ void place_lists(const PlaceArgs& p, const TileCounts
     if (g >= p.G) { a1 = 0; a2 = 0; }
     if (p.skip_always && g < p.n_always) a1 = 0;
     const long long ah = (long long)cnt * wp;
-    const bool deep = p.stream2 > 0 && wp > p.stream2;
+    const bool deep = !DECODE && p.stream2 > 0 && wp > p.stream2;
     const int run_i = wave_incl_scan(cnt, lane), w1_i = wave_incl_scan(a1, lane), w2_i = wave_incl_scan(deep ? 0 : a2, lane);
     const long long h_i = wave_incl_scan(ah, lane);
     const int run = run0 + run_i - cnt, w1 = w1_0 + w1_i - a1;
     int w2 = w2_0 + w2_i - a2;
-    if (p.stream2 > 0) {
+    if (!DECODE && p.stream2 > 0) {
       const int deep_i = wave_incl_scan(deep ? a2 : 0, lane);
       if (deep) w2 = w2_deep + deep_i - a2;
       w2_deep += __shfl(deep_i, 63, 64);
@@ -187,7 +189,7 @@ __device__ __forceinline__ void place_lists(const PlaceArgs& p, const TileCounts
     p.work2[p.G] = w2_0;
     p.h_off[p.G] = h0;
   }
-  if (p.stream2 > 0) {
+  if (!DECODE && p.stream2 > 0) {
     // the other tiles follow the deep ones: work2[g] = first tile of group g, [G] = tiles, [G + 1] = deep ones
 #pragma unroll
     for (int k = 0; k < GPL; ++k) {
@@ -199,7 +201,7 @@ __device__ __forceinline__ void place_lists(const PlaceArgs& p, const TileCounts
       p.work2[p.G + 1] = w2_deep;
     }
   }
-  if (p.decode) return;                    // (the decode kernels take their units in list order: no shares)
+  if (DECODE) return;                      // (the decode kernels take their units in list order: no shares)
   // Where each XCD's share of a work list starts (entries G+1 .. G+9 of the list): contiguous ranges of
   // equal estimated cost, so that the tiles sharing operands stay in one L2 while the eight dies finish
   // together.  A tile costs its depth (K steps of 64, plus a fixed part for prologue and epilogue: the shared
@@ -275,5 +277,9 @@ __device__ __forceinline__ void place_lists(const PlaceArgs& p, const TileCounts
   }
 }
 
+__device__ __forceinline__ void place_lists(const PlaceArgs& p, const TileCounts& tc, int lane, const LaneWidths& lw) {
+  if (p.decode) place_lists_of<true>(p, tc, lane, lw);
+  else place_lists_of<false>(p, tc, lane, lw);
+}
 
 }  // namespace cmoe

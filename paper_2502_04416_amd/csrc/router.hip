@@ -647,7 +647,8 @@ __global__ __launch_bounds__(512) void score_route_kernel(RouterDev r, RouteIO i
 // cold from HBM, so the launch is one memory latency long instead of several.
 constexpr int DEC_SLICES = 8;
 
-template <int NTT, int KSTEPS>
+// (COPY as a template argument: as a test in the loop it cost one token 0.2 us)
+template <int NTT, int KSTEPS, bool COPY>
 __global__ __launch_bounds__(64) void decode_score_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wr,
                                                           int d, int nch, int T, int n_rows, float* __restrict__ pre_g,
                                                           bf16_t* __restrict__ xt) {
@@ -681,8 +682,8 @@ __global__ __launch_bounds__(64) void decode_score_kernel(const bf16_t* __restri
           for (int i = 0; i < 8; ++i) b[i] = (__bf16)0.0f;
         }
         acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks], b, acc[tt], 0, 0, 0);
-        // (the first row block's workgroups also leave the copy [K step][token][32], where one is wanted)
-        if (xt && ok && blockIdx.x == 0)
+        // (the first row block's workgroups also leave the copy [K step of 32][token][32])
+        if (COPY && ok && blockIdx.x == 0)
           *reinterpret_cast<bf16x8_t*>(xt + ((int64_t)(slice * nch * KSTEPS + ch * KSTEPS + ks) * T + col) * 32 + kq * 8) = b;
       }
     }
@@ -1087,7 +1088,9 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
     const bf16_t* xx = static_cast<const bf16_t*>(x);
     const bf16_t* ww = static_cast<const bf16_t*>(e.wr);
     const DecodeK sk = score_k(e.d);
-#define CMOE_SCORE(KS) hipLaunchKernelGGL((decode_score_kernel<1, KS>), grid, block, 0, s, xx, ww, e.d, sk.nch, Ti, n_rows, pre_g, xt)
+#define CMOE_SCORE(KS)                                                                                                                   \
+  if (xt) hipLaunchKernelGGL((decode_score_kernel<1, KS, true>), grid, block, 0, s, xx, ww, e.d, sk.nch, Ti, n_rows, pre_g, xt); \
+  else hipLaunchKernelGGL((decode_score_kernel<1, KS, false>), grid, block, 0, s, xx, ww, e.d, sk.nch, Ti, n_rows, pre_g, xt)
     // (measurement aid: repeat_stage = 6 issues the scoring launch twice; it overwrites its partials)
     for (int rep = tuning().repeat_stage == 6 ? 2 : 1; rep > 0; --rep)
       CMOE_EVEN_KSTEPS(sk.ksteps, CMOE_SCORE)
