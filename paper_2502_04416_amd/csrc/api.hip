@@ -820,13 +820,15 @@ int cmoe_upload(cmoe_layer* L, void* dev_weights, void* hip_stream) {
   return CMOE_OK;
 }
 
-static int run_engine(const Engine& e, const void* x, int64_t T, void* y, int32_t* topk, int32_t* outer,
+static int run_engine(const Engine& layer, const void* x, int64_t T, void* y, int32_t* topk, int32_t* outer,
                       float* scores, int32_t* counts, void* ws, size_t ws_bytes, hipStream_t s,
                       hipEvent_t* ev = nullptr, size_t splitk_cap = ~(size_t)0) {
   if (T < 0) return fail(CMOE_EINVAL, "negative token count");
   if (T == 0) return CMOE_OK;
   if (!x || !y || !ws) return fail(CMOE_EINVAL, "x, y or workspace is null");
-  if (T * (int64_t)e.S_all() > (int64_t)0x7fffffff / 2) return fail(CMOE_EINVAL, "batch too large for 32-bit slot indices");
+  if (T * (int64_t)layer.S_all() > (int64_t)0x7fffffff / 2) return fail(CMOE_EINVAL, "batch too large for 32-bit slot indices");
+  Engine e = layer;
+  bf16_plan_tiles(e, T);
   WsLayout L = ws_layout(e, T, splitk_cap);
   if (ws_bytes < L.total) return fail(CMOE_EINVAL, "workspace too small: %zu bytes given, %zu needed", ws_bytes, L.total);
   if (((uintptr_t)ws & 255) != 0) return fail(CMOE_EINVAL, "workspace must be 256-byte aligned");

@@ -964,7 +964,7 @@ static bool streams_small_batch(const Engine& e, int64_t T) {
   return T * e.S_dyn * e.d <= (e.d <= 2048 || e.d > 5120 ? 26500 : 19000) * (int64_t)(e.G - e.n_always);
 }
 
-static int cfg_index(int which, const Engine& e, int64_t T) {
+static int choose_cfg(int which, const Engine& e, int64_t T) {
   int dflt = 0;
   if (which == 1) dflt = streams_small_batch(e, T) ? (stream_neurons(e, T) == 8 ? 24 : 23) : gate_up_cfg(e, T);
   if (which == 2) {
@@ -1041,6 +1041,19 @@ static int cfg_index(int which, const Engine& e, int64_t T) {
     }
   }
   return dflt;
+}
+
+static int cfg_index(int which, const Engine& e, int64_t T) {
+  if (e.plan_T == T) return which == 1 ? e.plan1 : e.plan2;
+  return choose_cfg(which, e, T);
+}
+
+void bf16_plan_tiles(Engine& e, int64_t T) {
+  e.plan_T = -1;
+  if (e.dtype != 1 || use_simt_experts(e.dtype) || decode_path_ok(e, T)) return;
+  e.plan1 = choose_cfg(1, e, T);
+  e.plan2 = choose_cfg(2, e, T);
+  e.plan_T = T;
 }
 
 bool tiles_gate_up_streams(const Engine& e, int64_t T) {
