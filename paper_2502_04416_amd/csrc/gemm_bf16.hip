@@ -13,6 +13,7 @@
 #include "cmoe_internal.h"
 #include "device_utils.h"
 #include "gemm_device.h"
+#include "lds_limit.h"
 
 namespace cmoe {
 
@@ -1182,30 +1183,26 @@ __global__ __launch_bounds__(256) void splitk_finish_down(const float* __restric
 }
 
 template <typename K>
-static hipError_t launch_kernel(K kern, size_t smem, int threads, bool& attr_done, const GemmArgs& a, hipStream_t s) {
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)smem);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
+static hipError_t launch_kernel(K kern, size_t smem, int threads, LdsLimit& limit, const GemmArgs& a, hipStream_t s) {
+  const hipError_t err = limit.raise(reinterpret_cast<const void*>(kern), smem);
+  if (err != hipSuccess) return err;
   hipLaunchKernelGGL(kern, dim3((unsigned)a.n_blocks * (unsigned)(a.k_split > 1 ? a.k_split : 1)), dim3(threads), smem, s, a);
   return hipGetLastError();
 }
 
 template <int BM, int BN, int BKT, int STAGES, int WGM, int WGN, int MODE, bool DYN = false>
 static hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
-  static bool attr_done = false;
+  static LdsLimit limit;
   constexpr size_t smem = (STAGES == 0 ? 5 * (size_t)(BM > BN ? BM : BN) : STAGES * (size_t)(BM + BN)) * BKT * sizeof(bf16_t);
-  return launch_kernel(grouped_gemm_bf16_dma<BM, BN, BKT, STAGES, WGM, WGN, MODE, DYN>, smem, WGM * WGN * 64, attr_done, a, s);
+  return launch_kernel(grouped_gemm_bf16_dma<BM, BN, BKT, STAGES, WGM, WGN, MODE, DYN>, smem, WGM * WGN * 64, limit, a, s);
 }
 
 template <int BM, int BN, int STAGES, int KU, int WGM, int WGN, int MODE, bool WIDE = false>
 static hipError_t launch_ring(const GemmArgs& a, hipStream_t s) {
-  static bool attr_done = false;
+  static LdsLimit limit;
   constexpr size_t smem = ring_smem_bytes(BM, BN, STAGES * KU, WGM * WGN, WGN, MODE);
   static_assert(smem <= 160 * 1024, "LDS of a CU");
-  return launch_kernel(grouped_gemm_bf16_ring<BM, BN, STAGES, KU, WGM, WGN, MODE, WIDE>, smem, WGM * WGN * 64, attr_done, a, s);
+  return launch_kernel(grouped_gemm_bf16_ring<BM, BN, STAGES, KU, WGM, WGN, MODE, WIDE>, smem, WGM * WGN * 64, limit, a, s);
 }
 
 template <int MODE>

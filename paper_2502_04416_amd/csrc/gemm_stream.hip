@@ -21,6 +21,7 @@
 #include "cmoe_internal.h"
 #include "device_utils.h"
 #include "gemm_device.h"
+#include "lds_limit.h"
 
 namespace cmoe {
 
@@ -328,14 +329,11 @@ hipError_t launch_down_stream(const Engine& e, const GemmArgs& args, hipStream_t
   const auto width = std::minmax_element(e.width_pad_host, e.width_pad_host + e.G);
   const int deep = *width.second / BK + 6, rest = *width.first / BK + 6;
   a.deep_rounds = (deep + rest / 2) / rest;
-  static bool attr_done = false;
+  static LdsLimit limit;
   constexpr size_t smem = (size_t)STAGES * (BM + BN) * BK * sizeof(bf16_t) + 64 * sizeof(TileLane);
   static_assert(2 * smem <= 160 * 1024, "two workgroups on a CU");
-  if (!attr_done) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(down_stream_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
+  const hipError_t err = limit.raise(reinterpret_cast<const void*>(down_stream_kernel), smem);
+  if (err != hipSuccess) return err;
   hipLaunchKernelGGL(down_stream_kernel, dim3((unsigned)std::min(a.n_blocks, 512)), dim3(256), smem, s, a);
   return hipGetLastError();
 }

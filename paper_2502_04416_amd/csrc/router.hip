@@ -10,6 +10,7 @@
 #include "cmoe_internal.h"
 #include "decode_device.h"
 #include "device_utils.h"
+#include "lds_limit.h"
 #include "place_device.h"
 
 namespace cmoe {
@@ -1006,15 +1007,11 @@ static hipError_t launch_score_route(const Engine& e, const RouteIO& io, const v
                                      int32_t* counts, hipStream_t s) {
   constexpr int TB = UPW >= 3 ? 1 : 2, NTOK = TB * 16;
   const size_t smem = sizeof(float) * (size_t)NTOK * (n_slices * (64 + 4) + e.r.n_sw_rows + 1 + LD_SC);
-  static bool attr_done = false;
-  if (!attr_done) {
-    // at most 8 slices (UPW 3, 4) or 2 (UPW 1) and two groups of 64 rows
-    constexpr int most = (int)sizeof(float) * NTOK * ((UPW >= 3 ? 8 : 2) * (64 + 4) + 128 + 1 + LD_SC);
-    const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(score_route_kernel<UPW, TB, ONE>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, most);
-    if (err != hipSuccess) return err;
-    attr_done = true;
-  }
+  // at most 8 slices (UPW 3, 4) or 2 (UPW 1) and two groups of 64 rows
+  constexpr size_t most = sizeof(float) * NTOK * ((UPW >= 3 ? 8 : 2) * (64 + 4) + 128 + 1 + LD_SC);
+  static LdsLimit limit;
+  const hipError_t err = limit.raise(reinterpret_cast<const void*>(score_route_kernel<UPW, TB, ONE>), most);
+  if (err != hipSuccess) return err;
   hipLaunchKernelGGL((score_route_kernel<UPW, TB, ONE>), dim3((unsigned)((T + NTOK - 1) / NTOK)), dim3(512), smem, s, e.r, io,
                      static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(e.wr_tiled), e.d, T, n_slices,
                      e.d / n_slices, counts, e.G);

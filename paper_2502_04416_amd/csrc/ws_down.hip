@@ -24,6 +24,7 @@
 #include <type_traits>
 #include "cmoe_internal.h"
 #include "device_utils.h"
+#include "lds_limit.h"
 
 namespace cmoe {
 
@@ -246,15 +247,12 @@ bool ws_down_handles(int width_pad) { return width_pad == 352 || width_pad == 44
 
 hipError_t launch_ws_down(const Engine& e, char* ws, const WsLayout& L, const void* y_slots, int rc, int n_blocks,
                           int xcd_remap, hipStream_t s) {
-  static bool attr_done = false;
+  static LdsLimit limit;
   constexpr int smem = ws_smem_bytes(22, 2) > ws_smem_bytes(28, 2)
                            ? (ws_smem_bytes(22, 2) > ws_smem_bytes(44, 1) ? ws_smem_bytes(22, 2) : ws_smem_bytes(44, 1))
                            : (ws_smem_bytes(28, 2) > ws_smem_bytes(44, 1) ? ws_smem_bytes(28, 2) : ws_smem_bytes(44, 1));
-  if (!attr_done) {
-    hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(ws_down_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (err != hipSuccess) return err;
-    attr_done = true;
-  }
+  const hipError_t err = limit.raise(reinterpret_cast<const void*>(ws_down_kernel), smem);
+  if (err != hipSuccess) return err;
   WsArgs a;
   a.H = reinterpret_cast<const bf16_t*>(ws + L.h);
   a.W2 = static_cast<const bf16_t*>(e.w2);

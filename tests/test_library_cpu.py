@@ -2,6 +2,7 @@
 header declares, and its argument checks turn bad input into error codes (never a crash)."""
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -9,6 +10,7 @@ import pytest
 from paper_2502_04416_amd import binding, synth
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2502_04416_amd", "csrc")
 
 
 @pytest.fixture(scope="module")
@@ -166,3 +168,48 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=120)
     assert r.returncode == 2
     assert "ONE GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_lds_limit_is_raised_on_every_device(tmp_path):
+    """The limit of dynamic LDS belongs to a kernel's copy on one device: the first launch on each raises it, one that failed is
+    tried again, and host threads may race for it.  (The two runtime calls are stand-ins that record.)"""
+    src = tmp_path / "limit.cpp"
+    src.write_text(r'''
+#include "lds_limit.h"
+#include <cassert>
+#include <thread>
+#include <vector>
+static thread_local int device = 0;
+static std::atomic<int> calls[80];
+static std::atomic<bool> refuse{false};
+extern "C" hipError_t hipGetDevice(int* d) { *d = device; return hipSuccess; }
+extern "C" hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) {
+  ++calls[device];
+  return refuse ? hipErrorInvalidValue : hipSuccess;
+}
+int main() {
+  cmoe::LdsLimit a, b;
+  int kernel = 0;
+  for (int rep = 0; rep < 3; ++rep)
+    for (device = 0; device < 70; ++device) assert(a.raise(&kernel, 100000) == hipSuccess);
+  for (int d = 0; d < 70; ++d) assert(calls[d] == (d < 64 ? 1 : 3));
+  device = 5;
+  refuse = true;
+  assert(b.raise(&kernel, 100000) != hipSuccess && calls[5] == 2);
+  refuse = false;
+  assert(b.raise(&kernel, 100000) == hipSuccess && b.raise(&kernel, 100000) == hipSuccess && calls[5] == 3);
+  cmoe::LdsLimit c;
+  std::vector<std::thread> threads;
+  for (int i = 0; i < 16; ++i)
+    threads.emplace_back([&, i] { device = i % 4 + 72; c.raise(&kernel, 1); device = i % 4; for (int k = 0; k < 100; ++k) c.raise(&kernel, 1); });
+  for (auto& t : threads) t.join();
+  for (int d = 0; d < 4; ++d) assert(calls[d] >= 2 && calls[d] <= 5);
+  return 0;
+}
+''')
+    exe = tmp_path / "limit"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + CSRC, str(src), "-o", str(exe),
+                    "-lpthread"], check=True)
+    subprocess.run([str(exe)], check=True)
+    callers = {f for f in os.listdir(CSRC) if "hipFuncSetAttribute" in open(os.path.join(CSRC, f)).read()}
+    assert callers == {"lds_limit.h", "profile.hip"}             # (the latter sets it before its launch every time)
