@@ -297,6 +297,18 @@ int cmoe_probe_hbm(size_t bytes, int reps, double* gbytes_per_s);
  * (6: the scoring launch of a batch of at most 16 tokens twice).  0 restores the plain forward.  CMOE_EINVAL on an unknown name. */
 int cmoe_set_tuning(const char* name, int value);
 
+/* Which kernels a forward of T tokens runs under the present tuning switches: plan[0] and plan[1] the gate/up contraction's
+ * kernel (CMOE_PLAN_*) and shape, plan[2] and plan[3] the down contraction's.  Host code alone; a layer need not be uploaded.
+ * dense != 0 asks for the un-restructured FFN.  For tests and measurements; the choice may change with the library. */
+#define CMOE_PLAN_TILES      0   /* a workgroup per tile; shape: index of the tile shape (CMOE_GEMM1_CFG, CMOE_GEMM2_CFG) */
+#define CMOE_PLAN_UNITS      1   /* weight-streaming decode units; shape: neurons (gate/up) or columns (down) per unit */
+#define CMOE_PLAN_STREAMED   2   /* streamed gate/up units; shape: neurons per unit */
+#define CMOE_PLAN_PERSISTENT 3   /* the persistent down contraction; shape: index of the tile shape */
+#define CMOE_PLAN_FMA        4   /* fp32 arithmetic; shape: rows of a tile */
+#define CMOE_PLAN_COMBINES   5   /* down contraction and weighted sum over slots in one launch; shape: columns per workgroup */
+int cmoe_forward_plan(const cmoe_layer* layer, int dense, int64_t T, int32_t plan[4]);
+int cmoe_hier_forward_plan(const cmoe_hier* h, int dense, int64_t T, int32_t plan[4]);
+
 const char* cmoe_last_error(void);   /* thread-local, never NULL */
 const char* cmoe_version(void);
 

@@ -41,6 +41,7 @@ EXPORTS = [
     "cmoe_balanced_assignment", "cmoe_probe_mfma", "cmoe_probe_hbm", "cmoe_get_gate_params", "cmoe_update_bias",
     "cmoe_build_gpu", "cmoe_profile_activations", "cmoe_set_baseline", "cmoe_hier_build", "cmoe_hier_expert",
     "cmoe_set_tuning", "cmoe_set_neuron_sparsity", "cmoe_forward_static", "cmoe_static_scratch_bytes", "cmoe_forward_static_max_tokens",
+    "cmoe_forward_plan", "cmoe_hier_forward_plan",
 ]
 
 
@@ -104,6 +105,8 @@ def load():
     lib.cmoe_static_scratch_bytes.restype = sz
     lib.cmoe_forward_static_max_tokens.argtypes = [vp]
     lib.cmoe_forward_static_max_tokens.restype = i64
+    lib.cmoe_forward_plan.argtypes = [vp, C.c_int, i64, i32p]
+    lib.cmoe_hier_forward_plan.argtypes = [vp, C.c_int, i64, i32p]
     lib.cmoe_last_error.restype = C.c_char_p
     lib.cmoe_version.restype = C.c_char_p
     _lib = lib
@@ -324,6 +327,17 @@ def cmoe_set_tuning(name: str, value: int) -> None:
     _check(load().cmoe_set_tuning(name.encode(), int(value)), "cmoe_set_tuning")
 
 
+PLAN_KERNELS = ("tiles", "units", "streamed", "persistent", "fma", "combines")
+
+
+def cmoe_forward_plan(layer: int, T: int, dense: bool = False, hier: bool = False) -> Dict[str, tuple]:
+    """{"gate_up": (kernel, shape), "down": (kernel, shape)} of a forward of T tokens (kernels: PLAN_KERNELS)."""
+    p = (C.c_int32 * 4)()
+    fn = load().cmoe_hier_forward_plan if hier else load().cmoe_forward_plan
+    _check(fn(layer, int(dense), T, p), "cmoe_forward_plan")
+    return {"gate_up": (PLAN_KERNELS[p[0]], p[1]), "down": (PLAN_KERNELS[p[2]], p[3])}
+
+
 def cmoe_hier_packed_bytes(h: int) -> int:
     return load().cmoe_hier_packed_bytes(h)
 
@@ -430,6 +444,9 @@ class Layer(_DeviceMixin):
     def _ws_bytes(self, T):
         return cmoe_workspace_bytes(self.h, T)
 
+    def forward_plan(self, T: int, dense: bool = False):
+        return cmoe_forward_plan(self.h, T, dense)
+
     def export_partition(self):
         return cmoe_export_partition(self.h, self.cfg.d_ff, self.cfg.n_routed)
 
@@ -528,6 +545,9 @@ class Hierarchy(_DeviceMixin):
         h = cmoe_hier_build(make_config(cfg, kmeans_iters, dist_mode, score_mode), outer_top_k, w_gate, w_up, w_down,
                             w_router, logit_offset, calib_x, min_tokens, on_gpu, with_baseline)
         return cls([], outer_top_k, None, None, handle=h, cfg=cfg)
+
+    def forward_plan(self, T: int, dense: bool = False):
+        return cmoe_forward_plan(self.h, T, dense, hier=True)
 
     def expert_partition(self, e: int):
         """Partition of outer expert e plus the calibration-token counts of cmoe_hier_build."""

@@ -1333,6 +1333,37 @@ int cmoe_set_tuning(const char* name, int value) {
   return fail(CMOE_EINVAL, "unknown tuning switch '%s'", name);
 }
 
+static int engine_plan(const Engine& engine, int64_t T, int32_t* plan) {
+  if (!plan) return fail(CMOE_EINVAL, "plan is null");
+  if (T < 1) return fail(CMOE_EINVAL, "need at least one token");
+  Engine e = engine;
+  bf16_plan_tiles(e, T);
+  auto set = [&](int which, int kernel, int shape) { plan[2 * which] = kernel; plan[2 * which + 1] = shape; };
+  if (use_simt_experts(e.dtype)) {
+    set(0, CMOE_PLAN_FMA, gemm_tile(e, T, 1));
+    set(1, CMOE_PLAN_FMA, gemm_tile(e, T, 2));
+    return CMOE_OK;
+  }
+  const bool units = decode_path_ok(e, T);
+  if (units) set(0, decode_gate_up_streams(e, T) ? CMOE_PLAN_STREAMED : CMOE_PLAN_UNITS, decode_unit_neurons(e, T));
+  else if (tiles_gate_up_streams(e, T)) set(0, CMOE_PLAN_STREAMED, gemm_tile(e, T, 3) / 2);
+  else set(0, CMOE_PLAN_TILES, bf16_shape(1, e, T));
+  if (decode_fuses_combine(e, T)) set(1, CMOE_PLAN_COMBINES, 16);
+  else if (units) set(1, CMOE_PLAN_UNITS, 16);
+  else set(1, gemm_tile(e, T, 7) > 0 ? CMOE_PLAN_PERSISTENT : CMOE_PLAN_TILES, bf16_shape(2, e, T));
+  return CMOE_OK;
+}
+
+int cmoe_forward_plan(const cmoe_layer* L, int dense, int64_t T, int32_t plan[4]) {
+  if (!L) return fail(CMOE_EINVAL, "layer is null");
+  return engine_plan(dense ? L->e_dense : L->e_moe, T, plan);
+}
+
+int cmoe_hier_forward_plan(const cmoe_hier* H, int dense, int64_t T, int32_t plan[4]) {
+  if (!H) return fail(CMOE_EINVAL, "hierarchy is null");
+  return engine_plan(dense ? H->e_dense : H->e_moe, T, plan);
+}
+
 const char* cmoe_last_error(void) { return g_err.c_str(); }
 const char* cmoe_version(void) { return "cmoe 0.1 (gfx950)"; }
 

@@ -210,6 +210,7 @@ bool use_simt_experts(int dtype);
 // dozen times (d = 512, 8 experts, 64 tokens: 27.5 -> 26.1 us per forward, bound by the host; 300 tokens 30.6 -> 28.6).
 void bf16_plan_tiles(Engine& e, int64_t T);
 int bf16_gemm_tile(int which, const Engine& e, int64_t T);
+int bf16_shape(int which, const Engine& e, int64_t T);     // index in the table of tile shapes
 // K split of the bf16 contractions at small batches (1 = none) and the bytes of fp32 partial sums it needs.
 int bf16_splitk(const Engine& e, int64_t T, int which);
 size_t bf16_splitk_bytes(const Engine& e, int64_t T);
@@ -236,6 +237,7 @@ hipError_t launch_decode_down_sparse(const Engine& e, int64_t T, char* ws, const
 hipError_t launch_mask_hidden(const Engine& e, int64_t T, char* ws, const WsLayout& L, hipStream_t s);
 hipError_t launch_experts_decode(const Engine& e, const void* x, int64_t T, char* ws, const WsLayout& L, void* y,
                                  hipStream_t s, int stage);
+int decode_unit_neurons(const Engine& e, int64_t T);       // neurons per gate/up unit of a decode batch (16 or 8)
 // Gate/up contraction of batches of 2 to STREAM_ROWS tokens by streamed units (gate_up_stream.hip): of a decode batch, and as
 // a tile shape of its own.
 constexpr int STREAM_ROWS = 64;

@@ -502,7 +502,5 @@ static_assert(decode_widths_covered(), "a model width without its step count");
 DecArgs make_dec_args(const Engine& e, const void* x, int64_t T, char* ws, const WsLayout& L, void* y);
 // The same for the streamed units (gate_up_stream.hip): tokens as the scorer of the front end laid them out, if it did.
 DecArgs make_stream_args(const Engine& e, const void* x, int64_t T, char* ws, const WsLayout& L);
-// Neurons per gate/up unit of the decode kernels for this batch (16, or 8 when that fills the chip better).
-int decode_unit_neurons(const Engine& e, int64_t T);
 
 }  // namespace cmoe

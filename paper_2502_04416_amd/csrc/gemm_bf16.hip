@@ -1049,6 +1049,8 @@ static int cfg_index(int which, const Engine& e, int64_t T) {
   return choose_cfg(which, e, T);
 }
 
+int bf16_shape(int which, const Engine& e, int64_t T) { return cfg_index(which, e, T); }
+
 void bf16_plan_tiles(Engine& e, int64_t T) {
   e.plan_T = -1;
   if (e.dtype != 1 || use_simt_experts(e.dtype) || decode_path_ok(e, T)) return;

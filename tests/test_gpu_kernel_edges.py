@@ -186,12 +186,20 @@ def test_decode_kernels_at_other_widths(binding, d, T, m):
 @pytest.mark.parametrize("d", list(range(512, 4097, 512)) + [5120, 6144, 7680, 8192, 10240])
 def test_every_decode_width(binding, d):
     """Every model width that the weight-streaming kernels serve; the widths above 4096, whose K slice takes several runs,
-    up to four tokens (five take the tile kernels)."""
+    up to four tokens (five choose between streamed units and tiles: both)."""
     for T in (1, 4, 5):
         cfg, weights, part, x, layer = _case(binding, d, 8, 40, 1, 2, T, seed=4)
         out = layer.forward(x)
         check_flat(cfg, weights, part, x, out)
         check_dense(cfg, weights, x, layer.dense_forward(x))
+        if d > 4096 and T == 5:
+            try:
+                for shape, kernel in ((7, "tiles"), (24, "streamed")):
+                    binding.cmoe_set_tuning("CMOE_GEMM1_CFG", shape)
+                    assert layer.forward_plan(T)["gate_up"][0] == kernel
+                    check_flat(cfg, weights, part, x, layer.forward(x))
+            finally:
+                binding.cmoe_set_tuning("CMOE_GEMM1_CFG", -1)
         layer.close()
 
 
@@ -242,8 +250,10 @@ def test_persistent_down_contraction(binding, d, N, m, n_s, k, T, remap):
         binding.cmoe_set_tuning("CMOE_SPLITK", 0)
         binding.cmoe_set_tuning("CMOE_XCD_REMAP", remap)
         binding.cmoe_set_tuning("CMOE_GEMM2_CFG", 8)
+        assert layer.forward_plan(T)["down"] == ("tiles", 8)
         ref = layer.forward(x)
         binding.cmoe_set_tuning("CMOE_GEMM2_CFG", 22)
+        assert layer.forward_plan(T)["down"] == ("persistent", 22)
         out = layer.forward(x)
     finally:
         binding.cmoe_set_tuning("CMOE_GEMM2_CFG", -1)
@@ -264,8 +274,9 @@ def test_persistent_down_contraction_many_tiles(binding):
     x = torch.randn((T, 4096), generator=torch.Generator(device="cuda").manual_seed(5), device="cuda", dtype=torch.bfloat16)
     y = {}
     try:
-        for shape in (8, 22):
+        for shape, kernel in ((8, "tiles"), (22, "persistent")):
             binding.cmoe_set_tuning("CMOE_GEMM2_CFG", shape)
+            assert layer.forward_plan(T)["down"] == (kernel, shape)
             y[shape] = torch.empty_like(x)
             layer.forward_device(x, y[shape])
     finally:
@@ -279,7 +290,8 @@ def test_persistent_down_contraction_many_tiles(binding):
     (64, 8, 40, 1, 2, 17),         # fewer chunks of K than waves; one row past a tile
     (328, 12, 50, 2, 3, 100),      # K = 20.5 chunks, columns that end inside a tile
     (640, 8, 136, 1, 1, 48),       # K of more than one batch of loads
-    (512, 12, 64, 1, 2, 690),      # as many entries as the placement counts by itself, over several tiles of tokens
+    (512, 12, 64, 1, 2, 1024),     # as many entries as the placement counts by itself, over several tiles of tokens
+    (512, 12, 64, 1, 2, 1025),     # one token more: the histogram of a launch of its own
     (512, 12, 64, 1, 3, 1500),     # batches of the large tiles
 ])
 def test_fp32_tiles(binding, d, N, m, n_s, k, T):
@@ -304,7 +316,9 @@ def test_fp32_tiles(binding, d, N, m, n_s, k, T):
 @pytest.mark.parametrize("d,N,m,n_s,k,T", [
     (512, 8, 100, 1, 2, 2),        # one chunk of K per wave, padded widths, two tokens
     (2560, 8, 64, 1, 2, 16),       # an odd number of chunks; a full token tile
-    (1024, 8, 64, 0, 3, 17),       # one chunk of four steps, no always-on group, one row past a token tile
+    (1024, 8, 64, 1, 2, 16),       # one chunk of four steps
+    (1024, 8, 64, 1, 2, 40),       # ... of four or two with four token tiles
+    (1024, 8, 64, 0, 3, 17),       # two chunks of two, no always-on group, one row past a token tile
     (1536, 6, 50, 2, 1, 33),       # three chunks of two; four token tiles, the third with one row
     (2048, 4, 96, 1, 3, 64),       # the largest batch, routed groups of two to four token tiles
     (5632, 8, 40, 1, 2, 5),        # a width without decode kernels
@@ -322,6 +336,7 @@ def test_streamed_gate_up(binding, d, N, m, n_s, k, T):
                 binding.cmoe_set_tuning("CMOE_FRONT_SHARED", shared)
                 binding.cmoe_set_tuning("CMOE_DECODE_SPLIT", split)
                 binding.cmoe_set_tuning("CMOE_GEMM1_CFG", shape)
+                assert layer.forward_plan(T)["gate_up"] == ("streamed", split)
                 outs.append(layer.forward(x))
     finally:
         for name, value in (("CMOE_FRONT_SHARED", 1), ("CMOE_DECODE_SPLIT", -1), ("CMOE_GEMM1_CFG", -1)):

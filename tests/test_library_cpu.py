@@ -213,3 +213,23 @@ int main() {
     subprocess.run([str(exe)], check=True)
     callers = {f for f in os.listdir(CSRC) if "hipFuncSetAttribute" in open(os.path.join(CSRC, f)).read()}
     assert callers == {"lds_limit.h", "profile.hip"}             # (the latter sets it before its launch every time)
+
+
+def test_forward_plan(lib):
+    """The query names the kernels of a batch on the host, and follows the switches."""
+    cfg = synth.scaled(synth.CONFIGS[1], d_model=512, d_ff=8 * 100, n_experts=8, n_shared=1, top_k=2)
+    part = synth.trivial_partition(cfg)
+    layer = binding.Layer.from_partition(cfg, *synth.make_weights(cfg), part["neuron_order"], part["rep_neuron"], upload=False)
+    try:
+        assert layer.forward_plan(1)["down"] == ("combines", 16)
+        binding.cmoe_set_tuning("CMOE_GEMM1_CFG", 6)
+        for shape, kernel in ((8, "tiles"), (22, "persistent")):
+            binding.cmoe_set_tuning("CMOE_GEMM2_CFG", shape)
+            assert layer.forward_plan(300) == {"gate_up": ("tiles", 6), "down": (kernel, shape)}
+            assert layer.forward_plan(300, dense=True)["down"][0] == "tiles"      # (no work list: a forced 22 is refused)
+    finally:
+        binding.cmoe_set_tuning("CMOE_GEMM1_CFG", -1)
+        binding.cmoe_set_tuning("CMOE_GEMM2_CFG", -1)
+    with pytest.raises(binding.CmoeError):
+        layer.forward_plan(0)
+    layer.close()
