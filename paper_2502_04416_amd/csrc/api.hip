@@ -50,7 +50,8 @@ static const TuningField kTuningFields[] = {
     {"CMOE_SKIP_ROWS", &Tuning::skip_rows},     {"CMOE_DECODE_SPLIT", &Tuning::decode_split},
     {"CMOE_WS_DOWN", &Tuning::ws_down},         {"CMOE_SKIP_STAGE", &Tuning::skip_stage},
     {"CMOE_REPEAT_STAGE", &Tuning::repeat_stage}, {"CMOE_FRONT_ALL", &Tuning::front_all},
-    {"CMOE_FRONT_TILE", &Tuning::front_tile},
+    {"CMOE_FRONT_TILE", &Tuning::front_tile},   {"CMOE_F32_ROWS1", &Tuning::f32_rows1},
+    {"CMOE_F32_ROWS2", &Tuning::f32_rows2},
 };
 
 Tuning& tuning() {
@@ -115,6 +116,8 @@ bool use_simt_experts(int dtype) { return dtype != CMOE_BF16 || tuning().force_s
 int gemm_tile(const Engine& e, int64_t T, int which) {
   return use_simt_experts(e.dtype) ? simt_gemm_tile(which, e, T) : bf16_gemm_tile(which, e, T);
 }
+
+void plan_tiles(Engine& e, int64_t T) { use_simt_experts(e.dtype) ? simt_plan_tiles(e, T) : bf16_plan_tiles(e, T); }
 
 int64_t gemm_work_bound(const Engine& e, int64_t T, int which) {
   const int bm = gemm_tile(e, T, which == 1 ? 1 : 2);
@@ -828,7 +831,7 @@ static int run_engine(const Engine& layer, const void* x, int64_t T, void* y, in
   if (!x || !y || !ws) return fail(CMOE_EINVAL, "x, y or workspace is null");
   if (T * (int64_t)layer.S_all() > (int64_t)0x7fffffff / 2) return fail(CMOE_EINVAL, "batch too large for 32-bit slot indices");
   Engine e = layer;
-  bf16_plan_tiles(e, T);
+  plan_tiles(e, T);
   WsLayout L = ws_layout(e, T, splitk_cap);
   if (ws_bytes < L.total) return fail(CMOE_EINVAL, "workspace too small: %zu bytes given, %zu needed", ws_bytes, L.total);
   if (((uintptr_t)ws & 255) != 0) return fail(CMOE_EINVAL, "workspace must be 256-byte aligned");
@@ -1337,7 +1340,7 @@ static int engine_plan(const Engine& engine, int64_t T, int32_t* plan) {
   if (!plan) return fail(CMOE_EINVAL, "plan is null");
   if (T < 1) return fail(CMOE_EINVAL, "need at least one token");
   Engine e = engine;
-  bf16_plan_tiles(e, T);
+  plan_tiles(e, T);
   auto set = [&](int which, int kernel, int shape) { plan[2 * which] = kernel; plan[2 * which + 1] = shape; };
   if (use_simt_experts(e.dtype)) {
     set(0, CMOE_PLAN_FMA, gemm_tile(e, T, 1));

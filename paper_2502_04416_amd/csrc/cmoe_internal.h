@@ -155,6 +155,8 @@ struct Tuning {
                            // more than the launch it saves: 35.0 against 29.6 us at 2 tokens, 59.3 against 55.8 us
                            // at 16, 16 experts of 688)
   int force_simt = 0;      // 1: bf16 layers run the plain FMA kernels
+  int f32_rows1 = -1;      // rows of a tile of the fp32 gate/up contraction, 16 or 64; -1: per batch
+  int f32_rows2 = -1;      // same for the down contraction
   int ldpad = 0;           // extra elements in the row stride of a row-major (fp32) packed gate/up matrix
   int host_threads = 0;    // worker threads of the host-side construction (0: hardware threads, at most 16)
   int skip_rows = 1;       // 0: the gate/up contraction multiplies the 32-row blocks past the end of a segment too
@@ -208,7 +210,9 @@ int gemm_tile(const Engine& e, int64_t T, int which);
 bool use_simt_experts(int dtype);
 // Choose both tile shapes once for a forward: the models behind the choice run on the host, and placement and launches ask a
 // dozen times (d = 512, 8 experts, 64 tokens: 27.5 -> 26.1 us per forward, bound by the host; 300 tokens 30.6 -> 28.6).
+void plan_tiles(Engine& e, int64_t T);
 void bf16_plan_tiles(Engine& e, int64_t T);
+void simt_plan_tiles(Engine& e, int64_t T);
 int bf16_gemm_tile(int which, const Engine& e, int64_t T);
 int bf16_shape(int which, const Engine& e, int64_t T);     // index in the table of tile shapes
 // K split of the bf16 contractions at small batches (1 = none) and the bytes of fp32 partial sums it needs.

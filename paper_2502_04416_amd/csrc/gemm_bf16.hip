@@ -1053,7 +1053,7 @@ int bf16_shape(int which, const Engine& e, int64_t T) { return cfg_index(which, 
 
 void bf16_plan_tiles(Engine& e, int64_t T) {
   e.plan_T = -1;
-  if (e.dtype != 1 || use_simt_experts(e.dtype) || decode_path_ok(e, T)) return;
+  if (decode_path_ok(e, T)) return;
   e.plan1 = choose_cfg(1, e, T);
   e.plan2 = choose_cfg(2, e, T);
   e.plan_T = T;

@@ -279,20 +279,43 @@ __global__ __launch_bounds__(256) void grouped_gemm_f32(SimtArgs<float> p) {
   }
 }
 
-// Which kernel an fp32 batch runs.  The small tiles read three times the operands of the large ones per product: up to 4096 of
-// them (down contraction, estimated) they win (12 experts of 128, d = 512, 512 tokens, 2128 tiles: 86 -> 54 us per forward; 8
-// experts of 512, d = 1024, 512 tokens, 3168: 152 -> 138), beyond the others do (the former at 4096 tokens: 186 against 231).
-static bool f32_small(const Engine& e, int64_t T) {
+// Which kernel contraction `which` of an fp32 batch runs.  While the large tiles leave the chip idle, their launch is as long as one
+// tile's chain of K steps of 64, 5.2 us each; that is what some 3500 of the small tiles take per step (a rate of 0.7 of the large
+// ones' on a full chip).  The small tiles' launch costs about 1.6 us more to start, which counts where K is short.  The two
+// contractions differ in tiles, so each decides for itself.  us per forward, gate/up + down in tiles of 64 + 64 rows / 64 + 16 / 16
+// + 16: dense, d = 256, d_ff = 1024 at 512 tokens (gate/up 2048 small tiles, down 256) 113 / 34.1 / 26.9, 1024 tokens 113 / 40.6 /
+// 44.2, 4096 tokens 157 / 124 / 157; d = d_ff = 256, 8192 tokens 63.9 / 66.1 / 80.9; d = 1024, d_ff = 4096, 128 tokens 432 / 115 /
+// 91, 2048 tokens 812 / 897 / 1145; 12 experts of 128, d = 512, 1024 tokens 90.7 / 89.0 / 78.5, 4096 tokens 193 / 215 / 230.
+static bool choose_f32_small(const Engine& e, int64_t T, int which) {
   if (e.dtype == 1) return false;
-  const int64_t entries = T * e.S_dyn, touched = std::min<int64_t>(e.G - e.n_always, entries);
-  const int64_t rows = e.n_always * ((T + FM - 1) / FM) + entries / FM + touched / 2;
-  return rows * cdiv(e.d, FN) <= 4096;
+  const int forced = which == 1 ? tuning().f32_rows1 : tuning().f32_rows2;
+  if (forced == FM || forced == SB) return forced == FM;
+  // K steps of a row of small tiles of group g, and of one tile
+  auto row_steps = [&](int g) { return which == 1 ? (int64_t)(e.width_pad_host[g] / 16) * cdiv(e.d, SK) : (int64_t)cdiv(e.d, FN) * cdiv(e.width_pad_host[g], SK); };
+  int64_t chain = cdiv(e.d, SK), always = 0, routed = 0;
+  if (which == 2) chain = cdiv(*std::max_element(e.width_pad_host, e.width_pad_host + e.G), SK);
+  for (int g = 0; g < e.G; ++g) (g < e.n_always ? always : routed) += row_steps(g);
+  const int64_t groups = e.G - e.n_always, entries = T * e.S_dyn, touched = std::min<int64_t>(groups, entries);
+  int64_t steps = always * ((T + FM - 1) / FM);
+  if (groups > 0) steps += (entries / FM + touched / 2) * routed / groups;
+  return steps <= 3500 * chain - 1100;
+}
+
+static bool f32_small(const Engine& e, int64_t T, int which) {
+  if (e.plan_T == T) return (which == 1 ? e.plan1 : e.plan2) != 0;
+  return choose_f32_small(e, T, which);
+}
+
+void simt_plan_tiles(Engine& e, int64_t T) {
+  e.plan1 = choose_f32_small(e, T, 1) ? 1 : 0;
+  e.plan2 = choose_f32_small(e, T, 2) ? 1 : 0;
+  e.plan_T = T;
 }
 
 template <int MODE>
 static hipError_t launch_simt(const Engine& e, int64_t T, const SimtArgs<float>& a, int64_t n, hipStream_t s) {
   const dim3 grid((unsigned)n), block(256);
-  if (!f32_small(e, T)) hipLaunchKernelGGL((grouped_gemm_simt<float, MODE>), grid, block, 0, s, a);
+  if (!f32_small(e, T, MODE)) hipLaunchKernelGGL((grouped_gemm_simt<float, MODE>), grid, block, 0, s, a);
   else if (a.vec) hipLaunchKernelGGL((grouped_gemm_f32<MODE, true>), grid, block, 0, s, a);
   else hipLaunchKernelGGL((grouped_gemm_f32<MODE, false>), grid, block, 0, s, a);
   return hipGetLastError();
@@ -345,7 +368,7 @@ hipError_t launch_experts_simt(const Engine& e, const void* x, int64_t T, char* 
 // which as in bf16_gemm_tile (no tiles of dynamic height and no persistent kernel here)
 int simt_gemm_tile(int which, const Engine& e, int64_t T) {
   if (which >= 5) return 0;
-  return !f32_small(e, T) ? SB : which <= 2 ? FM : FN;
+  return !f32_small(e, T, which == 1 || which == 3 ? 1 : 2) ? SB : which <= 2 ? FM : FN;
 }
 
 }  // namespace cmoe

@@ -310,6 +310,16 @@ def test_fp32_tiles(binding, d, N, m, n_s, k, T):
     y = torch.empty((T, d), device="cuda")
     layer.forward_device(xu, y)
     assert np.array_equal(y.cpu().numpy(), out["y"])             # the same sums in the same order
+    try:                                                         # either kernel for either contraction, whatever the rule takes
+        for rows in ((16, 64), (64, 16), (16, 16), (64, 64)):
+            binding.cmoe_set_tuning("CMOE_F32_ROWS1", rows[0])
+            binding.cmoe_set_tuning("CMOE_F32_ROWS2", rows[1])
+            assert layer.forward_plan(T) == {"gate_up": ("fma", rows[0]), "down": ("fma", rows[1])}
+            check_flat(cfg, weights, part, x, layer.forward(x))
+            check_dense(cfg, weights, x, layer.dense_forward(x))
+    finally:
+        binding.cmoe_set_tuning("CMOE_F32_ROWS1", -1)
+        binding.cmoe_set_tuning("CMOE_F32_ROWS2", -1)
     layer.close()
 
 

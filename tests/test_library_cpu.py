@@ -233,3 +233,20 @@ def test_forward_plan(lib):
     with pytest.raises(binding.CmoeError):
         layer.forward_plan(0)
     layer.close()
+
+
+@pytest.mark.parametrize("d,d_ff,T,dense,gate_up,down", [
+    (256, 1024, 64, True, 16, 16),
+    (256, 1024, 4096, True, 64, 16),      # the gate/up contraction fills the chip with large tiles long before the down does
+    (256, 1024, 8192, True, 64, 64),
+    (64, 1024, 16384, True, 64, 16),
+    (1024, 4096, 2048, True, 64, 64),
+    (64, 8192, 4096, False, 64, 16),
+    (512, 1536, 64, False, 16, 16),
+])
+def test_fp32_tiles_chosen_per_contraction(lib, d, d_ff, T, dense, gate_up, down):
+    cfg = synth.scaled(synth.CONFIGS[0], d_model=d, d_ff=d_ff, n_experts=8, n_shared=2, top_k=2)
+    part = synth.trivial_partition(cfg)
+    layer = binding.Layer.from_partition(cfg, *synth.make_weights(cfg), part["neuron_order"], part["rep_neuron"], upload=False)
+    assert layer.forward_plan(T, dense) == {"gate_up": ("fma", gate_up), "down": ("fma", down)}
+    layer.close()
