@@ -304,7 +304,7 @@ int cmoe_set_tuning(const char* name, int value);
 #define CMOE_PLAN_TILES      0   /* a workgroup per tile; shape: index of the tile shape (CMOE_GEMM1_CFG, CMOE_GEMM2_CFG) */
 #define CMOE_PLAN_UNITS      1   /* weight-streaming decode units; shape: neurons (gate/up) or columns (down) per unit */
 #define CMOE_PLAN_STREAMED   2   /* streamed gate/up units; shape: neurons per unit */
-#define CMOE_PLAN_PERSISTENT 3   /* the persistent down contraction; shape: index of the tile shape */
+#define CMOE_PLAN_PERSISTENT 3   /* the persistent down contraction; shape: 1 if it stores past the caches */
 #define CMOE_PLAN_FMA        4   /* fp32 arithmetic; shape: rows of a tile */
 #define CMOE_PLAN_COMBINES   5   /* down contraction and weighted sum over slots in one launch; shape: columns per workgroup */
 int cmoe_forward_plan(const cmoe_layer* layer, int dense, int64_t T, int32_t plan[4]);

@@ -1353,7 +1353,8 @@ static int engine_plan(const Engine& engine, int64_t T, int32_t* plan) {
   else set(0, CMOE_PLAN_TILES, bf16_shape(1, e, T));
   if (decode_fuses_combine(e, T)) set(1, CMOE_PLAN_COMBINES, 16);
   else if (units) set(1, CMOE_PLAN_UNITS, 16);
-  else set(1, gemm_tile(e, T, 7) > 0 ? CMOE_PLAN_PERSISTENT : CMOE_PLAN_TILES, bf16_shape(2, e, T));
+  else if (gemm_tile(e, T, 7) > 0) set(1, CMOE_PLAN_PERSISTENT, down_stream_past_caches(e, T) ? 1 : 0);
+  else set(1, CMOE_PLAN_TILES, bf16_shape(2, e, T));
   return CMOE_OK;
 }
 

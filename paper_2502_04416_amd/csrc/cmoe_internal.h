@@ -214,6 +214,7 @@ void plan_tiles(Engine& e, int64_t T);
 void bf16_plan_tiles(Engine& e, int64_t T);
 void simt_plan_tiles(Engine& e, int64_t T);
 int bf16_gemm_tile(int which, const Engine& e, int64_t T);
+bool down_stream_past_caches(const Engine& e, int64_t T);   // the persistent down contraction's results
 int bf16_shape(int which, const Engine& e, int64_t T);     // index in the table of tile shapes
 // K split of the bf16 contractions at small batches (1 = none) and the bytes of fp32 partial sums it needs.
 int bf16_splitk(const Engine& e, int64_t T, int which);

@@ -8,14 +8,12 @@
 //     tiles a workgroup does nothing but convert and store, while the CU's other one multiplies.
 //   * Results go from the registers to memory: the weight rows are dealt to the MFMA's columns such that a lane holds
 //     eight consecutive output columns and a store covers 256 bytes of each of four rows.  (16 rows of 64 bytes per store
-//     are written at 34 GB/s per CU, 4 rows of 256 at 90; the operands swapped, which gives the former: 282 us.)
-//   * The stores are non-temporal: in the L2 they would push out the operands (8192 tokens, seven slots: the launch 270 us
-//     with plain stores, 200 without any, 200 with these), and by the time they are read most are gone from every
-//     cache anyway.  The combine kernel reads them the same way.
-// Forwards, 128x256 tiles of the other kernel (two per CU, a workgroup per tile) -> this one, with the combine kernel's
-// loads: 2048 tokens of the 16-expert layer 211 -> 204 us, 4096 of the 32-expert layer with four shared 472 -> 460, 8192 of the
-// 32-expert layer 773 -> 732, 4096 of the hierarchy 1556 -> 1552 (its K loops are long, and its time is theirs).
-// 256x256 tiles, one workgroup per CU: 726, but 484 and 1570.
+//     are written at 34 GB/s per CU, 4 rows of 256 at 90.)
+//   * The stores go through the caches, where the combine kernel finds what the last level could hold, unless all results
+//     together are about as small as the L2s (SLOTS_NT_BYTES): then they are non-temporal.
+// Launches, 128x256 tiles of the other kernel (two per CU, a workgroup per tile) -> this one: 2048 tokens of the 16-expert
+// layer 73.8 -> 71.1 us, 4096 of the 32-expert layer with four shared 152 -> 144, 8192 of the 32-expert layer 269 -> 263, 4096
+// of the hierarchy 530 -> 523 (its K loops are long, and its time is theirs).
 #include <algorithm>
 #include <type_traits>
 #include "cmoe_internal.h"
@@ -32,12 +30,20 @@ __device__ __forceinline__ void mfma_first(floatx4_t& acc, const bf16x8_t& a, co
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(a), "v"(w));
 }
 
+// Slot outputs up to this size are stored past the caches: plain stores leave them dirty in the L2s, to be written back between
+// this launch and the combine kernel.  us per forward, plain / non-temporal: d = 1024, 25 MB 59.0 / 58.0; d = 2048, 18 MB 81.0 /
+// 80.3, 29 MB 75.5 / 74.6, 43 MB 85.0 / 82.9, 59 MB 95.0 / 95.1, 117 MB 163.5 / 166.6; d = 4096, 33 MB 149.7 / 149.5, 49 MB 194.5 /
+// 195.9, 67 MB 231 / 233, 168 MB 457 / 460, 470 MB 737 / 733.  Above, non-temporal stores shorten this launch by up to 4 % (470 MB)
+// and lengthen the combine launch by about as much or more: 253 + 94 us for 263 + 85, at 67 MB 71.2 + 15.8 for 71.1 + 13.8.
+constexpr int64_t SLOTS_NT_BYTES = (int64_t)45 << 20;
+
 // 16 bytes to base + lane_off (bytes; dropped where lane_off >= size).  Lanes without a target still issue the store, so
 // that the number of memory instructions of a wave is the same for every tile (see wait counts below).
+template <bool NT>
 __device__ __forceinline__ void store16_buffer(const bf16_t* base, uint32_t size, uint32_t lane_off, uintx4_t v) {
 #if defined(__HIP_DEVICE_COMPILE__)
   const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, size, 0x00020000);
-  __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, lane_off, 0, 2);   // 2: non-temporal
+  __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, lane_off, 0, NT ? 2 : 0);   // 2: non-temporal
 #endif
 }
 
@@ -118,6 +124,7 @@ __device__ __forceinline__ TileLane decode_tile(const GemmArgs& p, int item) {
 
 // Every group's K must hold at least STAGES steps (then the transfers are never more than one tile ahead of the
 // multiplication).
+template <bool NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void down_stream_kernel(GemmArgs p) {
   constexpr int NW = 4, WGN = 2;
   constexpr int TM = BM / 2, TN = BN / 2, MB = TM / 16, NB = TN / 16;
@@ -297,7 +304,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
       for (int i = 0; i < 4; ++i) {
         const floatx4_t lo = {read_acc(acc[mb][0][i]), read_acc(acc[mb][1][i]), read_acc(acc[mb][2][i]), read_acc(acc[mb][3][i])};
         const floatx4_t hi = {read_acc(acc[mb][4][i]), read_acc(acc[mb][5][i]), read_acc(acc[mb][6][i]), read_acc(acc[mb][7][i])};
-        store16_buffer(c_base, c_size, off + (uint32_t)(i * row_bytes), pack8(lo, hi));
+        store16_buffer<NT>(c_base, c_size, off + (uint32_t)(i * row_bytes), pack8(lo, hi));
         __builtin_amdgcn_sched_barrier(0);
       }
       off += (uint32_t)(16 * row_bytes);
@@ -323,19 +330,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
   }
 }
 
+template <bool NT>
+static hipError_t launch_form(const GemmArgs& a, hipStream_t s) {
+  static LdsLimit limit;
+  constexpr size_t smem = (size_t)STAGES * (BM + BN) * BK * sizeof(bf16_t) + 64 * sizeof(TileLane);
+  static_assert(2 * smem <= 160 * 1024, "two workgroups on a CU");
+  const hipError_t err = limit.raise(reinterpret_cast<const void*>(down_stream_kernel<NT>), smem);
+  if (err != hipSuccess) return err;
+  hipLaunchKernelGGL(down_stream_kernel<NT>, dim3((unsigned)std::min(a.n_blocks, 512)), dim3(256), smem, s, a);
+  return hipGetLastError();
+}
+
+bool down_stream_past_caches(const Engine& e, int64_t T) {
+  return T * e.S_all() * e.d * (int64_t)sizeof(bf16_t) <= SLOTS_NT_BYTES;
+}
+
 hipError_t launch_down_stream(const Engine& e, const GemmArgs& args, hipStream_t s) {
   GemmArgs a = args;
   // a tile costs its K steps and about six more
   const auto width = std::minmax_element(e.width_pad_host, e.width_pad_host + e.G);
   const int deep = *width.second / BK + 6, rest = *width.first / BK + 6;
   a.deep_rounds = (deep + rest / 2) / rest;
-  static LdsLimit limit;
-  constexpr size_t smem = (size_t)STAGES * (BM + BN) * BK * sizeof(bf16_t) + 64 * sizeof(TileLane);
-  static_assert(2 * smem <= 160 * 1024, "two workgroups on a CU");
-  const hipError_t err = limit.raise(reinterpret_cast<const void*>(down_stream_kernel), smem);
-  if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(down_stream_kernel, dim3((unsigned)std::min(a.n_blocks, 512)), dim3(256), smem, s, a);
-  return hipGetLastError();
+  return down_stream_past_caches(e, a.T) ? launch_form<true>(a, s) : launch_form<false>(a, s);
 }
 
 }  // namespace cmoe

@@ -167,8 +167,8 @@ __global__ __launch_bounds__(256) void combine_kernel(const T* __restrict__ y_sl
         acc[0] = fmaf(w, Elem<T>::ld(src), acc[0]);
       } else {
         T tmp[VEC];
-        // (read once, like the stores of the persistent down contraction past the caches: 8192 tokens of seven slots 773 -> 747 us
-        // per forward whichever kernel wrote them, 2048 tokens of four no change)
+        // (read once, past the caches: 8192 tokens of seven slots 762 -> 737 us per forward, 500 tokens of seven at d = 2048
+        // 58.5 -> 53.1, 2048 tokens of four no change)
         typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
         *reinterpret_cast<uintx4*>(tmp) = __builtin_nontemporal_load(reinterpret_cast<const uintx4*>(src));
 #pragma unroll

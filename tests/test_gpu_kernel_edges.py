@@ -253,7 +253,7 @@ def test_persistent_down_contraction(binding, d, N, m, n_s, k, T, remap):
         assert layer.forward_plan(T)["down"] == ("tiles", 8)
         ref = layer.forward(x)
         binding.cmoe_set_tuning("CMOE_GEMM2_CFG", 22)
-        assert layer.forward_plan(T)["down"] == ("persistent", 22)
+        assert layer.forward_plan(T)["down"] == ("persistent", 1)
         out = layer.forward(x)
     finally:
         binding.cmoe_set_tuning("CMOE_GEMM2_CFG", -1)
@@ -274,9 +274,9 @@ def test_persistent_down_contraction_many_tiles(binding):
     x = torch.randn((T, 4096), generator=torch.Generator(device="cuda").manual_seed(5), device="cuda", dtype=torch.bfloat16)
     y = {}
     try:
-        for shape, kernel in ((8, "tiles"), (22, "persistent")):
+        for shape, plan in ((8, ("tiles", 8)), (22, ("persistent", 0))):
             binding.cmoe_set_tuning("CMOE_GEMM2_CFG", shape)
-            assert layer.forward_plan(T)["down"] == (kernel, shape)
+            assert layer.forward_plan(T)["down"] == plan
             y[shape] = torch.empty_like(x)
             layer.forward_device(x, y[shape])
     finally:

@@ -142,11 +142,16 @@ def test_mfma_results_of_the_persistent_kernel_are_waited_for(tmp_path):
             path.write_bytes(obj)
             listing = subprocess.run([OBJDUMP, "-d", str(path)], capture_output=True, text=True, check=True).stdout
             code.update(parse(listing, "down_stream_kernel"))
-    (code,) = code.values()
-    mfmas = [i for i, ins in enumerate(code) if ins[1] == "v_mfma_f32_16x16x32_bf16"]
-    assert len(mfmas) == 4 * 32                     # two sets of fragment registers, each for a first and a later step
-    assert not violations(code)
-    assert not [ins for ins in code[mfmas[0]:mfmas[-1]] if ins[1].startswith(("scratch_", "global_", "flat_"))]
+    past_caches = []
+    for code in code.values():                      # its two forms
+        mfmas = [i for i, ins in enumerate(code) if ins[1] == "v_mfma_f32_16x16x32_bf16"]
+        assert len(mfmas) == 4 * 32                 # two sets of fragment registers, each for a first and a later step
+        assert not violations(code)
+        assert not [ins for ins in code[mfmas[0]:mfmas[-1]] if ins[1].startswith(("scratch_", "global_", "flat_"))]
+        nt = {"nt" in ins[2].split() for ins in code if ins[1].startswith("buffer_store")}
+        assert len(nt) == 1
+        past_caches += nt
+    assert sorted(past_caches) == [False, True]
 
 
 def test_the_check_sees_an_early_use():

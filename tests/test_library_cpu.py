@@ -223,15 +223,30 @@ def test_forward_plan(lib):
     try:
         assert layer.forward_plan(1)["down"] == ("combines", 16)
         binding.cmoe_set_tuning("CMOE_GEMM1_CFG", 6)
-        for shape, kernel in ((8, "tiles"), (22, "persistent")):
+        for shape, plan in ((8, ("tiles", 8)), (22, ("persistent", 1))):
             binding.cmoe_set_tuning("CMOE_GEMM2_CFG", shape)
-            assert layer.forward_plan(300) == {"gate_up": ("tiles", 6), "down": (kernel, shape)}
+            assert layer.forward_plan(300) == {"gate_up": ("tiles", 6), "down": plan}
             assert layer.forward_plan(300, dense=True)["down"][0] == "tiles"      # (no work list: a forced 22 is refused)
     finally:
         binding.cmoe_set_tuning("CMOE_GEMM1_CFG", -1)
         binding.cmoe_set_tuning("CMOE_GEMM2_CFG", -1)
     with pytest.raises(binding.CmoeError):
         layer.forward_plan(0)
+    layer.close()
+
+
+def test_large_slot_outputs_stay_in_the_caches(lib):
+    """The persistent down contraction stores past the caches up to 45 MB of slot outputs."""
+    cfg = synth.scaled(synth.CONFIGS[1], d_model=512, d_ff=8 * 100, n_experts=8, n_shared=1, top_k=2)
+    part = synth.trivial_partition(cfg)
+    layer = binding.Layer.from_partition(cfg, *synth.make_weights(cfg), part["neuron_order"], part["rep_neuron"], upload=False)
+    limit = (45 << 20) // (3 * 512 * 2)
+    try:
+        binding.cmoe_set_tuning("CMOE_GEMM2_CFG", 22)
+        assert layer.forward_plan(limit)["down"] == ("persistent", 1)
+        assert layer.forward_plan(limit + 1)["down"] == ("persistent", 0)
+    finally:
+        binding.cmoe_set_tuning("CMOE_GEMM2_CFG", -1)
     layer.close()
 
 
