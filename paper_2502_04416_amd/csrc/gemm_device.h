@@ -15,7 +15,7 @@ struct GemmArgs {
   bf16_t* C;
   const GroupDev* groups;
   const int32_t* seg_off;    // [G+1]
-  const int32_t* work;       // [G+1]
+  const int32_t* work;       // [G+1+9], see WsLayout::work1, work2
   const int64_t* h_off;      // [G+1]
   const int32_t* slot2tok;   // MODE 1 gather; null = identity
   int G;

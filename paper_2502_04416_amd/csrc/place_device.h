@@ -16,7 +16,7 @@ struct PlaceArgs {
   int32_t* seg_off;            // [G+1]
   int32_t* counts;             // [G]
   int32_t* work1;              // [G+1] prefix of work items, then [N_XCD+1] first item of each die's share
-  int32_t* work2;              // same for the down contraction
+  int32_t* work2;              // same for the down contraction; with stream2 first item per group, [G] items, [G+1] deep ones
   int64_t* h_off;              // [G+1]
   int32_t* slot2tok;           // [n_slots]
   int32_t* tok2slot;           // [T][S_all]

@@ -308,12 +308,6 @@ __device__ __forceinline__ void score_tile(const RouterDev& r, const RouteIO& io
   }
 }
 
-// Is router row `rr` one that some scored expert (or linear logit) uses?
-__device__ __forceinline__ bool router_row_used(const RouterDev& r, int rr) {
-  if (rr < r.n_sw_rows) return (rr / (2 * IL)) * IL + (rr % IL) < r.n_scored;
-  return rr - r.n_sw_rows < r.n_lin;
-}
-
 // ---- one token per workgroup ---------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(256) void router_simt_kernel(RouterDev r, RouteIO io, const T* __restrict__ x,
