@@ -953,16 +953,24 @@ static bool stream_ok(const Engine& e) {
   return true;
 }
 
-// Streamed units instead of a tile: few rows per expert, counted as routed entries per expert times d (what an operand of
-// tokens costs grows with the rows, what it is hidden behind does not).  us per forward on tiles / streamed: d = 512, 8
-// experts, 64 tokens 29.7 / 25.2; d = 2048, 12 experts, top-2: 17 tokens 36.7 / 30.9, 64 (26214) 47.5 / 45.5; d = 4096, 32
-// experts, top-4: 32 tokens (18724) 75.5 / 73.8, 48 (28086) 88.3 / 89.2; 16 experts, top-3: 17 tokens (13926) 63.1 / 62.4, 24
-// (19660) 65.9 / 67.0; d = 5120, 16 experts, top-2: 8 tokens 69.7 / 61.5, 32 (20480) 84.7 / 84.4, 48 86.1 / 90.9; d = 8192, 8
-// experts, top-2: 5 tokens 102.6 / 93.5, 12 (28086) 115.1 / 113.7, 16 119.7 / 121.0; 32 experts, top-5: 17 (24011) 110.2 / 109.6,
-// 24 117.4 / 120.5.  A hierarchy's outer experts meet more rows than its groups do on average: 17 tokens 65.3 / 66.1, 64 90 / 97.
+// Streamed units instead of a tile: few rows per expert, counted as routed entries per expert times d (q below).  Units of 8
+// neurons read the tokens twice as often for the weights they hide them behind, so their line lies lower.  us per forward on
+// tiles / streamed, units of 16: d = 2048, 12 experts, top-2, 64 tokens (q 23831) 47.2 / 42.7; d = 2560, 16 experts, top-3, 48
+// (24576) 57.7 / 52.6; d = 3072, 16 experts, top-3, 40 (26331) 61.2 / 56.5; d = 4096, 8 experts, top-2, 20 (23405) 72.0 / 70.1;
+// 16, top-3, 32 (26214) 70.1 / 69.9, 40 (32768) 76.0 / 77.1; 32 with four shared, top-4, 40 (23405) 83.0 / 82.2, 56 (32768) 89.9 /
+// 90.3; d = 5120, 16, top-2, 32 (21845) 91.4 / 88.1; 32, top-5, 24 (20480) 90.0 / 86.8, 32 (27306) 95.9 / 94.7.  Units of 8: d =
+// 5632, 16 experts, top-2, 24 tokens (18022) 99.0 / 97.9, 32 (24029) 106.4 / 108.4; d = 6144, 16, top-3, 17 (20889) 87.0 / 80.0, 32
+// (39321) 101.9 / 105.0; d = 8192, 8, top-2, 8 (18724) 110.8 / 105.2, 17 (39789) 125.5 / 127.2; 16, top-3, 12 (19660) 104.4 / 101.0,
+// 17 (27852) 108.9 / 110.5; 32, top-5, 17 (23210) 105.7 / 102.7, 24 (32768) 112.8 / 113.9.
+// Without an always-on group nothing streams beside the selection, and from d = 3584 to 5120 tiles win earlier (at 6144 and 8192
+// they do not: q 23040 88.3 / 86.0, 25600 100.7 / 96.1): d = 4096, 8
+// experts, top-2, 17 tokens (17408) 67.3 / 70.2; 16, top-4, 17 (17408) 65.3 / 67.1; 32, top-5, 24 (15360) 63.2 / 61.6; d = 3584, 8, top-2,
+// 17 (15232) 58.5 / 56.1; d = 5120, 16, top-3, 12 (11520) 77.7 / 73.5, 24 (23040) 85.4 / 85.6; at d = 3072 48 (27648) 59.7 / 57.7.
+// A hierarchy's outer experts meet more rows than its groups do on average: 17 tokens 65.3 / 66.1, 64 90 / 97.
 static bool streams_small_batch(const Engine& e, int64_t T) {
   if (!stream_gate_up_ok(e, T) || e.r.outer_top_k != 0) return false;
-  return T * e.S_dyn * e.d <= (e.d <= 2048 || e.d > 5120 ? 26500 : 19000) * (int64_t)(e.G - e.n_always);
+  const int64_t limit = e.n_always == 0 && e.d > 3072 && e.d <= 5120 ? 15500 : stream_neurons(e, T) == 8 ? 23500 : 26500;
+  return T * e.S_dyn * e.d <= limit * (int64_t)(e.G - e.n_always);
 }
 
 static int choose_cfg(int which, const Engine& e, int64_t T) {

@@ -265,3 +265,21 @@ def test_fp32_tiles_chosen_per_contraction(lib, d, d_ff, T, dense, gate_up, down
     layer = binding.Layer.from_partition(cfg, *synth.make_weights(cfg), part["neuron_order"], part["rep_neuron"], upload=False)
     assert layer.forward_plan(T, dense) == {"gate_up": ("fma", gate_up), "down": ("fma", down)}
     layer.close()
+
+
+@pytest.mark.parametrize("d,n,n_s,k,T,streamed", [
+    (2048, 12, 1, 2, 64, True),           # routed entries per expert times d: 23831
+    (4096, 16, 1, 3, 32, True),           # 26214, units of 16 neurons
+    (4096, 16, 1, 3, 33, False),          # 27034
+    (5632, 16, 1, 2, 31, True),           # 23279, units of 8
+    (5632, 16, 1, 2, 32, False),          # 24030
+    (4096, 32, 0, 5, 24, True),           # 15360, no always-on group
+    (4096, 16, 0, 4, 17, False),          # 17408
+    (3072, 16, 0, 3, 46, True),           # 26496, narrow enough for the common line
+])
+def test_streamed_units_where_they_win(lib, d, n, n_s, k, T, streamed):
+    cfg = synth.scaled(synth.CONFIGS[1], d_model=d, d_ff=n * 32, n_experts=n, n_shared=n_s, top_k=k)
+    part = synth.trivial_partition(cfg)
+    layer = binding.Layer.from_partition(cfg, *synth.make_weights(cfg), part["neuron_order"], part["rep_neuron"], upload=False)
+    assert (layer.forward_plan(T)["gate_up"][0] == "streamed") == streamed
+    layer.close()
