@@ -1001,11 +1001,20 @@ static int choose_cfg(int which, const Engine& e, int64_t T) {
       // average touched group half fills a row tile.  Below, its lookup of all tiles in advance costs more than it saves
       // (8 experts of 692, d = 2048, 441 tokens, 0.17 rounds: 54 against 65 us; 27 groups of 17 rows: 76 against 89).  From there
       // on, against the shape the models above take: 12 experts of 439, d = 2048, 2295 tokens 94 -> 84 us per forward, 32 of 324 at
-      // 603 tokens 119 -> 111, 16 of 300, d = 1536, 3254 tokens 80 -> 75; at worst 258.6 for 254.7 (16 of 704, d = 8192, 678 tokens).
+      // 603 tokens 119 -> 111, 16 of 300, d = 1536, 3254 tokens 80 -> 75.
       // With a K loop of more than 32 steps of 32 it takes the place of shape 8 only (8 experts of 1357, 5544 tokens: shape 0
       // 415, this one 426, shape 8 430).
       const int64_t entries = T * e.S_dyn, touched = std::min<int64_t>(e.G - e.n_always, entries);
-      if (stream_ok(e) && entries >= 64 * touched && n9 >= (k_min <= 640 ? 225 : 400) && (k_min <= 1024 || dflt == 8)) dflt = 22;
+      // In the place of shape 0, a single round of tall tiles, only where K is too short for those or an always-on group at least twice
+      // as deep makes their round as long as its own tiles (shape 0 / this one: d = 2048, 8 experts of 692, one of them
+      // shared, 2048 tokens 96.8 / 100.9, none, 3000 tokens 104.3 / 109.4, two, 2048 tokens 120.0 / 114.1; 12 of 439, 1400 tokens, one
+      // shared 75.3 / 77.9, three 94.7 / 89.7; of 320, one, 70.7 / 71.8; 16 of 256, 1400 tokens 74.9 / 73.0; d = 1024, 16 of 176,
+      // 2048 tokens 54.4 / 52.0), and never of shape 21 (d = 2048, 32 experts of 192, 400 tokens 59.9 / 62.4; d = 3072, 12 of
+      // 512, 678 tokens 87.5 / 89.0).  What is left of losses against the shape it replaces are single batches between others that
+      // gain (d = 8192, 16 of 704, two shared: 678 tokens 242.0 / 236.1, 800 tokens 242.9 / 248.6, 1000 tokens 291.6 / 283.2).
+      const int k_max = *std::max_element(e.width_pad_host, e.width_pad_host + e.G);
+      const bool in_place = dflt == 3 || dflt == 8 || (dflt == 0 && (k_min <= 256 || k_max >= 2 * k_min));
+      if (stream_ok(e) && in_place && entries >= 64 * touched && n9 >= (k_min <= 640 ? 225 : 400) && (k_min <= 1024 || dflt == 8)) dflt = 22;
     } else {
       // Deep K (dense FFN, un-restructured experts): 256x256 tiles with four waves when every CU gets one;
       // below that 256x128, whose round takes 0.56 of the time, unless it would need a second round; 128x128

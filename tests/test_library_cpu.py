@@ -283,3 +283,20 @@ def test_streamed_units_where_they_win(lib, d, n, n_s, k, T, streamed):
     layer = binding.Layer.from_partition(cfg, *synth.make_weights(cfg), part["neuron_order"], part["rep_neuron"], upload=False)
     assert (layer.forward_plan(T)["gate_up"][0] == "streamed") == streamed
     layer.close()
+
+
+@pytest.mark.parametrize("d,n,m,n_s,k,T,down", [
+    (2048, 8, 692, 1, 2, 2048, ("tiles", 0)),         # one round of tall tiles of one depth
+    (2048, 8, 692, 0, 2, 3000, ("tiles", 0)),
+    (2048, 8, 692, 2, 2, 2048, ("persistent", 1)),    # ... with an always-on group twice as deep
+    (2048, 12, 320, 1, 2, 1400, ("tiles", 0)),
+    (2048, 16, 256, 1, 3, 1400, ("persistent", 1)),   # K too short for tall tiles
+    (2048, 32, 192, 2, 6, 400, ("tiles", 21)),
+    (2048, 8, 692, 1, 2, 3000, ("persistent", 1)),
+])
+def test_persistent_down_contraction_where_it_wins(lib, d, n, m, n_s, k, T, down):
+    cfg = synth.scaled(synth.CONFIGS[1], d_model=d, d_ff=n * m, n_experts=n, n_shared=n_s, top_k=k)
+    part = synth.trivial_partition(cfg)
+    layer = binding.Layer.from_partition(cfg, *synth.make_weights(cfg), part["neuron_order"], part["rep_neuron"], upload=False)
+    assert layer.forward_plan(T)["down"] == down
+    layer.close()
