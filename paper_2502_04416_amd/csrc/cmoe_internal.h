@@ -251,6 +251,7 @@ bool stream_gate_up_ok(const Engine& e, int64_t T);
 int stream_neurons(const Engine& e, int64_t T);            // neurons per unit, 16 or 8
 bool decode_gate_up_streams(const Engine& e, int64_t T);   // a decode batch runs it
 bool tiles_gate_up_streams(const Engine& e, int64_t T);    // a batch on tiles does
+bool gate_up_streams_forced();                             // CMOE_GEMM1_CFG names one of its shapes
 // The scorer of the front end leaves a copy of the tokens for it, [K step of 32][token][32], where the slot outputs go later.
 bool front_lays_tokens(const Engine& e, int64_t T);
 hipError_t launch_stream_gate_up(const Engine& e, const void* x, int64_t T, char* ws, const WsLayout& L, int neurons, int n_blocks, hipStream_t s);

@@ -28,12 +28,18 @@ bool stream_gate_up_ok(const Engine& e, int64_t T) {
 // 67.0 / 68.3; d = 5120, 16 experts, top-2: 17 tokens 75.6 / 77.7; d = 8192, 32 experts, top-5: 8 tokens 86.9 / 81.7, 24 tokens 122.9 / 120.5.
 int stream_neurons(const Engine& e, int64_t T) { return T <= 16 || e.d > 5120 ? 8 : 16; }
 
-// us per forward on decode_gate_up_kernel / streamed: d = 4096, 16 experts, top-3: 2 tokens 34.4 / 33.2, 16 tokens 62.2 / 55.4; d = 5120
-// 44.1 / 37.1 at two tokens; d = 8192 85.9 / 72.2; up to d = 2048 both are bound by the host (20.3 / 20.5).  Without an always-on
-// group next to the selection, two tokens are the other way round at d = 4096 (30.8 / 32.1), three even.
+// From d = 3072 on: below, a unit's tokens fit its registers in a few loads and a launch is too short for a stream.  us per forward
+// on decode_gate_up_kernel / streamed: d = 1536, 8 experts, top-2: 2 tokens 18.7 / 19.1, 16 tokens 23.8 / 24.6; d = 2048, 32 experts,
+// top-4: 2 tokens 19.2 / 19.9, 12 tokens 26.4 / 27.3; d = 2560, 32 experts, top-4: 4 tokens 25.3 / 26.3, 16 tokens 34.0 / 33.5 (8, top-2:
+// 37.4 / 37.1); d = 3072, 16 experts, top-3: 4 tokens 34.0 / 33.2, 16 tokens 44.8 / 41.7; d = 3584, 8 experts, top-2: 47.0 / 41.5 and
+// 53.5 / 49.4; d = 4096, 16 experts, top-3: 2 tokens 33.8 / 33.4, 16 tokens 61.9 / 55.5.  Without an always-on group next to the
+// selection, two tokens are the other way round (d = 4096, 16 experts 29.5 / 30.3, 32 28.5 / 29.8), three even.  Hierarchies: d = 1024, 8
+// outer experts, 16 tokens 27.1 / 27.8; d = 2048 2 to 16 tokens 27.0 / 26.5 to 45.0 / 44.8; d = 3072, 4 outer, 4 tokens 52.7 / 51.8, 16
+// tokens 68.1 / 68.4.  A forced shape of streamed units counts at every width.
 bool decode_gate_up_streams(const Engine& e, int64_t T) {
   if (!decode_path_ok(e, T) || !stream_gate_up_ok(e, T) || decode_front_runs_all(e, T)) return false;
-  return T > 3 || e.n_always == 1 || e.r.outer_top_k != 0 || decode_k(e.d).nch > 1;
+  if (gate_up_streams_forced()) return true;
+  return e.d >= 3072 && (T > 3 || e.n_always == 1 || e.r.outer_top_k != 0 || decode_k(e.d).nch > 1);
 }
 
 bool front_lays_tokens(const Engine& e, int64_t T) {

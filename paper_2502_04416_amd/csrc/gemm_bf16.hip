@@ -839,6 +839,7 @@ static bool cfg_is_ws(int ci) { return ci >= 15 && ci <= 18; }
 static bool cfg_is_stream(int ci) { return ci == 22; }
 static bool cfg_is_ring(int ci) { return kCfgs[ci].stages >= 5 && !cfg_is_stream(ci); }
 static bool cfg_is_units(int ci) { return ci == 23 || ci == 24; }
+bool gate_up_streams_forced() { return cfg_is_units(tuning().gemm1_cfg); }
 static bool cfg_is_dyn(int ci) { return ci >= 11 && ci <= 18; }
 bool ws_down_handles(int width_pad);
 hipError_t launch_down_stream(const Engine& e, const GemmArgs& a, hipStream_t s);

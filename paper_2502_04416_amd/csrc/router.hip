@@ -828,7 +828,7 @@ __global__ __launch_bounds__(512) void route_place_shared_kernel(RouterDev r, Ro
   decode_gate_up<1, KSTEPS, RUNS>(da, 0, (int)blockIdx.x - 1, 0, T, da.groups[0].width_pad, 0, red);
 }
 
-// The same for the batches of 2 to 64 tokens that run streamed units (the form above is left with one token).
+// The same for the batches of 2 to 64 tokens that run streamed units.
 template <int MAXT, int CS, int NEUR>
 __global__ __launch_bounds__(512) void route_place_stream_kernel(RouterDev r, RouteIO io, PlaceArgs pl, const float* __restrict__ partial,
                                                                  int n_slices, int T, DecArgs da) {
@@ -1143,7 +1143,7 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
     return hipGetLastError();
   }
   if (L.skip_always) {
-    // (likewise, one token whose routed units have a launch of their own)
+    // (likewise, decode units: one token whose routed units have a launch of their own, or 2 to 16 below the streamed widths)
     DecArgs da = make_dec_args(e, x, T, ws, L, nullptr);
     da.slot2tok = nullptr;                        // group 0's slots are the tokens in order; the map is not written yet
     da.work = nullptr;

@@ -300,3 +300,20 @@ def test_persistent_down_contraction_where_it_wins(lib, d, n, m, n_s, k, T, down
     layer = binding.Layer.from_partition(cfg, *synth.make_weights(cfg), part["neuron_order"], part["rep_neuron"], upload=False)
     assert layer.forward_plan(T)["down"] == down
     layer.close()
+
+
+@pytest.mark.parametrize("d,n_s,T,kernel", [
+    (512, 1, 8, "units"), (2048, 1, 16, "units"), (2560, 2, 4, "units"),      # too narrow for a stream
+    (3072, 2, 4, "streamed"), (4096, 1, 2, "streamed"), (4096, 0, 2, "units"), (4096, 0, 4, "streamed"), (5120, 0, 2, "streamed"),
+])
+def test_decode_batches_stream_where_it_wins(lib, d, n_s, T, kernel):
+    cfg = synth.scaled(synth.CONFIGS[1], d_model=d, d_ff=16 * 32, n_experts=16, n_shared=n_s, top_k=3)
+    part = synth.trivial_partition(cfg)
+    layer = binding.Layer.from_partition(cfg, *synth.make_weights(cfg), part["neuron_order"], part["rep_neuron"], upload=False)
+    assert layer.forward_plan(T)["gate_up"][0] == kernel
+    try:                                                                      # a forced shape counts at every width
+        binding.cmoe_set_tuning("CMOE_GEMM1_CFG", 24)
+        assert layer.forward_plan(T)["gate_up"][0] == "streamed"
+    finally:
+        binding.cmoe_set_tuning("CMOE_GEMM1_CFG", -1)
+    layer.close()
