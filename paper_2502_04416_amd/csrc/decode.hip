@@ -377,12 +377,11 @@ __global__ __launch_bounds__(DS_WAVES * 64) void decode_down_sparse_kernel(DecAr
 // contractions; from 17 tokens on the routed layer chooses between streamed units and tiles (streams_small_batch), and the
 // dense one is 10-20 us faster on skinny tiles (measured at d = 4096).
 constexpr int DECODE_MAX_T = 16;
-// Above d = 4096 the batches from five tokens on choose as those from 17 on do below it.  (Measured before the streamed units, when
-// a wave's K slice took several dependent runs of loads and the tile kernels caught up early:)  us per
-// forward on tiles / streamed, d_ff = 11264, 16 experts, top-3: d = 5120 49.4 / 29.4 at one token, 64.3 / 50.7 at four, d = 8192
-// 55.9 / 38.6 and 86.2 / 77.5, d = 10240 63.8 / 46.4 and 117.6 / 109.8; at 16 tokens 79.2 / 81.0, 106.0 / 127.2 and 134.7 /
-// 154.0.  In between neither side wins throughout: five to eight tokens are 4 to 38 % faster streamed at d = 5120 and 6144,
-// 1 % slower to 10 % faster at d = 8192, and twelve tokens 3 % slower to 21 % faster.
+// Above d = 4096 the batches from five tokens on choose as those from 17 on do below it: a line between what routed layers gain and
+// lose by it.  us per forward with these launches up to 4 / up to 16 tokens, routed (the gate/up contraction on streamed units
+// either way): d = 5120, 16 experts, top-3, 5 tokens 62.3 / 58.1, 16 tokens 79.6 / 75.5; d = 6144, 8, top-2 64.0 / 63.2 and 94.5 / 89.0;
+// d = 7680, 16, top-2 70.8 / 70.6 and 90.0 / 88.7; d = 8192, 16, top-3 86.9 / 88.5 and 104.1 / 105.9; d = 10240 109.9 / 112.6 and
+// 143.1 / 144.7.  The dense layer: d = 5120 79.3 / 71.4 and 80.6 / 90.8, d = 8192 119.5 / 104.0 and 120.2 / 121.9.
 constexpr int DECODE_MAX_T_RUNS = 4;
 bool decode_path_ok(const Engine& e, int64_t T) {
   if (e.dtype != 1 || T < 1 || T > (decode_k(e.d).nch > 1 ? DECODE_MAX_T_RUNS : DECODE_MAX_T)) return false;
