@@ -10,9 +10,10 @@
 //     eight consecutive output columns and a store covers 256 bytes of each of four rows.  (16 rows of 64 bytes per store
 //     are written at 34 GB/s per CU, 4 rows of 256 at 90.)
 //   * The stores go through the caches, where the combine kernel finds what the last level could hold, unless all results
-//     together are about as small as the L2s (SLOTS_NT_BYTES): then they are non-temporal.
+//     together are about as small as the L2s or larger than the last level can use (SLOTS_NT_BYTES, SLOTS_NT_FROM): then they are
+//     non-temporal.
 // Launches, 128x256 tiles of the other kernel (two per CU, a workgroup per tile) -> this one: 2048 tokens of the 16-expert
-// layer 73.8 -> 71.1 us, 4096 of the 32-expert layer with four shared 152 -> 144, 8192 of the 32-expert layer 269 -> 263, 4096
+// layer 73.8 -> 71.1 us, 4096 of the 32-expert layer with four shared 152 -> 144, 8192 of the 32-expert layer 269 -> 253, 4096
 // of the hierarchy 530 -> 523 (its K loops are long, and its time is theirs).
 #include <algorithm>
 #include <type_traits>
@@ -30,12 +31,14 @@ __device__ __forceinline__ void mfma_first(floatx4_t& acc, const bf16x8_t& a, co
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(a), "v"(w));
 }
 
-// Slot outputs up to this size are stored past the caches: plain stores leave them dirty in the L2s, to be written back between
+// Slot outputs up to the first size are stored past the caches: plain stores leave them dirty in the L2s, to be written back between
 // this launch and the combine kernel.  us per forward, plain / non-temporal: d = 1024, 25 MB 59.0 / 58.0; d = 2048, 18 MB 81.0 /
 // 80.3, 29 MB 75.5 / 74.6, 43 MB 85.0 / 82.9, 59 MB 95.0 / 95.1, 117 MB 163.5 / 166.6; d = 4096, 33 MB 149.7 / 149.5, 49 MB 194.5 /
-// 195.9, 67 MB 231 / 233, 168 MB 457 / 460, 470 MB 737 / 733.  Above, non-temporal stores shorten this launch by up to 4 % (470 MB)
-// and lengthen the combine launch by about as much or more: 253 + 94 us for 263 + 85, at 67 MB 71.2 + 15.8 for 71.1 + 13.8.
-constexpr int64_t SLOTS_NT_BYTES = (int64_t)45 << 20;
+// 195.9, 67 MB 231 / 233, 117 MB 223.2 / 228.2, 168 MB 457 / 460, 234 MB 398.2 / 403.0.  In between the last-level cache holds enough of
+// them to pay the combine launch back what non-temporal stores give this one (67 MB 71.2 + 15.8 for 71.1 + 13.8); beyond the second
+// size it does not: 352 MB 555.7 / 558.2 and (d = 2048) 405.4 / 411.4, 402 MB 931.4 / 934.8 and (d = 8192) 679.2 / 678.1 and 997.2 / 990.7,
+// 469 MB 735.5 / 734.1 (on another box 760.8 / 749.7), 503 MB 1148.5 / 1145.9, 587 MB 888.7 / 879.4.
+constexpr int64_t SLOTS_NT_BYTES = (int64_t)45 << 20, SLOTS_NT_FROM = (int64_t)380 << 20;
 
 // 16 bytes to base + lane_off (bytes; dropped where lane_off >= size).  Lanes without a target still issue the store, so
 // that the number of memory instructions of a wave is the same for every tile (see wait counts below).
@@ -342,7 +345,8 @@ static hipError_t launch_form(const GemmArgs& a, hipStream_t s) {
 }
 
 bool down_stream_past_caches(const Engine& e, int64_t T) {
-  return T * e.S_all() * e.d * (int64_t)sizeof(bf16_t) <= SLOTS_NT_BYTES;
+  const int64_t bytes = T * e.S_all() * e.d * (int64_t)sizeof(bf16_t);
+  return bytes <= SLOTS_NT_BYTES || bytes > SLOTS_NT_FROM;
 }
 
 hipError_t launch_down_stream(const Engine& e, const GemmArgs& args, hipStream_t s) {

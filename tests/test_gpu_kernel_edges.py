@@ -264,17 +264,17 @@ def test_persistent_down_contraction(binding, d, N, m, n_s, k, T, remap):
     layer.close()
 
 
-def test_persistent_down_contraction_many_tiles(binding):
-    """More tiles per workgroup (65) than it looks up at a time."""
+@pytest.mark.parametrize("T,past_caches", [(38000, 1), (2100, 0)])
+def test_persistent_down_contraction_many_tiles(binding, T, past_caches):
+    """More tiles per workgroup (65) than it looks up at a time; few, with results that go through the caches."""
     import torch
-    T = 38000
     cfg = synth.scaled(synth.CONFIGS[1], d_model=4096, d_ff=8 * 96, n_experts=8, n_shared=1, top_k=6, n_centres=16)
     part, weights = synth.trivial_partition(cfg), synth.make_weights(cfg)
     layer = binding.Layer.from_partition(cfg, *weights, part["neuron_order"], part["rep_neuron"])
     x = torch.randn((T, 4096), generator=torch.Generator(device="cuda").manual_seed(5), device="cuda", dtype=torch.bfloat16)
     y = {}
     try:
-        for shape, plan in ((8, ("tiles", 8)), (22, ("persistent", 0))):
+        for shape, plan in ((8, ("tiles", 8)), (22, ("persistent", past_caches))):
             binding.cmoe_set_tuning("CMOE_GEMM2_CFG", shape)
             assert layer.forward_plan(T)["down"] == plan
             y[shape] = torch.empty_like(x)

@@ -236,7 +236,7 @@ def test_forward_plan(lib):
 
 
 def test_large_slot_outputs_stay_in_the_caches(lib):
-    """The persistent down contraction stores past the caches up to 45 MB of slot outputs."""
+    """The persistent down contraction stores past the caches up to 45 MB of slot outputs, and beyond 380 MB."""
     cfg = synth.scaled(synth.CONFIGS[1], d_model=512, d_ff=8 * 100, n_experts=8, n_shared=1, top_k=2)
     part = synth.trivial_partition(cfg)
     layer = binding.Layer.from_partition(cfg, *synth.make_weights(cfg), part["neuron_order"], part["rep_neuron"], upload=False)
@@ -245,6 +245,9 @@ def test_large_slot_outputs_stay_in_the_caches(lib):
         binding.cmoe_set_tuning("CMOE_GEMM2_CFG", 22)
         assert layer.forward_plan(limit)["down"] == ("persistent", 1)
         assert layer.forward_plan(limit + 1)["down"] == ("persistent", 0)
+        limit = (380 << 20) // (3 * 512 * 2)
+        assert layer.forward_plan(limit)["down"] == ("persistent", 0)
+        assert layer.forward_plan(limit + 1)["down"] == ("persistent", 1)
     finally:
         binding.cmoe_set_tuning("CMOE_GEMM2_CFG", -1)
     layer.close()
