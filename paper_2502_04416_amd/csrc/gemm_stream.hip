@@ -13,7 +13,7 @@
 //     together are about as small as the L2s or larger than the last level can use (SLOTS_NT_BYTES, SLOTS_NT_FROM): then they are
 //     non-temporal.
 // Launches, 128x256 tiles of the other kernel (two per CU, a workgroup per tile) -> this one: 2048 tokens of the 16-expert
-// layer 73.8 -> 71.1 us, 4096 of the 32-expert layer with four shared 152 -> 144, 8192 of the 32-expert layer 269 -> 253, 4096
+// layer 73.8 -> 71.1 us, 4096 of the 32-expert layer with four shared 152 -> 144, 8192 of the 32-expert layer 276 -> 265, 4096
 // of the hierarchy 530 -> 523 (its K loops are long, and its time is theirs).
 #include <algorithm>
 #include <type_traits>
