@@ -513,11 +513,15 @@ __global__ __launch_bounds__(RT_THREADS) void route_tile_kernel(RouterDev r, Rou
 // The sums are those of the two launches, bit for bit: K falls into n_slices slices of k_slice, a slice into four
 // classes of 64-wide chunks (chunk number mod 4), each of which is one chain of MFMAs; ((c0 + c1) + c2) + c3 is
 // the slice, and the slices are added in order.  Wave w runs the (slice, class) units w * UPW .. + UPW - 1.
-template <int UPW, int TB, bool ONE>
+//
+// NB: blocks of 16 rows that hold router rows, of the four of a group of 64 (32 gate rows, then 32 up rows).  Up to 16 scored
+// experts fill two, the first gate and the first up block, and a workgroup pulls half as much.
+template <int UPW, int TB, bool ONE, int NB>
 __global__ __launch_bounds__(512) void score_route_kernel(RouterDev r, RouteIO io, const bf16_t* __restrict__ x,
                                                           const bf16_t* __restrict__ wrt, int d, int64_t T, int n_slices,
                                                           int k_slice, int32_t* __restrict__ counts, int G) {
   constexpr int NTOK = TB * 16, LDP = 64 + 4;
+  constexpr int BSTEP = 4 / NB;                                // row block of operand b: b * BSTEP
   extern __shared__ __attribute__((aligned(16))) float sr_smem[];
   __shared__ int32_t hist[MAX_GROUPS];
   __shared__ GateLds gl;
@@ -541,7 +545,7 @@ __global__ __launch_bounds__(512) void score_route_kernel(RouterDev r, RouteIO i
   }
   const int n_units = 4 * n_slices, n_i = k_slice / 256, kt = d / 32;
   const int unit0 = wave * UPW;
-  struct Chunk { bf16x8_t w[2][4], a[2][TB]; };
+  struct Chunk { bf16x8_t w[2][NB], a[2][TB]; };
   Chunk c0, c1;
   for (int rg = 0; rg < n_rows / 64; ++rg) {
     auto load_chunk = [&](Chunk& c, int k, int i) {            // chunk i of this wave's k-th unit
@@ -551,26 +555,26 @@ __global__ __launch_bounds__(512) void score_route_kernel(RouterDev r, RouteIO i
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
-          c.w[h][b] = *reinterpret_cast<const bf16x8_t*>(wrt + (((int64_t)(rg * 4 + b) * kt + (kc >> 5) + h) * 64 + lane) * 8);
+        for (int b = 0; b < NB; ++b)
+          c.w[h][b] = *reinterpret_cast<const bf16x8_t*>(wrt + (((int64_t)(rg * 4 + b * BSTEP) * kt + (kc >> 5) + h) * 64 + lane) * 8);
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb) c.a[h][tb] = *reinterpret_cast<const bf16x8_t*>(xr[tb] + kc + h * 32);
       }
     };
-    floatx4_t acc[UPW][4][TB];
+    floatx4_t acc[UPW][NB][TB];
 #pragma unroll
     for (int k = 0; k < UPW; ++k)
 #pragma unroll
-      for (int b = 0; b < 4; ++b)
+      for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
           for (int i = 0; i < 4; ++i) acc[k][b][tb][i] = 0.0f;
-    auto mma_chunk = [&](const Chunk& c, floatx4_t (&ac)[4][TB]) {
+    auto mma_chunk = [&](const Chunk& c, floatx4_t (&ac)[NB][TB]) {
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+        for (int b = 0; b < NB; ++b)
 #pragma unroll
           for (int tb = 0; tb < TB; ++tb) ac[b][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c.w[h][b], c.a[h][tb], ac[b][tb], 0, 0, 0);
     };
@@ -596,7 +600,7 @@ __global__ __launch_bounds__(512) void score_route_kernel(RouterDev r, RouteIO i
         }
       }
     }
-    // D layout: a lane holds router rows b * 16 + kq * 4 .. + 3 of token tb * 16 + r16
+    // D layout: a lane holds router rows 16 b * BSTEP + kq * 4 .. + 3 of token tb * 16 + r16
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
 #pragma unroll
@@ -604,17 +608,17 @@ __global__ __launch_bounds__(512) void score_route_kernel(RouterDev r, RouteIO i
         const int q = unit0 + k;
         if (q >= n_units || (q & 3) != c) continue;
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+        for (int b = 0; b < NB; ++b)
 #pragma unroll
           for (int tb = 0; tb < TB; ++tb) {
-            floatx4_t* dst = reinterpret_cast<floatx4_t*>(slice_sum + ((q >> 2) * NTOK + tb * 16 + r16) * LDP + b * 16 + kq * 4);
+            floatx4_t* dst = reinterpret_cast<floatx4_t*>(slice_sum + ((q >> 2) * NTOK + tb * 16 + r16) * LDP + b * (16 * BSTEP) + kq * 4);
             *dst = c == 0 ? acc[k][b][tb] : *dst + acc[k][b][tb];
           }
       }
       __syncthreads();
     }
-    for (int idx = tid; idx < NTOK * 64; idx += 512) {
-      const int tok = idx >> 6, row = idx & 63;
+    for (int idx = tid; idx < NTOK * 16 * NB; idx += 512) {
+      const int tok = idx / (16 * NB), c = idx % (16 * NB), row = (c & 15) + (c >> 4) * (16 * BSTEP);
       float v = 0.0f;
       for (int sl = 0; sl < n_slices; ++sl) v += slice_sum[(sl * NTOK + tok) * LDP + row];
       pre[tok * ld + rg * 64 + row] = v;
@@ -975,38 +979,41 @@ static int scorer_slices(const Engine& e, int64_t T) {
 // router has a copy in operand order, whole pairs of chunks per unit (or one chunk), and either
 //  - at most two slices, i.e. a batch that fills the chip with 32 tokens per workgroup (8192 tokens of the 32-expert
 //    layer: 31 us against 34 + 10), or
-//  - five to eight slices, 16 tokens per workgroup, and a router matrix of at most 0.5 MB.
-// us per forward in two launches / in one, experts of 32: d = 512, 70 to 8192 tokens 31.6 / 27.5 to 55.0 / 49.6; d = 1536
-// 33.7 / 29.7 to 57.9 / 49.7; d = 2048 35.1 / 31.7 to 109 / 100; d = 4096, 64 router rows (0.5 MB) 40.3 / 39.3 at 70 tokens,
-// 78.9 / 75.0 at 2048.  Above 0.5 MB: 0.66 MB (d = 2560, 128 rows) 47.0 / 44.6 at 70 tokens, 74.1 / 63.2 at 2048 (one
-// launch would be the better one there); 1 MB (d = 4096, 128 rows) 50.0 / 53.0 and 93.9 / 85.0, (d = 8192, 64 rows)
-// 51.6 / 55.2 and 126 / 124; 2 MB (d = 8192, 128 rows) 63.8 / 76.1 and 151 / 145.
-// Three and four slices (4096 tokens) take the two launches: 29 against 31 us for them.
+//  - 16 tokens per workgroup, which then pulls at most 640 KB of tokens and router rows (a CU takes in about 50 KB per us).
+// us per forward in two launches / in one, d = 4096, 32 experts (64 rows, 640 KB): 70 tokens 40.3 / 39.3, 2048 78.9 / 75.0,
+// 3000 352.1 / 343.2, 4096 459.7 / 450.1; d = 2048, 32 experts, 4096 tokens 128.7 / 121.3.  Up to 16 experts (32 rows): d = 1024,
+// 333 tokens 36.5 / 31.4 and 4096 62.4 / 55.9; d = 5120 (480 KB) 70 tokens 105.3 / 101.9, 2048 345 / 336; d = 8192 (768 KB) 70
+// tokens 134.0 / 135.4, 333 179.8 / 181.5, 2048 378 / 374.  32 experts, d = 5120 (800 KB) 70 tokens 97.7 / 97.9, 2048 232 / 226;
+// d = 8192 (1.3 MB) 124 / 132 and 286 / 287.
+// Row blocks in use (see the kernel) of a layer of 16 experts, d = 4096, against all four: 333 tokens 109.8 -> 104.5 us per
+// forward, 2048 208.0 -> 202.7 (the launch 15.8 -> 10.5 us); d = 1024, 333 tokens 36.5 -> 31.4.
+static constexpr int score_route_tokens(int upw) { return upw >= 2 ? 16 : 32; }
+static int score_route_blocks(const Engine& e) { return e.r.n_scored <= 16 ? 2 : 4; }
 static int score_route_units(const Engine& e, int64_t T) {
   if (!mfma_scorer_ok(e) || e.wr_tiled == nullptr || e.r.outer_top_k != 0 || e.r.n_lin_rows != 0 || e.r.n_sw_rows % 64 != 0) return 0;
   const int S = scorer_slices(e, T), n_i = e.d / S / 256;
   if (n_i != 1 && n_i % 2 != 0) return 0;
-  if (S > 2 && (S < 5 || (int64_t)e.r.n_sw_rows * e.d > 64 * 4096)) return 0;
+  const int rows = e.r.n_sw_rows * score_route_blocks(e) / 4;
+  if (S > 2 && (int64_t)(16 + rows) * e.d > (16 + 64) * 4096) return 0;
   return (4 * S + 7) / 8;
 }
-static int score_route_tokens(int upw) { return upw >= 3 ? 16 : 32; }
 
 CountTable router_counts(const Engine& e, int64_t T, const WsLayout& L) {
   if (const int upw = score_route_units(e, T)) return {score_route_tokens(upw), L.scores};   // (no partial sums there)
   return {TOK_TILE, L.tile_counts};
 }
 
-template <int UPW, bool ONE>
+template <int UPW, bool ONE, int NB>
 static hipError_t launch_score_route(const Engine& e, const RouteIO& io, const void* x, int64_t T, int n_slices,
                                      int32_t* counts, hipStream_t s) {
-  constexpr int TB = UPW >= 3 ? 1 : 2, NTOK = TB * 16;
+  constexpr int TB = score_route_tokens(UPW) / 16, NTOK = TB * 16;
   const size_t smem = sizeof(float) * (size_t)NTOK * (n_slices * (64 + 4) + e.r.n_sw_rows + 1 + LD_SC);
-  // at most 8 slices (UPW 3, 4) or 2 (UPW 1) and two groups of 64 rows
-  constexpr size_t most = sizeof(float) * NTOK * ((UPW >= 3 ? 8 : 2) * (64 + 4) + 128 + 1 + LD_SC);
+  // at most 2 UPW slices and two groups of 64 rows
+  constexpr size_t most = sizeof(float) * NTOK * (2 * UPW * (64 + 4) + 128 + 1 + LD_SC);
   static LdsLimit limit;
-  const hipError_t err = limit.raise(reinterpret_cast<const void*>(score_route_kernel<UPW, TB, ONE>), most);
+  const hipError_t err = limit.raise(reinterpret_cast<const void*>(score_route_kernel<UPW, TB, ONE, NB>), most);
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL((score_route_kernel<UPW, TB, ONE>), dim3((unsigned)((T + NTOK - 1) / NTOK)), dim3(512), smem, s, e.r, io,
+  hipLaunchKernelGGL((score_route_kernel<UPW, TB, ONE, NB>), dim3((unsigned)((T + NTOK - 1) / NTOK)), dim3(512), smem, s, e.r, io,
                      static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(e.wr_tiled), e.d, T, n_slices,
                      e.d / n_slices, counts, e.G);
   return hipGetLastError();
@@ -1201,11 +1208,19 @@ hipError_t launch_router(const Engine& e, const void* x, int64_t T, char* ws, co
     const int S = scorer_slices(e, T);
     const bool one = e.d / S == 256;
     tile_counts = reinterpret_cast<int32_t*>(ws + L.scores);
+    const bool two = score_route_blocks(e) == 2;
+#define CMOE_LAUNCH_B(UPW, ONE, NB) return launch_score_route<UPW, ONE, NB>(e, io, x, T, S, tile_counts, s)
+#define CMOE_LAUNCH(UPW)                                                          \
+  if (one) { if (two) CMOE_LAUNCH_B(UPW, true, 2); else CMOE_LAUNCH_B(UPW, true, 4); } \
+  else { if (two) CMOE_LAUNCH_B(UPW, false, 2); else CMOE_LAUNCH_B(UPW, false, 4); }
     switch (upw) {
-      case 1: return one ? launch_score_route<1, true>(e, io, x, T, S, tile_counts, s) : launch_score_route<1, false>(e, io, x, T, S, tile_counts, s);
-      case 3: return one ? launch_score_route<3, true>(e, io, x, T, S, tile_counts, s) : launch_score_route<3, false>(e, io, x, T, S, tile_counts, s);
-      default: return one ? launch_score_route<4, true>(e, io, x, T, S, tile_counts, s) : launch_score_route<4, false>(e, io, x, T, S, tile_counts, s);
+      case 1: CMOE_LAUNCH(1)
+      case 2: CMOE_LAUNCH(2)
+      case 3: CMOE_LAUNCH(3)
+      default: CMOE_LAUNCH(4)
     }
+#undef CMOE_LAUNCH
+#undef CMOE_LAUNCH_B
   }
   if (mfma_scorer_ok(e)) {
     int n_slices = 1;

@@ -355,3 +355,25 @@ def test_streamed_gate_up(binding, d, N, m, n_s, k, T):
     check_flat(cfg, weights, part, x, layer.forward(x))
     assert all(np.array_equal(o["y"], outs[0]["y"]) for o in outs)
     layer.close()
+
+
+@pytest.mark.parametrize("gate", [False, True])
+@pytest.mark.parametrize("d,N,n_s,k,T", [
+    (768, 17, 1, 3, 65),        # 16 routed experts: two of four row blocks; three slices
+    (768, 17, 0, 3, 65),        # 17: all four
+    (1024, 17, 1, 16, 70),      # four slices of one chunk
+    (2048, 16, 0, 3, 2400),     # four slices of two chunks
+    (2560, 8, 1, 2, 2600),      # two slices of five chunks: the two launches
+    (512, 9, 1, 2, 8300),       # two slices, 32 tokens per workgroup
+])
+def test_router_row_blocks_in_use(binding, d, N, n_s, k, T, gate):
+    """Scoring and selection in one launch on either side of 16 routed experts, and batches of three and four K slices."""
+    cfg, weights, part, x, layer = _case(binding, d, N, 16, n_s, k, T, seed=2)
+    u = b = None
+    if gate:
+        u, b = synth.make_gate_params(cfg, seed=7300)
+        layer.set_gate_params(u, b)
+    out = layer.forward(x)
+    check_flat(cfg, weights, part, x, out, u=u, b=b)
+    assert np.array_equal(out["counts"], np.bincount(out["topk"].ravel(), minlength=cfg.n_routed))
+    layer.close()
