@@ -161,9 +161,9 @@ __global__ __launch_bounds__(DC_WAVES * 64) void decode_down_combine_kernel(DecA
       const int g = lane + 64 * k;
       int n = 0;
       if (g < p.G && p.seg_off[g + 1] > p.seg_off[g]) n = cdiv(p.groups[g].width_pad / 32, DC_CH);
-      const int inc = wave_incl_scan(n, lane);
+      const int inc = wave_incl_scan(n);
       if (g < p.G) item0[g] = run0 + inc - n;
-      run0 += __shfl(inc, 63, 64);
+      run0 += wave_last(inc);
     }
     if (lane == 0) item0[p.G] = run0;
   }
@@ -274,9 +274,9 @@ __global__ __launch_bounds__(DS_WAVES * 64) void decode_down_sparse_kernel(DecAr
       const int g = lane + 64 * k;
       int n = 0;
       if (g < n_always && p.seg_off[g + 1] > p.seg_off[g]) n = cdiv(p.groups[g].width_pad / 32, DC_CH);
-      const int inc = wave_incl_scan(n, lane);
+      const int inc = wave_incl_scan(n);
       if (g < p.G) item0[g] = run0 + inc - n;
-      run0 += __shfl(inc, 63, 64);
+      run0 += wave_last(inc);
     }
     if (lane == 0) item0[p.G] = run0;
   }

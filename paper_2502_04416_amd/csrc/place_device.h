@@ -99,9 +99,9 @@ __device__ __forceinline__ void place_slots(const PlaceArgs& p, int tile, const 
   for (int k = 0; k < GPL; ++k) {
     const int g = lane + 64 * k;
     if (k > 0 && 64 * k >= p.G) continue;
-    const int inc = wave_incl_scan(tc.tot[k], lane);
+    const int inc = wave_incl_scan(tc.tot[k]);
     if (g < p.G) base[g] = run0 + inc - tc.tot[k] + tc.prev[k];
-    run0 += __shfl(inc, 63, 64);
+    run0 += wave_last(inc);
   }
   wave_lds_sync();                          // base[] and present[] are complete
   // always-on groups: identity segments
@@ -139,6 +139,7 @@ __device__ __forceinline__ void place_lists_of(const PlaceArgs& p, const TileCou
   int run0 = 0, w1_0 = 0, w2_0 = 0, w2_deep = 0;
   long long h0 = 0;
   int n1[GPL], n2[GPL], w1x[GPL], w2x[GPL];     // work items of this lane's groups and their exclusive prefix
+  int rt[2][GPL], ct[2][GPL];                   // row and column tiles of the two contractions (a division is a long chain: once)
 #pragma unroll
   for (int k = 0; k < GPL; ++k) {
     const int g = lane + 64 * k;
@@ -152,21 +153,25 @@ __device__ __forceinline__ void place_lists_of(const PlaceArgs& p, const TileCou
       a1 = cnt > 0 ? wp / p.dec_unit1 : 0;
       a2 = cnt > 0 ? p.d / 16 : 0;
     } else {
-      a1 = cdiv(cnt, p.bm1) * cdiv(2 * wp, p.bn1);
-      a2 = cdiv(cnt, p.bm2) * cdiv(p.d, p.bn2);
+      rt[0][k] = cdiv(cnt, p.bm1);
+      ct[0][k] = cdiv(2 * wp, p.bn1);
+      rt[1][k] = cdiv(cnt, p.bm2);
+      ct[1][k] = cdiv(p.d, p.bn2);
+      a1 = rt[0][k] * ct[0][k];
+      a2 = rt[1][k] * ct[1][k];
     }
     if (g >= p.G) { a1 = 0; a2 = 0; }
     if (p.skip_always && g < p.n_always) a1 = 0;
     const long long ah = (long long)cnt * wp;
     const bool deep = !DECODE && p.stream2 > 0 && wp > p.stream2;
-    const int run_i = wave_incl_scan(cnt, lane), w1_i = wave_incl_scan(a1, lane), w2_i = wave_incl_scan(deep ? 0 : a2, lane);
-    const long long h_i = wave_incl_scan(ah, lane);
+    const int run_i = wave_incl_scan(cnt), w1_i = wave_incl_scan(a1), w2_i = wave_incl_scan(deep ? 0 : a2);
+    const long long h_i = wave_incl_scan(ah);
     const int run = run0 + run_i - cnt, w1 = w1_0 + w1_i - a1;
     int w2 = w2_0 + w2_i - a2;
     if (!DECODE && p.stream2 > 0) {
-      const int deep_i = wave_incl_scan(deep ? a2 : 0, lane);
+      const int deep_i = wave_incl_scan(deep ? a2 : 0);
       if (deep) w2 = w2_deep + deep_i - a2;
-      w2_deep += __shfl(deep_i, 63, 64);
+      w2_deep += wave_last(deep_i);
     }
     const long long h = h0 + h_i - ah;
     n1[k] = a1; n2[k] = a2; w1x[k] = w1; w2x[k] = w2;
@@ -178,10 +183,10 @@ __device__ __forceinline__ void place_lists_of(const PlaceArgs& p, const TileCou
       p.h_off[g] = h;
       if (p.counts_out && g >= p.n_always) p.counts_out[g - p.n_always] = cnt;
     }
-    run0 += __shfl(run_i, 63, 64);
-    w1_0 += __shfl(w1_i, 63, 64);
-    w2_0 += __shfl(w2_i, 63, 64);
-    h0 += __shfl(h_i, 63, 64);
+    run0 += wave_last(run_i);
+    w1_0 += wave_last(w1_i);
+    w2_0 += wave_last(w2_i);
+    h0 += wave_last(h_i);
   }
   if (lane == 0) {
     p.seg_off[p.G] = run0;
@@ -234,9 +239,9 @@ __device__ __forceinline__ void place_lists_of(const PlaceArgs& p, const TileCou
       const int n_items = list == 0 ? n1[k] : n2[k];
       const int cnt = tc.tot[k], wp = lw.w[k];
       if (n_items > 0) {
-        const int row_tiles = cdiv(cnt, bm), col_tiles = n_items / row_tiles;
+        const int row_tiles = rt[list][k], col_tiles = ct[list][k];
         const int depth = (list == 0 ? cdiv(p.d, 64) : cdiv(wp, 64)) + TILE_FIXED_COST;
-        const int full = cnt / bm, rem = cnt - full * bm;
+        const int full = row_tiles * bm == cnt ? row_tiles : row_tiles - 1, rem = cnt - full * bm;
         int last = 0;
         if (rem > 0) {
           last = blocks_full;
@@ -248,9 +253,9 @@ __device__ __forceinline__ void place_lists_of(const PlaceArgs& p, const TileCou
         }
         gc[k] = (long long)col_tiles * depth * (full * blocks_full + last);
       }
-      const long long ci = wave_incl_scan(gc[k], lane);
+      const long long ci = wave_incl_scan(gc[k]);
       gx[k] = c0 + ci - gc[k];
-      c0 += __shfl(ci, 63, 64);
+      c0 += wave_last(ci);
     }
 #pragma unroll
     for (int k = 0; k < GPL; ++k) {

@@ -790,7 +790,7 @@ __device__ __forceinline__ void route_place_body(const RouterDev& r, RouteIO io,
     if (wave == 0) {
       const int cnt = lane < pl.n_always ? T : (lane < pl.G ? hist[lane] : 0);
       const long long ah = (long long)cnt * lw.w[0];
-      const long long h_incl = wave_incl_scan(ah, lane);
+      const long long h_incl = wave_incl_scan(ah);
       if (lane == group) {
         mine->cnt = cnt;
         mine->h_off = h_incl - ah;
