@@ -448,41 +448,19 @@ static constexpr DecodeK decode_k(int d) {
   if (ks > 40) return {0, 0};
   return ks % 8 == 0 ? DecodeK{8, ks / 8} : ks % 10 == 0 ? DecodeK{10, ks / 10} : DecodeK{0, 0};
 }
-// The runs of decode_score_kernel at such a width.  It holds one operand, not two: the fewest runs of an even number of at
-// most 16 steps.
-static constexpr DecodeK score_k(int d) {
-  const int ks = decode_k(d).ksteps * decode_k(d).nch;
-  for (int nch = 1; 2 * nch <= ks; ++nch)
-    if (ks % (2 * nch) == 0 && ks / nch <= 16) return {ks / nch, nch};
-  return {0, 0};
-}
 // Every width served is covered to its end, in runs that the dispatches below have.
 static constexpr bool decode_widths_covered() {
   for (int d = 256; d <= 65536; d += 256) {
-    const DecodeK k = decode_k(d), s = score_k(d);
+    const DecodeK k = decode_k(d);
     if (k.ksteps == 0) continue;
-    if (k.ksteps * k.nch * 256 != d || s.ksteps * s.nch * 256 != d) return false;
+    if (k.ksteps * k.nch * 256 != d) return false;
     if (k.nch > 1 ? k.ksteps != 8 && k.ksteps != 10 : k.ksteps % 2 != 0 || k.ksteps > 16) return false;
-    if (s.ksteps % 2 != 0 || s.ksteps > 16) return false;
   }
   return true;
 }
 static_assert(decode_widths_covered(), "a model width without its step count");
-// CALL(KSTEPS) with the template argument for `ksteps` steps; returns an error from the enclosing function where there
-// is none.
-#define CMOE_EVEN_KSTEPS(ksteps, CALL)             \
-  switch (ksteps) {                                \
-    case 16: CALL(16); break;                      \
-    case 14: CALL(14); break;                      \
-    case 12: CALL(12); break;                      \
-    case 10: CALL(10); break;                      \
-    case 8: CALL(8); break;                        \
-    case 6: CALL(6); break;                        \
-    case 4: CALL(4); break;                        \
-    case 2: CALL(2); break;                        \
-    default: return hipErrorInvalidValue;          \
-  }
-// CALL(KSTEPS, RUNS) with the template arguments for model width d, likewise.
+// CALL(KSTEPS, RUNS) with the template arguments for model width d; returns an error from the enclosing function where there
+// are none.
 #define CMOE_DECODE_KSTEPS(d, CALL)                \
   switch (decode_k(d).nch > 1 ? -decode_k(d).ksteps : decode_k(d).ksteps) { \
     case -8: CALL(8, true); break;                 \

@@ -357,11 +357,9 @@ __global__ __launch_bounds__(256) void router_simt_kernel(RouterDev r, RouteIO i
 // memory, then the four partial sums are added in a fixed order through LDS.  NT = n_rows / 32 <= 5.
 constexpr int RT_TOK = 32;
 
-// COPY: the tokens also go to xt, [K step of 32][token][32].
-template <int NT, bool COPY>
+template <int NT>
 __global__ __launch_bounds__(256) void router_gemm_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wr,
-                                                          int d, int64_t T, int k_slice, float* __restrict__ partial,
-                                                          bf16_t* __restrict__ xt) {
+                                                          int d, int64_t T, int k_slice, float* __restrict__ partial) {
   __shared__ float red[RT_TOK][NT * 32 + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t t0 = (int64_t)blockIdx.x * RT_TOK;
@@ -395,23 +393,15 @@ __global__ __launch_bounds__(256) void router_gemm_kernel(const bf16_t* __restri
 #pragma unroll
       for (int ni = 0; ni < NT; ++ni) acc[ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s4], b[ni][s4], acc[ni], 0, 0, 0);
   };
-  auto copy_chunk = [&](int kc, bf16x8_t (&a)[4]) {
-    if (!COPY || t0 + l32 >= T) return;
-#pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4)
-      *reinterpret_cast<bf16x8_t*>(xt + (((int64_t)(kc / 32 + s4 / 2) * T + t) * 32 + (s4 % 2) * 16 + lh * 8)) = a[s4];
-  };
   int kc = k_begin + wave * 64;
   if (kc < k_end) load_chunk(kc, a0, b0);
   while (kc < k_end) {
     if (kc + 256 < k_end) load_chunk(kc + 256, a1, b1);
     mma_chunk(a0, b0);
-    copy_chunk(kc, a0);
     kc += 256;
     if (kc >= k_end) break;
     if (kc + 256 < k_end) load_chunk(kc + 256, a0, b0);
     mma_chunk(a1, b1);
-    copy_chunk(kc, a1);
     kc += 256;
   }
   for (int wsel = 0; wsel < 4; ++wsel) {
@@ -639,65 +629,71 @@ __global__ __launch_bounds__(512) void score_route_kernel(RouterDev r, RouteIO i
 // (Fusing all three behind a device-wide arrival counter was tried: on this multi-die part a device-scope
 // release/acquire pair writes back and invalidates the whole L2, which costs far more than a launch.)
 //
-// decode_score_kernel: one wave per (16 router rows, eighth of K): v_mfma_f32_16x16x32_bf16 with the router rows
-// as the A operand, all loads of the wave in flight at once; the eight K-slice partials of a row go to
-// pre_g[slice][token][row] and are added in slice order by route_place_kernel.  Eight times as many
-// workgroups as a K loop inside the workgroup would give: the router matrix (0.5 MB at d = 4096) comes
-// cold from HBM, so the launch is one memory latency long instead of several.
+// decode_score_kernel: a workgroup per (16 router rows, eighth of K, 16 tokens), v_mfma_f32_16x16x32_bf16 with the router rows
+// as the A operand.  Its four waves take a quarter of the slice each, all their loads in flight at once, and their sums
+// are added in wave order through LDS; the eight K-slice partials of a row go to pre_g[slice][token][row] and are added in
+// slice order by route_place_kernel.  The router matrix comes cold from HBM, so the launch is bound by one memory latency:
+// what counts is that nothing is asked for after something else has arrived.  (With a wave per slice, 32
+// loads behind one another, up to 16 tokens and router_gemm_kernel beyond / now, us per forward: d = 4096, 16 experts, one token
+// 22.9 / 21.5, 4 tokens 42.5 / 39.5, 16 tokens 58.1 / 55.0, 32 tokens 69.6 / 65.5; d = 8192, 8 experts, 2 tokens 67.2 / 59.9, 5 tokens
+// 79.6 / 74.3; d = 5120, 16 experts, 30 tokens 84.0 / 75.3; 8 outer experts, d = 4096, 4 tokens 161.5 / 158.8.)
+// Rows that pad the groups of 32 experts or the outer logits are left out; their partials are not written, and
+// the sums that are made of them are not used.
 constexpr int DEC_SLICES = 8;
 
-// (COPY as a template argument: as a test in the loop it cost one token 0.2 us)
-template <int NTT, int KSTEPS, bool COPY>
-__global__ __launch_bounds__(64) void decode_score_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wr,
-                                                          int d, int nch, int T, int n_rows, float* __restrict__ pre_g,
-                                                          bf16_t* __restrict__ xt) {
-  const int lane = threadIdx.x;
-  const int slice = blockIdx.y;
+// Row block rb holds rows in use: n_scored gate and up rows in groups of 32 + 32, then n_lin linear rows.
+__device__ __forceinline__ bool row_block_used(const RouterDev& r, int rb) {
+  const int lin = rb - r.n_sw_rows / 16;
+  return lin >= 0 ? lin * 16 < r.n_lin : (rb / 4) * IL + (rb & 1) * 16 < r.n_scored;
+}
+
+// CH: K steps of a wave's quarter in flight together.  COPY: the tokens also go to xt, [K step of 32][token][32].
+template <int CH, bool COPY>
+__global__ __launch_bounds__(256) void decode_score_kernel(RouterDev r, const bf16_t* __restrict__ x, const bf16_t* __restrict__ wr,
+                                                           int tiled, int d, int T, int n_rows, float* __restrict__ pre_g,
+                                                           bf16_t* __restrict__ xt) {
+  __shared__ float red[4][16][20];                             // [wave][token][row]
+  const int rb = blockIdx.x, slice = blockIdx.y, t0 = blockIdx.z * 16;
+  if (!row_block_used(r, rb)) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kq = lane >> 4;
-  const int row0 = blockIdx.x * 16;
-  const int kbase = slice * (KSTEPS * 32 * nch) + kq * 8;
-  const bf16_t* wrow = wr + (int64_t)(row0 + r16) * d + kbase;
-  floatx4_t acc[NTT];
+  const int steps = d / (DEC_SLICES * 32), per = (steps + 3) / 4;
+  const int first = wave * per, n = steps - first < per ? steps - first : per;
+  const int k0 = slice * steps + first;
+  // (tiled: the copy in operand order, K step k of row block rb is the 1 KB at ((rb * d / 32 + k) * 64 + lane) * 8)
+  const bf16_t* w = tiled ? wr + (((int64_t)rb * (d >> 5) + k0) * 64 + lane) * 8 : wr + (int64_t)(rb * 16 + r16) * d + k0 * 32 + kq * 8;
+  const int wadv = tiled ? 512 : 32;
+  const int t = t0 + r16;
+  const bf16_t* xr = x + (int64_t)(t < T ? t : T - 1) * d + k0 * 32 + kq * 8;      // (past the last token: a copy, never stored)
+  floatx4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int c = 0; c < n; c += CH) {
+    bf16x8_t a[CH], b[CH];
 #pragma unroll
-  for (int tt = 0; tt < NTT; ++tt)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[tt][i] = 0.0f;
-  int ch = 0;
-  do {
-    bf16x8_t a[KSTEPS];
-#pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) a[ks] = *reinterpret_cast<const bf16x8_t*>(wrow + ch * (KSTEPS * 32) + ks * 32);
-#pragma unroll
-    for (int tt = 0; tt < NTT; ++tt) {
-      const int col = tt * 16 + r16;
-      const bool ok = col < T;
-      const bf16_t* xr = x + (int64_t)(ok ? col : 0) * d + kbase + ch * (KSTEPS * 32);
-#pragma unroll
-      for (int ks = 0; ks < KSTEPS; ++ks) {
-        bf16x8_t b;
-        if (ok) b = *reinterpret_cast<const bf16x8_t*>(xr + ks * 32);
-        else {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) b[i] = (__bf16)0.0f;
-        }
-        acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks], b, acc[tt], 0, 0, 0);
-        // (the first row block's workgroups also leave the copy [K step of 32][token][32])
-        if (COPY && ok && blockIdx.x == 0)
-          *reinterpret_cast<bf16x8_t*>(xt + ((int64_t)(slice * nch * KSTEPS + ch * KSTEPS + ks) * T + col) * 32 + kq * 8) = b;
-      }
+    for (int s = 0; s < CH; ++s) {
+      const int k = c + s < n ? c + s : n - 1;
+      a[s] = *reinterpret_cast<const bf16x8_t*>(w + k * wadv);
+      b[s] = *reinterpret_cast<const bf16x8_t*>(xr + k * 32);
     }
-  } while (++ch < nch);
-  // D layout: lane holds rows kq*4 .. kq*4+3 of column (token) r16
 #pragma unroll
-  for (int tt = 0; tt < NTT; ++tt) {
-    const int col = tt * 16 + r16;
-    if (col < T) *reinterpret_cast<floatx4_t*>(pre_g + ((int64_t)slice * T + col) * n_rows + row0 + kq * 4) = acc[tt];
+    for (int s = 0; s < CH; ++s) {
+      if (c + s >= n) break;
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], b[s], acc, 0, 0, 0);
+      // (the first row block's workgroups also leave the copy)
+      if (COPY && rb == 0 && t < T) *reinterpret_cast<bf16x8_t*>(xt + ((int64_t)(k0 + c + s) * T + t) * 32 + kq * 8) = b[s];
+    }
   }
+  *reinterpret_cast<floatx4_t*>(&red[wave][r16][kq * 4]) = acc;      // D layout: rows kq*4 .. + 3 of column (token) r16
+  __syncthreads();
+  const int tok = tid >> 4, row = tid & 15;
+  if (t0 + tok < T)
+    pre_g[((int64_t)slice * T + t0 + tok) * n_rows + rb * 16 + row] =
+        ((red[0][tok][row] + red[1][tok][row]) + red[2][tok][row]) + red[3][tok][row];
 }
 
 // The same partials computed inside a workgroup of eight waves instead of by a launch of its own: wave w takes
-// K slice w of every block of 16 router rows, with decode_score_kernel's operands and MFMA sequence (the
-// router read from its copy in operand order), so the values are the same bits; they go to LDS as part[slice][token][row].  For at most 16 tokens.  The caller
+// K slice w of every block of 16 router rows, in decode_score_kernel's four chains (the router read from its copy in
+// operand order), so the values are the same bits; they go to LDS as part[slice][token][row].  For at most 16 tokens.  The caller
 // puts a barrier between this and the first read of `part`.
 template <int KSTEPS>
 __device__ __forceinline__ void score_slices_in_workgroup(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wr,
@@ -722,12 +718,15 @@ __device__ __forceinline__ void score_slices_in_workgroup(const bf16_t* __restri
     bf16x8_t a[KSTEPS];
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks) a[ks] = *reinterpret_cast<const bf16x8_t*>(wop + ks * 512);
-    floatx4_t acc;
+    constexpr int PER = (KSTEPS + 3) / 4;
+    floatx4_t acc[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] = 0.0f;
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks], b[ks], acc, 0, 0, 0);
-    if (ok) *reinterpret_cast<floatx4_t*>(part + ((int64_t)slice * T + r16) * n_rows + row0 + kq * 4) = acc;
+      for (int i = 0; i < 4; ++i) acc[q][i] = 0.0f;
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) acc[ks / PER] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks], b[ks], acc[ks / PER], 0, 0, 0);
+    if (ok) *reinterpret_cast<floatx4_t*>(part + ((int64_t)slice * T + r16) * n_rows + row0 + kq * 4) = ((acc[0] + acc[1]) + acc[2]) + acc[3];
   }
 }
 
@@ -1020,8 +1019,7 @@ static hipError_t launch_score_route(const Engine& e, const RouteIO& io, const v
 }
 
 // Pre-activation partials [slice][T][n_rows] of all router rows by router_gemm_kernel.
-static hipError_t launch_scorer_gemm(const Engine& e, const void* x, int64_t T, float* partial, hipStream_t s,
-                                     int& n_slices, bf16_t* xt = nullptr) {
+static hipError_t launch_scorer_gemm(const Engine& e, const void* x, int64_t T, float* partial, hipStream_t s, int& n_slices) {
   const int n_rows = e.r.n_sw_rows + e.r.n_lin_rows;
   const int n_tt = (int)((T + RT_TOK - 1) / RT_TOK);
   n_slices = scorer_slices(e, T);
@@ -1029,9 +1027,7 @@ static hipError_t launch_scorer_gemm(const Engine& e, const void* x, int64_t T, 
   dim3 grid(n_tt, n_slices), block(256);
   const bf16_t* xx = static_cast<const bf16_t*>(x);
   const bf16_t* ww = static_cast<const bf16_t*>(e.wr);
-#define CMOE_SCORER(NT)                                                                                              \
-  if (xt) hipLaunchKernelGGL((router_gemm_kernel<NT, true>), grid, block, 0, s, xx, ww, e.d, T, k_slice, partial, xt); \
-  else hipLaunchKernelGGL((router_gemm_kernel<NT, false>), grid, block, 0, s, xx, ww, e.d, T, k_slice, partial, xt)
+#define CMOE_SCORER(NT) hipLaunchKernelGGL(router_gemm_kernel<NT>, grid, block, 0, s, xx, ww, e.d, T, k_slice, partial)
   switch (n_rows / 32) {
     case 1: CMOE_SCORER(1); break;
     case 2: CMOE_SCORER(2); break;
@@ -1043,12 +1039,9 @@ static hipError_t launch_scorer_gemm(const Engine& e, const void* x, int64_t T, 
   return hipGetLastError();
 }
 
-// One tile of at most 64 tokens is scored in one launch and selected + placed by one workgroup in a second.
-// Up to 16 tokens (one MFMA token tile) the scorer is decode_score_kernel, which beats the general one by
-// 3-4 us there; from 17 tokens on, and where the layer's width has no decode kernels, it is the general scorer, whose
-// work spreads over hundreds of workgroups
-// (measured at d = 4096, 13 routed experts).  The larger batches need the tile's pre-activations and scores
-// to fit the 64 KB of LDS a workgroup gets by default next to 14 KB of static arrays.
+// One tile of at most 64 tokens is scored in one launch and selected + placed by one workgroup in a second.  The larger
+// batches need the tile's pre-activations and scores to fit the 64 KB of LDS a workgroup gets by default next to 14 KB of
+// static arrays.
 constexpr int FRONT_SCORE_MAX_T = 16;
 bool decode_front_ok(const Engine& e, int64_t T) {
   const int n_rows = e.r.n_sw_rows + e.r.n_lin_rows;
@@ -1075,27 +1068,26 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
   const int n_rows = e.r.n_sw_rows + e.r.n_lin_rows;
   float* pre_g = reinterpret_cast<float*>(ws + L.scores);
   const int Ti = (int)T;
-  int n_slices = DEC_SLICES;
+  const int n_slices = DEC_SLICES;
   bf16_t* xt = front_lays_tokens(e, T) ? reinterpret_cast<bf16_t*>(ws + L.y_slots) : nullptr;
   hipError_t err = hipSuccess;
   // one token, every gate/up unit in the selection launch: with front_all = 2 that launch also scores
   const bool own_scores = L.gate_up_done && tuning().front_all >= 2 && e.wr_tiled != nullptr && decode_k(e.d).nch == 1;
   if (own_scores) {
-  } else if (T <= FRONT_SCORE_MAX_T && decode_path_ok(e, T)) {
-    dim3 grid(n_rows / 16, DEC_SLICES), block(64);
+  } else {
+    const dim3 grid(n_rows / 16, DEC_SLICES, (unsigned)((T + 15) / 16)), block(256);
     const bf16_t* xx = static_cast<const bf16_t*>(x);
-    const bf16_t* ww = static_cast<const bf16_t*>(e.wr);
-    const DecodeK sk = score_k(e.d);
-#define CMOE_SCORE(KS)                                                                                                                   \
-  if (xt) hipLaunchKernelGGL((decode_score_kernel<1, KS, true>), grid, block, 0, s, xx, ww, e.d, sk.nch, Ti, n_rows, pre_g, xt); \
-  else hipLaunchKernelGGL((decode_score_kernel<1, KS, false>), grid, block, 0, s, xx, ww, e.d, sk.nch, Ti, n_rows, pre_g, xt)
+    const int tiled = e.wr_tiled != nullptr ? 1 : 0;
+    const bf16_t* ww = static_cast<const bf16_t*>(tiled ? e.wr_tiled : e.wr);
+#define CMOE_SCORE(CH)                                                                                                              \
+  if (xt) hipLaunchKernelGGL((decode_score_kernel<CH, true>), grid, block, 0, s, e.r, xx, ww, tiled, e.d, Ti, n_rows, pre_g, xt); \
+  else hipLaunchKernelGGL((decode_score_kernel<CH, false>), grid, block, 0, s, e.r, xx, ww, tiled, e.d, Ti, n_rows, pre_g, xt)
     // (measurement aid: repeat_stage = 6 issues the scoring launch twice; it overwrites its partials)
-    for (int rep = tuning().repeat_stage == 6 ? 2 : 1; rep > 0; --rep)
-      CMOE_EVEN_KSTEPS(sk.ksteps, CMOE_SCORE)
+    for (int rep = tuning().repeat_stage == 6 ? 2 : 1; rep > 0; --rep) {
+      if (e.d <= 4 * 4 * DEC_SLICES * 32) { CMOE_SCORE(4); } else { CMOE_SCORE(8); }
+    }
 #undef CMOE_SCORE
     err = hipGetLastError();
-  } else {
-    err = launch_scorer_gemm(e, x, T, pre_g, s, n_slices, xt);
   }
   if (err != hipSuccess) return err;
   if (tuning().skip_stage == 6) return hipSuccess;        // measurement aid: the scoring launch only

@@ -377,3 +377,19 @@ def test_router_row_blocks_in_use(binding, d, N, n_s, k, T, gate):
     check_flat(cfg, weights, part, x, out, u=u, b=b)
     assert np.array_equal(out["counts"], np.bincount(out["topk"].ravel(), minlength=cfg.n_routed))
     layer.close()
+
+
+@pytest.mark.parametrize("d,N,n_s,k,T", [
+    (512, 17, 1, 3, 1),         # two K steps per slice: two of the four waves; 16 routed experts: two of four row blocks
+    (512, 18, 1, 3, 16),        # 17: all four
+    (512, 50, 1, 3, 17),        # 49: six of eight
+    (768, 12, 1, 2, 33),        # three steps, a third block of tokens with one token
+    (2304, 12, 0, 2, 64),       # nine steps: waves of three, the last none
+    (4352, 8, 1, 2, 18),        # seventeen: waves of five, in two runs
+    (10240, 8, 1, 2, 3),        # forty: waves of ten, in runs of eight and two
+])
+def test_small_batch_scorer(binding, d, N, n_s, k, T):
+    """The scorer of at most 64 tokens: K steps over waves and runs, row blocks in use, blocks of 16 tokens."""
+    cfg, weights, part, x, layer = _case(binding, d, N, 16, n_s, k, T, seed=6)
+    check_flat(cfg, weights, part, x, layer.forward(x))
+    layer.close()
