@@ -14,6 +14,7 @@
 #include "cmoe_internal.h"
 #include "decode_device.h"
 #include "device_utils.h"
+#include "gemm_device.h"
 
 namespace cmoe {
 
@@ -144,70 +145,134 @@ __global__ __launch_bounds__(256) void decode_down_kernel(DecArgs p) {
 // timing.  All loads of an item are in flight together.
 constexpr int DC_CH = 8;
 constexpr int DC_WAVES = 16;
+// What an item needs of its group, in LDS: every lane requests all of it for its two groups at once, one round trip where the
+// offsets, then the widths, then (per item) offsets, width and places again were four.  us per forward before / now, with operands as
+// buffer loads: d = 4096, 16 experts, 4 tokens 38.8 / 38.6, 24 tokens 62.3 / 61.8; 32 experts, 32 tokens 67.7 / 67.9; d = 8192, one token
+// 61.7 / 61.2; d = 5120, one token 27.9 / 27.4; 8 outer experts, d = 4096, 4 tokens 157.4 / 156.1.
+struct DownGroups {
+  int32_t item0[MAX_GROUPS + 1];                  // prefix of work items over groups
+  int32_t seg0[MAX_GROUPS], cnt[MAX_GROUPS], wp[MAX_GROUPS];
+  int64_t w2_off[MAX_GROUPS], h_off[MAX_GROUPS];
+};
+// 16 bytes per lane from base + off (bytes; zeros where off >= size).
+__device__ __forceinline__ bf16x8_t ld_frag_buffer(const bf16_t* base, uint32_t size, uint32_t off) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, size, 0x00020000);
+  return __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
+#else
+  return zero_frag();
+#endif
+}
+// Called by one wave.
+__device__ __forceinline__ void load_down_groups(const DecArgs& p, int G, DownGroups& dg, int lane) {
+  constexpr int GPL = MAX_GROUPS / 64;
+  int s0[GPL], s1[GPL];
+  GroupDev gd[GPL];
+  int64_t ho[GPL];
+#pragma unroll
+  for (int k = 0; k < GPL; ++k) {
+    if (k > 0 && 64 * k >= G) break;
+    const int g = min(lane + 64 * k, G - 1);
+    s0[k] = p.seg_off[g];
+    s1[k] = p.seg_off[g + 1];
+    gd[k] = p.groups[g];
+    ho[k] = p.h_off[g];
+  }
+  int run0 = 0;
+#pragma unroll
+  for (int k = 0; k < GPL; ++k) {
+    if (k > 0 && 64 * k >= G) break;
+    const int g = lane + 64 * k;
+    const int cnt = g < G ? s1[k] - s0[k] : 0, n = cnt > 0 ? cdiv(gd[k].width_pad / 32, DC_CH) : 0;
+    const int inc = wave_incl_scan(n);
+    if (g < G) {
+      dg.item0[g] = run0 + inc - n;
+      dg.seg0[g] = s0[k];
+      dg.cnt[g] = cnt;
+      dg.wp[g] = gd[k].width_pad;
+      dg.w2_off[g] = gd[k].w2_off;
+      dg.h_off[g] = ho[k];
+    }
+    run0 += wave_last(inc);
+  }
+  if (lane == 0) dg.item0[G] = run0;
+}
+
 template <int NTT>
 __global__ __launch_bounds__(DC_WAVES * 64) void decode_down_combine_kernel(DecArgs p, const float* __restrict__ w_by_slot,
                                                                             bf16_t* __restrict__ y_out) {
   __shared__ float yacc[DC_WAVES][NTT * 16][17];
-  __shared__ int32_t item0[MAX_GROUPS + 1];       // prefix of work items over groups
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ DownGroups dg;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kq = lane >> 4;
   const int c0 = blockIdx.x * 16;
+  if (wave == 0) load_down_groups(p, p.G, dg, lane);
   float* mine = &yacc[wave][0][0];
   for (int e = lane; e < NTT * 16 * 17; e += 64) mine[e] = 0.0f;
-  if (wave == 0) {
-    int run0 = 0;
-#pragma unroll
-    for (int k = 0; k < MAX_GROUPS / 64; ++k) {
-      const int g = lane + 64 * k;
-      int n = 0;
-      if (g < p.G && p.seg_off[g + 1] > p.seg_off[g]) n = cdiv(p.groups[g].width_pad / 32, DC_CH);
-      const int inc = wave_incl_scan(n);
-      if (g < p.G) item0[g] = run0 + inc - n;
-      run0 += wave_last(inc);
-    }
-    if (lane == 0) item0[p.G] = run0;
-  }
   __syncthreads();
-  const int n_items = item0[p.G];
-  for (int u = wave; u < n_items; u += DC_WAVES) {
-    const int g = find_group(item0, p.G, u);
-    const int ks0 = (u - item0[g]) * DC_CH;
-    const int seg0 = p.seg_off[g], cnt = p.seg_off[g + 1] - seg0;
-    const int wp = p.groups[g].width_pad;
+  const int n_items = dg.item0[p.G];
+  // With two token tiles the next item's operands take the registers of this one's and are on their way while its products are
+  // added.  us per forward, requested when the item begins / ahead: d = 4096, 32 experts, 32 tokens 68.2 / 67.9, 16 experts, 32 tokens
+  // 65.9 / 65.5; one tile, 8 tokens, 16 experts 46.6 / 47.0, d = 8192, 5 tokens 74.5 / 74.9.
+  constexpr bool AHEAD = NTT > 1;
+  bf16x8_t a[DC_CH], b[NTT][DC_CH];
+  int tok[NTT];
+  float wt[NTT];
+  // Operands as buffer loads: rows past the group's tokens and steps past its width lie past the buffer's size and read
+  // as zeros, so that nothing branches and all loads of an item leave together.  (Weights of bf16 layers are tiled.)
+  auto request = [&](int u) {
+    const int g = find_group(dg.item0, p.G, u);
+    const int ks0 = (u - __builtin_amdgcn_readfirstlane(dg.item0[g])) * DC_CH;
+    const int seg0 = __builtin_amdgcn_readfirstlane(dg.seg0[g]), cnt = __builtin_amdgcn_readfirstlane(dg.cnt[g]);
+    const int wp = __builtin_amdgcn_readfirstlane(dg.wp[g]);
     const int ns = min(DC_CH, wp / 32 - ks0);
-    const int kadv = p.tiled ? TILE_ELEMS : 32;
-    const bf16_t* wrow = p.w2 + p.groups[g].w2_off +
-                         (p.tiled ? tiled_offset(c0 + r16, ks0 * 32 + kq * 8, wp / TILE_K)
-                                  : (int64_t)(c0 + r16) * wp + kq * 8 + ks0 * 32);
-    const bf16_t* hbase = p.h + p.h_off[g] + kq * 8 + ks0 * 32;
-    bf16x8_t a[DC_CH], b[NTT][DC_CH];
-    int tok[NTT];
-    float wt[NTT];
+    const bf16_t* wbase = uniform_ptr(p.w2 + dg.w2_off[g] + (int64_t)((c0 / 16) * (wp / 32) + ks0) * TILE_ELEMS);
+    const bf16_t* hbase = uniform_ptr(p.h + dg.h_off[g] + ks0 * 32);
+    const uint32_t wsize = (uint32_t)ns * (TILE_ELEMS * 2), hsize = (uint32_t)(cnt * wp - ks0 * 32) * 2u;
 #pragma unroll
-    for (int s = 0; s < DC_CH; ++s) a[s] = s < ns ? ld_frag(wrow + s * kadv) : zero_frag();
+    for (int s = 0; s < DC_CH; ++s) a[s] = ld_frag_buffer(wbase, wsize, (uint32_t)(r16 * 64 + kq * 16 + s * (TILE_ELEMS * 2)));
 #pragma unroll
     for (int tt = 0; tt < NTT; ++tt) {
-      const int col = tt * 16 + r16;
-      const bool ok = col < cnt;
-      const bf16_t* hrow = hbase + (int64_t)(ok ? col : 0) * wp;
+      if (tt * 16 >= cnt) continue;               // (uniform: most items have at most 16 tokens)
+      const int col = tt * 16 + r16, at = seg0 + min(col, cnt - 1);
+      const uint32_t row = (uint32_t)(col * wp * 2 + kq * 16);
 #pragma unroll
-      for (int s = 0; s < DC_CH; ++s) b[tt][s] = (ok && s < ns) ? ld_frag(hrow + s * 32) : zero_frag();
-      tok[tt] = ok ? p.slot2tok[seg0 + col] : -1;
-      wt[tt] = ok ? w_by_slot[seg0 + col] : 0.0f;
+      for (int s = 0; s < DC_CH; ++s) b[tt][s] = ld_frag_buffer(hbase, hsize, row + (s < ns ? (uint32_t)(s * 64) : DMA_NONE));
+      tok[tt] = p.slot2tok[at];
+      wt[tt] = w_by_slot[at];
     }
+    __builtin_amdgcn_sched_barrier(0);
+    return cnt;
+  };
+  int cnt = 0;                                    // tokens of the item whose operands are requested
+  if (AHEAD && wave < n_items) cnt = request(wave);
+  for (int u = wave; u < n_items; u += DC_WAVES) {
+    if (!AHEAD) cnt = request(u);
+    floatx4_t acc[NTT];
 #pragma unroll
     for (int tt = 0; tt < NTT; ++tt) {
-      floatx4_t acc;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] = 0.0f;
+      for (int i = 0; i < 4; ++i) acc[tt][i] = 0.0f;
+      if (tt * 16 >= cnt) continue;
 #pragma unroll
-      for (int s = 0; s < DC_CH; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], b[tt][s], acc, 0, 0, 0);
-      // accumulator element i: output column (lane/16)*4 + i, token of segment position lane%16
-      if (tok[tt] >= 0) {
+      for (int s = 0; s < DC_CH; ++s) acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], b[tt][s], acc[tt], 0, 0, 0);
+    }
+    int at[NTT];                                  // token of the lane's row, -1: there is none
+    float by[NTT];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) yacc[wave][tok[tt]][kq * 4 + i] += wt[tt] * acc[i];
+    for (int tt = 0; tt < NTT; ++tt) {
+      at[tt] = tt * 16 + r16 < cnt ? tok[tt] : -1;
+      by[tt] = wt[tt];
+    }
+    if (AHEAD && u + DC_WAVES < n_items) cnt = request(u + DC_WAVES);
+    // accumulator element i: output column (lane/16)*4 + i, token of segment position lane%16
+#pragma unroll
+    for (int tt = 0; tt < NTT; ++tt)
+      if (at[tt] >= 0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) yacc[wave][at[tt]][kq * 4 + i] += by[tt] * acc[tt][i];
       }
-    }
   }
   __syncthreads();
   for (int e = tid; e < (int)p.T * 16; e += DC_WAVES * 64) {
@@ -260,32 +325,21 @@ __global__ __launch_bounds__(DS_WAVES * 64) void decode_down_sparse_kernel(DecAr
                                                                            const float* __restrict__ nscale, int n_always,
                                                                            int mode, float tau, int cb_per_xcd) {
   __shared__ float yacc[DS_WAVES][2][16];
-  __shared__ int32_t item0[MAX_GROUPS + 1];
+  __shared__ DownGroups dg;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, kq = lane >> 4;
   const int cb = (blockIdx.x & 7) * cb_per_xcd + (blockIdx.x >> 3);
   if ((int)(blockIdx.x >> 3) >= cb_per_xcd || cb >= p.d / 16) return;
   const int c0 = cb * 16;
   if (lane < 32) yacc[wave][lane >> 4][lane & 15] = 0.0f;
-  if (wave == 0) {
-    int run0 = 0;
-#pragma unroll
-    for (int k = 0; k < MAX_GROUPS / 64; ++k) {
-      const int g = lane + 64 * k;
-      int n = 0;
-      if (g < n_always && p.seg_off[g + 1] > p.seg_off[g]) n = cdiv(p.groups[g].width_pad / 32, DC_CH);
-      const int inc = wave_incl_scan(n);
-      if (g < p.G) item0[g] = run0 + inc - n;
-      run0 += wave_last(inc);
-    }
-    if (lane == 0) item0[p.G] = run0;
-  }
+  if (n_always == 0 && tid == 0) dg.item0[0] = 0;
+  if (wave == 0 && n_always > 0) load_down_groups(p, n_always, dg, lane);
   __syncthreads();
   // ---- always-on groups: 16 columns x 8 K steps per work item, matrix cores ----
-  const int n_items = item0[p.G];
+  const int n_items = dg.item0[n_always];
   for (int u = wave; u < n_items; u += DS_WAVES) {
-    const int g = find_group(item0, p.G, u);
-    const int ks0 = (u - item0[g]) * DC_CH;
+    const int g = find_group(dg.item0, n_always, u);
+    const int ks0 = (u - dg.item0[g]) * DC_CH;
     const int seg0 = p.seg_off[g], cnt = p.seg_off[g + 1] - seg0;
     const int wp = p.groups[g].width_pad;
     const int ns = min(DC_CH, wp / 32 - ks0);
