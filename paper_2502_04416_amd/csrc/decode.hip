@@ -15,6 +15,7 @@
 #include "decode_device.h"
 #include "device_utils.h"
 #include "gemm_device.h"
+#include "work_item.h"
 
 namespace cmoe {
 
@@ -26,26 +27,17 @@ __device__ __forceinline__ void wave_lds_sync_decode() {
 }
 
 // Which unit is this workgroup?  Returns false when past the end of the list.
-__device__ __forceinline__ bool find_unit(const DecArgs& p, int units_single, int& g, int& local, int& seg0, int& cnt,
-                                          int& wp, int64_t& hoff) {
+__device__ __forceinline__ bool find_unit(const DecArgs& p, int units_single, WorkItem& it) {
   const int u = blockIdx.x;
   if (p.single) {
     if (u >= units_single) return false;
-    g = 0;
-    local = u;
-    seg0 = 0;
-    cnt = (int)p.T;
-    wp = p.groups[0].width_pad;
-    hoff = 0;
+    const GroupDev gd = p.groups[0];
+    it = {0, u, 0, (int)p.T, gd.width_pad, gd.w1_row0, 0, gd.w2_off};
     return true;
   }
+  const GroupLanes gl = request_groups(p.work, p.seg_off, p.groups, p.h_off, p.G);
   if (u >= p.work[p.G]) return false;
-  g = find_group(p.work, p.G, u);
-  local = u - p.work[g];
-  seg0 = p.seg_off[g];
-  cnt = p.seg_off[g + 1] - seg0;
-  wp = p.groups[g].width_pad;
-  hoff = p.h_off[g];
+  it = find_item(gl, p.G, u);
   return true;
 }
 
@@ -53,10 +45,9 @@ __device__ __forceinline__ bool find_unit(const DecArgs& p, int units_single, in
 template <int NTT, int KSTEPS, bool RUNS>
 __global__ __launch_bounds__(512) void decode_gate_up_kernel(DecArgs p) {
   __shared__ DecGateUpRed<NTT> red;
-  int g, local, seg0, cnt, wp;
-  int64_t hoff;
-  if (!find_unit(p, p.single ? p.groups[0].width_pad / p.unit1 : 0, g, local, seg0, cnt, wp, hoff)) return;
-  decode_gate_up<NTT, KSTEPS, RUNS>(p, g, local, seg0, cnt, wp, hoff, red);
+  WorkItem it;
+  if (!find_unit(p, p.single ? p.groups[0].width_pad / p.unit1 : 0, it)) return;
+  decode_gate_up<NTT, KSTEPS, RUNS>(p, it.w1_row0, it.local, it.seg0, it.cnt, it.wp, it.hoff, red);
 }
 
 // ---- down: Y[slot][c] = sum_n H[slot][n] * Wdown[n][c] for 16 output columns of one group --------------
@@ -64,13 +55,13 @@ __global__ __launch_bounds__(512) void decode_gate_up_kernel(DecArgs p) {
 template <int NTT>
 __global__ __launch_bounds__(256) void decode_down_kernel(DecArgs p) {
   __shared__ float red[4][NTT][16][17];
-  int g, local, seg0, cnt, wp;
-  int64_t hoff;
-  if (!find_unit(p, p.single ? p.d / 16 : 0, g, local, seg0, cnt, wp, hoff)) return;
+  WorkItem it;
+  if (!find_unit(p, p.single ? p.d / 16 : 0, it)) return;
+  const int seg0 = it.seg0, cnt = it.cnt, wp = it.wp;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, kq = lane >> 4;
-  const int c0 = local * 16;
-  const bf16_t* wrow = p.w2 + p.groups[g].w2_off +
+  const int c0 = it.local * 16;
+  const bf16_t* wrow = p.w2 + it.w2_off +
                        (p.tiled ? tiled_offset(c0 + r16, kq * 8, wp / TILE_K) : (int64_t)(c0 + r16) * wp + kq * 8);
   const int kadv = p.tiled ? TILE_ELEMS : 32;                 // elements from one K step's operand to the next
   const bf16_t* hrow[NTT];
@@ -79,7 +70,7 @@ __global__ __launch_bounds__(256) void decode_down_kernel(DecArgs p) {
   for (int tt = 0; tt < NTT; ++tt) {
     const int col = tt * 16 + r16;
     hok[tt] = col < cnt;
-    hrow[tt] = p.h + hoff + (int64_t)(hok[tt] ? col : 0) * wp + kq * 8;
+    hrow[tt] = p.h + it.hoff + (int64_t)(hok[tt] ? col : 0) * wp + kq * 8;
   }
   floatx4_t acc[NTT];
 #pragma unroll

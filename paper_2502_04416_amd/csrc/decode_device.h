@@ -44,14 +44,14 @@ __device__ __forceinline__ bf16x8_t zero_frag() {
 template <int NTT>
 struct DecGateUpRed { float v[8][2][NTT][16][17]; };
 
-// H[slot][n] = Swish(x . wgate_n) * (x . wup_n) for the 16 neurons [local*16, local*16+16) of group g, whose
+// H[slot][n] = Swish(x . wgate_n) * (x . wup_n) for the 16 neurons [local*16, local*16+16) of the group at packed row w1_row0, whose
 // cnt <= 16*NTT tokens are the slots seg0 .. seg0+cnt-1 and whose rows of H start at element hoff.
 // Called by all 512 threads of a workgroup: 8 waves, wave w multiplies the K slice [w*d/8, (w+1)*d/8).
 // NTT = token tiles of 16.  KSTEPS = d/8/32.  The _runs forms below take a wave's slice in p.nch runs of KSTEPS steps
 // (d above 4096: the operands of the whole slice would leave room for one workgroup per CU); as one loop for both
 // cases the code of the single run came out 5-8 % slower (62 -> 67 us at 16 tokens, d = 4096).
 template <int NTT, int KSTEPS>
-__device__ __forceinline__ void decode_gate_up_unit(const DecArgs& p, int g, int local, int seg0, int cnt, int wp,
+__device__ __forceinline__ void decode_gate_up_unit(const DecArgs& p, int w1_row0, int local, int seg0, int cnt, int wp,
                                                     int64_t hoff, DecGateUpRed<NTT>& redbuf) {
   float (*red)[2][NTT][16][17] = redbuf.v;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -60,7 +60,7 @@ __device__ __forceinline__ void decode_gate_up_unit(const DecArgs& p, int g, int
   const int kbase = wave * (KSTEPS * 32) + kq * 8;
   // weight rows of this lane: packed row = (n / IL) * 2 * IL + n % IL (+ IL for the up row)
   const int n = neuron0 + r16;
-  const int64_t grow = (int64_t)p.groups[g].w1_row0 + (n / IL) * 2 * IL + (n % IL);
+  const int64_t grow = (int64_t)w1_row0 + (n / IL) * 2 * IL + (n % IL);
   // (grow is a multiple of 16 plus lane%16, kbase a multiple of 32 plus (lane/16)*8: one tile per K step)
   const bf16_t* wg = p.w1 + (p.tiled ? tiled_offset(grow, kbase, p.ldw / TILE_K) : grow * p.ldw + kbase);
   const bf16_t* wu = wg + (p.tiled ? (int64_t)(IL / TILE_ROWS) * (p.ldw / TILE_K) * TILE_ELEMS : (int64_t)IL * p.ldw);
@@ -119,7 +119,7 @@ __device__ __forceinline__ void decode_gate_up_unit(const DecArgs& p, int g, int
 }
 
 template <int NTT, int KSTEPS>
-__device__ __forceinline__ void decode_gate_up_unit_runs(const DecArgs& p, int g, int local, int seg0, int cnt, int wp,
+__device__ __forceinline__ void decode_gate_up_unit_runs(const DecArgs& p, int w1_row0, int local, int seg0, int cnt, int wp,
                                                     int64_t hoff, DecGateUpRed<NTT>& redbuf) {
   float (*red)[2][NTT][16][17] = redbuf.v;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -128,7 +128,7 @@ __device__ __forceinline__ void decode_gate_up_unit_runs(const DecArgs& p, int g
   const int kbase = wave * (KSTEPS * 32 * p.nch) + kq * 8;
   // weight rows of this lane: packed row = (n / IL) * 2 * IL + n % IL (+ IL for the up row)
   const int n = neuron0 + r16;
-  const int64_t grow = (int64_t)p.groups[g].w1_row0 + (n / IL) * 2 * IL + (n % IL);
+  const int64_t grow = (int64_t)w1_row0 + (n / IL) * 2 * IL + (n % IL);
   // (grow is a multiple of 16 plus lane%16, kbase a multiple of 32 plus (lane/16)*8: one tile per K step)
   const bf16_t* wg = p.w1 + (p.tiled ? tiled_offset(grow, kbase, p.ldw / TILE_K) : grow * p.ldw + kbase);
   const bf16_t* wu = wg + (p.tiled ? (int64_t)(IL / TILE_ROWS) * (p.ldw / TILE_K) * TILE_ELEMS : (int64_t)IL * p.ldw);
@@ -203,7 +203,7 @@ __device__ __forceinline__ void decode_gate_up_unit_runs(const DecArgs& p, int g
 // 512-byte pieces instead of 1 KB.  K slices, their order and the order of the final sum are those of the
 // 16-neuron unit: H comes out bit for bit the same.
 template <int NTT, int KSTEPS>
-__device__ __forceinline__ void decode_gate_up_unit8(const DecArgs& p, int g, int local, int seg0, int cnt, int wp,
+__device__ __forceinline__ void decode_gate_up_unit8(const DecArgs& p, int w1_row0, int local, int seg0, int cnt, int wp,
                                                      int64_t hoff, DecGateUpRed<NTT>& redbuf) {
   float (*red)[2][NTT][16][17] = redbuf.v;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -211,7 +211,7 @@ __device__ __forceinline__ void decode_gate_up_unit8(const DecArgs& p, int g, in
   const int neuron0 = local * 8;
   const int kbase = wave * (KSTEPS * 32) + kq * 8;
   const int n = neuron0 + (r16 & 7);
-  const int64_t grow = (int64_t)p.groups[g].w1_row0 + (n / IL) * 2 * IL + (n % IL) + (r16 >= 8 ? IL : 0);
+  const int64_t grow = (int64_t)w1_row0 + (n / IL) * 2 * IL + (n % IL) + (r16 >= 8 ? IL : 0);
   const bf16_t* wrow = p.w1 + (p.tiled ? tiled_offset(grow, kbase, p.ldw / TILE_K) : grow * p.ldw + kbase);
   const int kadv = p.tiled ? TILE_ELEMS : 32;
   bf16x8_t a[KSTEPS];
@@ -252,7 +252,7 @@ __device__ __forceinline__ void decode_gate_up_unit8(const DecArgs& p, int g, in
 }
 
 template <int NTT, int KSTEPS>
-__device__ __forceinline__ void decode_gate_up_unit8_runs(const DecArgs& p, int g, int local, int seg0, int cnt, int wp,
+__device__ __forceinline__ void decode_gate_up_unit8_runs(const DecArgs& p, int w1_row0, int local, int seg0, int cnt, int wp,
                                                      int64_t hoff, DecGateUpRed<NTT>& redbuf) {
   float (*red)[2][NTT][16][17] = redbuf.v;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -260,7 +260,7 @@ __device__ __forceinline__ void decode_gate_up_unit8_runs(const DecArgs& p, int 
   const int neuron0 = local * 8;
   const int kbase = wave * (KSTEPS * 32 * p.nch) + kq * 8;
   const int n = neuron0 + (r16 & 7);
-  const int64_t grow = (int64_t)p.groups[g].w1_row0 + (n / IL) * 2 * IL + (n % IL) + (r16 >= 8 ? IL : 0);
+  const int64_t grow = (int64_t)w1_row0 + (n / IL) * 2 * IL + (n % IL) + (r16 >= 8 ? IL : 0);
   const bf16_t* wrow = p.w1 + (p.tiled ? tiled_offset(grow, kbase, p.ldw / TILE_K) : grow * p.ldw + kbase);
   const int kadv = p.tiled ? TILE_ELEMS : 32;
   floatx4_t acc[NTT];
@@ -308,14 +308,14 @@ __device__ __forceinline__ void decode_gate_up_unit8_runs(const DecArgs& p, int 
 
 // A unit of unit1 neurons, in whichever form.  RUNS: the slice of a wave is more than one run of KSTEPS steps.
 template <int NTT, int KSTEPS, bool RUNS>
-__device__ __forceinline__ void decode_gate_up(const DecArgs& p, int g, int local, int seg0, int cnt, int wp, int64_t hoff,
+__device__ __forceinline__ void decode_gate_up(const DecArgs& p, int w1_row0, int local, int seg0, int cnt, int wp, int64_t hoff,
                                                DecGateUpRed<NTT>& redbuf) {
   if constexpr (RUNS) {
-    if (p.unit1 == 8) decode_gate_up_unit8_runs<NTT, KSTEPS>(p, g, local, seg0, cnt, wp, hoff, redbuf);
-    else decode_gate_up_unit_runs<NTT, KSTEPS>(p, g, local, seg0, cnt, wp, hoff, redbuf);
+    if (p.unit1 == 8) decode_gate_up_unit8_runs<NTT, KSTEPS>(p, w1_row0, local, seg0, cnt, wp, hoff, redbuf);
+    else decode_gate_up_unit_runs<NTT, KSTEPS>(p, w1_row0, local, seg0, cnt, wp, hoff, redbuf);
   } else {
-    if (p.unit1 == 8) decode_gate_up_unit8<NTT, KSTEPS>(p, g, local, seg0, cnt, wp, hoff, redbuf);
-    else decode_gate_up_unit<NTT, KSTEPS>(p, g, local, seg0, cnt, wp, hoff, redbuf);
+    if (p.unit1 == 8) decode_gate_up_unit8<NTT, KSTEPS>(p, w1_row0, local, seg0, cnt, wp, hoff, redbuf);
+    else decode_gate_up_unit<NTT, KSTEPS>(p, w1_row0, local, seg0, cnt, wp, hoff, redbuf);
   }
 }
 
@@ -323,11 +323,11 @@ __device__ __forceinline__ void decode_gate_up(const DecArgs& p, int g, int loca
 // CS steps, the operands of the next chunk requested before the current one is multiplied, so that between one and two
 // chunks of weights are always on their way.  What bounds a unit is the stream of its weights from HBM; its tokens, NTT KB
 // for every KB of gate and every KB of up rows, come from L2.  NEUR = 16, or 8 as in decode_gate_up_unit8 (gate and up rows in
-// one operand).  row0, cnt: the unit's first slot and how many there are; columns past them repeat the first row and are not
+// one operand).  w1_row0: the group's first packed row; row0, cnt: the unit's first slot and how many there are; columns past them repeat the first row and are not
 // stored.  d must be a multiple of 256 * CS, the weights tiled.
 constexpr int STREAM_RED_FLOATS = 8 * 2 * 16 * 17;
 template <int NTT, int CS, int NEUR>
-__device__ __forceinline__ void stream_gate_up_unit(const DecArgs& p, int g, int local, int row0, int cnt, int wp, int64_t hoff,
+__device__ __forceinline__ void stream_gate_up_unit(const DecArgs& p, int w1_row0, int local, int row0, int cnt, int wp, int64_t hoff,
                                                     float* redbuf) {
   constexpr int OPS = NEUR / 8;                               // operands per K step: gate and up, or both in one
   float (*red)[OPS][16][17] = reinterpret_cast<float (*)[OPS][16][17]>(redbuf);
@@ -337,7 +337,7 @@ __device__ __forceinline__ void stream_gate_up_unit(const DecArgs& p, int g, int
   const int neuron0 = local * NEUR;
   const int steps = p.d / 256, kbase = wave * steps * 32 + kq * 8, chunks = steps / CS;
   const int n = neuron0 + (r16 & (NEUR - 1));
-  const int64_t grow = (int64_t)p.groups[g].w1_row0 + (n / IL) * 2 * IL + (n % IL) + (r16 >= NEUR ? IL : 0);
+  const int64_t grow = (int64_t)w1_row0 + (n / IL) * 2 * IL + (n % IL) + (r16 >= NEUR ? IL : 0);
   const bf16_t* w[OPS];
   w[0] = p.w1 + tiled_offset(grow, kbase, p.ldw / TILE_K);
   if (OPS == 2) w[OPS - 1] = w[0] + (int64_t)(IL / TILE_ROWS) * (p.ldw / TILE_K) * TILE_ELEMS;
@@ -426,10 +426,10 @@ __device__ __forceinline__ void stream_gate_up_unit(const DecArgs& p, int g, int
 
 // A unit in the instantiation for its rows; MAXT: token tiles of the fullest unit the caller can have.
 template <int MAXT, int CS, int NEUR>
-__device__ __forceinline__ void stream_gate_up(const DecArgs& p, int g, int local, int row0, int cnt, int wp, int64_t hoff, float* redbuf) {
-  if (MAXT == 1 || cnt <= 16) stream_gate_up_unit<1, CS, NEUR>(p, g, local, row0, cnt, wp, hoff, redbuf);
-  else if (MAXT == 2 || cnt <= 32) stream_gate_up_unit<MAXT < 2 ? MAXT : 2, CS, NEUR>(p, g, local, row0, cnt, wp, hoff, redbuf);
-  else stream_gate_up_unit<MAXT, NEUR == 8 ? CS : 2, NEUR>(p, g, local, row0, cnt, wp, hoff, redbuf);    // (16 neurons, four steps: spills)
+__device__ __forceinline__ void stream_gate_up(const DecArgs& p, int w1_row0, int local, int row0, int cnt, int wp, int64_t hoff, float* redbuf) {
+  if (MAXT == 1 || cnt <= 16) stream_gate_up_unit<1, CS, NEUR>(p, w1_row0, local, row0, cnt, wp, hoff, redbuf);
+  else if (MAXT == 2 || cnt <= 32) stream_gate_up_unit<MAXT < 2 ? MAXT : 2, CS, NEUR>(p, w1_row0, local, row0, cnt, wp, hoff, redbuf);
+  else stream_gate_up_unit<MAXT, NEUR == 8 ? CS : 2, NEUR>(p, w1_row0, local, row0, cnt, wp, hoff, redbuf);    // (16 neurons, four steps: spills)
 }
 
 // CALL(MAXT, CS) with the template arguments for a batch of T <= 64 tokens at model width d (a multiple of 512).

@@ -13,6 +13,7 @@
 #include "cmoe_internal.h"
 #include "device_utils.h"
 #include "gemm_device.h"
+#include "work_item.h"
 #include "lds_limit.h"
 
 namespace cmoe {
@@ -53,6 +54,11 @@ constexpr int min_waves_per_simd(int bm, int bn, int bkt, int stages, int nw) {
 // of the kernel runs in the instantiation for exactly that many blocks per wave (MI_ACT below; the blocks are
 // dealt to the WGM wave rows in turn): blocks past the end of a ragged segment are neither fetched nor
 // multiplied, so a tile costs what its rows cost, in steps of 32 * WGM rows.
+// Tiles up to this size ask for all groups before they know theirs (work_item.h): their launches are a round or two long.  us per
+// forward, one lookup after the other / at once: 16 experts, d = 4096, 70 tokens 75.3 / 74.6, 333 tokens 102.3 / 101.7; 32 experts, d =
+// 2048, 200 tokens 42.1 / 41.2; 256x256 tiles, 16 experts, 2048 tokens 200.3 / 200.8; 192x256, 32 experts, 4096 tokens 452.3 / 454.1.
+constexpr int LOW_TILE_AREA = 256 * 128;
+
 template <int BM, int BN, int BKT, int STAGES, int WGM, int WGN, int MODE, bool DYN = false>
 __global__ __launch_bounds__(WGM* WGN * 64)
 __attribute__((amdgpu_waves_per_eu(min_waves_per_simd(BM, BN, BKT, STAGES, WGM* WGN)))) void grouped_gemm_bf16_dma(GemmArgs p) {
@@ -75,6 +81,7 @@ __attribute__((amdgpu_waves_per_eu(min_waves_per_simd(BM, BN, BKT, STAGES, WGM* 
   static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "loader");
   static_assert(MODE != 1 || TN % 64 == 0, "gate/up pairs must stay inside a wave tile");
   static_assert(HR || (STAGES >= 2 && (STAGES - 2) * LPT < 64), "ring depth");
+  constexpr bool LOW_TILE = BM * BN <= LOW_TILE_AREA;
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -82,12 +89,16 @@ __attribute__((amdgpu_waves_per_eu(min_waves_per_simd(BM, BN, BKT, STAGES, WGM* 
   const int wm = wave / WGN, wn = wave % WGN;
   const int l32 = lane & 31, lh = lane >> 5;
 
-  int g = 0, cnt, seg0 = 0, wp;
-  int64_t hoff = 0;
+  int g = 0, cnt, seg0 = 0, wp, w1_row0 = 0;
+  int64_t hoff = 0, w2_off = 0;
   int n_work;
+  GroupLanes gl;
+  if (LOW_TILE && !p.single) gl = request_groups(p.work, p.seg_off, p.groups, p.h_off, p.G);
   if (p.single) {
     cnt = (int)p.T;
     wp = p.groups[0].width_pad;
+    if (LOW_TILE) w1_row0 = p.groups[0].w1_row0;
+    if (LOW_TILE) w2_off = p.groups[0].w2_off;
     const int nc = (MODE == 1) ? 2 * wp : p.d;
     n_work = ((cnt + BM - 1) / BM) * ((nc + BN - 1) / BN);
   } else {
@@ -116,12 +127,23 @@ __attribute__((amdgpu_waves_per_eu(min_waves_per_simd(BM, BN, BKT, STAGES, WGM* 
   if (wid >= n_work) return;
   int local = wid;
   if (!p.single) {
-    g = find_group(p.work, p.G, wid);
-    local = wid - p.work[g];
-    seg0 = p.seg_off[g];
-    cnt = p.seg_off[g + 1] - seg0;
-    wp = p.groups[g].width_pad;
-    hoff = p.h_off[g];
+    if (LOW_TILE) {
+      const WorkItem it = find_item(gl, p.G, wid);
+      local = it.local;
+      seg0 = it.seg0;
+      cnt = it.cnt;
+      wp = it.wp;
+      hoff = it.hoff;
+      w1_row0 = it.w1_row0;
+      w2_off = it.w2_off;
+    } else {
+      g = find_group(p.work, p.G, wid);
+      local = wid - p.work[g];
+      seg0 = p.seg_off[g];
+      cnt = p.seg_off[g + 1] - seg0;
+      wp = p.groups[g].width_pad;
+      hoff = p.h_off[g];
+    }
     if (MODE == 2 && p.ws_skip && (wp == 352 || wp == 448 || wp == 704)) return;
   }
   // this workgroup's range of K tiles (all of them without a K split); from here on K and the tile
@@ -187,13 +209,13 @@ __attribute__((amdgpu_waves_per_eu(min_waves_per_simd(BM, BN, BKT, STAGES, WGM* 
     if (past) n = n_cols - 1;
     if (p.b_tiled) {
       // the lane's chunk of K tile kt lies 64 / 32 = 2 tiles (BKT / TILE_K) further for every kt
-      const int64_t rowg = (MODE == 1) ? (int64_t)p.groups[g].w1_row0 + n : n;
-      const int64_t base = (MODE == 1) ? 0 : p.groups[g].w2_off;
+      const int64_t rowg = (MODE == 1) ? (int64_t)(LOW_TILE ? w1_row0 : p.groups[g].w1_row0) + n : n;
+      const int64_t base = (MODE == 1) ? 0 : (LOW_TILE ? w2_off : p.groups[g].w2_off);
       const int kt32 = (MODE == 1) ? p.ldb / TILE_K : wp / TILE_K;
       b_src[i] = p.B + base + tiled_offset(rowg, k_first + b_coff[i], kt32);
     } else {
-      if (MODE == 1) b_src[i] = p.B + ((int64_t)p.groups[g].w1_row0 + n) * p.ldb + b_coff[i] + k_first;
-      else b_src[i] = p.B + p.groups[g].w2_off + (int64_t)n * wp + b_coff[i] + k_first;
+      if (MODE == 1) b_src[i] = p.B + ((int64_t)(LOW_TILE ? w1_row0 : p.groups[g].w1_row0) + n) * p.ldb + b_coff[i] + k_first;
+      else b_src[i] = p.B + (LOW_TILE ? w2_off : p.groups[g].w2_off) + (int64_t)n * wp + b_coff[i] + k_first;
       if (past && use_zero_row) b_src[i] = g_zero_row + b_coff[i] + k_first;
     }
   }
@@ -512,6 +534,7 @@ __attribute__((amdgpu_waves_per_eu(ring_groups_per_cu(BM, BN, STAGES * KU, WGM* 
   static_assert(BM % (16 * WGM) == 0 && BN % (16 * WGN) == 0, "whole blocks per wave");
   static_assert(MODE != 1 || TN % 64 == 0, "gate/up pairs must stay inside a wave tile");
   static_assert(STAGES >= 3 && (STAGES - 1) * KU * LPT < 64, "ring depth");
+  constexpr bool LOW_TILE = BM * BN <= LOW_TILE_AREA;
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -519,12 +542,16 @@ __attribute__((amdgpu_waves_per_eu(ring_groups_per_cu(BM, BN, STAGES * KU, WGM* 
   const int wm = wave / WGN, wn = wave % WGN;
   const int r16 = lane & 15, kq = lane >> 4;
 
-  int g = 0, cnt, seg0 = 0, wp;
-  int64_t hoff = 0;
+  int g = 0, cnt, seg0 = 0, wp, w1_row0 = 0;
+  int64_t hoff = 0, w2_off = 0;
   int n_work;
+  GroupLanes gl;
+  if (LOW_TILE && !p.single) gl = request_groups(p.work, p.seg_off, p.groups, p.h_off, p.G);
   if (p.single) {
     cnt = (int)p.T;
     wp = p.groups[0].width_pad;
+    if (LOW_TILE) w1_row0 = p.groups[0].w1_row0;
+    if (LOW_TILE) w2_off = p.groups[0].w2_off;
     const int nc = (MODE == 1) ? 2 * wp : p.d;
     n_work = ((cnt + BM - 1) / BM) * ((nc + BN - 1) / BN);
   } else {
@@ -553,12 +580,23 @@ __attribute__((amdgpu_waves_per_eu(ring_groups_per_cu(BM, BN, STAGES * KU, WGM* 
   if (wid >= n_work) return;
   int local = wid;
   if (!p.single) {
-    g = find_group(p.work, p.G, wid);
-    local = wid - p.work[g];
-    seg0 = p.seg_off[g];
-    cnt = p.seg_off[g + 1] - seg0;
-    wp = p.groups[g].width_pad;
-    hoff = p.h_off[g];
+    if (LOW_TILE) {
+      const WorkItem it = find_item(gl, p.G, wid);
+      local = it.local;
+      seg0 = it.seg0;
+      cnt = it.cnt;
+      wp = it.wp;
+      hoff = it.hoff;
+      w1_row0 = it.w1_row0;
+      w2_off = it.w2_off;
+    } else {
+      g = find_group(p.work, p.G, wid);
+      local = wid - p.work[g];
+      seg0 = p.seg_off[g];
+      cnt = p.seg_off[g + 1] - seg0;
+      wp = p.groups[g].width_pad;
+      hoff = p.h_off[g];
+    }
     if (MODE == 2 && p.ws_skip && (wp == 352 || wp == 448 || wp == 704)) return;
   }
   // this workgroup's range of K steps (all of them without a K split); K counts from the start of the range
@@ -620,7 +658,7 @@ __attribute__((amdgpu_waves_per_eu(ring_groups_per_cu(BM, BN, STAGES * KU, WGM* 
   const bool k_past = (KT - 1) * BK + coff >= K;
   const int kt32 = (MODE == 1) ? p.ldb / TILE_K : wp / TILE_K;
   const int col_blk0 = nt * (BN / 16);
-  const bf16_t* b_base = (MODE == 1) ? p.B + (int64_t)p.groups[g].w1_row0 * p.ldb : p.B + p.groups[g].w2_off;
+  const bf16_t* b_base = (MODE == 1) ? p.B + (int64_t)(LOW_TILE ? w1_row0 : p.groups[g].w1_row0) * p.ldb : p.B + (LOW_TILE ? w2_off : p.groups[g].w2_off);
   b_base = uniform_ptr(b_base + ((int64_t)col_blk0 * kt32 + k_first / TILE_K) * TILE_ELEMS);
   // column blocks the tile has: the rest of the buffer's size would be the next tile's
   const int col_blks = min(BN / 16, (n_cols + 15) / 16 - col_blk0);

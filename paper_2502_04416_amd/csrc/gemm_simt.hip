@@ -6,6 +6,7 @@
 #include <algorithm>
 #include "cmoe_internal.h"
 #include "device_utils.h"
+#include "work_item.h"
 
 namespace cmoe {
 
@@ -47,13 +48,15 @@ __global__ __launch_bounds__(256) void grouped_gemm_simt(SimtArgs<T> p) {
     cnt = (int)p.T_tokens;
     wp = p.groups[0].width_pad;
   } else {
+    const GroupLanes gl = request_groups(p.work, p.seg_off, p.groups, p.h_off, p.G);
     if (wid >= p.work[p.G]) return;
-    g = find_group(p.work, p.G, wid);
-    local = wid - p.work[g];
-    seg0 = p.seg_off[g];
-    cnt = p.seg_off[g + 1] - seg0;
-    wp = p.groups[g].width_pad;
-    hoff = p.h_off[g];
+    const WorkItem it = find_item(gl, p.G, wid);
+    g = it.g;
+    local = it.local;
+    seg0 = it.seg0;
+    cnt = it.cnt;
+    wp = it.wp;
+    hoff = it.hoff;
   }
   const int K = (MODE == 1) ? p.d : wp;
   const int n_cols = (MODE == 1) ? 2 * wp : p.d;
@@ -189,19 +192,24 @@ __global__ __launch_bounds__(256) void grouped_gemm_f32(SimtArgs<float> p) {
   __shared__ float red[4][FM][FN + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, kq = lane >> 4;
-  int g = 0, local = blockIdx.x, cnt, seg0 = 0, wp;
-  int64_t hoff = 0;
+  int local = blockIdx.x, cnt, seg0 = 0, wp, w1_row0;
+  int64_t hoff = 0, w2_off;
   if (p.single) {
     cnt = (int)p.T_tokens;
     wp = p.groups[0].width_pad;
+    w1_row0 = p.groups[0].w1_row0;
+    w2_off = p.groups[0].w2_off;
   } else {
+    const GroupLanes gl = request_groups(p.work, p.seg_off, p.groups, p.h_off, p.G);
     if (local >= p.work[p.G]) return;
-    g = find_group(p.work, p.G, local);
-    local -= p.work[g];
-    seg0 = p.seg_off[g];
-    cnt = p.seg_off[g + 1] - seg0;
-    wp = p.groups[g].width_pad;
-    hoff = p.h_off[g];
+    const WorkItem it = find_item(gl, p.G, local);
+    local = it.local;
+    seg0 = it.seg0;
+    cnt = it.cnt;
+    wp = it.wp;
+    hoff = it.hoff;
+    w1_row0 = it.w1_row0;
+    w2_off = it.w2_off;
   }
   const int K = (MODE == 1) ? p.d : wp;
   const int n_nt = (MODE == 1) ? wp / 16 : (p.d + FN - 1) / FN;
@@ -212,11 +220,11 @@ __global__ __launch_bounds__(256) void grouped_gemm_f32(SimtArgs<float> p) {
   const int ar = min(mt * FM + r16, cnt - 1);
   const float *b0, *b1;
   if (MODE == 1) {
-    b0 = p.B + ((int64_t)p.groups[g].w1_row0 + (nt >> 1) * 2 * IL + (nt & 1) * 16 + r16) * p.ldb;
+    b0 = p.B + ((int64_t)w1_row0 + (nt >> 1) * 2 * IL + (nt & 1) * 16 + r16) * p.ldb;
     b1 = b0 + (int64_t)IL * p.ldb;
   } else {
-    b0 = p.B + p.groups[g].w2_off + (int64_t)min(nt * FN + r16, p.d - 1) * wp;
-    b1 = p.B + p.groups[g].w2_off + (int64_t)min(nt * FN + 16 + r16, p.d - 1) * wp;
+    b0 = p.B + w2_off + (int64_t)min(nt * FN + r16, p.d - 1) * wp;
+    b1 = p.B + w2_off + (int64_t)min(nt * FN + 16 + r16, p.d - 1) * wp;
   }
   auto fetch = [&](const float* row, int k) {
     f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};

@@ -833,7 +833,7 @@ __global__ __launch_bounds__(512) void route_place_shared_kernel(RouterDev r, Ro
     route_place_body(r, io, pl, partial, n_slices, T, pre);
     return;
   }
-  decode_gate_up<1, KSTEPS, RUNS>(da, 0, (int)blockIdx.x - 1, 0, T, da.groups[0].width_pad, 0, red);
+  decode_gate_up<1, KSTEPS, RUNS>(da, da.groups[0].w1_row0, (int)blockIdx.x - 1, 0, T, da.groups[0].width_pad, 0, red);
 }
 
 // The same for the batches of 2 to 64 tokens that run streamed units.
@@ -845,7 +845,7 @@ __global__ __launch_bounds__(512) void route_place_stream_kernel(RouterDev r, Ro
     route_place_body(r, io, pl, partial, n_slices, T, pre);
     return;
   }
-  stream_gate_up<MAXT, CS, NEUR>(da, 0, (int)blockIdx.x - 1, 0, T, da.groups[0].width_pad, 0, pre);
+  stream_gate_up<MAXT, CS, NEUR>(da, da.groups[0].w1_row0, (int)blockIdx.x - 1, 0, T, da.groups[0].width_pad, 0, pre);
 }
 
 // One token on a flat layer: the launch that selects and places also runs *every* gate/up unit, the routed
@@ -870,7 +870,7 @@ __global__ __launch_bounds__(512) void route_place_all_kernel(RouterDev r, Route
   const int n_rows = r.n_sw_rows + r.n_lin_rows;
   const int b = (int)blockIdx.x - 1;
   if (b >= 0 && b < units_shared) {
-    decode_gate_up<1, KSTEPS, RUNS>(da, 0, b, 0, 1, da.groups[0].width_pad, 0, red);
+    decode_gate_up<1, KSTEPS, RUNS>(da, da.groups[0].w1_row0, b, 0, 1, da.groups[0].width_pad, 0, red);
     return;
   }
   if constexpr (!RUNS) {                                   // (own_scores asks for one run)
@@ -891,6 +891,14 @@ __global__ __launch_bounds__(512) void route_place_all_kernel(RouterDev r, Route
   }
   const int k = (b - units_shared) / units_routed, local = (b - units_shared) % units_routed;
   const int tid = threadIdx.x;
+  // (where every group's rows lie, requested before the choice is known)
+  int row0[MAX_GROUPS / 64];
+#pragma unroll
+  for (int q = 0; q < MAX_GROUPS / 64; ++q) {
+    if (q > 0 && 64 * q >= da.G) break;
+    row0[q] = da.groups[min((tid & 63) + 64 * q, da.G - 1)].w1_row0;
+  }
+  const int wp = da.groups[r.n_always].width_pad;          // (the routed groups have one width)
   if (tid < 64) {
     for (int row = tid; row < n_rows; row += 64) {
       // all slices in flight together (one after the other: 16 experts, d = 4096 21.5 us per forward, now 19.8)
@@ -911,12 +919,15 @@ __global__ __launch_bounds__(512) void route_place_all_kernel(RouterDev r, Route
     route_token(r, mine, pre, 0, nullptr);
   }
   __syncthreads();
-  const int g = my_sel_g[k];
+  const int g = __builtin_amdgcn_readfirstlane(my_sel_g[k]);
   int rank = 0;
   for (int i = 0; i < r.top_k; ++i) rank += my_sel_g[i] < g ? 1 : 0;
-  const int wp = da.groups[g].width_pad;
+  int w1_row0 = __builtin_amdgcn_readlane(row0[0], g & 63);
+#pragma unroll
+  for (int q = 1; q < MAX_GROUPS / 64; ++q)
+    if (g >= 64 * q) w1_row0 = __builtin_amdgcn_readlane(row0[q], g & 63);
   const int64_t hoff = (r.n_always ? (int64_t)da.groups[0].width_pad : 0) + (int64_t)rank * wp;
-  decode_gate_up<1, KSTEPS, RUNS>(da, g, local, 0, 1, wp, hoff, red);
+  decode_gate_up<1, KSTEPS, RUNS>(da, w1_row0, local, 0, 1, wp, hoff, red);
 }
 
 // Two to sixteen tokens on a flat layer, the same idea: workgroup 0 selects and places the batch, the next
@@ -937,7 +948,7 @@ __global__ __launch_bounds__(512) void route_place_tile_all_kernel(RouterDev r, 
   __shared__ OwnSegment own;
   const int b = (int)blockIdx.x - 1;
   if (b >= 0 && b < units_shared) {
-    decode_gate_up<1, KSTEPS, RUNS>(da, 0, b, 0, T, da.groups[0].width_pad, 0, red);
+    decode_gate_up<1, KSTEPS, RUNS>(da, da.groups[0].w1_row0, b, 0, T, da.groups[0].width_pad, 0, red);
     return;
   }
   if (blockIdx.x == 0) {
@@ -949,7 +960,7 @@ __global__ __launch_bounds__(512) void route_place_tile_all_kernel(RouterDev r, 
   const int cnt = own.cnt;
   if (cnt == 0) return;
   da.slot2tok = own.tok;                          // slot j of this group = its j-th token in ascending order
-  decode_gate_up<1, KSTEPS, RUNS>(da, g, local, 0, cnt, da.groups[g].width_pad, own.h_off, red);
+  decode_gate_up<1, KSTEPS, RUNS>(da, da.groups[g].w1_row0, local, 0, cnt, da.groups[g].width_pad, own.h_off, red);
 }
 
 // Per-tile histogram of the routed entries (used when the scoring kernel did not produce one).

@@ -393,3 +393,20 @@ def test_small_batch_scorer(binding, d, N, n_s, k, T):
     cfg, weights, part, x, layer = _case(binding, d, N, 16, n_s, k, T, seed=6)
     check_flat(cfg, weights, part, x, layer.forward(x))
     layer.close()
+
+
+@pytest.mark.parametrize("dtype,N,m,n_s,k,T", [
+    ("bf16", 65, 16, 1, 16, 3),       # 65 groups: the last one alone in the second half of the lookup
+    ("bf16", 64, 16, 0, 9, 12),       # 64: the first half full
+    ("bf16", 65, 40, 1, 12, 21),      # fused down contraction with two token tiles, widths that end inside an item
+    ("bf16", 65, 40, 1, 3, 70),       # low tiles
+    ("fp32", 65, 16, 1, 2, 40),
+])
+def test_work_items_of_many_groups(binding, dtype, N, m, n_s, k, T):
+    """The group of a work item, looked up for all groups at once: at most 64 groups, and more."""
+    cfg = synth.scaled(synth.CONFIGS[0 if dtype == "fp32" else 1], d_model=512, d_ff=N * m, n_experts=N, n_shared=n_s, top_k=k, n_centres=16)
+    weights, part = synth.make_weights(cfg, seed=3107), synth.trivial_partition(cfg, seed=7)
+    x = synth.make_token_source(cfg).eval_batch(7, n=T)
+    layer = binding.Layer.from_partition(cfg, *weights, part["neuron_order"], part["rep_neuron"])
+    check_flat(cfg, weights, part, x, layer.forward(x))
+    layer.close()
