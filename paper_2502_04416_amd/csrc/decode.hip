@@ -1,4 +1,4 @@
-// Expert kernels for decode batches (T <= 16 tokens, bf16; the fused down + combine kernel up to 32):
+// Expert kernels for decode batches (T <= 16 tokens, bf16; the fused down + combine kernel up to 64):
 // weight streaming bound by HBM bandwidth.
 //
 // Every expert group with at least one token is cut into units of 16 neurons (gate/up) or 16 output
@@ -206,27 +206,21 @@ __global__ __launch_bounds__(DC_WAVES * 64) void decode_down_combine_kernel(DecA
   // With two token tiles the next item's operands take the registers of this one's and are on their way while its products are
   // added.  us per forward, requested when the item begins / ahead: d = 4096, 32 experts, 32 tokens 68.2 / 67.9, 16 experts, 32 tokens
   // 65.9 / 65.5; one tile, 8 tokens, 16 experts 46.6 / 47.0, d = 8192, 5 tokens 74.5 / 74.9.
-  constexpr bool AHEAD = NTT > 1;
-  bf16x8_t a[DC_CH], b[NTT][DC_CH];
-  int tok[NTT];
-  float wt[NTT];
-  // Operands as buffer loads: rows past the group's tokens and steps past its width lie past the buffer's size and read
-  // as zeros, so that nothing branches and all loads of an item leave together.  (Weights of bf16 layers are tiled.)
-  auto request = [&](int u) {
-    const int g = find_group(dg.item0, p.G, u);
-    const int ks0 = (u - __builtin_amdgcn_readfirstlane(dg.item0[g])) * DC_CH;
-    const int seg0 = __builtin_amdgcn_readfirstlane(dg.seg0[g]), cnt = __builtin_amdgcn_readfirstlane(dg.cnt[g]);
-    const int wp = __builtin_amdgcn_readfirstlane(dg.wp[g]);
-    const int ns = min(DC_CH, wp / 32 - ks0);
-    const bf16_t* wbase = uniform_ptr(p.w2 + dg.w2_off[g] + (int64_t)((c0 / 16) * (wp / 32) + ks0) * TILE_ELEMS);
-    const bf16_t* hbase = uniform_ptr(p.h + dg.h_off[g] + ks0 * 32);
-    const uint32_t wsize = (uint32_t)ns * (TILE_ELEMS * 2), hsize = (uint32_t)(cnt * wp - ks0 * 32) * 2u;
+  // With four token tiles an item's rows go through the registers two tiles at a time, its weights once.
+  constexpr int NP = NTT < 2 ? NTT : 2;
+  constexpr bool AHEAD = NTT == 2;
+  bf16x8_t a[DC_CH], b[NP][DC_CH];
+  int tok[NP];
+  float wt[NP];
+  int seg0 = 0, cnt = 0, wp = 0, ns = 0;          // the item whose operands are requested: slots, width, K steps
+  const bf16_t* hbase = nullptr;
+  uint32_t hsize = 0;
+  auto request_rows = [&](int first_tile) {
 #pragma unroll
-    for (int s = 0; s < DC_CH; ++s) a[s] = ld_frag_buffer(wbase, wsize, (uint32_t)(r16 * 64 + kq * 16 + s * (TILE_ELEMS * 2)));
-#pragma unroll
-    for (int tt = 0; tt < NTT; ++tt) {
-      if (tt * 16 >= cnt) continue;               // (uniform: most items have at most 16 tokens)
-      const int col = tt * 16 + r16, at = seg0 + min(col, cnt - 1);
+    for (int tt = 0; tt < NP; ++tt) {
+      const int col = (first_tile + tt) * 16 + r16;
+      if ((first_tile + tt) * 16 >= cnt) continue;      // (uniform: most items have at most 16 tokens)
+      const int at = seg0 + min(col, cnt - 1);
       const uint32_t row = (uint32_t)(col * wp * 2 + kq * 16);
 #pragma unroll
       for (int s = 0; s < DC_CH; ++s) b[tt][s] = ld_frag_buffer(hbase, hsize, row + (s < ns ? (uint32_t)(s * 64) : DMA_NONE));
@@ -234,36 +228,54 @@ __global__ __launch_bounds__(DC_WAVES * 64) void decode_down_combine_kernel(DecA
       wt[tt] = w_by_slot[at];
     }
     __builtin_amdgcn_sched_barrier(0);
-    return cnt;
   };
-  int cnt = 0;                                    // tokens of the item whose operands are requested
-  if (AHEAD && wave < n_items) cnt = request(wave);
+  // Operands as buffer loads: rows past the group's tokens and steps past its width lie past the buffer's size and read
+  // as zeros, so that nothing branches and all loads of an item leave together.  (Weights of bf16 layers are tiled.)
+  auto request = [&](int u) {
+    const int g = find_group(dg.item0, p.G, u);
+    const int ks0 = (u - __builtin_amdgcn_readfirstlane(dg.item0[g])) * DC_CH;
+    seg0 = __builtin_amdgcn_readfirstlane(dg.seg0[g]);
+    cnt = __builtin_amdgcn_readfirstlane(dg.cnt[g]);
+    wp = __builtin_amdgcn_readfirstlane(dg.wp[g]);
+    ns = min(DC_CH, wp / 32 - ks0);
+    const bf16_t* wbase = uniform_ptr(p.w2 + dg.w2_off[g] + (int64_t)((c0 / 16) * (wp / 32) + ks0) * TILE_ELEMS);
+    hbase = uniform_ptr(p.h + dg.h_off[g] + ks0 * 32);
+    const uint32_t wsize = (uint32_t)ns * (TILE_ELEMS * 2);
+    hsize = (uint32_t)(cnt * wp - ks0 * 32) * 2u;
+#pragma unroll
+    for (int s = 0; s < DC_CH; ++s) a[s] = ld_frag_buffer(wbase, wsize, (uint32_t)(r16 * 64 + kq * 16 + s * (TILE_ELEMS * 2)));
+    request_rows(0);
+  };
+  if (AHEAD && wave < n_items) request(wave);
   for (int u = wave; u < n_items; u += DC_WAVES) {
-    if (!AHEAD) cnt = request(u);
-    floatx4_t acc[NTT];
+    if (!AHEAD) request(u);
+    const int n = cnt;
 #pragma unroll
-    for (int tt = 0; tt < NTT; ++tt) {
+    for (int t0 = 0; t0 < NTT; t0 += NP) {
+      if (t0 * 16 >= n) break;
+      if (t0 > 0) request_rows(t0);
+      floatx4_t acc[NP];
+      int at[NP];                                 // token of the lane's row, -1: there is none
+      float by[NP];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc[tt][i] = 0.0f;
-      if (tt * 16 >= cnt) continue;
+      for (int tt = 0; tt < NP; ++tt) {
 #pragma unroll
-      for (int s = 0; s < DC_CH; ++s) acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], b[tt][s], acc[tt], 0, 0, 0);
-    }
-    int at[NTT];                                  // token of the lane's row, -1: there is none
-    float by[NTT];
+        for (int i = 0; i < 4; ++i) acc[tt][i] = 0.0f;
+        at[tt] = (t0 + tt) * 16 + r16 < n ? tok[tt] : -1;
+        by[tt] = wt[tt];
+        if ((t0 + tt) * 16 >= n) continue;
 #pragma unroll
-    for (int tt = 0; tt < NTT; ++tt) {
-      at[tt] = tt * 16 + r16 < cnt ? tok[tt] : -1;
-      by[tt] = wt[tt];
-    }
-    if (AHEAD && u + DC_WAVES < n_items) cnt = request(u + DC_WAVES);
-    // accumulator element i: output column (lane/16)*4 + i, token of segment position lane%16
-#pragma unroll
-    for (int tt = 0; tt < NTT; ++tt)
-      if (at[tt] >= 0) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) yacc[wave][at[tt]][kq * 4 + i] += by[tt] * acc[tt][i];
+        for (int s = 0; s < DC_CH; ++s) acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], b[tt][s], acc[tt], 0, 0, 0);
       }
+      if (AHEAD && u + DC_WAVES < n_items) request(u + DC_WAVES);
+      // accumulator element i: output column (lane/16)*4 + i, token of segment position lane%16
+#pragma unroll
+      for (int tt = 0; tt < NP; ++tt)
+        if (at[tt] >= 0) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) yacc[wave][at[tt]][kq * 4 + i] += by[tt] * acc[tt][i];
+        }
+    }
   }
   __syncthreads();
   for (int e = tid; e < (int)p.T * 16; e += DC_WAVES * 64) {
@@ -433,13 +445,24 @@ bool decode_path_ok(const Engine& e, int64_t T) {
   return decode_k(e.d).ksteps != 0;
 }
 
-// The fused down + combine kernel serves every routed bf16 batch of at most 32 tokens with more than one slot
-// per token, whichever kernel produced the hidden activations (the decode_fuse tuning switch selects the separate
-// kernels, for comparison).
-constexpr int DOWN_COMBINE_MAX_T = 32;
+// The fused down + combine kernel serves routed bf16 batches with more than one slot per token, whichever kernel produced the
+// hidden activations (the decode_fuse tuning switch selects the separate kernels, for comparison): every one of at most 32
+// tokens, and of 33 to 64 tokens those whose d / 16 workgroups are about one per CU and whose hidden activations, which every
+// workgroup reads, come to at most 16 rows per row of weights.  us per forward, separate kernels / this one, rows per weight row in
+// brackets: d = 3072, 12 experts, top-2, 33 tokens (8) 50.9 / 48.6, 64 (16) 62.8 / 61.4; d = 3584, 16, top-3, 48 (12) 68.8 / 66.2; d = 4096,
+// 16, top-3, 33 (8) 68.8 / 66.2, 64 (16) 76.4 / 76.0; 32 with four shared, top-4, 33 (8) 75.8 / 70.0, 64 (16) 86.1 / 83.3; 8, top-2, 33 (12)
+// 76.6 / 70.6, 64 (24) 82.3 / 82.0; 8 with two shared, top-1, 33 (12) 105.8 / 81.2; 12, top-3, 48 (16) 76.3 / 75.8, 64 (21) 80.3 / 83.9;
+// 8 outer experts, 33 (4) 185.6 / 169.0, 64 (8) 209.2 / 199.9.  Other widths: d = 1024, 16 experts, 40 tokens 26.8 / 27.3; d = 2048, 32
+// experts, 33 tokens 33.1 / 31.6, 64 tokens 39.2 / 39.5, 8 outer experts, 33 tokens 67.9 / 70.9; d = 5120, 16 experts, 40 tokens
+// 87.2 / 88.6; d = 8192, 8 experts, 33 tokens 120.5 / 122.5, 64 tokens 128.7 / 140.4.
+constexpr int DOWN_COMBINE_ALL_T = 32, DOWN_COMBINE_MAX_T = 64;
 bool decode_fuses_combine(const Engine& e, int64_t T) {
   if (tuning().decode_fuse == 0 || use_simt_experts(e.dtype) || e.dtype != 1 || T < 1 || T > DOWN_COMBINE_MAX_T || e.d % 16 != 0) return false;
-  return !(e.G == 1 && e.n_always == 1) && e.S_all() > 1;
+  if ((e.G == 1 && e.n_always == 1) || e.S_all() <= 1) return false;
+  if (T <= DOWN_COMBINE_ALL_T) return true;
+  int64_t widths = 0;
+  for (int g = 0; g < e.G; ++g) widths += e.width_pad_host[g];
+  return e.d >= 3072 && e.d <= 4096 && T * e.h_per_token <= 16 * widths;
 }
 
 // 8-neuron units when they still number at most one per CU (the always-on groups count unless the routing
@@ -503,7 +526,8 @@ hipError_t launch_decode_down_combine(const Engine& e, int64_t T, char* ws, cons
   const DecArgs a = make_dec_args(e, nullptr, T, ws, L, y);
   const float* wbs = reinterpret_cast<const float*>(ws + L.w_by_slot);
   bf16_t* yo = static_cast<bf16_t*>(y);
-  if (T > 16) hipLaunchKernelGGL((decode_down_combine_kernel<2>), dim3(e.d / 16), dim3(DC_WAVES * 64), 0, s, a, wbs, yo);
+  if (T > 32) hipLaunchKernelGGL((decode_down_combine_kernel<4>), dim3(e.d / 16), dim3(DC_WAVES * 64), 0, s, a, wbs, yo);
+  else if (T > 16) hipLaunchKernelGGL((decode_down_combine_kernel<2>), dim3(e.d / 16), dim3(DC_WAVES * 64), 0, s, a, wbs, yo);
   else hipLaunchKernelGGL((decode_down_combine_kernel<1>), dim3(e.d / 16), dim3(DC_WAVES * 64), 0, s, a, wbs, yo);
   return hipGetLastError();
 }

@@ -410,3 +410,17 @@ def test_work_items_of_many_groups(binding, dtype, N, m, n_s, k, T):
     layer = binding.Layer.from_partition(cfg, *weights, part["neuron_order"], part["rep_neuron"])
     check_flat(cfg, weights, part, x, layer.forward(x))
     layer.close()
+
+
+@pytest.mark.parametrize("d,N,m,n_s,k,T,kernel", [
+    (3072, 8, 40, 1, 2, 33, "combines"),      # a third token tile of one row; two K steps per group
+    (3072, 8, 300, 0, 2, 64, "combines"),     # no always-on group, items of eight and two K steps, at the line
+    (4096, 16, 32, 4, 1, 51, "combines"),     # a fourth tile of three rows in the always-on group, one or two in the others
+    (4096, 4, 32, 2, 2, 63, "tiles"),         # every token chooses every expert: 63 rows per row of weights
+])
+def test_down_and_combine_in_one_launch_beyond_32_tokens(binding, d, N, m, n_s, k, T, kernel):
+    """Token tiles two at a time through the registers of the fused down + combine launch."""
+    cfg, weights, part, x, layer = _case(binding, d, N, m, n_s, k, T, seed=8)
+    assert layer.forward_plan(T)["down"][0] == kernel
+    check_flat(cfg, weights, part, x, layer.forward(x))
+    layer.close()
