@@ -31,8 +31,9 @@ __device__ __forceinline__ int find_group(const int32_t* __restrict__ work, int 
 
 // Inclusive prefix sums over the 64 lanes of a wave, all of which must call.  The partial sums move up the wave in DPP
 // operands, within rows of 16 lanes, then from row to row: a scan is a chain of vector instructions, where exchanges through
-// the LDS crossbar are a chain of six round trips, and selection and placement are mostly such chains.  us per forward with exchanges / now: d = 4096, 16 experts, one token 23.2 / 22.9, 4 tokens 43.3 / 42.4, 32 experts, 32 tokens
-// 73.2 / 71.9, 2048 tokens 203.1 / 202.3; fp32, d = 256, 512 tokens 26.2 / 25.4.
+// the LDS crossbar are a chain of six round trips, and selection and placement are mostly such chains.  us per forward with
+// exchanges / now: d = 4096, 16 experts, one token 23.2 / 22.9, 4 tokens 43.3 / 42.4, 32 experts, 32 tokens 73.2 / 71.9, 2048 tokens
+// 203.1 / 202.3; fp32, d = 256, 512 tokens 26.2 / 25.4.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ int dpp_from(int v) {               // 0 for lanes without a source
   return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
