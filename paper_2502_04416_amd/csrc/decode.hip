@@ -213,8 +213,14 @@ __global__ __launch_bounds__(DC_WAVES * 64) void decode_down_combine_kernel(DecA
   int tok[NP];
   float wt[NP];
   int seg0 = 0, cnt = 0, wp = 0, ns = 0;          // the item whose operands are requested: slots, width, K steps
-  const bf16_t* hbase = nullptr;
-  uint32_t hsize = 0;
+  const bf16_t *wbase = nullptr, *hbase = nullptr;
+  uint32_t wsize = 0, hsize = 0;
+  // A load past the width returns zeros but takes its turn all the same.  With one token tile, where a wave's items are many
+  // short chains (narrow experts), an item of at most four steps leaves the second half of its operands out.  us per forward, all
+  // eight steps / now: d = 1024, 64 experts of 64, top-12, 16 tokens 26.9 / 23.0; 64 of 32, top-6 21.6 / 18.2; d = 512, 64 of 128,
+  // top-16, 12 tokens 31.3 / 27.7; 8 outer experts of 8 of 32, 16 tokens 20.9 / 18.3; experts of 256 (eight steps) even.
+  constexpr int HALF = DC_CH / 2;
+  constexpr bool SHORT_ITEMS = NTT == 1;
   auto request_rows = [&](int first_tile) {
 #pragma unroll
     for (int tt = 0; tt < NP; ++tt) {
@@ -223,7 +229,14 @@ __global__ __launch_bounds__(DC_WAVES * 64) void decode_down_combine_kernel(DecA
       const int at = seg0 + min(col, cnt - 1);
       const uint32_t row = (uint32_t)(col * wp * 2 + kq * 16);
 #pragma unroll
-      for (int s = 0; s < DC_CH; ++s) b[tt][s] = ld_frag_buffer(hbase, hsize, row + (s < ns ? (uint32_t)(s * 64) : DMA_NONE));
+      for (int s = 0; s < HALF; ++s) b[tt][s] = ld_frag_buffer(hbase, hsize, row + (s < ns ? (uint32_t)(s * 64) : DMA_NONE));
+      if (!SHORT_ITEMS || ns > HALF) {
+#pragma unroll
+        for (int s = HALF; s < DC_CH; ++s) {
+          if (SHORT_ITEMS) a[s] = ld_frag_buffer(wbase, wsize, (uint32_t)(r16 * 64 + kq * 16 + s * (TILE_ELEMS * 2)));
+          b[tt][s] = ld_frag_buffer(hbase, hsize, row + (s < ns ? (uint32_t)(s * 64) : DMA_NONE));
+        }
+      }
       tok[tt] = p.slot2tok[at];
       wt[tt] = w_by_slot[at];
     }
@@ -238,12 +251,12 @@ __global__ __launch_bounds__(DC_WAVES * 64) void decode_down_combine_kernel(DecA
     cnt = __builtin_amdgcn_readfirstlane(dg.cnt[g]);
     wp = __builtin_amdgcn_readfirstlane(dg.wp[g]);
     ns = min(DC_CH, wp / 32 - ks0);
-    const bf16_t* wbase = uniform_ptr(p.w2 + dg.w2_off[g] + (int64_t)((c0 / 16) * (wp / 32) + ks0) * TILE_ELEMS);
+    wbase = uniform_ptr(p.w2 + dg.w2_off[g] + (int64_t)((c0 / 16) * (wp / 32) + ks0) * TILE_ELEMS);
     hbase = uniform_ptr(p.h + dg.h_off[g] + ks0 * 32);
-    const uint32_t wsize = (uint32_t)ns * (TILE_ELEMS * 2);
+    wsize = (uint32_t)ns * (TILE_ELEMS * 2);
     hsize = (uint32_t)(cnt * wp - ks0 * 32) * 2u;
 #pragma unroll
-    for (int s = 0; s < DC_CH; ++s) a[s] = ld_frag_buffer(wbase, wsize, (uint32_t)(r16 * 64 + kq * 16 + s * (TILE_ELEMS * 2)));
+    for (int s = 0; s < (SHORT_ITEMS ? HALF : DC_CH); ++s) a[s] = ld_frag_buffer(wbase, wsize, (uint32_t)(r16 * 64 + kq * 16 + s * (TILE_ELEMS * 2)));
     request_rows(0);
   };
   if (AHEAD && wave < n_items) request(wave);
@@ -265,7 +278,11 @@ __global__ __launch_bounds__(DC_WAVES * 64) void decode_down_combine_kernel(DecA
         by[tt] = wt[tt];
         if ((t0 + tt) * 16 >= n) continue;
 #pragma unroll
-        for (int s = 0; s < DC_CH; ++s) acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], b[tt][s], acc[tt], 0, 0, 0);
+        for (int s = 0; s < HALF; ++s) acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], b[tt][s], acc[tt], 0, 0, 0);
+        if (!SHORT_ITEMS || ns > HALF) {
+#pragma unroll
+          for (int s = HALF; s < DC_CH; ++s) acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], b[tt][s], acc[tt], 0, 0, 0);
+        }
       }
       if (AHEAD && u + DC_WAVES < n_items) request(u + DC_WAVES);
       // accumulator element i: output column (lane/16)*4 + i, token of segment position lane%16

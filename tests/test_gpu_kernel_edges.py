@@ -424,3 +424,13 @@ def test_down_and_combine_in_one_launch_beyond_32_tokens(binding, d, N, m, n_s, 
     assert layer.forward_plan(T)["down"][0] == kernel
     check_flat(cfg, weights, part, x, layer.forward(x))
     layer.close()
+
+
+@pytest.mark.parametrize("m", [32, 128, 129, 384, 385])
+@pytest.mark.parametrize("T", [1, 9, 16])
+def test_down_and_combine_of_narrow_experts(binding, m, T):
+    """Work items of up to four K steps and of more, alone and behind a full one: 1, 4, 5, 8 + 4 and 8 + 5 steps."""
+    cfg, weights, part, x, layer = _case(binding, 512, 24, m, 1, 10, T, seed=9)
+    assert layer.forward_plan(T)["down"][0] == "combines"
+    check_flat(cfg, weights, part, x, layer.forward(x))
+    layer.close()
