@@ -464,14 +464,16 @@ bool decode_path_ok(const Engine& e, int64_t T) {
 
 // The fused down + combine kernel serves routed bf16 batches with more than one slot per token, whichever kernel produced the
 // hidden activations (the decode_fuse tuning switch selects the separate kernels, for comparison): every one of at most 32
-// tokens, and of 33 to 64 tokens those whose d / 16 workgroups are about one per CU and whose hidden activations, which every
-// workgroup reads, come to at most 16 rows per row of weights.  us per forward, separate kernels / this one, rows per weight row in
-// brackets: d = 3072, 12 experts, top-2, 33 tokens (8) 50.9 / 48.6, 64 (16) 62.8 / 61.4; d = 3584, 16, top-3, 48 (12) 68.8 / 66.2; d = 4096,
-// 16, top-3, 33 (8) 68.8 / 66.2, 64 (16) 76.4 / 76.0; 32 with four shared, top-4, 33 (8) 75.8 / 70.0, 64 (16) 86.1 / 83.3; 8, top-2, 33 (12)
-// 76.6 / 70.6, 64 (24) 82.3 / 82.0; 8 with two shared, top-1, 33 (12) 105.8 / 81.2; 12, top-3, 48 (16) 76.3 / 75.8, 64 (21) 80.3 / 83.9;
-// 8 outer experts, 33 (4) 185.6 / 169.0, 64 (8) 209.2 / 199.9.  Other widths: d = 1024, 16 experts, 40 tokens 26.8 / 27.3; d = 2048, 32
-// experts, 33 tokens 33.1 / 31.6, 64 tokens 39.2 / 39.5, 8 outer experts, 33 tokens 67.9 / 70.9; d = 5120, 16 experts, 40 tokens
-// 87.2 / 88.6; d = 8192, 8 experts, 33 tokens 120.5 / 122.5, 64 tokens 128.7 / 140.4.
+// tokens, and of 33 to 64 tokens those whose d / 16 workgroups are about one per CU (d = 3072 to 4096) and whose hidden activations,
+// which every workgroup reads, come to at most 16 rows per row of weights and to little more than what the launches it replaces
+// cost: over 3700 calls it gained 2.6 us + 1.9 us per 10000 rows of weights and lost 1.5 us (4096 / d)^2 per 100000 neurons
+// of hidden activations (the fewer workgroups there are, the more CUs stand by).  us per forward, separate kernels / this one, where it is
+// taken: d = 3584, 16 experts of 604, top-3, 48 tokens 55.4 / 53.6; d = 4096, 16 of 691, top-3, 33 67.2 / 65.1, 64 72.1 / 72.1; 32 with
+// four shared, top-4, 33 72.7 / 66.9, 64 77.3 / 74.4; 8 with two shared, top-1, 33 89.4 / 65.3, 64 91.7 / 91.6; 8 outer experts of 8, 33
+// 439 / 408, 64 438 / 417.  Where it is not: d = 3072, 16 of 2496, top-3, 64 157.8 / 175.3; d = 4096, 16 of 3328, top-4,
+// 64 254.9 / 268.5; whole experts, two of eight, d = 3072, 33 378 / 387, 64 395 / 435, d = 4096, 48 485 / 500.  Other widths: d = 1024,
+// 16 experts, 40 tokens 26.8 / 27.3; d = 2048, 32 experts, 33 tokens 33.1 / 31.6, 64 tokens 39.2 / 39.5, 8 outer experts, 33 tokens 67.9 /
+// 70.9; d = 5120, 16 experts, 40 tokens 87.2 / 88.6; d = 8192, 8 experts, 33 tokens 120.5 / 122.5, 64 tokens 128.7 / 140.4.
 constexpr int DOWN_COMBINE_ALL_T = 32, DOWN_COMBINE_MAX_T = 64;
 bool decode_fuses_combine(const Engine& e, int64_t T) {
   if (tuning().decode_fuse == 0 || use_simt_experts(e.dtype) || e.dtype != 1 || T < 1 || T > DOWN_COMBINE_MAX_T || e.d % 16 != 0) return false;
@@ -479,7 +481,8 @@ bool decode_fuses_combine(const Engine& e, int64_t T) {
   if (T <= DOWN_COMBINE_ALL_T) return true;
   int64_t widths = 0;
   for (int g = 0; g < e.G; ++g) widths += e.width_pad_host[g];
-  return e.d >= 3072 && e.d <= 4096 && T * e.h_per_token <= 16 * widths;
+  const int64_t hidden = T * e.h_per_token;
+  return e.d >= 3072 && e.d <= 4096 && hidden <= 16 * widths && hidden * 4096 * 4096 <= (10 * widths + 200000) * e.d * e.d;
 }
 
 // 8-neuron units when they still number at most one per CU (the always-on groups count unless the routing

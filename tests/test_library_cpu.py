@@ -320,3 +320,36 @@ def test_decode_batches_stream_where_it_wins(lib, d, n_s, T, kernel):
     finally:
         binding.cmoe_set_tuning("CMOE_GEMM1_CFG", -1)
     layer.close()
+
+
+@pytest.mark.parametrize("d,n,m,n_s,k,T,down", [
+    (3072, 16, 704, 0, 4, 64, "tiles"),        # 16 rows per row of weights, 320398 against 312640
+    (3072, 16, 704, 0, 4, 62, "combines"),
+    (4096, 16, 704, 0, 4, 64, "combines"),     # a wider layer, more workgroups: 180224
+    (3072, 16, 96, 0, 4, 64, "combines"),      # narrow experts
+    (4096, 4, 96, 1, 2, 40, "tiles"),          # 30 rows per row of weights
+])
+def test_down_and_combine_where_it_wins(lib, d, n, m, n_s, k, T, down):
+    """The fused down + combine launch beyond 32 tokens: hidden activations per workgroup against rows of weights."""
+    cfg = synth.scaled(synth.CONFIGS[1], d_model=d, d_ff=n * m, n_experts=n, n_shared=n_s, top_k=k)
+    part = synth.trivial_partition(cfg)
+    zeros = np.zeros((d, n * m), dtype=np.float32)
+    layer = binding.Layer.from_partition(cfg, zeros, zeros, zeros.T, part["neuron_order"], part["rep_neuron"], upload=False)
+    assert layer.forward_plan(T)["down"][0] == down
+    layer.close()
+
+
+def test_down_and_combine_of_a_dense_hierarchy(lib):
+    """Whole experts, two of eight per token: a quarter of the weights' rows per token, 3072 wide."""
+    cfg = synth.scaled(synth.CONFIGS[4], d_model=3072, d_ff=8 * 192, n_experts=8, n_shared=2, top_k=2, n_outer=8, outer_top_k=2)
+    part = synth.trivial_partition(cfg)
+    zeros = np.zeros((cfg.d_model, cfg.d_ff), dtype=np.float32)
+    layers = [binding.Layer.from_partition(cfg, zeros, zeros, zeros.T, part["neuron_order"], part["rep_neuron"], upload=False)
+              for _ in range(cfg.n_outer)]
+    h = binding.cmoe_hier_create([l.h for l in layers], cfg.outer_top_k, np.zeros((cfg.d_model, cfg.n_outer)), None)
+    assert binding.cmoe_forward_plan(h, 33, dense=True, hier=True)["down"][0] == "combines"
+    assert binding.cmoe_forward_plan(h, 64, dense=True, hier=True)["down"][0] == "tiles"
+    assert binding.cmoe_forward_plan(h, 64, hier=True)["down"][0] == "combines"
+    binding.cmoe_hier_destroy(h)
+    for l in layers:
+        l.close()
