@@ -434,3 +434,32 @@ def test_down_and_combine_of_narrow_experts(binding, m, T):
     assert layer.forward_plan(T)["down"][0] == "combines"
     check_flat(cfg, weights, part, x, layer.forward(x))
     layer.close()
+
+
+@pytest.mark.parametrize("d,N,m,n_s,k,T", [
+    (3072, 16, 40, 1, 3, 48),     # slot weights of Eq. 9
+    (4096, 65, 32, 1, 9, 64),     # 65 groups: the last one alone in the second half of the lookup
+    (3072, 64, 16, 0, 16, 33),    # 64, no always-on group, as many slots per token as there can be
+])
+def test_gated_down_and_combine_beyond_32_tokens(binding, d, N, m, n_s, k, T):
+    """The fused down + combine launch with four token tiles, slot weights other than one and many groups."""
+    cfg, weights, part, x, layer = _case(binding, d, N, m, n_s, k, T, seed=10)
+    u, b = synth.make_gate_params(cfg, seed=7300)
+    layer.set_gate_params(u, b)
+    assert layer.forward_plan(T)["down"][0] == "combines"
+    check_flat(cfg, weights, part, x, layer.forward(x), u=u, b=b)
+    layer.close()
+
+
+@pytest.mark.parametrize("n_outer,N,n_s,k", [(4, 8, 2, 2), (16, 5, 1, 1)])       # 28 groups; 80
+def test_hierarchical_down_and_combine_beyond_32_tokens(binding, n_outer, N, n_s, k):
+    """The same for hierarchies, whose slots carry the outer weight, and for their dense form."""
+    cfg = synth.scaled(synth.CONFIGS[4], d_model=3072, d_ff=N * 24, n_experts=N, n_shared=n_s, top_k=k, n_outer=n_outer,
+                       outer_top_k=2, n_centres=16)
+    hier, experts, w_router, offsets = _make(binding, cfg, gate=True)
+    for T in (33, 64):
+        assert hier.forward_plan(T)["down"][0] == "combines"
+        assert hier.forward_plan(T, dense=True)["down"][0] == ("combines" if T * 2 <= 16 * n_outer else "tiles")
+        x = synth.make_token_source(cfg).eval_batch(8, n=T)
+        _check(cfg, experts, w_router, offsets, x, hier.forward(x), hier.dense_forward(x), np.arange(0, T, 5))
+    hier.close()
