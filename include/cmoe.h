@@ -310,6 +310,14 @@ int cmoe_set_tuning(const char* name, int value);
 int cmoe_forward_plan(const cmoe_layer* layer, int dense, int64_t T, int32_t plan[4]);
 int cmoe_hier_forward_plan(const cmoe_hier* h, int dense, int64_t T, int32_t plan[4]);
 
+/* Likewise how a forward of T tokens scores its routed experts: plan[0] one of CMOE_SCORER_*, plan[1] the slices of K.  The layer
+ * must be uploaded. */
+#define CMOE_SCORER_TOKENS  0    /* a workgroup per token (no slices: 0) */
+#define CMOE_SCORER_SMALL   1    /* at most 64 tokens: partial sums, then selection and placement in one launch */
+#define CMOE_SCORER_SELECTS 2    /* scoring and selection in one launch */
+#define CMOE_SCORER_SPLIT   3    /* partial sums, then selection */
+int cmoe_scorer_plan(const cmoe_layer* layer, int64_t T, int32_t plan[2]);
+
 const char* cmoe_last_error(void);   /* thread-local, never NULL */
 const char* cmoe_version(void);
 

@@ -41,7 +41,7 @@ EXPORTS = [
     "cmoe_balanced_assignment", "cmoe_probe_mfma", "cmoe_probe_hbm", "cmoe_get_gate_params", "cmoe_update_bias",
     "cmoe_build_gpu", "cmoe_profile_activations", "cmoe_set_baseline", "cmoe_hier_build", "cmoe_hier_expert",
     "cmoe_set_tuning", "cmoe_set_neuron_sparsity", "cmoe_forward_static", "cmoe_static_scratch_bytes", "cmoe_forward_static_max_tokens",
-    "cmoe_forward_plan", "cmoe_hier_forward_plan",
+    "cmoe_forward_plan", "cmoe_hier_forward_plan", "cmoe_scorer_plan",
 ]
 
 
@@ -107,6 +107,7 @@ def load():
     lib.cmoe_forward_static_max_tokens.restype = i64
     lib.cmoe_forward_plan.argtypes = [vp, C.c_int, i64, i32p]
     lib.cmoe_hier_forward_plan.argtypes = [vp, C.c_int, i64, i32p]
+    lib.cmoe_scorer_plan.argtypes = [vp, i64, i32p]
     lib.cmoe_last_error.restype = C.c_char_p
     lib.cmoe_version.restype = C.c_char_p
     _lib = lib
@@ -338,6 +339,16 @@ def cmoe_forward_plan(layer: int, T: int, dense: bool = False, hier: bool = Fals
     return {"gate_up": (PLAN_KERNELS[p[0]], p[1]), "down": (PLAN_KERNELS[p[2]], p[3])}
 
 
+SCORERS = ("tokens", "small", "selects", "split")
+
+
+def cmoe_scorer_plan(layer: int, T: int) -> tuple:
+    """(scorer, slices of K) of a forward of T tokens (scorers: SCORERS); the layer must be uploaded."""
+    p = (C.c_int32 * 2)()
+    _check(load().cmoe_scorer_plan(layer, T, p), "cmoe_scorer_plan")
+    return SCORERS[p[0]], p[1]
+
+
 def cmoe_hier_packed_bytes(h: int) -> int:
     return load().cmoe_hier_packed_bytes(h)
 
@@ -446,6 +457,9 @@ class Layer(_DeviceMixin):
 
     def forward_plan(self, T: int, dense: bool = False):
         return cmoe_forward_plan(self.h, T, dense)
+
+    def scorer_plan(self, T: int):
+        return cmoe_scorer_plan(self.h, T)
 
     def export_partition(self):
         return cmoe_export_partition(self.h, self.cfg.d_ff, self.cfg.n_routed)

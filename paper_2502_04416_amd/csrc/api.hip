@@ -1368,6 +1368,15 @@ int cmoe_hier_forward_plan(const cmoe_hier* H, int dense, int64_t T, int32_t pla
   return engine_plan(dense ? H->e_dense : H->e_moe, T, plan);
 }
 
+int cmoe_scorer_plan(const cmoe_layer* L, int64_t T, int32_t plan[2]) {
+  if (!L) return fail(CMOE_EINVAL, "layer is null");
+  if (!L->uploaded) return fail(CMOE_ESTATE, "cmoe_upload has not been called");
+  if (!plan) return fail(CMOE_EINVAL, "plan is null");
+  if (T < 1) return fail(CMOE_EINVAL, "need at least one token");
+  scorer_plan(L->e_moe, T, plan);
+  return CMOE_OK;
+}
+
 const char* cmoe_last_error(void) { return g_err.c_str(); }
 const char* cmoe_version(void) { return "cmoe 0.1 (gfx950)"; }
 

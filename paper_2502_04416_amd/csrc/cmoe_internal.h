@@ -195,6 +195,7 @@ hipError_t launch_router(const Engine& e, const void* x, int64_t T, char* ws, co
 // The histogram table launch_router leaves behind: tokens per row (16, 32 or TOK_TILE) and where it is.
 struct CountTable { int tokens; size_t offset; };
 CountTable router_counts(const Engine& e, int64_t T, const WsLayout& L);
+void scorer_plan(const Engine& e, int64_t T, int32_t plan[2]);      // CMOE_SCORER_*, slices of K
 bool place_counts_itself(const Engine& e, int64_t T);      // ... or none: the placement counts the entries
 hipError_t launch_permute(const Engine& e, int64_t T, char* ws, const WsLayout& L, int32_t* counts_out,
                           hipStream_t s);

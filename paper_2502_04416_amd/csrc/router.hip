@@ -7,6 +7,7 @@
 // and score_route_kernel does both for prefill batches of a flat layer.
 #include <algorithm>
 #include <cstdlib>
+#include "../../include/cmoe.h"
 #include "cmoe_internal.h"
 #include "decode_device.h"
 #include "device_utils.h"
@@ -1193,6 +1194,12 @@ bool decode_front_runs_all(const Engine& e, int64_t T) {
   for (int g = e.n_always; g < e.G; ++g)
     if (e.width_pad_host[g] != e.width_pad_host[e.n_always]) return false;
   return true;
+}
+
+void scorer_plan(const Engine& e, int64_t T, int32_t plan[2]) {
+  const bool front = !use_simt_experts(e.dtype) && decode_front_ok(e, T), sliced = mfma_scorer_ok(e);
+  plan[0] = front ? CMOE_SCORER_SMALL : score_route_units(e, T) ? CMOE_SCORER_SELECTS : sliced ? CMOE_SCORER_SPLIT : CMOE_SCORER_TOKENS;
+  plan[1] = front ? DEC_SLICES : sliced ? scorer_slices(e, T) : 0;
 }
 
 // Few entries behind the scorer without a histogram: every workgroup of the placement counts them all, which a launch of

@@ -463,3 +463,25 @@ def test_hierarchical_down_and_combine_beyond_32_tokens(binding, n_outer, N, n_s
         x = synth.make_token_source(cfg).eval_batch(8, n=T)
         _check(cfg, experts, w_router, offsets, x, hier.forward(x), hier.dense_forward(x), np.arange(0, T, 5))
     hier.close()
+
+
+@pytest.mark.parametrize("d,N,n_s,k,T,scorer", [
+    (328, 8, 1, 2, 70, ("tokens", 0)),         # a width without K slices
+    (512, 9, 1, 2, 64, ("small", 8)),
+    (8448, 8, 1, 2, 18, ("small", 8)),         # 33 K steps per slice: waves of nine, in runs of eight and one, the last of six
+    (768, 17, 1, 3, 65, ("selects", 3)),
+    (1024, 17, 1, 16, 70, ("selects", 4)),
+    (2048, 16, 0, 3, 2400, ("selects", 4)),
+    (2560, 8, 1, 2, 4064, ("selects", 5)),     # slices of two chunks
+    (2560, 8, 1, 2, 4065, ("split", 2)),       # two slices of five chunks: one more than the pairs that the one launch takes
+    (2304, 8, 1, 2, 200, ("split", 3)),        # three of three
+    (512, 9, 1, 2, 8300, ("selects", 2)),      # 32 tokens per workgroup
+    (2560, 40, 2, 5, 150, ("split", 5)),       # 128 router rows, more than a workgroup pulls
+])
+def test_scorer_of_a_batch(binding, d, N, n_s, k, T, scorer):
+    cfg, weights, part, x, layer = _case(binding, d, N, 16, n_s, k, T, seed=11)
+    assert layer.scorer_plan(T) == scorer
+    out = layer.forward(x)
+    check_flat(cfg, weights, part, x, out)
+    assert np.array_equal(out["counts"], np.bincount(out["topk"].ravel(), minlength=cfg.n_routed))
+    layer.close()
