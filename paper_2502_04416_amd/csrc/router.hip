@@ -753,7 +753,7 @@ struct OwnSegment {
 };
 
 __device__ __forceinline__ void route_place_body(const RouterDev& r, RouteIO io, const PlaceArgs& pl,
-                                                 const float* __restrict__ partial, int n_slices, int T, float* pre,
+                                                 const float* __restrict__ partial, int T, float* pre,
                                                  int group = -1, OwnSegment* mine = nullptr) {
   __shared__ int32_t hist[MAX_GROUPS];
   __shared__ int32_t sel_g[TOK_TILE * MAX_DYN];
@@ -772,7 +772,7 @@ __device__ __forceinline__ void route_place_body(const RouterDev& r, RouteIO io,
     io.scores_out = nullptr;
   }
   const float2 gate = request_gate(r, io, tid);
-  sum_partials(r, partial, n_slices, T, 0, T, n_rows, pre, ld, tid, n_threads);
+  sum_partials_of<DEC_SLICES, 2>(r, partial, DEC_SLICES, T, 0, T, n_rows, pre, ld, tid, n_threads);
   for (int i = tid; i < MAX_GROUPS; i += n_threads) hist[i] = 0;
   store_gate(gl, gate, tid);
   __syncthreads();
@@ -814,9 +814,9 @@ __device__ __forceinline__ void route_place_body(const RouterDev& r, RouteIO io,
 }
 
 __global__ __launch_bounds__(RT_THREADS) void route_place_kernel(RouterDev r, RouteIO io, PlaceArgs pl,
-                                                          const float* __restrict__ partial, int n_slices, int T) {
+                                                          const float* __restrict__ partial, int T) {
   extern __shared__ float pre[];
-  route_place_body(r, io, pl, partial, n_slices, T, pre);
+  route_place_body(r, io, pl, partial, T, pre);
 }
 
 // The same launch with company: workgroup 0 selects and places, the others run the gate/up units of the
@@ -826,12 +826,12 @@ __global__ __launch_bounds__(RT_THREADS) void route_place_kernel(RouterDev r, Ro
 // workgroups and no second stream.  The gate/up work list then leaves that group out.
 template <int KSTEPS, bool RUNS>
 __global__ __launch_bounds__(512) void route_place_shared_kernel(RouterDev r, RouteIO io, PlaceArgs pl,
-                                                                 const float* __restrict__ partial, int n_slices, int T,
+                                                                 const float* __restrict__ partial, int T,
                                                                  DecArgs da) {
   extern __shared__ float pre[];
   __shared__ DecGateUpRed<1> red;
   if (blockIdx.x == 0) {
-    route_place_body(r, io, pl, partial, n_slices, T, pre);
+    route_place_body(r, io, pl, partial, T, pre);
     return;
   }
   decode_gate_up<1, KSTEPS, RUNS>(da, da.groups[0].w1_row0, (int)blockIdx.x - 1, 0, T, da.groups[0].width_pad, 0, red);
@@ -840,10 +840,10 @@ __global__ __launch_bounds__(512) void route_place_shared_kernel(RouterDev r, Ro
 // The same for the batches of 2 to 64 tokens that run streamed units.
 template <int MAXT, int CS, int NEUR>
 __global__ __launch_bounds__(512) void route_place_stream_kernel(RouterDev r, RouteIO io, PlaceArgs pl, const float* __restrict__ partial,
-                                                                 int n_slices, int T, DecArgs da) {
+                                                                 int T, DecArgs da) {
   extern __shared__ float pre[];
   if (blockIdx.x == 0) {
-    route_place_body(r, io, pl, partial, n_slices, T, pre);
+    route_place_body(r, io, pl, partial, T, pre);
     return;
   }
   stream_gate_up<MAXT, CS, NEUR>(da, da.groups[0].w1_row0, (int)blockIdx.x - 1, 0, T, da.groups[0].width_pad, 0, pre);
@@ -861,7 +861,7 @@ __global__ __launch_bounds__(512) void route_place_stream_kernel(RouterDev r, Ro
 // units; the separate gate/up launch is skipped.
 template <int KSTEPS, bool RUNS>
 __global__ __launch_bounds__(512) void route_place_all_kernel(RouterDev r, RouteIO io, PlaceArgs pl,
-                                                              const float* __restrict__ partial, int n_slices,
+                                                              const float* __restrict__ partial,
                                                               DecArgs da, int units_shared, int units_routed,
                                                               const bf16_t* __restrict__ wr) {
   extern __shared__ float pre[];
@@ -883,11 +883,10 @@ __global__ __launch_bounds__(512) void route_place_all_kernel(RouterDev r, Route
       score_slices_in_workgroup<KSTEPS>(da.x, wr, da.d, 1, n_rows, part);
       __syncthreads();
       partial = part;
-      n_slices = DEC_SLICES;
     }
   }
   if (blockIdx.x == 0) {
-    route_place_body(r, io, pl, partial, n_slices, 1, pre);
+    route_place_body(r, io, pl, partial, 1, pre);
     return;
   }
   const int k = (b - units_shared) / units_routed, local = (b - units_shared) % units_routed;
@@ -942,7 +941,7 @@ __global__ __launch_bounds__(512) void route_place_all_kernel(RouterDev r, Route
 // the tuning switch front_tile asks for it.
 template <int KSTEPS, bool RUNS>
 __global__ __launch_bounds__(512) void route_place_tile_all_kernel(RouterDev r, RouteIO io, PlaceArgs pl,
-                                                                   const float* __restrict__ partial, int n_slices, int T,
+                                                                   const float* __restrict__ partial, int T,
                                                                    DecArgs da, int units_shared, int units_routed) {
   extern __shared__ float pre[];
   __shared__ DecGateUpRed<1> red;
@@ -953,11 +952,11 @@ __global__ __launch_bounds__(512) void route_place_tile_all_kernel(RouterDev r, 
     return;
   }
   if (blockIdx.x == 0) {
-    route_place_body(r, io, pl, partial, n_slices, T, pre);
+    route_place_body(r, io, pl, partial, T, pre);
     return;
   }
   const int g = r.n_always + (b - units_shared) / units_routed, local = (b - units_shared) % units_routed;
-  route_place_body(r, io, pl, partial, n_slices, T, pre, g, &own);
+  route_place_body(r, io, pl, partial, T, pre, g, &own);
   const int cnt = own.cnt;
   if (cnt == 0) return;
   da.slot2tok = own.tok;                          // slot j of this group = its j-th token in ascending order
@@ -1089,13 +1088,11 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
   const int n_rows = e.r.n_sw_rows + e.r.n_lin_rows;
   float* pre_g = reinterpret_cast<float*>(ws + L.scores);
   const int Ti = (int)T;
-  const int n_slices = DEC_SLICES;
   bf16_t* xt = front_lays_tokens(e, T) ? reinterpret_cast<bf16_t*>(ws + L.y_slots) : nullptr;
   hipError_t err = hipSuccess;
   // one token, every gate/up unit in the selection launch: with front_all = 2 that launch also scores
   const bool own_scores = L.gate_up_done && tuning().front_all >= 2 && e.wr_tiled != nullptr && decode_k(e.d).nch == 1;
-  if (own_scores) {
-  } else {
+  if (!own_scores) {
     const dim3 grid(n_rows / 16, DEC_SLICES, (unsigned)((T + 15) / 16)), block(256);
     const bf16_t* xx = static_cast<const bf16_t*>(x);
     const int tiled = e.wr_tiled != nullptr ? 1 : 0;
@@ -1123,7 +1120,7 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
     const int ur = e.width_pad_host[e.n_always] / 16;
     const dim3 grid(1 + us + (e.G - e.n_always) * ur), block(512);
     for (int rep = tuning().repeat_stage == 3 ? 2 : 1; rep > 0; --rep)       // (measurement aid, as below)
-#define CMOE_LAUNCH(KS, RUNS) hipLaunchKernelGGL((route_place_tile_all_kernel<KS, RUNS>), grid, block, smem, s, e.r, io, pl, pre_g, n_slices, Ti, da, us, ur)
+#define CMOE_LAUNCH(KS, RUNS) hipLaunchKernelGGL((route_place_tile_all_kernel<KS, RUNS>), grid, block, smem, s, e.r, io, pl, pre_g, Ti, da, us, ur)
       { CMOE_DECODE_KSTEPS(e.d, CMOE_LAUNCH) }
 #undef CMOE_LAUNCH
     return hipGetLastError();
@@ -1142,7 +1139,7 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
     // only the scorer's partials, the token and the weights, and every write is a plain store of a value that
     // depends on those alone, so the second launch leaves the same bits)
     for (int rep = tuning().repeat_stage == 3 ? 2 : 1; rep > 0; --rep)
-#define CMOE_LAUNCH(KS, RUNS) hipLaunchKernelGGL((route_place_all_kernel<KS, RUNS>), grid, block, smem, s, e.r, io, pl, pre_g, n_slices, da, us, ur, wr_in)
+#define CMOE_LAUNCH(KS, RUNS) hipLaunchKernelGGL((route_place_all_kernel<KS, RUNS>), grid, block, smem, s, e.r, io, pl, pre_g, da, us, ur, wr_in)
       { CMOE_DECODE_KSTEPS(e.d, CMOE_LAUNCH) }
 #undef CMOE_LAUNCH
     return hipGetLastError();
@@ -1155,7 +1152,7 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
     // (units of 8 neurons while each finds a CU of its own: 17 tokens, 16 experts of 688, 63.2 -> 62.5 us per forward)
     const bool half = tuning().decode_split == 8 || (tuning().decode_split != 16 && e.width_pad_host[0] / 8 < 256);
     const dim3 grid(1 + e.width_pad_host[0] / (half ? 8 : 16)), block(512);
-#define CMOE_LAUNCH_N(MAXT, CS, NEUR) hipLaunchKernelGGL((route_place_stream_kernel<MAXT, CS, NEUR>), grid, block, smem, s, e.r, io, pl, pre_g, n_slices, Ti, da)
+#define CMOE_LAUNCH_N(MAXT, CS, NEUR) hipLaunchKernelGGL((route_place_stream_kernel<MAXT, CS, NEUR>), grid, block, smem, s, e.r, io, pl, pre_g, Ti, da)
 #define CMOE_LAUNCH(MAXT, CS) if (half) CMOE_LAUNCH_N(MAXT, CS, 8); else CMOE_LAUNCH_N(MAXT, CS, 16)
     CMOE_STREAM_FORM(T, e.d, CMOE_LAUNCH)
 #undef CMOE_LAUNCH
@@ -1168,12 +1165,12 @@ hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* 
     da.slot2tok = nullptr;                        // group 0's slots are the tokens in order; the map is not written yet
     da.work = nullptr;
     const dim3 grid(1 + e.width_pad_host[0] / da.unit1), block(512);
-#define CMOE_LAUNCH(KS, RUNS) hipLaunchKernelGGL((route_place_shared_kernel<KS, RUNS>), grid, block, smem, s, e.r, io, pl, pre_g, n_slices, Ti, da)
+#define CMOE_LAUNCH(KS, RUNS) hipLaunchKernelGGL((route_place_shared_kernel<KS, RUNS>), grid, block, smem, s, e.r, io, pl, pre_g, Ti, da)
     { CMOE_DECODE_KSTEPS(e.d, CMOE_LAUNCH) }
 #undef CMOE_LAUNCH
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(route_place_kernel, dim3(1), dim3(RT_THREADS), smem, s, e.r, io, pl, pre_g, n_slices, Ti);
+  hipLaunchKernelGGL(route_place_kernel, dim3(1), dim3(RT_THREADS), smem, s, e.r, io, pl, pre_g, Ti);
   return hipGetLastError();
 }
 
