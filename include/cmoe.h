@@ -295,7 +295,7 @@ int cmoe_probe_hbm(size_t bytes, int reps, double* gbytes_per_s);
  * included (6: a batch of at most 64 tokens runs its scoring launch and nothing else);
  * CMOE_REPEAT_STAGE = 3, 4 or 5 launches that stage twice instead (same inputs and outputs: the
  * result is unchanged), and the time a loop gains is one more launch of it under the forward's own clocks
- * (6: the scoring launch of a batch of at most 16 tokens twice).  0 restores the plain forward.  CMOE_EINVAL on an unknown name. */
+ * (6: the scoring launch of a batch of at most 64 tokens twice).  0 restores the plain forward.  CMOE_EINVAL on an unknown name. */
 int cmoe_set_tuning(const char* name, int value);
 
 /* Which kernels a forward of T tokens runs under the present tuning switches: plan[0] and plan[1] the gate/up contraction's

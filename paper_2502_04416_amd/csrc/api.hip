@@ -682,11 +682,10 @@ static FlatOffsets flat_offsets(const cmoe_layer* L) {
   return o;
 }
 
-// Second copy of a bf16 router in the MFMA operand order of the one-token front end: the 1 KB that one wave
-// loads as an A operand (16 rows x 32 columns; lane = (column / 8) * 16 + row holds 8 consecutive columns) is
-// consecutive memory, [row block][K step][lane][8].  In the row-major matrix the 16 rows of an operand lie a
-// power of two apart and meet in one L2 channel, which does not matter for the one scoring launch that reads
-// the matrix once but does when hundreds of workgroups read it at the same time.
+// Second copy of a bf16 router in MFMA operand order: the 1 KB that one wave loads as an A operand (16 rows x 32
+// columns; lane = (column / 8) * 16 + row holds 8 consecutive columns) is consecutive memory, [row block][K step][lane][8].  In
+// the row-major matrix the 16 rows of an operand lie a power of two apart and meet in one L2 channel.  Read by the
+// scorer of small batches and by the prefill scorer that also selects (a flat layer's; router_gemm_kernel reads the rows).
 static std::vector<uint8_t> tile_router_rows(const std::vector<uint8_t>& rows, int d) {
   const size_t n_rows = rows.size() / ((size_t)d * 2);
   std::vector<uint8_t> out(rows.size());

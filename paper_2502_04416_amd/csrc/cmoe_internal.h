@@ -143,7 +143,7 @@ struct Tuning {
   int splitk = 1;          // 0: never split K
   int zero_pad = 1;        // 0: tile rows past the end of a group repeat its last row instead of reading zeros (not on
                            // the deep ring, whose buffer loads deliver zeros there)
-  int decode_fuse = 1;     // 0: separate down and combine kernels for batches of at most 32 tokens
+  int decode_fuse = 1;     // 0: separate down and combine kernels for batches of at most 64 tokens
   int front_shared = 1;    // 0: the shared expert's gate/up units stay in the gate/up launch at decode
   int front_all = 1;       // one token on a flat layer.  0: the routed gate/up units keep a launch of their own;
                            // 1: the selection launch runs them; 2: that launch also scores, every workgroup
@@ -230,7 +230,7 @@ bool decode_front_ok(const Engine& e, int64_t T);
 hipError_t launch_decode_front(const Engine& e, const void* x, int64_t T, char* ws, const WsLayout& L,
                                int32_t* topk_out, int32_t* outer_out, float* scores_out, int32_t* counts_out,
                                hipStream_t s);
-// Decode batches (bf16, T <= 16; the fused down + combine kernel up to 32): weight-streaming expert kernels,
+// Decode batches (bf16, T <= 16; the fused down + combine kernel up to 64): weight-streaming expert kernels,
 // see decode.hip.
 bool decode_path_ok(const Engine& e, int64_t T);
 bool decode_front_runs_shared(const Engine& e, int64_t T);   // the front end's second launch also runs group 0's gate/up

@@ -68,6 +68,7 @@ __device__ __forceinline__ void decode_gate_up_unit(const DecArgs& p, int w1_row
   // The gate rows of the unit are requested before anything else (the stream from HBM is what the kernel
   // waits for; left to itself the compiler keeps half a dozen weight loads in flight per wave), the up rows
   // as the loop goes.  Requesting those up front as well costs a third workgroup per CU and gains nothing.
+  // (Loads return in order: the wait for the token index below is one for the gate rows, and the up rows follow the tokens.)
   bf16x8_t ag[KSTEPS];
 #pragma unroll
   for (int ks = 0; ks < KSTEPS; ++ks) ag[ks] = ld_frag(wg + ks * kadv);
@@ -320,8 +321,9 @@ __device__ __forceinline__ void decode_gate_up(const DecArgs& p, int w1_row0, in
 }
 
 // The same contraction for up to 16 * NTT rows of a group whose tokens do not stay in registers: K is walked in chunks of
-// CS steps, the operands of the next chunk requested before the current one is multiplied, so that between one and two
-// chunks of weights are always on their way.  What bounds a unit is the stream of its weights from HBM; its tokens, NTT KB
+// CS steps, the operands of the next chunk requested before the current one is multiplied, so that from the second chunk on
+// between one and two of them are always on their way.  (The first chunk is alone: loads return in order, so waiting for the token
+// index behind it is waiting for all of it.)  What bounds a unit is the stream of its weights from HBM; its tokens, NTT KB
 // for every KB of gate and every KB of up rows, come from L2.  NEUR = 16, or 8 as in decode_gate_up_unit8 (gate and up rows in
 // one operand).  w1_row0: the group's first packed row; row0, cnt: the unit's first slot and how many there are; columns past them repeat the first row and are not
 // stored.  d must be a multiple of 256 * CS, the weights tiled.

@@ -377,8 +377,9 @@ __global__ __launch_bounds__(256) void router_gemm_kernel(const bf16_t* __restri
   const bf16_t* brow = wr + (int64_t)l32 * d + lh * 8;
   const int k_begin = ks * k_slice;
   const int k_end = (k_begin + k_slice < d) ? k_begin + k_slice : d;     // host guarantees multiples of 64
-  // software pipeline over this wave's 64-wide chunks: the loads of the next chunk are issued before
-  // the MFMAs of the current one, so a wave always has a chunk of loads in flight
+  // software pipeline over this wave's 64-wide chunks: the loads of the next chunk are issued before the MFMAs of the
+  // current one.  (Because they are conditional, the compiler counts as if they had not been issued: the MFMAs of a chunk also wait
+  // for the next one, and a wave makes a round trip per chunk.)
   bf16x8_t a0[4], a1[4], b0[NT][4], b1[NT][4];
   auto load_chunk = [&](int kc, bf16x8_t (&a)[4], bf16x8_t (&b)[NT][4]) {
 #pragma unroll
@@ -433,11 +434,12 @@ __device__ __forceinline__ bool row_block_used(const RouterDev& r, int rb) {
 }
 
 // Adds the K-slice partials [slice][T][n_rows] of tokens t0 .. t0+rows-1 in slice order into pre[row][ld]
-// (LDS; rows past T become zero, and so do row blocks that hold no router row).  n_rows is a multiple of 4: float4 loads, SL
-// slices of V vectors per thread in flight together: another die wrote them, and a round trip there is a tenth of a small
+// (LDS; rows past T become zero, and so do row blocks that hold no router row).  n_rows is a multiple of 4: float4 loads of SL
+// slices of V vectors per thread, all asked for before the sums.  Another die wrote them, and a round trip there is a tenth of a small
 // batch's selection launch (16 experts, d = 4096, 4 slices of four vectors, then the other 4 / all 8 of two: 4 tokens 39.5 / 38.8 us
 // per forward, 8 tokens 47.7 / 46.9; 8 experts, d = 8192, 5 tokens 74.3 / 74.7, 12 tokens 100.0 / 98.4; 8 outer experts, d = 4096, 4
-// tokens 158.8 / 157.4).
+// tokens 158.8 / 157.4).  As compiled a vector is two round trips: the first slice, whose conditional load has the addition to zero
+// folded in, is awaited before the others are asked for, and the second vector's first slice awaits them.
 template <int SL, int V>
 __device__ __forceinline__ void sum_partials_of(const RouterDev& r, const float* __restrict__ partial, int n_slices, int64_t T, int64_t t0,
                                                 int rows, int n_rows, float* pre, int ld, int tid, int n_threads) {
@@ -472,7 +474,7 @@ __device__ __forceinline__ void sum_partials_of(const RouterDev& r, const float*
     }
   }
 }
-// (at most eight slices)
+// The tile router's (at most eight slices; the front end of small batches always has eight).
 __device__ __forceinline__ void sum_partials(const RouterDev& r, const float* __restrict__ partial, int n_slices, int64_t T, int64_t t0,
                                              int rows, int n_rows, float* pre, int ld, int tid, int n_threads) {
   if (n_slices <= 4) sum_partials_of<4, 4>(r, partial, n_slices, T, t0, rows, n_rows, pre, ld, tid, n_threads);
@@ -508,9 +510,10 @@ __global__ __launch_bounds__(RT_THREADS) void route_tile_kernel(RouterDev r, Rou
 
 // ---- scoring and selection in one launch (prefill batches of flat layers) ------------------------------------
 // A workgroup of eight waves owns TB * 16 tokens and all of K: the partial sums that router_gemm_kernel leaves in memory
-// for route_tile_kernel stay in its LDS.  What bounds it is the router matrix (0.5 MB at d = 4096, 64 rows) that
-// every workgroup pulls through L2, so the matrix is read in operand order (1 KB of consecutive memory per MFMA
-// operand) and a wave has two chunks of K (2 x 64) in flight.  Where it pays: see score_route_units.
+// for route_tile_kernel stay in its LDS.  What bounds it is the latency of the router matrix (0.5 MB at d = 4096, 64 rows) that
+// every workgroup pulls through L2 in operand order (1 KB of consecutive memory per MFMA operand): as compiled a wave asks for
+// the second of two chunks of K (2 x 64) when the first is there, then for the next first one, and awaits both, so that a
+// workgroup takes in about 50 KB per us.  Where it pays: see score_route_units.
 //
 // The sums are those of the two launches, bit for bit: K falls into n_slices slices of k_slice, a slice into four
 // classes of 64-wide chunks (chunk number mod 4), each of which is one chain of MFMAs; ((c0 + c1) + c2) + c3 is
@@ -642,10 +645,11 @@ __global__ __launch_bounds__(512) void score_route_kernel(RouterDev r, RouteIO i
 // release/acquire pair writes back and invalidates the whole L2, which costs far more than a launch.)
 //
 // decode_score_kernel: a workgroup per (16 router rows, eighth of K, 16 tokens), v_mfma_f32_16x16x32_bf16 with the router rows
-// as the A operand.  Its four waves take a quarter of the slice each, all their loads in flight at once, and their sums
-// are added in wave order through LDS; the eight K-slice partials of a row go to pre_g[slice][token][row] and are added in
-// slice order by route_place_kernel.  The router matrix comes cold from HBM, so the launch is bound by one memory latency:
-// what counts is that nothing is asked for after something else has arrived.  (With a wave per slice, 32
+// as the A operand.  Its four waves take a quarter of the slice each, and their sums are added in wave order through
+// LDS; the eight K-slice partials of a row go to pre_g[slice][token][row] and are added in slice order by route_place_kernel.
+// The router matrix comes cold from HBM, so the launch is bound by memory latency.  As compiled the form that also copies the
+// tokens has all loads of a run in flight at once; in the other one the test for the last step stands between a step's products and the
+// next step's loads, a round trip per K step of a wave (four at d = 4096, eight at 8192).  (With a wave per slice, 32
 // loads behind one another, up to 16 tokens and router_gemm_kernel beyond / now, us per forward: d = 4096, 16 experts, one token
 // 22.9 / 21.5, 4 tokens 42.5 / 39.5, 16 tokens 58.1 / 55.0, 32 tokens 69.6 / 65.5; d = 8192, 8 experts, 2 tokens 67.2 / 59.9, 5 tokens
 // 79.6 / 74.3; d = 5120, 16 experts, 30 tokens 84.0 / 75.3; 8 outer experts, d = 4096, 4 tokens 161.5 / 158.8.)
@@ -653,7 +657,7 @@ __global__ __launch_bounds__(512) void score_route_kernel(RouterDev r, RouteIO i
 // the sums that are made of them are not used.
 constexpr int DEC_SLICES = 8;
 
-// CH: K steps of a wave's quarter in flight together.  COPY: the tokens also go to xt, [K step of 32][token][32].
+// CH: K steps of a wave's quarter per run.  COPY: the tokens also go to xt, [K step of 32][token][32].
 template <int CH, bool COPY>
 __global__ __launch_bounds__(256) void decode_score_kernel(RouterDev r, const bf16_t* __restrict__ x, const bf16_t* __restrict__ wr,
                                                            int tiled, int d, int T, int n_rows, float* __restrict__ pre_g,
@@ -998,12 +1002,14 @@ static int scorer_slices(const Engine& e, int64_t T) {
 // router has a copy in operand order, whole pairs of chunks per unit (or one chunk), and either
 //  - at most two slices, i.e. a batch that fills the chip with 32 tokens per workgroup (8192 tokens of the 32-expert
 //    layer: 31 us against 34 + 10), or
-//  - 16 tokens per workgroup, which then pulls at most 640 KB of tokens and router rows (a CU takes in about 50 KB per us).
+//  - 16 tokens per workgroup, which then pulls at most 640 KB of tokens and router rows (one takes in about 50 KB per us, see the kernel).
 // us per forward in two launches / in one, d = 4096, 32 experts (64 rows, 640 KB): 70 tokens 40.3 / 39.3, 2048 78.9 / 75.0,
 // 3000 352.1 / 343.2, 4096 459.7 / 450.1; d = 2048, 32 experts, 4096 tokens 128.7 / 121.3.  Up to 16 experts (32 rows): d = 1024,
-// 333 tokens 36.5 / 31.4 and 4096 62.4 / 55.9; d = 5120 (480 KB) 70 tokens 105.3 / 101.9, 2048 345 / 336; d = 8192 (768 KB) 70
-// tokens 134.0 / 135.4, 333 179.8 / 181.5, 2048 378 / 374.  32 experts, d = 5120 (800 KB) 70 tokens 97.7 / 97.9, 2048 232 / 226;
-// d = 8192 (1.3 MB) 124 / 132 and 286 / 287.
+// 333 tokens 36.5 / 31.4 and 4096 62.4 / 55.9; d = 5120 (480 KB) 70 tokens 105.3 / 101.9, 2048 345 / 336.
+// Above 640 KB it is the tokens that decide, and the line is on the safe side for many of them.  Layers of narrow experts, ratio of two
+// launches to one at 65-1000 / 1300-2048 / 3000-4096 tokens (five to eight slices): 32 rows, d = 7168 (672 KB) 1.03 / 1.08 / -, 8192
+// 1.01 / 1.07 / 1.12; 64 rows, d = 5120 (800 KB) 1.01 / 1.05 / 1.08, 8192 (1.3 MB) 0.93 / 1.02 / 1.09; 128 rows, d = 2560 (720 KB) 1.02 / 1.11 /
+// 1.17, 3072 (864 KB) 0.99 / 1.08 / 1.25, 4096 (1.1 MB) 0.95 / 1.09 / 1.15, 8192 (2.3 MB) 0.88 / 1.02 / 1.10.
 // Row blocks in use (see the kernel) of a layer of 16 experts, d = 4096, against all four: 333 tokens 109.8 -> 104.5 us per
 // forward, 2048 208.0 -> 202.7 (the launch 15.8 -> 10.5 us); d = 1024, 333 tokens 36.5 -> 31.4.
 static constexpr int score_route_tokens(int upw) { return upw >= 2 ? 16 : 32; }

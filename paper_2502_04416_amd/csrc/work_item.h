@@ -7,7 +7,8 @@ namespace cmoe {
 
 // Every workgroup of a grouped launch starts with this lookup, and nothing else can be asked for before it is done.  Each lane
 // requests everything about its (at most two) groups at once, before the work item is even known, so that the lookup is
-// one round trip to memory; the prefix array, then the group's offsets and places, then its matrix one after the other were three.
+// one round trip to memory (in the streamed gate/up units two: they first ask whether there is an item at all); the prefix array, then
+// the group's offsets and places, then its matrix one after the other were three.
 // us per forward: d = 4096, 16 experts, 4 tokens 37.3 -> 37.1, 32 tokens 64.7 -> 63.9; d = 8192, 5 tokens 93.5 -> 92.6; d = 2048, 32 experts,
 // 16 tokens 23.7 -> 23.2; fp32, d = 256, 512 tokens 25.6 -> 24.6.
 struct GroupLanes {
